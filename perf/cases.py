@@ -123,15 +123,20 @@ def _cameras(kind, w, h, seed):
     return synth.city_flythrough(300, w, h)[i0:i0 + PATH]
 
 
-def _predictor_params(seed):
+def _typical_size(kind, n):
+    """log2 of a visible anchor's usual size on screen, in pixels: fewer anchors cover the same city with larger ones."""
+    return 5.8 if kind == "tiny" else 3.5 + 0.5 * math.log2(1e6 / n)
+
+
+def _predictor_params(seed, size):
     """Predictor weights whose decision is a real one: anchors that are large on screen, seen from another place
-    than when they were decoded, are decoded again (a sixth of the visible ones on the fly-through)."""
-    p = [0.05 * np.asarray(x) for x in synth.predictor_init(seed=3 + seed % 5)]
-    p[0][0] = (0.0, 0.0, 0.0, 0.0, 0.0, 0.8)       # log2 of the size on screen ...
-    p[1][0] = 0.6
+    than when they were decoded, are decoded again (an eighth to a third of the visible ones, by their age)."""
+    p = [0.01 * np.asarray(x) for x in synth.predictor_init(seed=3 + seed % 5)]
+    p[0][0] = (0.0, 0.0, 0.0, 0.0, 0.0, 1.0)       # log2 of the size on screen over the usual one ...
+    p[1][0] = -size
     p[0][1] = (0.0, 0.0, 0.0, 0.0, 25.0, 0.0)      # ... and the way the camera went, over the distance
     p[2][0] = 0.0
-    p[2][0, 0], p[2][0, 1], p[3][0] = 1.0, 1.0, -2.0
+    p[2][0, 0], p[2][0, 1], p[3][0] = 1.0, 1.0, -1.0
     p[4][0, 0], p[5][0] = 4.0, -1.5
     return gs.pack_params(p)
 
@@ -145,8 +150,8 @@ def _predictor_rows(rows, seed):
     X[:, 1] = X[:, 4] * r.uniform(-1.0, 1.0, rows)
     X[:, 2] = r.integers(1, 11, rows) / 10.0
     X[:, 3] = r.integers(0, 11, rows) / 10.0
-    X[:, 5] = r.normal(0.5, 1.5, rows)
-    y = (X[:, 5] + 0.7 * np.log2(X[:, 4]) + r.normal(0.0, 0.7, rows) > -3.5).astype(np.uint8)
+    X[:, 5] = r.normal(3.7, 0.9, rows)
+    y = (X[:, 5] + 0.7 * np.log2(X[:, 4]) + r.normal(0.0, 0.7, rows) > -0.5).astype(np.uint8)
     return X, y
 
 
@@ -181,7 +186,7 @@ def prepare(case, seed):
                         max_width=w, max_height=h, cache_capacity=case["lines"], lod_fade=case["fade"])
         r.load(sc)
         if case["predictor"]:
-            r.predictor_load(_predictor_params(seed))
+            r.predictor_load(_predictor_params(seed, _typical_size(case["scene"], case["n"])))
         s = {"kind": kind, "r": r, "cams": _cameras(case["scene"], w, h, seed), "at": 0, "l": _blank(h, w), "r_img": _blank(h, w)}
         for _ in range(WARM if case["reuse"] else 0):
             run(s)
@@ -220,7 +225,7 @@ def prepare(case, seed):
     if kind == "train":
         r.predictor_load(gs.pack_params(synth.predictor_init(seed=3 + seed % 5)))
         return {"kind": kind, "r": r, "X": X, "y": y, "batch": case["batch"], "epochs": case["epochs"]}
-    r.predictor_load(_predictor_params(seed))
+    r.predictor_load(_predictor_params(seed, 3.5))
     return {"kind": kind, "r": r, "X": torch.from_numpy(X).to(DEV), "p": torch.zeros(case["rows"], device=DEV)}
 
 
@@ -397,7 +402,7 @@ def exact(case, seed):
         img, T, _ = _render64(*[_t(x) for x in _gaussians(case["n"], seed)], _raster_camera(case))
         return img, T, None          # (contributor counts and the status are whole numbers)
     if kind == "infer":
-        W1, b1, W2, b2, W3, b3 = [_t(x) for x in gs.unpack_params(_predictor_params(seed))]
+        W1, b1, W2, b2, W3, b3 = [_t(x) for x in gs.unpack_params(_predictor_params(seed, 3.5))]
         X = _t(_predictor_rows(case["rows"], seed)[0])
         return torch.sigmoid(torch.relu(torch.relu(X @ W1.T + b1) @ W2.T + b2) @ W3.T + b3)[:, 0]
     if kind == "ssim":
