@@ -332,12 +332,4 @@ void seg_camera(Seg& s, const gsc_camera& c);
 // from the segments' tile grids, in segment order.
 void seg_supers(SegTable& tab);
 
-// Predictor kernels.
-hipError_t pred_forward_bwd(const float* w, const float* X, const float* y, int n, float pos_weight, float* grads,
-                            float* loss, hipStream_t st);
-hipError_t pred_adam(float* w, const float* grads, float* m, float* v, int nparams, int step, float lr,
-                     hipStream_t st);
-hipError_t pred_infer(const uint16_t* wbf, const float* w32, const float* X, int n, float* p, hipStream_t st);
-hipError_t pred_to_bf16(const float* w, uint16_t* wbf, int n, hipStream_t st);
-
 }  // namespace gsc

@@ -128,9 +128,7 @@ struct gsc_ctx {
     float* pred_m = nullptr;      // Adam moments
     float* pred_v = nullptr;
     float* pred_g = nullptr;      // gradients
-    float* pred_loss = nullptr;   // [1]
     float* pred_work = nullptr;   // per-row activations and gradients of a batch
-    int32_t* pred_idx = nullptr;
     int pred_step = 0;            // Adam steps taken
     bool pred_loaded = false;
     int collect_features = 0;

@@ -6,11 +6,13 @@
 // parameters packed W1[64,6] b1 W2[64,64] b2 W3[1,64] b3.  Loss: mean BCE
 // with positive-class weight w:  -(w y log p + (1-y) log(1-p)).
 //
-//   k_pred_fwdbwd   one thread per row: forward, dLoss/dlogit (/ rows),
-//                   back-propagated dZ2, dZ1; stores X, H1, H2, dZ1, dZ2
-//   k_pred_reduce   one thread per parameter: the batch sum of its gradient
-//                   (fixed order, deterministic) and the batch loss
-//   k_pred_adam     bias-corrected Adam step, then the BF16 inference copy
+//   k_pred_fwdbwd   one lane per unit, two rows per wave: forward,
+//                   dLoss/dlogit (/ rows), back-propagated dZ2, dZ1; stores
+//                   what the gradient sums read, in the layouts they read
+//   k_pred_grads    one wave per column of a gradient, four columns a block: the batch sum of every
+//                   parameter's gradient (row order, deterministic) and the
+//                   batch loss, then (training) the bias-corrected Adam step
+//                   and the BF16 inference copy of that parameter
 //   k_pred_infer    BF16 weights and activations, FP32 accumulate (the form
 //                   the cache lookup uses)
 //   k_pred_labels   compare every candidate's fresh derivation with its line
@@ -40,9 +42,18 @@ __device__ __forceinline__ int64_t gtid() { return (int64_t)blockIdx.x * blockDi
 
 __device__ __forceinline__ float softplus(float x) { return x > 0.f ? x + log1pf(expf(-x)) : log1pf(expf(x)); }
 
+__device__ __forceinline__ uint16_t to_bf16(float x) {
+    uint32_t u = __float_as_uint(x);
+    u += 0x7fffu + ((u >> 16) & 1u);
+    return (uint16_t)(u >> 16);
+}
+
+// Batch buffers.  The gradient sums run one lane per row of a [rows][64]
+// matrix's columns times a vector over the rows, so the matrices are
+// row-major and the vectors (the other factor) contiguous over the rows.
 struct Work {
-    float* X;    // [B][6]
-    float* H1;   // [B][64]
+    float* XT;   // [6][kMaxRows]
+    float* H1T;  // [64][kMaxRows]
     float* H2;   // [B][64]
     float* DZ1;  // [B][64]
     float* DZ2;  // [B][64]
@@ -50,113 +61,293 @@ struct Work {
     float* LS;   // [B] loss terms
 };
 
+constexpr int kRowsWave = 2;                      // rows a wave takes together
+constexpr int kRowsBlock = kRowsWave * (NT / 64);
+
+// One lane per unit: lane j holds row j of W2 (forward) and column j of W2
+// (backward) in registers, and the row's vector comes from LDS, four values
+// a read, broadcast to the wave.  A batch of 1,024 rows is then 128 blocks
+// of four waves instead of four blocks of one row per lane, whose 64-step
+// chains and their scalar weight loads nothing overlapped: 61 -> 8 us.
+// Every sum runs in the same order as one thread per row would run it (i
+// and j ascending, one FMA each), so splitting the units over the lanes
+// changes no result.
 __global__ __launch_bounds__(NT) void k_pred_fwdbwd(const float* __restrict__ w, const float* __restrict__ Xin,
                                                     const float* __restrict__ yf, const uint8_t* __restrict__ yb,
                                                     const int32_t* __restrict__ idx, int rows, float pos_weight,
                                                     Work wk) {
-    const int r = (int)gtid();
-    if (r >= rows) return;
-    const int64_t src = idx ? idx[r] : r;
-    float x[kPredIn];
-#pragma unroll
-    for (int i = 0; i < kPredIn; ++i) {
-        x[i] = Xin[src * kPredIn + i];
-        wk.X[(int64_t)r * kPredIn + i] = x[i];
+    __shared__ __align__(16) float s_x[kRowsBlock][8];
+    __shared__ __align__(16) float s_h1[kRowsBlock][kPredW];
+    __shared__ float s_h2[kRowsBlock][kPredW + 1];
+    __shared__ __align__(16) float s_dz2[kRowsBlock][kPredW];
+    __shared__ float s_dl[kRowsBlock];
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int row0 = blockIdx.x * kRowsBlock;
+    const int nr = rows - row0 < kRowsBlock ? rows - row0 : kRowsBlock;
+    if ((int)threadIdx.x < kRowsBlock * 8) {
+        const int r = threadIdx.x >> 3, i = threadIdx.x & 7;
+        float x = 0.f;
+        if (r < nr && i < kPredIn) {
+            const int64_t src = idx ? idx[row0 + r] : row0 + r;
+            x = Xin[src * kPredIn + i];
+        }
+        s_x[r][i] = x;
     }
-    const float y = yf ? yf[src] : (float)yb[src];
-    float z1[kPredW], h1[kPredW];
+    float w1[kPredIn], w2r[kPredW], w2c[kPredW];
 #pragma unroll
-    for (int j = 0; j < kPredW; ++j) {
-        float a = w[ob1 + j];
+    for (int i = 0; i < kPredIn; ++i) w1[i] = w[oW1 + lane * kPredIn + i];
 #pragma unroll
-        for (int i = 0; i < kPredIn; ++i) a = fmaf(w[oW1 + j * kPredIn + i], x[i], a);
-        z1[j] = a;
-        h1[j] = fmaxf(a, 0.f);
-        wk.H1[(int64_t)r * kPredW + j] = h1[j];
+    for (int i = 0; i < kPredW; i += 4) {
+        const float4 v = *reinterpret_cast<const float4*>(w + oW2 + lane * kPredW + i);
+        w2r[i] = v.x; w2r[i + 1] = v.y; w2r[i + 2] = v.z; w2r[i + 3] = v.w;
     }
-    float logit = w[ob3];
-    float z2m[kPredW];  // sign mask of z2 (1 if positive)
-    for (int j = 0; j < kPredW; ++j) {
-        float a = w[ob2 + j];
 #pragma unroll
-        for (int i = 0; i < kPredW; ++i) a = fmaf(w[oW2 + j * kPredW + i], h1[i], a);
-        float h2 = fmaxf(a, 0.f);
-        z2m[j] = a > 0.f ? 1.f : 0.f;
-        wk.H2[(int64_t)r * kPredW + j] = h2;
-        logit = fmaf(w[oW3 + j], h2, logit);
+    for (int j = 0; j < kPredW; ++j) w2c[j] = w[oW2 + j * kPredW + lane];
+    const float b1 = w[ob1 + lane], b2 = w[ob2 + lane], w3 = w[oW3 + lane];
+    __syncthreads();
+    const int q0 = wv * kRowsWave;
+    float z1[kRowsWave], z2m[kRowsWave];
+#pragma unroll
+    for (int u = 0; u < kRowsWave; ++u) {
+        float a = b1;
+#pragma unroll
+        for (int i = 0; i < kPredIn; ++i) a = fmaf(w1[i], s_x[q0 + u][i], a);
+        z1[u] = a;
+        s_h1[q0 + u][lane] = fmaxf(a, 0.f);
     }
-    const float p = 1.0f / (1.0f + expf(-logit));
-    wk.LS[r] = pos_weight * y * softplus(-logit) + (1.0f - y) * softplus(logit);
-    const float dl = (pos_weight * y * (p - 1.0f) + (1.0f - y) * p) / (float)rows;
-    wk.DL[r] = dl;
-    float dz2[kPredW];
+    __builtin_amdgcn_wave_barrier();  // the wave reads only its own rows; its LDS accesses complete in order
+    {
+        float a[kRowsWave];
 #pragma unroll
-    for (int j = 0; j < kPredW; ++j) {
-        dz2[j] = dl * w[oW3 + j] * z2m[j];
-        wk.DZ2[(int64_t)r * kPredW + j] = dz2[j];
+        for (int u = 0; u < kRowsWave; ++u) a[u] = b2;
+#pragma unroll
+        for (int i = 0; i < kPredW; i += 4)
+#pragma unroll
+            for (int u = 0; u < kRowsWave; ++u) {
+                const float4 h = *reinterpret_cast<const float4*>(&s_h1[q0 + u][i]);
+                a[u] = fmaf(w2r[i], h.x, a[u]);
+                a[u] = fmaf(w2r[i + 1], h.y, a[u]);
+                a[u] = fmaf(w2r[i + 2], h.z, a[u]);
+                a[u] = fmaf(w2r[i + 3], h.w, a[u]);
+            }
+#pragma unroll
+        for (int u = 0; u < kRowsWave; ++u) {
+            const float h2 = fmaxf(a[u], 0.f);
+            z2m[u] = a[u] > 0.f ? 1.f : 0.f;
+            s_h2[q0 + u][lane] = h2;
+            if (q0 + u < nr) wk.H2[(int64_t)(row0 + q0 + u) * kPredW + lane] = h2;
+        }
     }
-    for (int i = 0; i < kPredW; ++i) {
-        float a = 0.f;
+    __syncthreads();
+    if ((int)threadIdx.x < nr) {  // one lane per row of the block: the output unit
+        const int r = row0 + threadIdx.x;
+        float logit = w[ob3];
+#pragma unroll 16
+        for (int j = 0; j < kPredW; ++j) logit = fmaf(w[oW3 + j], s_h2[threadIdx.x][j], logit);
+        const int64_t src = idx ? idx[r] : r;
+        const float y = yf ? yf[src] : (float)yb[src];
+        const float p = 1.0f / (1.0f + expf(-logit));
+        wk.LS[r] = pos_weight * y * softplus(-logit) + (1.0f - y) * softplus(logit);
+        const float dl = (pos_weight * y * (p - 1.0f) + (1.0f - y) * p) / (float)rows;
+        wk.DL[r] = dl;
+        s_dl[threadIdx.x] = dl;
+    }
+    __syncthreads();
 #pragma unroll
-        for (int j = 0; j < kPredW; ++j) a = fmaf(w[oW2 + j * kPredW + i], dz2[j], a);
-        wk.DZ1[(int64_t)r * kPredW + i] = z1[i] > 0.f ? a : 0.f;
+    for (int u = 0; u < kRowsWave; ++u) {
+        const float dz2 = q0 + u < nr ? s_dl[q0 + u] * w3 * z2m[u] : 0.f;
+        s_dz2[q0 + u][lane] = dz2;
+        if (q0 + u < nr) wk.DZ2[(int64_t)(row0 + q0 + u) * kPredW + lane] = dz2;
+    }
+    __builtin_amdgcn_wave_barrier();
+    {
+        float a[kRowsWave];
+#pragma unroll
+        for (int u = 0; u < kRowsWave; ++u) a[u] = 0.f;
+#pragma unroll
+        for (int j = 0; j < kPredW; j += 4)
+#pragma unroll
+            for (int u = 0; u < kRowsWave; ++u) {
+                const float4 d = *reinterpret_cast<const float4*>(&s_dz2[q0 + u][j]);
+                a[u] = fmaf(w2c[j], d.x, a[u]);
+                a[u] = fmaf(w2c[j + 1], d.y, a[u]);
+                a[u] = fmaf(w2c[j + 2], d.z, a[u]);
+                a[u] = fmaf(w2c[j + 3], d.w, a[u]);
+            }
+#pragma unroll
+        for (int u = 0; u < kRowsWave; ++u)
+            if (q0 + u < nr) wk.DZ1[(int64_t)(row0 + q0 + u) * kPredW + lane] = z1[u] > 0.f ? a[u] : 0.f;
+    }
+    // the transposed factors, the block's rows of a unit side by side
+    for (int i = threadIdx.x; i < kPredW * kRowsBlock; i += NT) {
+        const int u = i / kRowsBlock, r = i % kRowsBlock;
+        if (r < nr) wk.H1T[(int64_t)u * kMaxRows + row0 + r] = s_h1[r][u];
+    }
+    if ((int)threadIdx.x < kPredIn * kRowsBlock) {
+        const int u = threadIdx.x / kRowsBlock, r = threadIdx.x % kRowsBlock;
+        if (r < nr) wk.XT[(int64_t)u * kMaxRows + row0 + r] = s_x[r][u];
     }
 }
 
-// grads[p] for every parameter, and grads[P] = mean loss.
-__global__ __launch_bounds__(NT) void k_pred_reduce(Work wk, int rows, float* __restrict__ grads) {
-    const int p = (int)gtid();
-    if (p > P) return;
-    float acc = 0.f;
-    if (p == P) {
-        for (int r = 0; r < rows; ++r) acc += wk.LS[r];
-        grads[P] = acc / (float)rows;
+// One parameter's Adam step (bias corrections bc1, bc2) and its BF16 copy.
+struct AdamArgs {
+    float* w;  // nullptr: gradients only, to `grads`
+    float* m;
+    float* v;
+    uint16_t* wbf;
+    float* loss;  // the epoch's loss: set by its first batch, added to by the others
+    float lr, bc1, bc2;
+    int first;
+};
+
+__device__ __forceinline__ void adam_step(const AdamArgs& a, int p, float gi) {
+    const float b1 = 0.9f, b2 = 0.999f, eps = 1e-8f;
+    const float mi = b1 * a.m[p] + (1.f - b1) * gi;
+    const float vi = b2 * a.v[p] + (1.f - b2) * gi * gi;
+    a.m[p] = mi;
+    a.v[p] = vi;
+    const float nw = a.w[p] - a.lr * (mi / a.bc1) / (sqrtf(vi / a.bc2) + eps);
+    a.w[p] = nw;
+    a.wbf[p] = to_bf16(nw);
+}
+
+__device__ __forceinline__ float lane_value(float v, int lane) {
+    return __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(v), lane));
+}
+
+// Gradient sums.  A block's four waves take four columns of one gradient:
+// column i of W2's is sum over r of DZ2[r][lane] H1[r][i], of W1's DZ1[r][lane]
+// X[r][i], of W3's H2[r][lane] DL[r], of b1's and b2's DZ1 and DZ2 themselves;
+// one more block sums DL and the losses.  Each parameter's sum keeps the row
+// order of a serial loop, a chain of `rows` FMAs that a lane runs at about
+// ten cycles a row (the matrix from LDS, the row's factor broadcast from the
+// lane that holds it): ~4 us at 1,024 rows, which bounds the kernel beside
+// the latency of one chunk's loads.  kGradRows rows of the matrix are staged
+// at a time, read as whole lines by all four waves while the chunk before is
+// summed.  One thread per parameter with two dependent loads a row, 19
+// blocks in all, took 281 us for a batch of 1,024 rows, and the Adam step was
+// a kernel of its own (5 us); a wave per column reading its rows itself took
+// 27 us (at most 63 loads a wave are in flight); this takes 14.
+constexpr int kGradRows = 256;
+constexpr int kGradVec = kGradRows * kPredW / 4 / NT;  // 16-byte words a thread stages
+constexpr int kGradW2 = kPredW / 4, kGradW1 = (kPredIn + 3) / 4;
+constexpr int kGradBlocks = kGradW2 + kGradW1 + 4;     // W3, b1, b2, and the sums over rows alone
+static_assert(2 * kMaxRows <= kGradRows * kPredW, "a batch's loss terms fit the staging array");
+
+__global__ __launch_bounds__(NT) void k_pred_grads(Work wk, int rows, float* __restrict__ grads, AdamArgs ad) {
+    __shared__ float4 s_m[kGradRows * kPredW / 4];
+    const int t = blockIdx.x, lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    if (t == kGradBlocks - 1) {  // b3 and the loss
+        // lane 0 sums dLoss/dlogit, lane 1 the losses, both from LDS (kMaxRows of each fit)
+        float* s_dl = reinterpret_cast<float*>(s_m);
+        for (int r = threadIdx.x; r < rows; r += NT) {
+            s_dl[2 * r] = wk.DL[r];
+            s_dl[2 * r + 1] = wk.LS[r];
+        }
+        __syncthreads();
+        if (wv) return;
+        float acc = 0.f;
+        const float* src = s_dl + (lane & 1);
+#pragma unroll 16
+        for (int r = 0; r < rows; ++r) acc += src[2 * r];
+        const float d = lane_value(acc, 0), l = lane_value(acc, 1);
+        const float loss = l / (float)rows;
+        if (lane == 0) {
+            if (ad.w) {
+                adam_step(ad, ob3, d);
+                *ad.loss = ad.first ? loss : *ad.loss + loss;
+            } else {
+                grads[ob3] = d;
+                grads[P] = loss;
+            }
+        }
         return;
     }
-    if (p < ob1) {  // W1[j][i] = sum dz1[r][j] x[r][i]
-        const int j = p / kPredIn, i = p % kPredIn;
-        for (int r = 0; r < rows; ++r) acc = fmaf(wk.DZ1[(int64_t)r * kPredW + j], wk.X[(int64_t)r * kPredIn + i], acc);
-    } else if (p < oW2) {
-        const int j = p - ob1;
-        for (int r = 0; r < rows; ++r) acc += wk.DZ1[(int64_t)r * kPredW + j];
-    } else if (p < ob2) {
-        const int j = (p - oW2) / kPredW, i = (p - oW2) % kPredW;
-        for (int r = 0; r < rows; ++r) acc = fmaf(wk.DZ2[(int64_t)r * kPredW + j], wk.H1[(int64_t)r * kPredW + i], acc);
-    } else if (p < oW3) {
-        const int j = p - ob2;
-        for (int r = 0; r < rows; ++r) acc += wk.DZ2[(int64_t)r * kPredW + j];
-    } else if (p < ob3) {
-        const int i = p - oW3;
-        for (int r = 0; r < rows; ++r) acc = fmaf(wk.DL[r], wk.H2[(int64_t)r * kPredW + i], acc);
+    const float* M;
+    const float* V = nullptr;  // (none: the matrix alone)
+    int p;
+    bool mine = true;  // this wave has a column
+    if (t < kGradW2) {
+        const int i = 4 * t + wv;
+        M = wk.DZ2; V = wk.H1T + (int64_t)i * kMaxRows; p = oW2 + lane * kPredW + i;
+    } else if (t < kGradW2 + kGradW1) {
+        const int i = 4 * (t - kGradW2) + wv;
+        mine = i < kPredIn;
+        M = wk.DZ1; V = wk.XT + (int64_t)(mine ? i : 0) * kMaxRows; p = oW1 + lane * kPredIn + i;
     } else {
-        for (int r = 0; r < rows; ++r) acc += wk.DL[r];
+        mine = wv == 0;
+        const int q = t - kGradW2 - kGradW1;
+        M = q == 0 ? wk.H2 : (q == 1 ? wk.DZ1 : wk.DZ2);
+        V = q == 0 ? wk.DL : nullptr;
+        p = (q == 0 ? oW3 : (q == 1 ? ob1 : ob2)) + lane;
     }
-    grads[p] = acc;
-}
-
-__device__ __forceinline__ uint16_t to_bf16(float x) {
-    uint32_t u = __float_as_uint(x);
-    u += 0x7fffu + ((u >> 16) & 1u);
-    return (uint16_t)(u >> 16);
-}
-
-__global__ __launch_bounds__(NT) void k_pred_adam(float* __restrict__ w, const float* __restrict__ g,
-                                                  float* __restrict__ m, float* __restrict__ v, float lr, float bc1,
-                                                  float bc2, uint16_t* __restrict__ wbf, float* __restrict__ loss_acc,
-                                                  int batches_done) {
-    const int p = (int)gtid();
-    if (p == 0 && loss_acc) *loss_acc += g[P];
-    if (p >= P) return;
-    const float b1 = 0.9f, b2 = 0.999f, eps = 1e-8f;
-    const float gi = g[p];
-    const float mi = b1 * m[p] + (1.f - b1) * gi;
-    const float vi = b2 * v[p] + (1.f - b2) * gi * gi;
-    m[p] = mi;
-    v[p] = vi;
-    const float nw = w[p] - lr * (mi / bc1) / (sqrtf(vi / bc2) + eps);
-    w[p] = nw;
-    wbf[p] = to_bf16(nw);
-    (void)batches_done;
+    const float4* M4 = reinterpret_cast<const float4*>(M);
+    const int total = rows * (kPredW / 4);
+    float4 nx[kGradVec];
+    float vn[kGradRows / 64];
+    auto fetch = [&](int r0) {
+#pragma unroll
+        for (int q = 0; q < kGradVec; ++q) {
+            const int i = r0 * (kPredW / 4) + q * NT + (int)threadIdx.x;
+            nx[q] = i < total ? M4[i] : make_float4(0.f, 0.f, 0.f, 0.f);
+        }
+#pragma unroll
+        for (int q = 0; q < kGradRows / 64; ++q) {
+            const int r = r0 + q * 64 + lane;
+            vn[q] = V ? (r < rows ? V[r] : 0.f) : 1.f;
+        }
+    };
+    float acc = 0.f;
+    fetch(0);
+    for (int r0 = 0; r0 < rows; r0 += kGradRows) {
+        float v[kGradRows / 64];
+#pragma unroll
+        for (int q = 0; q < kGradVec; ++q) s_m[q * NT + (int)threadIdx.x] = nx[q];
+#pragma unroll
+        for (int q = 0; q < kGradRows / 64; ++q) v[q] = vn[q];
+        __syncthreads();
+        if (r0 + kGradRows < rows) fetch(r0 + kGradRows);
+        if (mine) {
+            const float* m = reinterpret_cast<const float*>(s_m) + lane;
+#pragma unroll
+            for (int q = 0; q < kGradRows / 64; ++q) {
+                const int n = rows - r0 - q * 64;
+                if (n >= 64) {
+                    // groups of 16 rows: the factors of a group are read
+                    // from their lanes together (an FMA right behind its own
+                    // v_readlane waits for it), the next group's matrix
+                    // values while this group is added
+                    float mm[16];
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) mm[r] = m[(q * 64 + r) * kPredW];
+#pragma unroll
+                    for (int g = 0; g < 4; ++g) {
+                        float x[16], cur[16];
+#pragma unroll
+                        for (int r = 0; r < 16; ++r) x[r] = lane_value(v[q], 16 * g + r);
+#pragma unroll
+                        for (int r = 0; r < 16; ++r) cur[r] = mm[r];
+                        if (g < 3) {
+#pragma unroll
+                            for (int r = 0; r < 16; ++r) mm[r] = m[(q * 64 + 16 * (g + 1) + r) * kPredW];
+                        }
+                        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                        for (int r = 0; r < 16; ++r) acc = fmaf(cur[r], x[r], acc);
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                } else if (n > 0) {
+#pragma unroll 8
+                    for (int r = 0; r < n; ++r) acc = fmaf(m[(q * 64 + r) * kPredW], lane_value(v[q], r), acc);
+                }
+            }
+        }
+        __syncthreads();  // the chunk is summed before the next one overwrites it
+    }
+    if (mine) {
+        if (ad.w) adam_step(ad, p, acc);
+        else grads[p] = acc;
+    }
 }
 
 __global__ __launch_bounds__(NT) void k_pred_to_bf16(const float* __restrict__ w, uint16_t* __restrict__ wbf) {
@@ -247,9 +438,8 @@ hipError_t ensure_pred(gsc_ctx* c) {
     hipError_t e;
     if ((e = dalloc(c->pmem, b, &c->pred_w, P)) != hipSuccess || (e = dalloc(c->pmem, b, &c->pred_wbf, P)) != hipSuccess ||
         (e = dalloc(c->pmem, b, &c->pred_m, P)) != hipSuccess || (e = dalloc(c->pmem, b, &c->pred_v, P)) != hipSuccess ||
-        (e = dalloc(c->pmem, b, &c->pred_g, P + 1)) != hipSuccess || (e = dalloc(c->pmem, b, &c->pred_loss, 1)) != hipSuccess ||
-        (e = dalloc(c->pmem, b, &c->pred_work, (size_t)kMaxRows * (kPredIn + 4 * kPredW + 2))) != hipSuccess ||
-        (e = dalloc(c->pmem, b, &c->pred_idx, kMaxRows)) != hipSuccess) {
+        (e = dalloc(c->pmem, b, &c->pred_g, P + 1)) != hipSuccess ||
+        (e = dalloc(c->pmem, b, &c->pred_work, (size_t)kMaxRows * (kPredIn + 4 * kPredW + 2))) != hipSuccess) {
         return e;
     }
     return hipSuccess;
@@ -258,8 +448,8 @@ hipError_t ensure_pred(gsc_ctx* c) {
 Work work_of(gsc_ctx* c) {
     Work w;
     float* p = c->pred_work;
-    w.X = p; p += (size_t)kMaxRows * kPredIn;
-    w.H1 = p; p += (size_t)kMaxRows * kPredW;
+    w.XT = p; p += (size_t)kMaxRows * kPredIn;
+    w.H1T = p; p += (size_t)kMaxRows * kPredW;
     w.H2 = p; p += (size_t)kMaxRows * kPredW;
     w.DZ1 = p; p += (size_t)kMaxRows * kPredW;
     w.DZ2 = p; p += (size_t)kMaxRows * kPredW;
@@ -268,6 +458,7 @@ Work work_of(gsc_ctx* c) {
     return w;
 }
 
+inline unsigned batch_blocks(int rows) { return (unsigned)((rows + kRowsBlock - 1) / kRowsBlock); }
 inline unsigned blocks_for(int64_t n) { return (unsigned)std::max<int64_t>(1, std::min<int64_t>((n + NT - 1) / NT, kGridBlocks)); }
 
 }  // namespace
@@ -279,8 +470,7 @@ void pred_free(gsc_ctx* c) {
     c->pmem.release();
     c->pred_w = nullptr;
     c->pred_wbf = nullptr;
-    c->pred_m = c->pred_v = c->pred_g = c->pred_loss = c->pred_work = nullptr;
-    c->pred_idx = nullptr;
+    c->pred_m = c->pred_v = c->pred_g = c->pred_work = nullptr;
     c->pred_loaded = false;
 }
 
@@ -381,9 +571,9 @@ int gsc_predictor_grad(gsc_ctx* c, const float* X, const float* y, int64_t n, fl
     if (n < 1 || n > kMaxRows) return fail(c, GSC_E_INVALID_ARG, "gsc_predictor_grad: n must be in [1, 4096]");
     if (!c->pred_loaded) return fail(c, GSC_E_NOT_LOADED, "gsc_predictor_grad: no predictor loaded");
     Work wk = work_of(c);
-    hipLaunchKernelGGL(k_pred_fwdbwd, dim3(blocks_for(n)), dim3(NT), 0, c->stream, c->pred_w, X, y, nullptr, nullptr,
-                       (int)n, pos_weight, wk);
-    hipLaunchKernelGGL(k_pred_reduce, dim3(blocks_for(P + 1)), dim3(NT), 0, c->stream, wk, (int)n, c->pred_g);
+    hipLaunchKernelGGL(k_pred_fwdbwd, dim3(batch_blocks((int)n)), dim3(NT), 0, c->stream, c->pred_w, X, y, nullptr,
+                       nullptr, (int)n, pos_weight, wk);
+    hipLaunchKernelGGL(k_pred_grads, dim3(kGradBlocks), dim3(NT), 0, c->stream, wk, (int)n, c->pred_g, AdamArgs{});
     std::vector<float> g(P + 1);
     if (hipStreamSynchronize(c->stream) != hipSuccess ||
         hipMemcpy(g.data(), c->pred_g, (P + 1) * 4, hipMemcpyDeviceToHost) != hipSuccess)
@@ -400,53 +590,74 @@ int gsc_predictor_train(gsc_ctx* c, const float* X, const uint8_t* y, int64_t n,
         return fail(c, GSC_E_INVALID_ARG, "gsc_predictor_train: bad sizes");
     if (!c->pred_loaded) return fail(c, GSC_E_NOT_LOADED, "gsc_predictor_train: load initial weights first");
     hipStream_t st = c->stream;
+    // device copies of the rows, two permutations (device and pinned) and
+    // the epochs' losses: the host shuffles the next epoch's order while the
+    // device trains on this one's, and waits only at the end
+    AllocSet tmp;
+    size_t acct = 0;
     float* dX = nullptr;
     uint8_t* dy = nullptr;
-    int32_t* dperm = nullptr;
-    if (hipMalloc((void**)&dX, n * kPredIn * 4) != hipSuccess || hipMalloc((void**)&dy, n) != hipSuccess ||
-        hipMalloc((void**)&dperm, n * 4) != hipSuccess) {
-        (void)hipFree(dX); (void)hipFree(dy); (void)hipFree(dperm);
+    float* dloss = nullptr;
+    int32_t* dperm[2] = {nullptr, nullptr};
+    int32_t* hperm = nullptr;
+    if (dalloc(tmp, acct, &dX, n * kPredIn) != hipSuccess || dalloc(tmp, acct, &dy, n) != hipSuccess ||
+        dalloc(tmp, acct, &dloss, epochs) != hipSuccess || dalloc(tmp, acct, &dperm[0], n) != hipSuccess ||
+        dalloc(tmp, acct, &dperm[1], n) != hipSuccess || halloc(tmp, &hperm, 2 * n) != hipSuccess) {
+        tmp.release();
         return fail(c, GSC_E_OOM, "gsc_predictor_train: device allocation");
     }
+    hipEvent_t copied[2] = {nullptr, nullptr};
     int rc = GSC_OK;
+    for (int i = 0; i < 2 && rc == GSC_OK; ++i)
+        if (hipEventCreateWithFlags(&copied[i], hipEventDisableTiming) != hipSuccess)
+            rc = fail(c, GSC_E_HIP, "gsc_predictor_train: event creation");
     std::vector<int32_t> perm(n);
     std::iota(perm.begin(), perm.end(), 0);
     std::mt19937_64 rng(seed);
     Work wk = work_of(c);
-    if (hipMemcpyAsync(dX, X, n * kPredIn * 4, hipMemcpyHostToDevice, st) != hipSuccess ||
-        hipMemcpyAsync(dy, y, n, hipMemcpyHostToDevice, st) != hipSuccess)
+    if (rc == GSC_OK && (hipMemcpyAsync(dX, X, n * kPredIn * 4, hipMemcpyHostToDevice, st) != hipSuccess ||
+                         hipMemcpyAsync(dy, y, n, hipMemcpyHostToDevice, st) != hipSuccess))
         rc = fail(c, GSC_E_HIP, "gsc_predictor_train: upload failed");
     for (int ep = 0; ep < epochs && rc == GSC_OK; ++ep) {
         std::shuffle(perm.begin(), perm.end(), rng);
-        if (hipMemcpyAsync(dperm, perm.data(), n * 4, hipMemcpyHostToDevice, st) != hipSuccess ||
-            hipMemsetAsync(c->pred_loss, 0, 4, st) != hipSuccess) {
-            rc = fail(c, GSC_E_HIP, "gsc_predictor_train: upload failed");
-            break;
-        }
-        int nb = 0;
-        for (int64_t b0 = 0; b0 < n; b0 += batch, ++nb) {
-            const int rows = (int)std::min<int64_t>(batch, n - b0);
-            hipLaunchKernelGGL(k_pred_fwdbwd, dim3(blocks_for(rows)), dim3(NT), 0, st, c->pred_w, dX, nullptr, dy,
-                               dperm + b0, rows, pos_weight, wk);
-            hipLaunchKernelGGL(k_pred_reduce, dim3(blocks_for(P + 1)), dim3(NT), 0, st, wk, rows, c->pred_g);
-            c->pred_step += 1;
-            const float bc1 = 1.0f - (float)std::pow(0.9, c->pred_step);
-            const float bc2 = 1.0f - (float)std::pow(0.999, c->pred_step);
-            hipLaunchKernelGGL(k_pred_adam, dim3(blocks_for(P)), dim3(NT), 0, st, c->pred_w, c->pred_g, c->pred_m,
-                               c->pred_v, lr, bc1, bc2, c->pred_wbf, c->pred_loss, nb);
-        }
-        float lsum = 0.f;
-        if (hipMemcpyAsync(&lsum, c->pred_loss, 4, hipMemcpyDeviceToHost, st) != hipSuccess ||
-            hipStreamSynchronize(st) != hipSuccess) {
+        const int set = ep & 1;
+        int32_t* hp = hperm + (int64_t)set * n;
+        // (the pinned half was last read by the copy of two epochs back)
+        if (ep >= 2 && hipEventSynchronize(copied[set]) != hipSuccess) {
             rc = fail(c, GSC_E_HIP, "gsc_predictor_train: training kernels failed");
             break;
         }
-        if (loss_out) loss_out[ep] = lsum / (float)nb;
+        std::memcpy(hp, perm.data(), n * 4);
+        if (hipMemcpyAsync(dperm[set], hp, n * 4, hipMemcpyHostToDevice, st) != hipSuccess ||
+            hipEventRecord(copied[set], st) != hipSuccess) {
+            rc = fail(c, GSC_E_HIP, "gsc_predictor_train: upload failed");
+            break;
+        }
+        for (int64_t b0 = 0; b0 < n; b0 += batch) {
+            const int rows = (int)std::min<int64_t>(batch, n - b0);
+            hipLaunchKernelGGL(k_pred_fwdbwd, dim3(batch_blocks(rows)), dim3(NT), 0, st, c->pred_w, dX, nullptr, dy,
+                               dperm[set] + b0, rows, pos_weight, wk);
+            c->pred_step += 1;
+            AdamArgs ad;
+            ad.w = c->pred_w; ad.m = c->pred_m; ad.v = c->pred_v; ad.wbf = c->pred_wbf;
+            ad.loss = dloss + ep; ad.first = b0 == 0 ? 1 : 0;
+            ad.lr = lr;
+            ad.bc1 = 1.0f - (float)std::pow(0.9, c->pred_step);
+            ad.bc2 = 1.0f - (float)std::pow(0.999, c->pred_step);
+            hipLaunchKernelGGL(k_pred_grads, dim3(kGradBlocks), dim3(NT), 0, st, wk, rows, c->pred_g, ad);
+        }
+    }
+    if (rc == GSC_OK && (hipGetLastError() != hipSuccess || hipStreamSynchronize(st) != hipSuccess ||
+                         (loss_out && hipMemcpy(loss_out, dloss, (size_t)epochs * 4, hipMemcpyDeviceToHost) != hipSuccess)))
+        rc = fail(c, GSC_E_HIP, "gsc_predictor_train: training kernels failed");
+    if (rc == GSC_OK && loss_out) {
+        const int nb = (int)((n + batch - 1) / batch);
+        for (int ep = 0; ep < epochs; ++ep) loss_out[ep] /= (float)nb;
     }
     (void)hipStreamSynchronize(st);
-    (void)hipFree(dX);
-    (void)hipFree(dy);
-    (void)hipFree(dperm);
+    for (int i = 0; i < 2; ++i)
+        if (copied[i]) (void)hipEventDestroy(copied[i]);
+    tmp.release();
     return rc;
 }
 

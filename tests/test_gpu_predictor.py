@@ -55,6 +55,28 @@ def test_gradients_match_oracle(gs):
         assert rel <= 1e-4, rel
 
 
+@pytest.mark.parametrize("rows", [1, 7, 8, 9, 63, 64, 65, 255, 256, 257, 600, 4095, 4096])
+def test_gradients_at_block_and_chunk_edges(gs, rows):
+    """Eight rows a block in the forward/backward kernel, 64-row runs and
+    256-row chunks in the gradient sums: sizes around each, up to the largest
+    batch.  Tolerance: a sum of n FP32 terms is off by at most n eps of the
+    sum of their sizes (4096 x 6e-8 = 2.4e-4; rounding errors that do not all
+    have one sign leave ~sqrt(n) eps = 4e-6), so 1e-4 of each tensor's largest
+    entry, as for one size above."""
+    r = gs.Renderer(k=10, max_width=64, max_height=64)
+    params = rnd_params(7)
+    r.predictor_load(gs.pack_params(params))
+    params32 = [p.astype(np.float32).astype(np.float64) for p in params]
+    rng = np.random.default_rng(rows)
+    X = rng.standard_normal((rows, 6)).astype(np.float32)
+    y = (rng.uniform(size=rows) < 0.4).astype(np.float32)
+    loss, g = r.predictor_grad(torch.from_numpy(X).cuda(), torch.from_numpy(y).cuda(), pos_weight=1.5)
+    lo, go = oracle.pred_loss_grad(params32, X.astype(np.float64), y, 1.5)
+    assert abs(loss - lo) <= 1e-5 * max(1.0, abs(lo))
+    for a, b in zip(gs.unpack_params(g), go):
+        assert np.abs(a - b).max() <= 1e-4 * max(np.abs(b).max(), 1e-12)
+
+
 def test_bf16_inference_close_to_fp64(gs):
     r = gs.Renderer(k=10, max_width=64, max_height=64)
     params = rnd_params(5)
