@@ -21,9 +21,8 @@ constexpr int kTile = 16;             // 16x16 pixel tiles
 constexpr int kSupShift = 1;          // log2 tiles per super-tile side
 constexpr int kMaskShift = 28;        // value = entry | mask << kMaskShift
 constexpr uint32_t kEntryMask = (1u << kMaskShift) - 1u;
-constexpr int kBlendThreads = 64;     // one wave per 16x16 tile, four pixels per thread (blend)
-constexpr int kBlendBatch = 128;      // Gaussians staged in LDS per step (blend)
-constexpr int kBlendRun = 128;        // consecutive tiles one XCD takes in a row (blend)
+constexpr int kBlendThreads = 64;     // one wave per 16x16 tile, half or quarter of one (blend)
+constexpr int kBlendRun = 128;        // consecutive parts of tiles one XCD takes in a row (blend)
 constexpr int kMaxSeg = 16;           // (viewer, eye) images per raster batch
 constexpr int kGridBlocks = 2048;     // fixed grid of the grid-stride kernels
 constexpr int kScanBlocks = 1024;     // blocks of the device-wide scan

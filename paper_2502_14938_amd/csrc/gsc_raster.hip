@@ -19,10 +19,10 @@
 //                      stable sort of the items by global super-tile id
 //   k_ranges           [start, end) of every super tile's run
 //   k_blend            front-to-back compositing, one launch over every
-//                      (segment, tile) of the batch, one block per 16x16
-//                      tile (interleaved tile runs per XCD); a tile stages the
-//                      entries of its super tile's list that carry its mask
-//                      bit, LDS batches, block-wide early exit
+//                      (segment, tile) of the batch, one wave per 16x16
+//                      tile, half or quarter of one (interleaved runs per
+//                      XCD); a tile stages the entries of its super tile's
+//                      list that carry its mask bit, wave-wide early exit
 // With full_key_sort the items carry the whole 64-bit (super tile << 32 |
 // depth) key and are sorted after duplication instead; the order is the same.
 #include <cmath>
@@ -948,15 +948,17 @@ __global__ __launch_bounds__(NT) void k_ranges(const K* __restrict__ keys, const
 }
 
 
-// One wave (one block) per global tile; the block -> tile map gives each
-// XCD runs of kBlendRun adjacent tiles, interleaved over the image, so
-// Gaussians shared by neighbouring tiles are gathered through one L2 and the
-// XCDs get equal shares of dense and sparse image regions.  Thread t owns the
-// four pixels (t & 15, (t >> 4) + 4 i), i < 4, of its 16x16 tile, which share
-// their column offset dx and the per-Gaussian terms that depend on it only.
-// Gaussians of the tile's depth-sorted list are staged in LDS, kBlendBatch at
-// a time, with the conic pre-scaled so that the exponent is base 2 and the
-// log2 of the opacity folded in:
+// One wave (one block) per part of a global tile: kPx = 4, 2 or 1 pixels a
+// lane cover the whole tile, a 16x8 half or an 8x8 quarter of it (see
+// blend_px for when).  The block -> part map gives each XCD runs of kBlendRun
+// adjacent parts, interleaved over the image, so Gaussians shared by
+// neighbouring tiles are gathered through one L2 and the XCDs get equal
+// shares of dense and sparse image regions.  A lane's pixels lie in one
+// column, so they share the offset dx and the per-Gaussian terms that depend
+// on it only.
+// Gaussians of the tile's depth-sorted list are staged in LDS, 64 list
+// positions at a time, with the conic pre-scaled so that the exponent is base
+// 2 and the log2 of the opacity folded in:
 //   alpha = min(0.99, 2^(a' dx^2 + b' dx dy + c' dy^2 + log2 o)),
 //   a' = -log2(e)/2 a, b' = -log2(e) b, c' = -log2(e)/2 c,
 // equal to min(0.99, o exp(-q/2)) of the conic quadratic q (the hardware
@@ -964,134 +966,202 @@ __global__ __launch_bounds__(NT) void k_ranges(const K* __restrict__ keys, const
 // Per pixel: skip alpha < 1/255; stop before a Gaussian that would take
 // T(1 - alpha) below 1e-4; otherwise composite.  The composite step is
 // predicated (no branches); the wave stops once all its pixels are done.
-static_assert(kBlendThreads == 64, "k_blend maps one wave of 64 threads onto a 16x16 tile");
-template <bool kCount>
-__global__ __launch_bounds__(kBlendThreads) void k_blend(SegTable tab, const int32_t* __restrict__ ranges,
+static_assert(kBlendThreads == 64, "k_blend maps one wave onto a part of a 16x16 tile");
+
+// Can a staged Gaussian reach alpha >= 1/255 anywhere on the pixel centres
+// [x0, x1] x [y0, y1]?  The largest exponent over the rectangle is at the
+// minimum of the (convex) quadratic, which lies on an edge that faces the
+// centre (or is the centre); a Gaussian is left out only when that exponent
+// is below log2(1/255) by a margin above the rounding of this test and of
+// the pixels' own exponents: each is a sum of terms of at most 2 m in size,
+// m = |a'| dx^2 + |c'| dy^2 at the rectangle's farthest offsets (b'^2 < 4 a'
+// c'), good to ~10 roundings of it, 1.2e-6 m; 4e-6 m + 1e-3 covers both.  A
+// NaN keeps it.
+__device__ __forceinline__ bool part_hit(const float4& a, const float2& b, float x0, float x1, float y0, float y1) {
+    const float l = x0 - a.x, r = x1 - a.x, t = y0 - a.y, d = y1 - a.y;
+    const float dx = fminf(fmaxf(0.f, l), r), dy = fminf(fmaxf(0.f, t), d);
+    const float hb = -0.5f * a.w;  // the minimiser along an edge: -b' / 2 over the free axis's coefficient
+    const float ey = fminf(fmaxf(hb * dx * __builtin_amdgcn_rcpf(b.x), t), d);
+    const float ex = fminf(fmaxf(hb * dy * __builtin_amdgcn_rcpf(a.z), l), r);
+    const float e1 = a.z * dx * dx + (a.w * dx + b.x * ey) * ey;
+    const float e2 = b.x * dy * dy + (a.w * dy + a.z * ex) * ex;
+    const float mx = fmaxf(fabsf(l), fabsf(r)), my = fmaxf(fabsf(t), fabsf(d));
+    const float m = fabsf(a.z) * mx * mx + fabsf(b.x) * my * my;
+    constexpr float kLogMin = -7.994353436858858f;  // log2(1 / 255)
+    return !(fmaxf(e1, e2) + b.y < kLogMin - 1e-3f - 4e-6f * m);
+}
+
+// kCount 0: no counts; 1: contributors per pixel (out_nc); 2: also the visits
+// and contributions of each tile (whole tiles only, nothing left out).
+template <int kPx, int kCount>
+__global__ __launch_bounds__(kBlendThreads) __attribute__((amdgpu_waves_per_eu(kPx == 4 ? 6 : 7))) void k_blend(SegTable tab, const int32_t* __restrict__ ranges,
                                               const uint32_t* __restrict__ vals, const float4* __restrict__ rec,
                                               uint32_t max_entries, int32_t* __restrict__ tile_eval) {
-    constexpr int BB = kBlendBatch;
-    __shared__ float4 sA[BB];  // mx, my, a', b'
-    __shared__ float4 sB[BB];  // c', log2 o, r, g
-    __shared__ float sC[BB];   // b
+    static_assert(kCount < 2 || kPx == 4, "work is counted per tile");
+    constexpr int kParts = 4 / kPx;           // waves per tile
+    constexpr int kPW = kPx == 1 ? 8 : 16;    // pixels a part is wide
+    constexpr int BB = kBlendThreads + 8;     // a step's entries and what the step before left over
+    __shared__ float4 sA[BB];    // mx, my, a', b'
+    __shared__ float4 sB[BB];    // c', log2 o, r, g
+    __shared__ float sC[BB];     // b
     constexpr float kL2e = 1.4426950408889634f;
-    const int total = tab.total_tiles;
+    const int total = tab.total_tiles * kParts;
     // Blocks go to the 8 XCDs round-robin (block b to XCD b mod 8).  Each
     // run of 8 x kBlendRun blocks covers 8 runs of kBlendRun consecutive
-    // tiles, one per XCD, so neighbouring tiles (which share Gaussians)
+    // parts, one per XCD, so neighbouring tiles (which share Gaussians)
     // meet in one L2 while every XCD draws tiles from all over the image;
     // the last partial run keeps the identity map.
     const int bb = blockIdx.x, sc = bb / (8 * kBlendRun);
-    const int gt = (sc + 1) * 8 * kBlendRun <= total ? sc * 8 * kBlendRun + (bb & 7) * kBlendRun + (bb % (8 * kBlendRun)) / 8
-                                                      : bb;
+    const int item = (sc + 1) * 8 * kBlendRun <= total
+                         ? sc * 8 * kBlendRun + (bb & 7) * kBlendRun + (bb % (8 * kBlendRun)) / 8
+                         : bb;
+    const int gt = item / kParts, part = item % kParts;
     int si = 0;
     while (si + 1 < tab.n && gt >= tab.s[si + 1].tile_base) ++si;
     const Seg& s = tab.s[si];
     const int lt = gt - s.tile_base;
     const int tx = lt % s.ntx, ty = lt / s.ntx;
-    // thread t owns the pixels (t & 15, (t >> 4) + 4 i), i < 4, of the tile
-    const int px = tx * kTile + (threadIdx.x & (kTile - 1));
+    const int lane = threadIdx.x;
+    // the part's first pixel: quarters 2 (y) + (x), halves one above the other
+    const int qx = tx * kTile + (kPx == 1 ? (part & 1) * 8 : 0);
+    const int qy = ty * kTile + (kPx == 1 ? (part >> 1) * 8 : part * 8);
+    const int px = qx + lane % kPW;
     const float fx = (float)px + 0.5f;
-    int py[4];
-    float fy[4], T[4], cr[4], cg[4], cbl[4];
-    int32_t nc[4], stp[4];
-    bool d[4], in[4];
+    int py[kPx];
+    float fy[kPx], T[kPx], cr[kPx], cg[kPx], cbl[kPx];
+    int32_t nc[kPx], stp[kPx];
+    bool live[kPx], in[kPx];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        py[i] = ty * kTile + (threadIdx.x >> 4) + 4 * i;
+    for (int i = 0; i < kPx; ++i) {
+        py[i] = qy + lane / kPW + 4 * i;
         in[i] = px < s.W && py[i] < s.H;
         fy[i] = (float)py[i] + 0.5f;
         T[i] = 1.0f; cr[i] = 0.f; cg[i] = 0.f; cbl[i] = 0.f;
         nc[i] = 0; stp[i] = -1;
-        d[i] = !in[i];
+        live[i] = in[i];
     }
+    auto any_live = [&]() {
+        bool l = live[0];
+#pragma unroll
+        for (int i = 1; i < kPx; ++i) l = l || live[i];
+        return __any(l) != 0;
+    };
+    const float rx0 = (float)qx + 0.5f, ry0 = (float)qy + 0.5f;
+    const float rx1 = rx0 + (float)(kPW - 1), ry1 = ry0 + (kPx == 4 ? 15.f : 7.f);
     // the tile's list: the entries of its super tile's list whose mask has
     // the tile's bit, in list order
     const int S = s.sup_base + (ty >> kSupShift) * s.nsx + (tx >> kSupShift);
     const uint32_t bit = 1u << (kMaskShift + ((ty & 1) << 1) + (tx & 1));
     const int32_t end = ranges[2 * S + 1];
-    int32_t rd = ranges[2 * S];  // next list position to read
-    int32_t own = 0;             // the tile's entries staged so far
-    const uint64_t below = (1ull << threadIdx.x) - 1ull;  // lanes before this one
+    int32_t rd = ranges[2 * S];  // first list position of the step being staged
+    int32_t own = 0;             // the tile's entries composited so far
+    const uint64_t below = (1ull << lane) - 1ull;  // lanes before this one
+    // Two steps ahead (halves and quarters): while a step's entries are
+    // composited, the next step's records and the list words of the one
+    // after it are in flight (a wave's LDS accesses complete in order, so no
+    // barrier waits for them).  Whole tiles are for batches with waves enough
+    // to cover a step's loads, and keep the registers (six waves per SIMD
+    // without a spill).
+    constexpr bool kAhead = kPx < 4;
+    float4 A = make_float4(0.f, 0.f, 0.f, 0.f), B = A;
+    float cb = 0.f;
+    auto fetch = [&](uint32_t v) {
+        const bool m = (v & bit) != 0u;
+        if (m) {
+            uint32_t e = v & kEntryMask;
+            e = e < max_entries ? e : 0u;  // entries always are; keeps a stray id in bounds
+            const float4* rp = rec + kRec * (int64_t)e;
+            A = rp[0];
+            B = rp[1];
+            cb = rp[2].x;
+        }
+        return m;
+    };
+    auto word = [&](int32_t at) { return at + lane < end ? vals[at + lane] : 0u; };
+    bool mine = kAhead && fetch(word(rd));
+    uint32_t vn = kAhead ? word(rd + 64) : 0u;
+    int lead = 0;  // entries left over from the step before (fewer than 8)
     while (rd < end) {
-        if (__all(d[0] && d[1] && d[2] && d[3])) break;
-        // stage up to BB of the tile's entries: 64 list positions a step,
-        // the tile's ones packed in order
-        int nb = 0;
-        while (nb < BB && rd < end) {
-            const int32_t i = rd + (int32_t)threadIdx.x;
-            const uint32_t v = i < end ? vals[i] : 0u;
-            const bool mine = (v & bit) != 0u;
-            const uint64_t mm = __ballot(mine);
-            const int at = nb + (int)__popcll(mm & below);
-            const bool take = mine && at < BB;
-            const uint64_t tk = __ballot(take);
-            if (take) {
-                uint32_t e = v & kEntryMask;
-                e = e < max_entries ? e : 0u;  // entries always are; keeps a stray id in bounds
-                const float4* rp = rec + kRec * (int64_t)e;
-                const float4 A = rp[0], B = rp[1];
-                sA[at] = make_float4(A.x, A.y, -0.5f * kL2e * A.z, -kL2e * A.w);
-                sB[at] = make_float4(-0.5f * kL2e * B.x, __log2f(B.y), B.z, B.w);
-                sC[at] = rp[2].x;
-            }
-            nb += (int)__popcll(tk);
-            // past the last position read: the whole step, or up to the last
-            // entry taken when the batch filled
-            rd = __popcll(mm) == __popcll(tk) ? rd + 64 : rd + 64 - (int)__builtin_clzll(tk);
+        if (!kAhead) mine = fetch(word(rd));
+        const float4 a4 = make_float4(A.x, A.y, -0.5f * kL2e * A.z, -kL2e * A.w);
+        const float2 b2 = make_float2(-0.5f * kL2e * B.x, __log2f(B.y));
+        // a half or quarter takes only the entries that reach it
+        const bool take = mine && (kPx == 4 || part_hit(a4, b2, rx0, rx1, ry0, ry1));
+        const uint64_t mm = __ballot(take);
+        if (take) {
+            const int at = lead + (int)__popcll(mm & below);
+            sA[at] = a4;
+            sB[at] = make_float4(b2.x, b2.y, B.z, B.w);
+            sC[at] = cb;
         }
-        // padding to the next group of 8: alpha = 2^-inf = 0 is below the
-        // 1/255 cut, so these change no pixel and the unrolled loop below
-        // needs no bound of its own
-        for (int l = nb + (int)threadIdx.x; l < ((nb + 7) & ~7); l += kBlendThreads) {
-            sA[l] = make_float4(0.f, 0.f, 0.f, 0.f);
-            sB[l] = make_float4(0.f, -INFINITY, 0.f, 0.f);
-            sC[l] = 0.f;
+        const int nb = lead + (int)__popcll(mm);
+        rd += 64;
+        const bool last = rd >= end;
+        if (kAhead) {
+            mine = fetch(vn);  // (past the end: no entry)
+            vn = word(rd + 64);
         }
-        __syncthreads();
-        // groups of 8: the done flags stay in scalar masks inside a group
-        // and the LDS reads take immediate offsets; the padding above makes
-        // a partial last group safe
-        for (int k0 = 0; k0 < nb; k0 += 8) {
-            if (__all(d[0] && d[1] && d[2] && d[3])) break;
+        // whole groups of 8; the last step is padded to one: alpha = 2^-inf
+        // = 0 is below the 1/255 cut, so the padding changes no pixel
+        const int n8 = last ? (nb + 7) & ~7 : nb & ~7;
+        if (last && lane < n8 - nb) {
+            sA[nb + lane] = make_float4(0.f, 0.f, 0.f, 0.f);
+            sB[nb + lane] = make_float4(0.f, -INFINITY, 0.f, 0.f);
+            sC[nb + lane] = 0.f;
+        }
+        __builtin_amdgcn_wave_barrier();
+        // groups of 8: the live flags stay in scalar masks inside a group
+        // and the LDS reads take immediate offsets
+        for (int k0 = 0; k0 < n8; k0 += 8) {
+            if (!any_live()) break;
 #pragma unroll
             for (int kk = 0; kk < 8; ++kk) {
                 const int k = k0 + kk;
-                const float4 A = sA[k];
-                const float4 B = sB[k];
-                const float cb = sC[k];
-                const float dx = fx - A.x;
-                const float u = A.w * dx;
-                const float t = fmaf(A.z * dx, dx, B.y);
+                const float4 ga = sA[k];
+                const float4 gb = sB[k];
+                const float gc = sC[k];
+                const float dx = fx - ga.x;
+                const float u = ga.w * dx;
+                const float t = fmaf(ga.z * dx, dx, gb.y);
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const float e0 = fy[i] - A.y;
-                    const float al = fminf(0.99f, __builtin_amdgcn_exp2f(fmaf(e0, fmaf(B.x, e0, u), t)));
+                for (int i = 0; i < kPx; ++i) {
+                    const float e0 = fy[i] - ga.y;
+                    const float al = fminf(0.99f, __builtin_amdgcn_exp2f(fmaf(e0, fmaf(gb.x, e0, u), t)));
                     // weight alpha T; the next transmittance T (1 - alpha) as T - alpha T
                     const float wf = al * T[i];
-                    const float tn = T[i] - wf;
-                    const bool uu = !d[i] && al >= kMinAlpha;
+                    const float tn = fmaf(-T[i], al, T[i]);
+                    const bool uu = live[i] && al >= kMinAlpha;
                     const bool ac = uu && tn >= kTStop;  // composite
-                    const bool st = uu != ac;            // stop here (uu and not ac)
+                    const bool st = uu && !ac;           // stop here
                     const float w = ac ? wf : 0.f;
-                    cr[i] = fmaf(B.z, w, cr[i]); cg[i] = fmaf(B.w, w, cg[i]); cbl[i] = fmaf(cb, w, cbl[i]);
+                    cr[i] = fmaf(gb.z, w, cr[i]); cg[i] = fmaf(gb.w, w, cg[i]); cbl[i] = fmaf(gc, w, cbl[i]);
                     T[i] = ac ? tn : T[i];
-                    if (kCount) {
-                        nc[i] += ac ? 1 : 0;
-                        stp[i] = st ? own + k : stp[i];
-                    }
-                    d[i] = d[i] || st;
+                    if (kCount) nc[i] += ac ? 1 : 0;
+                    if (kCount == 2) stp[i] = st ? own + k : stp[i];
+                    live[i] = live[i] && !st;
                 }
             }
         }
-        own += nb;
-        __syncthreads();  // the batch is read before the next one is staged
+        own += last ? nb : n8;
+        if (!any_live()) break;
+        // the fewer than 8 entries past the last whole group go first in the next step
+        lead = last ? 0 : nb - n8;
+        if (n8 && lane < lead) {
+            const float4 ga = sA[n8 + lane], gb = sB[n8 + lane];
+            const float gc = sC[n8 + lane];
+            __builtin_amdgcn_wave_barrier();
+            sA[lane] = ga;
+            sB[lane] = gb;
+            sC[lane] = gc;
+        }
+        __builtin_amdgcn_wave_barrier();
     }
-    if (kCount) {
+    if (kCount == 2) {
         // a pixel that never stopped visited the whole list: the loop then
         // ran to the list's end, so `own` is its length
         int32_t ne = 0, nce = 0;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
+        for (int i = 0; i < kPx; ++i) {
             ne += in[i] ? (stp[i] >= 0 ? stp[i] + 1 : own) : 0;
             nce += nc[i];
         }
@@ -1099,14 +1169,14 @@ __global__ __launch_bounds__(kBlendThreads) void k_blend(SegTable tab, const int
             ne += __shfl_xor(ne, o);
             nce += __shfl_xor(nce, o);
         }
-        if (threadIdx.x == 0) {
+        if (lane == 0) {
             tile_eval[2 * gt] = ne;
             tile_eval[2 * gt + 1] = nce;
         }
     }
     const int64_t np = (int64_t)s.W * s.H;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
+    for (int i = 0; i < kPx; ++i) {
         if (!in[i]) continue;
         const int64_t p = (int64_t)py[i] * s.W + px;
         s.out_rgb[p] = cr[i];
@@ -1115,6 +1185,44 @@ __global__ __launch_bounds__(kBlendThreads) void k_blend(SegTable tab, const int
         if (s.out_T) s.out_T[p] = T[i];
         if (kCount && s.out_nc) s.out_nc[p] = nc[i];
     }
+}
+
+// Pixels per lane of k_blend for a batch of `tiles` tiles.  The shared terms
+// of a Gaussian cost a wave the same for one pixel a lane as for four, so
+// whole tiles take the fewest instructions; but a tile is then one wave
+// working through its list alone, and a batch of few tiles neither fills
+// the chip's 1,024 SIMDs nor ends before its longest list does.  Halves and
+// quarters shorten that list (and skip the entries that miss them).  Measured
+// (us of k_blend; whole tiles / halves / quarters):
+//   512 tiles     (256x256 stereo, 10k Gaussians)      109 /  50 /  30
+//   2,205 tiles   (1000x560, 60k)                       84 /  58 /  46
+//   8,160 tiles   (1920x1081, 500k)                    167 / 131 / 120
+//   17,408 tiles  (2048x1080 stereo, 1M anchors)
+//     high above the city                              220 / 178 / 186
+//     near the ground                                  130 / 138 / 160
+//   131,000 tiles (eight viewers up to 2560x1440)      820 / 880 / 1055
+int blend_px(int64_t tiles) { return tiles > 20480 ? 4 : (tiles > 12288 ? 2 : 1); }
+
+hipError_t launch_blend(const SegTable& tab, const Raster& r, bool count_work, hipStream_t st) {
+    // a call that wants contributor counts per pixel does not need the tiles' work
+    const int count = !count_work ? 0 : (tab.s[0].out_nc ? 1 : 2);
+    const int px = count == 2 ? 4 : blend_px(tab.total_tiles);
+    const dim3 grid((unsigned)(tab.total_tiles * (4 / px)));
+    const uint32_t* vals = r.pval[r.sorted_buf];
+#define GSC_BLEND(P, C)                                                                                            \
+    hipLaunchKernelGGL((k_blend<P, C>), grid, dim3(kBlendThreads), 0, st, tab, r.ranges, vals, r.rec,              \
+                       (uint32_t)r.max_entries, r.tile_eval)
+    if (count == 2) {
+        GSC_BLEND(4, 2);
+    } else if (px == 4) {
+        if (count) GSC_BLEND(4, 1); else GSC_BLEND(4, 0);
+    } else if (px == 2) {
+        if (count) GSC_BLEND(2, 1); else GSC_BLEND(2, 0);
+    } else {
+        if (count) GSC_BLEND(1, 1); else GSC_BLEND(1, 0);
+    }
+#undef GSC_BLEND
+    return hipGetLastError();
 }
 
 int bits_for(int64_t v) {
@@ -1275,12 +1383,8 @@ hipError_t raster_batch(const SegTable& tab_in, Raster& r, bool full_key_sort, b
         bs = blend_st;
     }
     mark(mk, 12, bs);
-    if (count_work)
-        hipLaunchKernelGGL(k_blend<true>, dim3((unsigned)tab.total_tiles), dim3(kBlendThreads), 0, bs, tab, r.ranges,
-                           r.pval[r.sorted_buf], r.rec, (uint32_t)r.max_entries, r.tile_eval);
-    else
-        hipLaunchKernelGGL(k_blend<false>, dim3((unsigned)tab.total_tiles), dim3(kBlendThreads), 0, bs, tab, r.ranges,
-                           r.pval[r.sorted_buf], r.rec, (uint32_t)r.max_entries, r.tile_eval);
+    e = launch_blend(tab, r, count_work, bs);
+    if (e != hipSuccess) return e;
     mark(mk, 13, bs);
     return hipGetLastError();
 }

@@ -114,3 +114,24 @@ def test_many_tiles_two_pass_sort_and_ranges(gs):
     assert_pairs(pairs, ref, ref["pre"]["depth"])
     assert_image(img, ref)
     r.close()
+
+
+@pytest.mark.parametrize("n,W,H", [(2000, 2050, 1585), (2000, 2561, 2449), (700, 1, 1), (900, 17, 33), (1500, 250, 9)])
+def test_halves_and_whole_tiles_match_oracle(gs, n, W, H):
+    """The blend takes quarters of tiles up to 12,288 tiles, halves up to
+    20,480 and whole tiles above: one size of each of the larger two (ragged
+    right and bottom edges), and the smallest ones, where a part of a tile
+    has no pixel at all.  Thin footprints among them, whose exponents are
+    differences of large terms (few enough of them to fit the context's
+    tall footprints and their rows)."""
+    mu, cov, rgb, al = synth.random_gaussians(n, seed=n + W, box=3.0, zc=8.0, s_lo=0.002, s_hi=0.02)
+    cov[::31] = 0.0
+    cov[::31, 0], cov[::31, 3], cov[::31, 5] = 0.09, 1e-6, 1e-6   # needles along x ...
+    cov[::62, 1], cov[::62, 3] = 0.0899, 0.09                  # ... and along the diagonal
+    cam = synth.look_camera((0.1, -0.2, 0), (0.05, 0.02, 1), (0, -1, 0), W, H, math.radians(60), math.radians(60))
+    img, T, nc, pairs, _ = run(gs, mu, cov, rgb, al, cam)
+    ref = oracle.render_gaussians(mu, cov, rgb, al, cam, debug=True)
+    assert_image(img, ref)
+    ok = ref["band"] == 0
+    assert np.abs(T - ref["T"])[ok].max() <= 1e-4
+    assert np.array_equal(nc[ok], ref["n_contrib"][ok])
