@@ -1,5 +1,6 @@
 // C ABI of libgscache (declared in include/gscache.h): context lifetime,
 // scene loading, the stereo camera pair, and the frame entry points.
+#include <algorithm>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
@@ -943,15 +944,6 @@ int gsc_debug_copy(gsc_ctx* c, int what, int eye, void* dst, int64_t cap, int64_
             count = (int64_t)val.size();
             int64_t m = count < cap ? count : cap;
             if (m <= 0) break;
-            if (R.order) {  // pair values are depth ranks: map them back to entries
-                int32_t ne = r.n_entries;
-                std::vector<uint32_t> ord(ne > 0 ? ne : 1);
-                if (ne > 0) HIP_OR_FAIL(c, hipMemcpy(ord.data(), R.order, (size_t)ne * 4, hipMemcpyDeviceToHost));
-                for (auto& v : val) {
-                    const uint32_t x = v & kEntryMask;
-                    v = x < (uint32_t)ne ? ord[x] : kEntryMask;
-                }
-            }
             int32_t* o = (int32_t*)dst;
             const uint32_t stride = r.entry_stride > 1 ? (uint32_t)r.entry_stride : 1u;
             int64_t i = 0;
@@ -1021,16 +1013,21 @@ int gsc_debug_copy(gsc_ctx* c, int what, int eye, void* dst, int64_t cap, int64_
             count = ns;
             int64_t m = count < cap ? count : cap;
             if (m <= 0) break;
-            if (R.pkey64[R.sorted_buf] && (c->cfg.flags & GSC_FLAG_FULL_KEY_SORT)) {
+            if (R.pkey64[R.sorted_buf]) {
                 std::vector<uint64_t> k64(m);
                 HIP_OR_FAIL(c, hipMemcpy(k64.data(), R.pkey64[R.sorted_buf], m * 8, hipMemcpyDeviceToHost));
                 for (int64_t i = 0; i < m; ++i) ((uint32_t*)dst)[i] = (uint32_t)(k64[i] >> 32);
-            } else if (R.key16) {
-                std::vector<uint16_t> k16(m);
-                HIP_OR_FAIL(c, hipMemcpy(k16.data(), R.pkey[R.sorted_buf], m * 2, hipMemcpyDeviceToHost));
-                for (int64_t i = 0; i < m; ++i) ((uint32_t*)dst)[i] = k16[i];
             } else {
-                HIP_OR_FAIL(c, hipMemcpy(dst, R.pkey[R.sorted_buf], m * 4, hipMemcpyDeviceToHost));
+                // the lists are in super-tile order: each item's key is the
+                // super tile whose range holds it
+                SegTable tab = c->last_tab;
+                seg_supers(tab);
+                std::vector<int32_t> rg(2 * (size_t)tab.total_sup);
+                HIP_OR_FAIL(c, hipMemcpy(rg.data(), R.ranges, rg.size() * 4, hipMemcpyDeviceToHost));
+                std::fill((uint32_t*)dst, (uint32_t*)dst + m, 0xffffffffu);
+                for (int32_t q = 0; q < tab.total_sup; ++q)
+                    for (int64_t i = rg[2 * (size_t)q]; i < rg[2 * (size_t)q + 1] && i < m; ++i)
+                        ((uint32_t*)dst)[i] = (uint32_t)q;
             }
             break;
         }

@@ -1,0 +1,826 @@
+// Binning of a raster batch: from the entries' tile spans to every super
+// tile's depth-ordered list.
+//
+//   k_bin<false>   per block of entries, how many items each super tile gets
+//                  (counters in LDS)
+//   k_bin_columns  per super tile, the blocks' first positions and the total
+//   k_bin<true>    every block writes its items (depth key, entry, tile mask)
+//                  at its positions of each super tile's range
+//   k_bin_split    the lists of more than kSortCap items, divided by depth
+//                  into pieces that fit
+//   k_bin_sort     every list and piece in the order (depth key, entry), one
+//                  block each, in LDS
+//   k_bin_merge    long lists whose depths no division separates: their
+//                  chunks, which k_bin_sort sorted one by one
+//
+// One counting pass over the super tiles puts every item in its list, and
+// what is left to sort are lists that fit a block's LDS: two passes over the
+// items in place of a radix sort of the Gaussians by depth (four passes), of
+// the items by super tile (two) and the scans between them, with 14 launches
+// less in a frame.  The order within a list is that of the whole (super tile,
+// depth) key with ties by entry, so it does not depend on the order in which
+// the blocks' lanes take positions.
+//
+// Measured, a whole pass with the radix sorts and with this: 2,000 Gaussians
+// at 256x256 141 and 57 us, 60,000 at 1000x560 194 and 103 us, 500,000 at
+// 1920x1081 325 and 225 us, a stereo frame of 2 x 2048x1080 (6 M items) 729
+// and 699 us.  Of that last one's 230 us the writes take 75: they go to 4,352
+// lists at once, more than an XCD's L2 holds the ends of, so four of five
+// 8-byte items leave it as a partial line of their own (195 MB for 48); the
+// sort takes 74 (LDS), the division of the long lists 48, the counts 28.
+// With more lists the writes gather less and less, and the radix sorts, whose
+// launches are spread over more items, win: batches of stereo images with 6,192
+// super tiles take 588 us binned and 611 radix-sorted, with 13,392 1,031 and
+// 979, with 33,400 2,546 and 2,080.  The line is drawn at kBinLists = 8,192,
+// where a block's counters for all lists still leave room for two blocks a CU.
+#include "gsc_common.h"
+#include "gsc_spans.h"
+
+namespace gsc {
+
+namespace {
+
+constexpr int NB = 1024;            // threads of a counting / writing block
+constexpr int kColTile = 64;        // super tiles per block of k_bin_columns
+constexpr int kColRows = 32;        // blocks' counts a thread of it adds
+constexpr int kMaxBinBlocks = kColRows * (NB / kColTile);
+
+struct BinArgs {
+    SupGeo sg[kMaxSeg];
+    RasterCounters* rc;
+    const uint4* brec;        // binning record per entry
+    const uint4* srow;        // super rows of the tall footprints (see k_tall_spans)
+    const int32_t* srow_y;
+    int64_t srow_cap;
+    uint32_t* hist;           // [blocks][stride] counts, then first positions, of each super tile
+    uint32_t* total;          // [stride]
+    uint64_t* items;          // depth key << 32 | entry << 4 | mask
+    int32_t* ranges;
+    int32_t* n_sort;
+    int32_t* long_lists;      // super tiles with more than kSortCap items
+    int64_t max_pairs;
+    int32_t total_sup, stride;
+    int32_t run;              // entries a block takes at a time: 16 waves of 16, 32 or 64
+};
+
+// Counting: a super row adds one to n neighbouring super tiles, i.e. +1 where
+// it begins and -1 past its end, two updates whatever its width; a running
+// sum over the super tiles then gives the counts.
+__device__ __forceinline__ void count_row(uint32_t* s_cnt, int sup, int n, int total_sup) {
+    atomicAdd(&s_cnt[sup], 1u);
+    if (sup + n < total_sup) atomicAdd(&s_cnt[sup + n], 0xffffffffu);
+}
+
+// Writing: each item at its super tile's next position.
+__device__ __forceinline__ void write_item(const BinArgs& a, uint32_t* s_cnt, int sup, uint32_t low, uint32_t depth) {
+    const uint32_t pos = atomicAdd(&s_cnt[sup], 1u);
+    if ((int64_t)pos < a.max_pairs) a.items[pos] = ((uint64_t)depth << 32) | low;
+}
+
+__device__ __forceinline__ uint32_t lane_word(uint32_t v, int lane) {
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, lane);
+}
+
+// A super row: n items from super tile sup (tile column pair x0) on, the
+// spans sa, sb of its two tile rows.
+struct Row {
+    int n, sup, x0;
+    uint32_t sa, sb;
+};
+
+// Items [from, r.n) of lane l's row r, written by the whole wave.
+__device__ __forceinline__ void write_wide(const BinArgs& a, uint32_t* s_cnt, const Row& r, int l, int from,
+                                           uint32_t entry, uint32_t depth) {
+    const int n = (int)lane_word((uint32_t)r.n, l), x0 = (int)lane_word((uint32_t)r.x0, l);
+    const int sup = (int)lane_word((uint32_t)r.sup, l);
+    const uint32_t sa = lane_word(r.sa, l), sb = lane_word(r.sb, l);
+    for (int k = max(from, 0) + (int)(threadIdx.x & 63); k < n; k += 64)
+        write_item(a, s_cnt, sup + k, (entry << 4) | sup_mask(sa, sb, x0 + k), depth);
+}
+
+// Items of a short footprint's three super rows (n = 0: no such row), one
+// footprint per lane: every lane writes its own first kOwnItems, four at a
+// time with their positions asked for together; the rest of the wide ones
+// are written by the whole wave.  All lanes of the wave take part.
+constexpr int kOwnItems = 12;
+__device__ __forceinline__ void write_rows(const BinArgs& a, uint32_t* s_cnt, uint32_t e, uint32_t depth, const Row& r0,
+                                           const Row& r1, const Row& r2) {
+    const int n01 = r0.n + r1.n, all = n01 + r2.n, own = min(all, kOwnItems);
+    for (int t0 = 0; t0 < own; t0 += 4) {
+        uint32_t pos[4], low[4];
+        bool on[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int t = t0 + q;
+            const bool p1 = t >= r0.n, p2 = t >= n01;  // past row 0, past row 1
+            const int k = t - (p2 ? n01 : (p1 ? r0.n : 0));
+            const int x = (p2 ? r2.x0 : (p1 ? r1.x0 : r0.x0)) + k, c = (p2 ? r2.sup : (p1 ? r1.sup : r0.sup)) + k;
+            low[q] = (e << 4) | sup_mask(p2 ? r2.sa : (p1 ? r1.sa : r0.sa), p2 ? r2.sb : (p1 ? r1.sb : r0.sb), x);
+            on[q] = t < own;
+            pos[q] = on[q] ? atomicAdd(&s_cnt[c], 1u) : 0u;
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            if (on[q] && (int64_t)pos[q] < a.max_pairs) a.items[pos[q]] = ((uint64_t)depth << 32) | low[q];
+    }
+    for (uint64_t wide = __ballot(all > kOwnItems); wide; wide &= wide - 1) {
+        const int l = __ffsll((unsigned long long)wide) - 1;
+        const uint32_t d = lane_word(depth, l), el = lane_word(e, l);
+        const int n0 = (int)lane_word((uint32_t)r0.n, l), n1 = (int)lane_word((uint32_t)n01, l);
+        write_wide(a, s_cnt, r0, l, kOwnItems, el, d);
+        write_wide(a, s_cnt, r1, l, kOwnItems - n0, el, d);
+        write_wide(a, s_cnt, r2, l, kOwnItems - n1, el, d);
+    }
+}
+
+// A footprint's super row at row Y of its image from the spans of its two
+// tile rows.
+__device__ __forceinline__ Row make_row(const SupGeo& sg, int Y, uint32_t sa, uint32_t sb) {
+    Row r;
+    r.sa = sa;
+    r.sb = sb;
+    r.n = (int)sup_cols(sa, sb, r.x0);
+    r.sup = sg.base + Y * sg.nsx + r.x0;
+    return r;
+}
+
+// Block b takes every nblk-th run of the entries, for their short footprints
+// (from their binning records), and every nblk-th run of the stored super
+// rows of the tall ones: entries come in anchor order, coarse levels first, so
+// a contiguous share would give a few blocks all the wide footprints (264 us
+// instead of 20 on the city).  The same runs when counting and when writing.  Blocks go to the XCDs round-robin, so blocks
+// whose items land side by side in every list are given to one XCD: its L2
+// then completes most of the lines that they write parts of.
+template <bool kWrite>
+__global__ __launch_bounds__(NB) void k_bin(BinArgs a) {
+    __shared__ __align__(16) uint32_t s_cnt[kBinLists];
+    __shared__ uint32_t s_part[NB / 64];
+    __shared__ SupGeo s_sg[kMaxSeg];
+    constexpr int PER = kBinLists / NB;
+    const int nblk = gridDim.x, lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int b = nblk % 8 == 0 ? (int)(blockIdx.x % 8) * (nblk / 8) + (int)(blockIdx.x / 8) : (int)blockIdx.x;
+    uint32_t* row = a.hist + (int64_t)b * a.stride;
+    if (threadIdx.x < kMaxSeg) s_sg[threadIdx.x] = a.sg[threadIdx.x];
+    if (kWrite) {
+        // the super tiles' first positions, 8 a thread
+        uint32_t t[PER], sum = 0;
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+            const int c = threadIdx.x * PER + i;
+            t[i] = c < a.stride ? a.total[c] : 0u;
+            sum += t[i];
+        }
+        uint32_t x = sum;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const uint32_t v = __shfl_up(x, o, 64);
+            if (lane >= o) x += v;
+        }
+        if (lane == 63) s_part[wv] = x;
+        __syncthreads();
+        uint32_t first = x - sum;
+        for (int i = 0; i < wv; ++i) first += s_part[i];
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+            const int c = threadIdx.x * PER + i;
+            if (c < a.stride) s_cnt[c] = first + row[c];
+            if (b == 0 && c < a.total_sup) {
+                const int64_t lo = first, hi = min((int64_t)first + t[i], a.max_pairs);
+                const int n = (int)max(hi - lo, (int64_t)0);
+                a.ranges[2 * c] = n ? (int32_t)lo : 0;
+                a.ranges[2 * c + 1] = n ? (int32_t)hi : 0;
+                if (n > kSortCap) a.long_lists[atomicAdd(&a.rc->n_long, 1)] = c;
+            }
+            first += t[i];
+        }
+        if (b == 0 && threadIdx.x == NB - 1) {
+            // (`first` is now the total)
+            const int64_t all = first;
+            a.rc->n_pairs = (int32_t)first;
+            if (all > a.max_pairs) atomicOr(&a.rc->overflow, 1);
+            *a.n_sort = (int32_t)min(all, a.max_pairs);
+        }
+        __syncthreads();
+    } else {
+        for (int c = threadIdx.x; c < a.stride; c += NB) s_cnt[c] = 0u;
+        __syncthreads();
+    }
+    // Sixteen lanes run / 16 entries apart (and up to four neighbours at each):
+    // a Gaussian's eyes and an anchor's Gaussians, which fall on the same super
+    // tiles, come together, and LDS adds to one address wait for each other.
+    // (block-uniform loop: whole waves take part in the wide footprints' items)
+    const int ne = a.rc->n_entries, near = a.run >> 8;
+    const int place = (lane & 15) * (a.run >> 4) + wv * near + (lane >> 4);
+    for (int64_t eb = (int64_t)b * a.run; eb < ne; eb += (int64_t)nblk * a.run) {
+        const int64_t e = eb + place;
+        Row r0{0, 0, 0, 0u, 0u}, r1 = r0, r2 = r0;
+        uint32_t depth = 0;
+        if (e < ne && (lane >> 4) < near) {
+            const uint4 w = a.brec[e];
+            const BinRec r = unpack_bin(w);
+            if (r.binned) {
+                const SupGeo sg = s_sg[r.seg];
+                depth = w.w;
+                // super row i is Y = y0 / 2 + i: tile rows (0, 1), (2, 3)
+                // from an even y0; (-, 0), (1, 2), (3, -) from an odd one
+                const bool odd = r.y0 & 1;
+                const int Y = r.y0 >> kSupShift;
+                r0 = make_row(sg, Y, odd ? kEmptySpan : r.sp[0], odd ? r.sp[0] : r.sp[1]);
+                r1 = make_row(sg, Y + 1, odd ? r.sp[1] : r.sp[2], odd ? r.sp[2] : r.sp[3]);
+                r2 = make_row(sg, Y + 2, odd ? r.sp[3] : kEmptySpan, kEmptySpan);
+            }
+        }
+        if (kWrite) {
+            write_rows(a, s_cnt, (uint32_t)e, depth, r0, r1, r2);
+        } else {
+            if (r0.n) count_row(s_cnt, r0.sup, r0.n, a.total_sup);
+            if (r1.n) count_row(s_cnt, r1.sup, r1.n, a.total_sup);
+            if (r2.n) count_row(s_cnt, r2.sup, r2.n, a.total_sup);
+        }
+    }
+    // the tall footprints' super rows, runs b, b + nblk, ... of kRowRun: a
+    // lane per row of several runs when counting (two updates a row), eight
+    // lanes per row of one run when writing (a lane per item, or nearly: a
+    // lane per row writes the city's in 103 us instead of 76)
+    constexpr int kRowLanes = kWrite ? 8 : 1, kRowRun = NB / 8, kRuns = 8 / kRowLanes;
+    const int64_t nsr = min((int64_t)a.rc->n_srows, a.srow_cap);
+    const int sub = threadIdx.x % kRowLanes, at = threadIdx.x / kRowLanes;
+    for (int64_t q = ((int64_t)b + (at / kRowRun) * nblk) * kRowRun + at % kRowRun; q < nsr;
+         q += (int64_t)nblk * kRowRun * kRuns) {
+        const uint4 sr = a.srow[q];
+        const uint32_t e = sr.z, ys = (uint32_t)a.srow_y[q];
+        int x0;
+        const int n = (int)sup_cols(sr.x, sr.y, x0);
+        if (sub >= n) continue;
+        const SupGeo sg = s_sg[(ys >> kRowSegShift) % kMaxSeg];
+        const int64_t sup = sg.base + (int64_t)(ys & kRowMask) * sg.nsx + x0;
+        // (a row that a capacity overflow left unwritten may hold anything)
+        if (e >= (uint32_t)ne || sup < 0 || sup + n > a.total_sup) continue;
+        if (!kWrite) {
+            count_row(s_cnt, (int)sup, n, a.total_sup);
+            continue;
+        }
+        const uint32_t depth = a.brec[e].w;
+        for (int k = sub; k < n; k += kRowLanes)
+            write_item(a, s_cnt, (int)sup + k, (e << 4) | sup_mask(sr.x, sr.y, x0 + k), depth);
+    }
+    if (!kWrite) {
+        // the running sum over the super tiles, 8 a thread
+        __syncthreads();
+        uint32_t t[PER], sum = 0;
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+            const int c = threadIdx.x * PER + i;
+            sum += c < a.stride ? s_cnt[c] : 0u;
+            t[i] = sum;
+        }
+        uint32_t x = sum;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const uint32_t v = __shfl_up(x, o, 64);
+            if (lane >= o) x += v;
+        }
+        if (lane == 63) s_part[wv] = x;
+        __syncthreads();
+        uint32_t before = x - sum;
+        for (int i = 0; i < wv; ++i) before += s_part[i];
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+            const int c = threadIdx.x * PER + i;
+            if (c < a.stride) row[c] = c < a.total_sup ? before + t[i] : 0u;
+        }
+    }
+}
+
+// kColTile columns (super tiles): each column's counts become exclusive
+// prefixes over the blocks, in place, and its total.  A thread holds kColRows counts of one column, all in flight at once.
+__global__ __launch_bounds__(NB) void k_bin_columns(uint32_t* __restrict__ hist, uint32_t* __restrict__ total,
+                                                    int nblk, int stride) {
+    constexpr int NG = NB / kColTile;
+    __shared__ uint32_t s_sum[NG][kColTile];
+    const int col = threadIdx.x % kColTile, rg = threadIdx.x / kColTile;
+    const int c = blockIdx.x * kColTile + col;
+    const int per = (nblk + NG - 1) / NG;  // at most kColRows
+    uint32_t* h = hist + c;
+    uint32_t v[kColRows], sum = 0;
+#pragma unroll
+    for (int i = 0; i < kColRows; ++i) {
+        const int r = rg * per + i;
+        v[i] = i < per && r < nblk ? h[(int64_t)r * stride] : 0u;
+        sum += v[i];
+    }
+    s_sum[rg][col] = sum;
+    __syncthreads();
+    uint32_t pre = 0, all = 0;
+    for (int i = 0; i < NG; ++i) {
+        const uint32_t x = s_sum[i][col];
+        pre += i < rg ? x : 0u;
+        all += x;
+    }
+#pragma unroll
+    for (int i = 0; i < kColRows; ++i) {
+        const int r = rg * per + i;
+        if (i < per && r < nblk) h[(int64_t)r * stride] = pre;
+        pre += v[i];
+    }
+    if (rg == 0) total[c] = all;
+}
+
+// ------------------------------------------------------------------ lists
+constexpr int NS = 256;  // threads of a sorting block
+static_assert(NS * 8 == kSortCap, "a list is at most 8 items a thread");
+
+__device__ __forceinline__ uint32_t list_word(uint64_t item) {
+    const uint32_t low = (uint32_t)item;
+    return (low >> 4) | (low << kMaskShift);  // entry | mask << kMaskShift
+}
+static_assert(kMaskShift == 28, "an item's low word is the list word rotated by the mask's four bits");
+
+// Bucket of a depth key among nb over the keys [lo, lo + span]: every step of
+// the mapping is monotone, so the buckets are in depth order.
+__device__ __forceinline__ int bucket_of(uint32_t key, uint32_t lo, float scale, int nb) {
+    return min((int)((float)(key - lo) * scale), nb - 1);
+}
+__device__ __forceinline__ float bucket_scale(uint32_t lo, uint32_t hi, int nb) {
+    return (float)nb / ((float)(hi - lo) + 1.f);
+}
+
+// The same with the buckets of equal share of n items (share = nb / n) whose
+// counts up to each of the buckets above are cdf: the distribution function,
+// linear within a bucket.  Rounded at every step (an exact f - bk from an
+// unrounded product could be negative where f rounds up to bk, and the
+// order of the buckets with it).
+__device__ __forceinline__ int bucket_by_share(uint32_t key, uint32_t lo, float scale, int nb,
+                                               const uint16_t* __restrict__ cdf, float share) {
+#pragma clang fp contract(off)
+    const float f = (float)(key - lo) * scale;
+    const int bk = min((int)f, nb - 1);
+    const float c0 = (float)cdf[bk], c1 = (float)cdf[bk + 1];
+    const float at = c0 + fminf(f - (float)bk, 1.f) * (c1 - c0);
+    return min((int)(at * share), nb - 1);
+}
+
+// Smallest and largest of the block's values; s2: 2 x waves words.
+template <int kThreads>
+__device__ __forceinline__ void block_min_max(uint32_t& lo, uint32_t& hi, uint32_t* s2) {
+    for (int o = 32; o > 0; o >>= 1) {
+        lo = min(lo, (uint32_t)__shfl_xor((int)lo, o, 64));
+        hi = max(hi, (uint32_t)__shfl_xor((int)hi, o, 64));
+    }
+    constexpr int W = kThreads / 64;
+    if ((threadIdx.x & 63) == 0) {
+        s2[threadIdx.x >> 6] = lo;
+        s2[W + (threadIdx.x >> 6)] = hi;
+    }
+    __syncthreads();
+    for (int i = 0; i < W; ++i) {
+        lo = min(lo, s2[i]);
+        hi = max(hi, s2[W + i]);
+    }
+    __syncthreads();
+}
+
+// Exclusive prefixes of the block's n counts in place (c[n] = the total), and
+// the largest count; n is a multiple of the threads, PER = n / threads.
+template <int kThreads, int PER>
+__device__ __forceinline__ uint32_t block_scan_counts(uint32_t* c, uint32_t* s2) {
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    constexpr int W = kThreads / 64;
+    uint32_t v[PER], sum = 0, big = 0;
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+        v[i] = c[threadIdx.x * PER + i];
+        sum += v[i];
+        big = max(big, v[i]);
+    }
+    uint32_t x = sum;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t y = __shfl_up(x, o, 64);
+        if (lane >= o) x += y;
+    }
+    for (int o = 32; o > 0; o >>= 1) big = max(big, (uint32_t)__shfl_xor((int)big, o, 64));
+    if (lane == 63) s2[wv] = x;
+    if (lane == 0) s2[W + wv] = big;
+    __syncthreads();
+    uint32_t first = x - sum;
+    for (int i = 0; i < W; ++i) {
+        first += i < wv ? s2[i] : 0u;
+        big = max(big, s2[W + i]);
+    }
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+        c[threadIdx.x * PER + i] = first;
+        first += v[i];
+    }
+    if (threadIdx.x == kThreads - 1) c[kThreads * PER] = first;
+    __syncthreads();
+    return big;
+}
+
+
+__device__ __forceinline__ void order_pair(uint64_t& x, uint64_t& y) {
+    const uint64_t lo = x < y ? x : y, hi = x < y ? y : x;
+    x = lo;
+    y = hi;
+}
+
+// Batcher's odd-even merge sort of K values in registers.
+template <int K>
+__device__ __forceinline__ void sort_regs(uint64_t (&v)[K]) {
+#pragma unroll
+    for (int p = 1; p < K; p <<= 1)
+#pragma unroll
+        for (int k = p; k >= 1; k >>= 1)
+#pragma unroll
+            for (int j = k % p; j + k < K; j += 2 * k)
+#pragma unroll
+                for (int i = 0; i < k; ++i)
+                    if (i + j + k < K && (i + j) / (2 * p) == (i + j + k) / (2 * p)) order_pair(v[i + j], v[i + j + k]);
+}
+
+// Merge sort of n <= NS * 8 items, 8 a thread (item i of thread t: v[j], t * 8
+// + j, padded with ~0): in registers, then merges of runs twice as long each,
+// every thread finding where its 8 outputs begin in the two runs (a binary
+// search along the merge path) and merging from there.  Whatever the keys.
+// Runs of one wave's threads need no block barrier.
+__device__ __forceinline__ void merge_sort(int n, uint64_t* lds, uint64_t (&v)[8]) {
+    constexpr int K = 8;
+    const int o = threadIdx.x * K;
+    sort_regs<K>(v);
+    for (int L = K; L < n; L <<= 1) {
+        const bool block = 2 * L > 64 * K;
+        // (the runs' readers are done: a wave's own LDS accesses complete in order)
+        if (block) __syncthreads();
+        else __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int j = 0; j < K; ++j) lds[(o + j)] = v[j];
+        if (block) __syncthreads();
+        else __builtin_amdgcn_wave_barrier();
+        const int base = o & ~(2 * L - 1), d = o - base;
+        if (base + L >= n) continue;  // the second run is all padding: already in order
+        const int A = base, B = base + L;
+        int lo = d > L ? d - L : 0, hi = d < L ? d : L;
+        while (lo < hi) {
+            const int mid = (lo + hi) >> 1;
+            if (lds[(A + mid)] <= lds[(B + d - 1 - mid)]) lo = mid + 1;
+            else hi = mid;
+        }
+        int ia = lo, ib = d - lo;
+        uint64_t ka = ia < L ? lds[(A + ia)] : ~0ull, kb = ib < L ? lds[(B + ib)] : ~0ull;
+#pragma unroll
+        for (int j = 0; j < K; ++j) {
+            const bool ta = ka <= kb;
+            v[j] = ta ? ka : kb;
+            ia += ta ? 1 : 0;
+            ib += ta ? 0 : 1;
+            const int i = ta ? ia : ib;
+            const uint64_t nx = i < L ? lds[((ta ? A : B) + i)] : ~0ull;
+            ka = ta ? nx : ka;
+            kb = ta ? kb : nx;
+        }
+    }
+}
+
+// A long list's pieces and chunks: pos, count, and for a piece (by_index) the
+// list's first item.
+struct SortPiece {
+    int32_t pos, n, list, by_index;
+};
+static_assert(sizeof(SortPiece) == sizeof(int4), "one 16-byte word");
+
+// Divides the long lists by depth: a block per list counts its items into
+// kSplitBuckets buckets between its nearest and farthest, writes the items'
+// indices in bucket order to the list's (not yet used) words, and hands the
+// buckets out as pieces of kPieceRun items or more, up to kSortCap.  The
+// items themselves stay where they are.  A list that this does not divide
+// (one bucket holds too much, or it has more pieces than the block counts)
+// is sorted in chunks and merged instead.
+constexpr int NP = 1024;
+constexpr int kSplitBuckets = 8192;
+constexpr int kPieceRun = kSortCap / 2;
+constexpr int kMaxPieces = 2048;
+__global__ __launch_bounds__(NP) void k_bin_split(const uint64_t* __restrict__ items, const int32_t* __restrict__ ranges,
+                                                  const int32_t* __restrict__ long_lists, RasterCounters* rc,
+                                                  SortPiece* __restrict__ pieces, uint2* __restrict__ chunks,
+                                                  uint32_t* __restrict__ words) {
+    __shared__ uint32_t s_cnt[kSplitBuckets + 1];
+    __shared__ uint32_t s_piece[kMaxPieces + 1];
+    __shared__ uint32_t s_red[2 * NP / 64];
+    const int nl = rc->n_long;
+    for (int li = blockIdx.x; li < nl; li += gridDim.x) {
+        const int S = long_lists[li];
+        const int start = ranges[2 * S], n = ranges[2 * S + 1] - start;
+        const uint64_t* src = items + start;
+        uint32_t lo = 0xffffffffu, hi = 0u;
+#pragma unroll 4
+        for (int i = threadIdx.x; i < n; i += NP) {
+            const uint32_t k = (uint32_t)(src[i] >> 32);
+            lo = min(lo, k);
+            hi = max(hi, k);
+        }
+        for (int i = threadIdx.x; i < kSplitBuckets; i += NP) s_cnt[i] = 0u;
+        block_min_max<NP>(lo, hi, s_red);
+        const float scale = bucket_scale(lo, hi, kSplitBuckets);
+#pragma unroll 4
+        for (int i = threadIdx.x; i < n; i += NP)
+            atomicAdd(&s_cnt[bucket_of((uint32_t)(src[i] >> 32), lo, scale, kSplitBuckets)], 1u);
+        __syncthreads();
+        const uint32_t big = block_scan_counts<NP, kSplitBuckets / NP>(s_cnt, s_red);
+        const int np = (n + kPieceRun - 1) / kPieceRun;
+        if (big > (uint32_t)kPieceRun || np > kMaxPieces) {  // block-uniform
+            if (threadIdx.x == 0) {
+                const int m = (n + kSortCap - 1) / kSortCap, at = atomicAdd(&rc->n_chunks, m);
+                for (int q = 0; q < m; ++q) chunks[at + q] = make_uint2((uint32_t)S, (uint32_t)q);
+            }
+            __syncthreads();
+            continue;
+        }
+        // piece p begins at the first bucket that begins at or after p * kPieceRun
+        for (int i = threadIdx.x; i <= np; i += NP) s_piece[i] = (uint32_t)n;
+        __syncthreads();
+        for (int i = threadIdx.x; i < kSplitBuckets; i += NP)
+            if (s_cnt[i + 1] > s_cnt[i]) atomicMin(&s_piece[s_cnt[i] / kPieceRun], s_cnt[i]);
+        __syncthreads();
+        for (int p = threadIdx.x; p < np; p += NP) {
+            const uint32_t first = s_piece[p];
+            if (first >= (uint32_t)n) continue;  // no bucket begins there
+            int q = p + 1;
+            while (q < np && s_piece[q] >= (uint32_t)n) ++q;
+            const uint32_t end = q < np ? s_piece[q] : (uint32_t)n;
+            pieces[atomicAdd(&rc->n_pieces, 1)] = SortPiece{start + (int)first, (int)(end - first), start, 1};
+        }
+        __syncthreads();  // (the prefixes become cursors)
+#pragma unroll 4
+        for (int i = threadIdx.x; i < n; i += NP) {
+            const uint32_t at = atomicAdd(&s_cnt[bucket_of((uint32_t)(src[i] >> 32), lo, scale, kSplitBuckets)], 1u);
+            words[start + at] = (uint32_t)i;
+        }
+        __syncthreads();  // before the next list
+    }
+}
+
+// Blocks up to total_sup: one super tile's list each, if it fits; the blocks
+// after them: the long lists' pieces, and the chunks for k_bin_merge (in
+// place).
+//
+// A list is spread over buckets between its nearest and farthest item (four
+// items or so each), an item's place among its bucket's is the number of
+// smaller ones there: O(n) LDS accesses, where a merge sort's twelve rounds
+// of data-dependent reads conflict on the banks at every step.  Where the
+// depths crowd (a near footprint among far ones is enough), the counts
+// themselves say how: read as a piecewise linear distribution function they
+// spread the same keys over buckets of equal share.  What still crowds after
+// that (ties, mostly) takes the merge sort.
+constexpr int kBuckets = 1024;
+constexpr uint32_t kCrowd = 64;
+__global__ __launch_bounds__(NS) __attribute__((amdgpu_waves_per_eu(6))) void k_bin_sort(uint64_t* __restrict__ items, const int32_t* __restrict__ ranges,
+                                                 int total_sup, const RasterCounters* rc,
+                                                 const SortPiece* __restrict__ pieces,
+                                                 const uint2* __restrict__ chunks, uint32_t* __restrict__ words) {
+    __shared__ uint64_t lds[kSortCap];
+    __shared__ uint32_t s_cnt[kBuckets + 1];
+    __shared__ uint16_t s_cdf[kBuckets + 2];
+    __shared__ uint32_t s_red[2 * NS / 64];
+    const bool own = (int)blockIdx.x < total_sup;
+    const int np = own ? 1 : rc->n_pieces, total = own ? 1 : np + rc->n_chunks;
+    const int step = own ? 1 : (int)gridDim.x - total_sup;
+    for (int i = own ? 0 : (int)blockIdx.x - total_sup; i < total; i += step) {  // block-uniform
+        SortPiece p;
+        if (own) {
+            p = SortPiece{ranges[2 * blockIdx.x], 0, 0, 0};
+            p.n = ranges[2 * blockIdx.x + 1] - p.pos;
+            if (p.n <= 0 || p.n > kSortCap) return;
+        } else if (i < np) {
+            p = pieces[i];
+        } else {
+            const uint2 ch = chunks[i - np];
+            p = SortPiece{ranges[2 * ch.x] + (int)ch.y * kSortCap, 0, 0, 2};
+            p.n = min(ranges[2 * ch.x + 1] - p.pos, kSortCap);
+        }
+        const int n = p.n;
+        if (p.by_index < 2) {
+            uint64_t v[8];
+            uint32_t r[8];
+            uint32_t lo = 0xffffffffu, hi = 0u;
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                const int k = j * NS + (int)threadIdx.x;
+                v[j] = ~0ull;
+                if (k < n) {
+                    v[j] = p.by_index ? items[p.list + words[p.pos + k]] : items[p.pos + k];
+                    lo = min(lo, (uint32_t)(v[j] >> 32));
+                    hi = max(hi, (uint32_t)(v[j] >> 32));
+                }
+            }
+            for (int k = threadIdx.x; k < kBuckets; k += NS) s_cnt[k] = 0u;
+            block_min_max<NS>(lo, hi, s_red);
+            const float scale = bucket_scale(lo, hi, kBuckets);
+            bool eq = false;  // equalised buckets
+            const float share = (float)kBuckets / (float)n;
+            auto bucket = [&](uint64_t x) {
+                const uint32_t key = (uint32_t)(x >> 32);
+                return eq ? bucket_by_share(key, lo, scale, kBuckets, s_cdf, share) : bucket_of(key, lo, scale, kBuckets);
+            };
+            auto count = [&]() {
+#pragma unroll
+                for (int j = 0; j < 8; ++j)
+                    if (j * NS + (int)threadIdx.x < n) r[j] = atomicAdd(&s_cnt[bucket(v[j])], 1u);
+                __syncthreads();
+                return block_scan_counts<NS, kBuckets / NS>(s_cnt, s_red);
+            };
+            uint32_t big = count();
+            if (big > kCrowd) {  // block-uniform
+                for (int k = threadIdx.x; k <= kBuckets; k += NS) s_cdf[k] = (uint16_t)s_cnt[k];
+                __syncthreads();
+                for (int k = threadIdx.x; k < kBuckets; k += NS) s_cnt[k] = 0u;
+                eq = true;
+                __syncthreads();
+                big = count();
+            }
+            if (big <= kCrowd) {
+#pragma unroll
+                for (int j = 0; j < 8; ++j)
+                    if (j * NS + (int)threadIdx.x < n) lds[s_cnt[bucket(v[j])] + r[j]] = v[j];
+                __syncthreads();
+                for (int k = threadIdx.x; k < n; k += NS) {
+                    const uint64_t x = lds[k];
+                    const int bk = bucket(x);
+                    const int b0 = (int)s_cnt[bk], b1 = (int)s_cnt[bk + 1];
+                    int at = b0;
+                    for (int q = b0; q < b1; ++q) at += lds[q] < x ? 1 : 0;
+                    words[p.pos + at] = list_word(x);
+                }
+                __syncthreads();  // before the next piece
+                continue;
+            }
+            // crowded: back to 8 consecutive items a thread
+#pragma unroll
+            for (int j = 0; j < 8; ++j) lds[(j * NS + (int)threadIdx.x)] = v[j];
+            __syncthreads();
+            const int o = threadIdx.x * 8;
+#pragma unroll
+            for (int j = 0; j < 8; ++j) v[j] = lds[(o + j)];
+            __syncthreads();
+            merge_sort(n, lds, v);
+#pragma unroll
+            for (int j = 0; j < 8; ++j)
+                if (o + j < n) words[p.pos + o + j] = list_word(v[j]);
+        } else {
+            uint64_t v[8];
+            const int o = threadIdx.x * 8;
+#pragma unroll
+            for (int j = 0; j < 8; ++j) v[j] = o + j < n ? items[p.pos + o + j] : ~0ull;
+            merge_sort(n, lds, v);
+#pragma unroll
+            for (int j = 0; j < 8; ++j)
+                if (o + j < n) items[p.pos + o + j] = v[j];
+        }
+        __syncthreads();
+    }
+}
+
+// Sorted chunks of a list: a block takes kMergeRun consecutive items of one;
+// an item's place is its index plus the items before it in every other
+// chunk, which are found in that chunk's window between the run's first and
+// last item, through LDS.
+constexpr int kMergeRun = 1024, NM = 256;
+__global__ __launch_bounds__(NM) void k_bin_merge(const uint64_t* __restrict__ items,
+                                                  const int32_t* __restrict__ ranges, const RasterCounters* rc,
+                                                  const uint2* __restrict__ chunks, uint32_t* __restrict__ words) {
+    constexpr int PER = kMergeRun / NM, kUnits = kSortCap / kMergeRun;
+    __shared__ uint64_t s_win[kMergeRun];
+    __shared__ int s_lo[NM], s_hi[NM];
+    const int nu = rc->n_chunks * kUnits;
+    for (int u = blockIdx.x; u < nu; u += gridDim.x) {
+        const uint2 ch = chunks[u / kUnits];
+        const int start = ranges[2 * ch.x], n = ranges[2 * ch.x + 1] - start;
+        const int m = (n + kSortCap - 1) / kSortCap;
+        const int mine = (int)ch.y * kSortCap;                  // the chunk's first item within the list
+        const int mlen = min(n - mine, kSortCap), r0 = (u % kUnits) * kMergeRun;
+        const int cnt = min(mlen - r0, kMergeRun);
+        if (cnt <= 0) continue;  // block-uniform
+        const uint64_t* list = items + start;
+        uint64_t v[PER];
+        int rank[PER];
+#pragma unroll
+        for (int j = 0; j < PER; ++j) {
+            const int i = j * NM + (int)threadIdx.x;
+            v[j] = i < cnt ? list[mine + r0 + i] : ~0ull;
+            rank[j] = r0 + i;
+        }
+        const uint64_t first = list[mine + r0], last = list[mine + r0 + cnt - 1];
+        for (int g0 = 0; g0 < m; g0 += NM) {  // the other chunks, NM windows at a time
+            const int gn = min(m - g0, NM);
+            __syncthreads();
+            if ((int)threadIdx.x < gn) {
+                const int c = g0 + threadIdx.x;
+                const uint64_t* p = list + (int64_t)c * kSortCap;
+                const int len = min(n - c * kSortCap, kSortCap);
+                int w[2];
+#pragma unroll
+                for (int q = 0; q < 2; ++q) {
+                    const uint64_t key = q ? last : first;
+                    int lo = 0, hi = len;
+                    while (lo < hi) {
+                        const int mid = (lo + hi) >> 1;
+                        if (p[mid] < key) lo = mid + 1;
+                        else hi = mid;
+                    }
+                    w[q] = lo;
+                }
+                s_lo[threadIdx.x] = w[0];
+                s_hi[threadIdx.x] = w[1];
+            }
+            __syncthreads();
+            for (int q = 0; q < gn; ++q) {
+                const int c = g0 + q;
+                if (c == (int)ch.y) continue;
+                const int wl = s_lo[q], wh = s_hi[q];
+#pragma unroll
+                for (int j = 0; j < PER; ++j) rank[j] += wl;
+                const uint64_t* p = list + (int64_t)c * kSortCap;
+                for (int t0 = wl; t0 < wh; t0 += kMergeRun) {  // block-uniform bounds
+                    const int tn = min(wh - t0, kMergeRun);
+                    __syncthreads();
+                    for (int i = threadIdx.x; i < tn; i += NM) s_win[i] = p[t0 + i];
+                    __syncthreads();
+#pragma unroll
+                    for (int j = 0; j < PER; ++j) {
+                        int lo = 0, hi = tn;
+                        while (lo < hi) {
+                            const int mid = (lo + hi) >> 1;
+                            if (s_win[mid] < v[j]) lo = mid + 1;
+                            else hi = mid;
+                        }
+                        rank[j] += lo;
+                    }
+                }
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < PER; ++j) {
+            const int i = j * NM + (int)threadIdx.x;
+            if (i < cnt) words[start + rank[j]] = list_word(v[j]);
+        }
+    }
+}
+
+}  // namespace
+
+hipError_t bin_items(const SegTable& tab, Raster& r, hipStream_t st, Marks* mk) {
+    BinArgs a;
+    for (int q = 0; q < kMaxSeg; ++q)
+        a.sg[q] = SupGeo{q < tab.n ? tab.s[q].sup_base : 0, q < tab.n ? tab.s[q].nsx : 0};
+    a.rc = r.cnt; a.brec = r.brec; a.srow = r.srow; a.srow_y = r.srow_y; a.srow_cap = r.srow_cap;
+    a.items = r.items; a.ranges = r.ranges; a.n_sort = r.n_sort; a.long_lists = r.long_lists;
+    a.max_pairs = r.max_pairs; a.total_sup = tab.total_sup;
+    a.stride = (tab.total_sup + kColTile - 1) / kColTile * kColTile;
+    if (a.stride > kBinLists) return hipErrorInvalidValue;
+    const int per = tab.paired ? 2 : 1;
+    int64_t entries = 0;  // where the host knows them
+    for (int q = 0; q < tab.n; q += per)
+        entries = entries < 0 || tab.s[q].nG ? -1 : entries + per * (int64_t)tab.s[q].nG_host;
+    if (entries < 0 || entries > r.max_entries) entries = r.max_entries;
+    // Blocks: one per run of entries, up to what two blocks on every CU hold
+    // (more only lengthen k_bin_columns), within the counts' buffer.  A batch
+    // that runs of 1,024 would leave on a few CUs takes shorter ones, with
+    // fewer footprints to a wave (k_bin<true> of 60,000 Gaussians 18 -> 13 us,
+    // of 2,000 13 -> 9 us).  The counts lie in a buffer of the radix sorts,
+    // idle here: the second value buffer, or the digit counts where that is
+    // smaller.
+    const int64_t digits = 256 * (int64_t)kSortBlocks, hist_cap = r.max_pairs > digits ? r.max_pairs : digits;
+    a.run = entries <= 64 * 1024 ? 256 : (entries <= 128 * 1024 ? 512 : 1024);
+    int64_t nblk = (entries + a.run - 1) / a.run;
+    if (nblk > kMaxBinBlocks) nblk = kMaxBinBlocks;
+    if (nblk > hist_cap / a.stride) nblk = hist_cap / a.stride;
+    if (nblk < 1) nblk = 1;
+    if (nblk >= 8) nblk &= ~(int64_t)7;
+    a.hist = r.max_pairs > digits ? r.pval[1] : r.hist;
+    a.total = r.sup_total;
+    mark(mk, 6, st);
+    hipLaunchKernelGGL(k_bin<false>, dim3((unsigned)nblk), dim3(NB), 0, st, a);
+    hipLaunchKernelGGL(k_bin_columns, dim3((unsigned)(a.stride / kColTile)), dim3(NB), 0, st, a.hist, r.sup_total,
+                       (int)nblk, a.stride);
+    mark(mk, 7, st);
+    hipLaunchKernelGGL(k_bin<true>, dim3((unsigned)nblk), dim3(NB), 0, st, a);
+    mark(mk, 8, st);
+    mark(mk, 9, st);
+    mark(mk, 10, st);
+    // a list longer than kSortCap needs as many entries
+    const bool longer = entries > kSortCap;
+    SortPiece* pieces = reinterpret_cast<SortPiece*>(r.pieces);
+    if (longer)
+        hipLaunchKernelGGL(k_bin_split, grid_fit(k_bin_split, (int64_t)tab.total_sup * NP, NP), dim3(NP), 0, st, r.items,
+                           r.ranges, r.long_lists, r.cnt, pieces, r.chunks, r.pval[0]);
+    hipLaunchKernelGGL(k_bin_sort, dim3((unsigned)(tab.total_sup + (longer ? 1024 : 0))), dim3(NS), 0, st, r.items,
+                       r.ranges, tab.total_sup, r.cnt, pieces, r.chunks, r.pval[0]);
+    if (longer)
+        hipLaunchKernelGGL(k_bin_merge, grid_fit(k_bin_merge, r.max_pairs / 4, NM), dim3(NM), 0, st, r.items, r.ranges,
+                           r.cnt, r.chunks, r.pval[0]);
+    mark(mk, 11, st);
+    r.sorted_buf = 0;
+    return hipGetLastError();
+}
+
+}  // namespace gsc

@@ -27,6 +27,8 @@ constexpr int kMaxSeg = 16;           // (viewer, eye) images per raster batch
 constexpr int kGridBlocks = 2048;     // fixed grid of the grid-stride kernels
 constexpr int kScanBlocks = 1024;     // blocks of the device-wide scan
 constexpr int kSortBlocks = 1024;     // blocks of each radix pass
+constexpr int kSortCap = 2048;        // items a block sorts in LDS (binning)
+constexpr int kBinLists = 8192;       // super tiles of the largest batch that is binned
 constexpr int kF = 32;                // feature length the kernels are built for
 constexpr int kH = 32;                // MLP hidden width the kernels are built for
 constexpr int kMaxK = 16;             // max neural Gaussians per anchor
@@ -63,6 +65,9 @@ struct RasterCounters {
     int32_t n_srows;              // their super rows (pairs of tile rows), stored
     int32_t overflow;             // bit0: pair capacity, bit1: entries, bit2: tall footprints' super rows
     int32_t n_gpairs;             // entries / 2: the depth sort's length when the eyes share it
+    int32_t n_long;               // super tiles whose lists are longer than kSortCap
+    int32_t n_pieces;             // the pieces they are sorted in
+    int32_t n_chunks;             // chunks of those that are merged instead
 };
 
 // One (viewer, eye) image of a raster batch; passed by value in kernel args.
@@ -194,18 +199,26 @@ struct Raster {
     int64_t tall_cap = 0;
     uint4* srow = nullptr;        // [srow_cap] super rows of the tall footprints: span of tile row 2 Y,
                                   // of tile row 2 Y + 1 (lo | hi << 16), entry, items of the earlier ones
-    int32_t* srow_y = nullptr;    // [srow_cap] Y of each stored super row
+    int32_t* srow_y = nullptr;    // [srow_cap] Y | segment of each stored super row
     int64_t srow_cap = 0;
     uint32_t* ntiles = nullptr; // tile count per entry
-    uint32_t* nsup = nullptr;   // (super tile, entry) pair count per entry
-    uint32_t* scnt = nullptr;   // pair count per depth rank
-    int32_t* n_sort = nullptr;  // [1] pairs to sort (clamped to capacity)
-    uint32_t* dkey[2] = {nullptr, nullptr};  // depth keys (double buffer)
-    uint32_t* dval[2] = {nullptr, nullptr};  // entry ids
-    uint32_t* offs = nullptr;   // pair offset per depth rank
+    uint4* brec = nullptr;      // binning record per entry (gsc_spans.h)
+    int32_t* n_sort = nullptr;  // [1] (super tile, entry) items (clamped to capacity)
+    uint64_t* items = nullptr;  // [max_pairs] depth key << 32 | entry << 4 | mask, by super tile
+    int32_t* long_lists = nullptr;  // [max_pairs / kSortCap + 1] super tiles with more than kSortCap items
+    int4* pieces = nullptr;     // [max_pairs / 512 + 1] their pieces (see k_bin_split)
+    uint2* chunks = nullptr;    // [max_pairs / (kSortCap / 2) + 1] chunks of those merged (super tile, chunk)
+    uint32_t* sup_total = nullptr;  // [kBinLists] items per super tile
+    // in place of brec and items, the radix sorts' double buffers (depth keys,
+    // entry ids; super-tile ids), and their counts and offsets
+    uint32_t* dkey[2] = {nullptr, nullptr};
+    uint32_t* dval[2] = {nullptr, nullptr};
+    uint32_t* pkey[2] = {nullptr, nullptr};
+    uint32_t* nsup = nullptr;   // item count per entry
+    uint32_t* scnt = nullptr;   // item count per depth rank
+    uint32_t* offs = nullptr;   // item offset per depth rank (per entry with full keys)
     int32_t* tile_eval = nullptr;  // [max_tiles][2] blend visits and contributions of each tile
-    uint32_t* pkey[2] = {nullptr, nullptr};  // global tile id
-    uint32_t* pval[2] = {nullptr, nullptr};  // entry id
+    uint32_t* pval[2] = {nullptr, nullptr};  // list words: entry | mask << kMaskShift
     uint64_t* pkey64[2] = {nullptr, nullptr};// full-key mode
     int32_t* ranges = nullptr;  // [max_tiles][2]
     uint32_t* hist = nullptr;   // [256 * kSortBlocks] radix digit counts per block
@@ -213,10 +226,9 @@ struct Raster {
     uint64_t* block_sums64 = nullptr;  // [kScanBlocks] scan scratch of the tall path's 64-bit scan
     RasterCounters* cnt = nullptr;
     RasterCounters* cnt_host = nullptr;
-    int sorted_buf = 0;         // which pkey/pval buffer holds the sorted pairs
-    bool key16 = false;         // the last batch's tile keys were 16-bit (pkey read as uint16_t)
-    bool shared_depth = false;  // this batch's eyes of a view share one depth sort
-    const uint32_t* order = nullptr;  // depth rank -> entry (null: pair values are entries)
+    int sorted_buf = 0;         // which pval (pkey, pkey64) buffer holds the sorted items
+    bool binned = false;        // this batch's lists come from bin_items
+    bool shared_depth = false;  // this batch's eyes of a view share their depth keys
     size_t bytes = 0;
 };
 
@@ -227,11 +239,11 @@ struct Raster {
 // writing exclusive prefixes to out and the total to *total (device).
 hipError_t scan_u32(const uint32_t* in, uint32_t* out, const int32_t* n_dev, int64_t n_host, int32_t* total,
                     uint32_t* block_sums, hipStream_t st);
-// Exclusive scan of n (from *n_dev) uint64 values, each two 32-bit counts
-// (low, high) that scan independently; the totals of the two go to
-// *total_lo and *total_hi (device).  block_sums: kScanBlocks values.
-hipError_t scan_u64(const uint64_t* in, uint64_t* out, const int32_t* n_dev, int32_t* total_lo, int32_t* total_hi,
-                    uint64_t* block_sums, hipStream_t st);
+// Exclusive scan of n (from *n_dev, at most n_max) uint64 values, each two
+// 32-bit counts (low, high) that scan independently; the totals of the two go
+// to *total_lo and *total_hi (device).  block_sums: kScanBlocks values.
+hipError_t scan_u64(const uint64_t* in, uint64_t* out, const int32_t* n_dev, int64_t n_max, int32_t* total_lo,
+                    int32_t* total_hi, uint64_t* block_sums, hipStream_t st);
 // Stream compaction: ids[k] = the k-th i with flags[i] != 0 (flags 0 or 1,
 // n from *n_dev if non-null), the count to *total (device).
 hipError_t compact_u32(const uint32_t* flags, const int32_t* n_dev, int64_t n_host, int32_t* total, int32_t* ids,
@@ -251,14 +263,11 @@ hipError_t compact_u32(const uint32_t* flags, const int32_t* n_dev, int64_t n_ho
 hipError_t radix_sort_u32(uint32_t* keys[2], uint32_t* vals[2], const int32_t* n_dev, int64_t n_host, int bit0,
                           int bit1, uint32_t* hist, uint32_t* block_sums, int* which, hipStream_t st,
                           const uint32_t* gsrc = nullptr, uint32_t* gout = nullptr, bool pairs = false);
-hipError_t radix_sort_u64(uint64_t* keys[2], uint32_t* vals[2], const int32_t* n_dev, int64_t n_host, int bit0,
-                          int bit1, uint32_t* hist, uint32_t* block_sums, int* which, hipStream_t st);
-// 16-bit keys (tile ids of batches with at most 65,536 tiles).
+// 16-bit keys (super-tile ids of batches with at most 65,536 of them).
 hipError_t radix_sort_u16(uint16_t* keys[2], uint32_t* vals[2], const int32_t* n_dev, int64_t n_host, int bit0,
                           int bit1, uint32_t* hist, uint32_t* block_sums, int* which, hipStream_t st);
-
-
-
+hipError_t radix_sort_u64(uint64_t* keys[2], uint32_t* vals[2], const int32_t* n_dev, int64_t n_host, int bit0,
+                          int bit1, uint32_t* hist, uint32_t* block_sums, int* which, hipStream_t st);
 
 // Derive stage of one view.
 struct DeriveArgs {
@@ -309,6 +318,10 @@ hipError_t ssim_launch(const float* a, const float* b, int C, int H, int W, cons
 // blend go to blend_st as well).
 hipError_t raster_batch(const SegTable& tab, Raster& r, bool full_key_sort, bool count_work, hipStream_t st,
                         Marks* mk = nullptr, hipStream_t blend_st = nullptr, hipEvent_t front_done = nullptr);
+
+// Every super tile's depth-ordered list of a batch (pval[0], ranges) from the
+// entries' spans, after the preprocess and the tall footprints' spans.
+hipError_t bin_items(const SegTable& tab, Raster& r, hipStream_t st, Marks* mk);
 
 // Blocks of `threads` threads of `kernel` the whole device holds at once
 // (occupancy x compute units; cached per kernel and device).  Grid-stride

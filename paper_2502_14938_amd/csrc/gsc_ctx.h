@@ -45,15 +45,25 @@ template <class Fn>
 hipError_t raster_layout(Raster& r, int64_t max_entries, int64_t max_pairs, int64_t max_tiles, bool full_key, Fn&& A) {
     hipError_t e;
 #define A_(p, cnt) if ((e = A(p, cnt)) != hipSuccess) return e
-    A_(r.rec, 4 * max_entries); A_(r.ntiles, max_entries); A_(r.nsup, max_entries); A_(r.scnt, max_entries);
+    A_(r.rec, 4 * max_entries); A_(r.ntiles, max_entries);
     A_(r.pt_list, max_entries); A_(r.pt_pack, max_entries / 256 + 1); A_(r.pt_off, max_entries / 256 + 1);
     // tall footprints: at most a quarter of the entries (more are flagged as overflow)
     A_(r.trec, max_entries / 4 + 256); A_(r.pt_sroff, max_entries / 4 + 256);
     A_(r.srow, max_entries); A_(r.srow_y, max_entries);
-    A_(r.dkey[0], max_entries); A_(r.dkey[1], max_entries);
-    A_(r.dval[0], max_entries); A_(r.dval[1], max_entries); A_(r.offs, max_entries);
-    A_(r.pkey[0], max_pairs); A_(r.pkey[1], max_pairs); A_(r.pval[0], max_pairs); A_(r.pval[1], max_pairs);
+    A_(r.nsup, max_entries); A_(r.scnt, max_entries); A_(r.offs, max_entries);
+    A_(r.pval[0], max_pairs); A_(r.pval[1], max_pairs);
+    const int64_t ne = (max_entries + 3) / 4 * 4, np = (max_pairs + 3) / 4 * 4;
+    A_(r.brec, ne); A_(r.items, np);
+    if (r.brec && r.items) {  // (the binning's records and items in the place of the radix sorts' buffers)
+        for (int i = 0; i < 2; ++i) {
+            r.dkey[i] = reinterpret_cast<uint32_t*>(r.brec) + i * ne;
+            r.dval[i] = reinterpret_cast<uint32_t*>(r.brec) + (2 + i) * ne;
+            r.pkey[i] = reinterpret_cast<uint32_t*>(r.items) + i * np;
+        }
+    }
     if (full_key) { A_(r.pkey64[0], max_pairs); A_(r.pkey64[1], max_pairs); }
+    A_(r.chunks, max_pairs / (kSortCap / 2) + 1); A_(r.long_lists, max_pairs / kSortCap + 1);
+    A_(r.pieces, max_pairs / 512 + 1); A_(r.sup_total, kBinLists);
     A_(r.ranges, 2 * max_tiles); A_(r.tile_eval, 2 * max_tiles); A_(r.hist, 256 * kSortBlocks);
     A_(r.block_sums, kScanBlocks); A_(r.block_sums64, kScanBlocks);
     A_(r.n_sort, 1); A_(r.cnt, 1);

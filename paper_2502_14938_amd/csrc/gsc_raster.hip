@@ -6,6 +6,15 @@
 //                      rows (per entry); segment bases; clears the ranges
 //   tall spans         the taller footprints' super rows (pairs of tile rows),
 //                      a group of lanes per footprint, one tile row per lane
+//   binning            (gsc_bin.hip) every super tile's (2x2 tiles) list of
+//                      entries with the mask of its tiles they cover, in the
+//                      order (depth key, entry)
+//   k_blend            front-to-back compositing, one launch over every
+//                      (segment, tile) of the batch, one wave per 16x16
+//                      tile, half or quarter of one (interleaved runs per
+//                      XCD); a tile stages the entries of its super tile's
+//                      list that carry its mask bit, wave-wide early exit
+// Batches of more than kBinLists super tiles are radix-sorted instead:
 //   depth radix pass   stable sort of entries by float32 depth (the low 32
 //                      bits of the (tile | depth) key, applied per Gaussian
 //                      before duplication); the last pass also lays the tile
@@ -18,11 +27,6 @@
 //   super-tile radix pass
 //                      stable sort of the items by global super-tile id
 //   k_ranges           [start, end) of every super tile's run
-//   k_blend            front-to-back compositing, one launch over every
-//                      (segment, tile) of the batch, one wave per 16x16
-//                      tile, half or quarter of one (interleaved runs per
-//                      XCD); a tile stages the entries of its super tile's
-//                      list that carry its mask bit, wave-wide early exit
 // With full_key_sort the items carry the whole 64-bit (super tile << 32 |
 // depth) key and are sorted after duplication instead; the order is the same.
 #include <cmath>
@@ -30,12 +34,14 @@
 
 #include "gsc_blockscan.h"
 #include "gsc_common.h"
+#include "gsc_spans.h"
 
 namespace gsc {
 
 namespace {
 
 constexpr int NT = 256;
+static_assert(NT == kEntryChunk, "the preprocess lists a chunk's tall footprints per block step");
 constexpr float kMinAlpha = 1.0f / 255.0f;
 constexpr float kTStop = 1e-4f;
 
@@ -278,11 +284,6 @@ __device__ __forceinline__ Ellipse shfl_ellipse(const Ellipse& el, int src) {
     return eb;
 }
 
-// Footprints taller than this many tile rows get one thread per row for
-// their spans (k_tall_spans) and are emitted by super rows (k_dup_big); shorter
-// ones keep their row spans in the record and are emitted from them.
-constexpr int kSmallRows = 4;
-
 // Fractional level transition: weight clamp(2 - |x - p_u| / d_l, 0, 1) of a
 // level-l anchor's opacities (1 at level 0), the distance taken in FP32 as
 // the selection takes it.
@@ -292,37 +293,6 @@ __device__ __forceinline__ float lod_fade_weight(float4 ap, int l, const Seg& s)
     const float d = sqrtf(vx * vx + vy * vy + vz * vz);
     return fminf(fmaxf(2.f - d / ldexpf(s.d_ref, -l), 0.f), 1.f);
 }
-
-// Span word of a tile row: lo | hi << 16, hi < lo (0xffff, 0) when empty.
-__device__ __forceinline__ int span_lo(uint32_t sp) { return (int)(sp & 0xffffu); }
-__device__ __forceinline__ int span_hi(uint32_t sp) { return (int)(sp >> 16); }
-
-// Super-tile columns [x0, x1] of a super row from the spans of its two tile
-// rows a (even) and b (odd), either possibly empty: the hull of the rows'
-// super columns (a convex footprint's rows give adjacent or overlapping
-// ranges; a column of the hull whose mask is empty is emitted with mask 0,
-// which no tile reads).  Returns the column count (0: both rows empty).
-__device__ __forceinline__ uint32_t sup_cols(uint32_t sa, uint32_t sb, int& x0) {
-    int lo = 0x7fffffff, hi = -1;
-    if (span_hi(sa) >= span_lo(sa)) { lo = span_lo(sa) >> kSupShift; hi = span_hi(sa) >> kSupShift; }
-    if (span_hi(sb) >= span_lo(sb)) {
-        lo = min(lo, span_lo(sb) >> kSupShift);
-        hi = max(hi, span_hi(sb) >> kSupShift);
-    }
-    x0 = lo;
-    return hi >= lo ? (uint32_t)(hi - lo + 1) : 0u;
-}
-
-// Mask of the tiles of super column x covered by tile rows a and b: bit
-// 2 (ty & 1) + (tx & 1).
-__device__ __forceinline__ uint32_t sup_mask(uint32_t sa, uint32_t sb, int x) {
-    const int t0 = x << kSupShift, t1 = t0 + 1;
-    const int la = span_lo(sa), ha = span_hi(sa), lb = span_lo(sb), hb = span_hi(sb);
-    return (uint32_t)(la <= t0 && t0 <= ha) | ((uint32_t)(la <= t1 && t1 <= ha) << 1) |
-           ((uint32_t)(lb <= t0 && t0 <= hb) << 2) | ((uint32_t)(lb <= t1 && t1 <= hb) << 3);
-}
-
-constexpr uint32_t kEmptySpan = 0x0000ffffu;
 
 // Super pairs of a footprint of at most kSmallRows tile rows from y0 (row i
 // at y0 + i, empty rows past the footprint): its super rows are the pairs
@@ -339,24 +309,18 @@ __device__ __forceinline__ uint32_t small_sup_count(const uint32_t (&sp)[4], int
     return n;
 }
 
-// Per-entry record, 4 x float4 (64 B, one cache line):
-//   A = (mean2d.x, mean2d.y, conic a, conic b)
-//   B = (conic c, alpha, r, g)
-//   C = (b, bits: tile rows y0 | y1 << 16, bits: segment, bits: (super tile, entry) pair count)
-//   D = bits: exact tile span lo | hi << 16 of each of up to kSmallRows rows
-//       (footprints of at most kSmallRows tile rows; hi < lo: empty row)
-constexpr int kRec = 4;
 struct PreArgs {
     SegTable tab;
     RasterCounters* rc;
     float4* rec;
     uint32_t* ntiles;
-    uint32_t* nsup;
+    uint4* brec;          // binning records (else nullptr)
+    uint32_t* nsup;       // otherwise: item counts and depth keys,
     uint32_t* dkey;
-    uint32_t* dval;
+    uint32_t* dval;       // and the depth sort's values (nullptr with full keys)
     int32_t* tall_list;   // tall entries of each chunk of 256 entries, in the chunk's slots
     uint64_t* tall_pack;  // per chunk: its tall entries | their super rows << 32
-    int32_t* ranges;     // [2 * tiles] cleared here for this batch's ranges
+    int32_t* ranges;     // [2 * super tiles] cleared here, unless the binning (n_ranges = 0) writes them all
     int64_t n_ranges;
     int64_t max_entries;
     int32_t shared_depth;  // paired eyes of one rotation: one depth key per Gaussian
@@ -382,6 +346,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(7))) void k_
             p.rc->overflow = over ? 2 : 0;
             p.rc->n_entries = s_ne;
             p.rc->n_gpairs = s_ne >> 1;
+            p.rc->n_long = p.rc->n_pieces = p.rc->n_chunks = 0;
             p.rc->n_echunks = (s_ne + NT - 1) / NT;
         }
     }
@@ -492,10 +457,10 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(7))) void k_
             s_rec[kRec * threadIdx.x + 3] = make_float4(__uint_as_float(spans[0]), __uint_as_float(spans[1]),
                                                         __uint_as_float(spans[2]), __uint_as_float(spans[3]));
             p.ntiles[e] = count;
-            p.nsup[e] = scount;
-            if (!p.shared_depth) {
+            if (!p.brec) p.nsup[e] = scount;
+            if (!p.brec && !p.shared_depth) {
                 p.dkey[e] = (count || tall) ? __float_as_uint(depth) : 0u;  // tall: settled by k_tall_spans
-                p.dval[e] = (uint32_t)e;
+                if (p.dval) p.dval[e] = (uint32_t)e;
             }
         }
         const uint64_t m = __ballot(tall);
@@ -520,28 +485,25 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(7))) void k_
             for (int i = threadIdx.x; i < kRec * nv; i += NT) dst[i] = s_rec[i];
         }
         __syncthreads();  // s_wtall and s_rec are rewritten by the next step
+        // The eyes' entries 2j, 2j+1 sit in neighbouring lanes.  With one
+        // rotation for both eyes their view depths differ by a constant, so
+        // one key orders both: the left eye's depth when that eye draws the
+        // Gaussian, else the right eye's.
+        const bool draws = valid && (count || tall);
+        uint32_t key = draws ? __float_as_uint(depth) : 0u;
         if (p.shared_depth) {
-            // The eyes' entries 2j, 2j+1 sit in neighbouring lanes.  With one
-            // rotation for both eyes their view depths differ by a constant,
-            // so one key orders both: the left eye's depth when that eye
-            // draws the Gaussian, else the right eye's.
-            const bool draws = valid && (count || tall);
-            const uint32_t mine = draws ? __float_as_uint(depth) : 0u;
-            const uint32_t other = (uint32_t)__shfl_xor((int)mine, 1);
-            const int odraws = __shfl_xor((int)draws, 1);
-            if (valid && !(e & 1)) {
-                p.dkey[e >> 1] = draws ? mine : (odraws ? other : 0u);
-                p.dval[e >> 1] = (uint32_t)(e >> 1);
-            }
+            const uint32_t other = (uint32_t)__shfl_xor((int)key, 1);
+            const bool odraws = __shfl_xor((int)draws, 1) != 0;
+            key = !(lane & 1) ? (draws ? key : other) : (odraws ? other : key);
+        }
+        if (p.brec) {
+            if (valid) p.brec[e] = pack_bin(spans, y0, (uint32_t)si, count != 0u && !tall, key);
+        } else if (p.shared_depth && valid && !(e & 1)) {
+            p.dkey[e >> 1] = key;
+            p.dval[e >> 1] = (uint32_t)(e >> 1);
         }
     }
 }
-
-// Super-tile grid of one segment, as the pair emission needs it.
-struct SupGeo {
-    int32_t base;  // first global super-tile id
-    int32_t nsx;   // super tiles per row
-};
 
 struct DupArgs {
     SupGeo sg[kMaxSeg];
@@ -558,7 +520,7 @@ struct DupArgs {
     int64_t max_pairs;
     int32_t* n_sort;         // pairs to sort (set by k_dup_rows)
     const uint4* srow;       // super rows of the tall footprints (see k_tall_spans)
-    const int32_t* srow_y;   // their super-row index in the image
+    const int32_t* srow_y;   // their super-row index in the image | segment << kRowSegShift
     int64_t srow_cap;
 };
 
@@ -769,7 +731,7 @@ __global__ __launch_bounds__(NT) void k_dup_big(DupArgs d) {
         int x0 = 0;
         if (q < nr) {
             const uint4 sr = d.srow[q];
-            const int y = d.srow_y[q];
+            const int y = (int)((uint32_t)d.srow_y[q] & kRowMask);
             sa = sr.x;
             sb = sr.y;
             np = sup_cols(sa, sb, x0);
@@ -866,7 +828,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(8))) void k_
             const int si = (b + sub) >> kSupShift;  // super row within the footprint
             if (even && ybase + b + sub <= y1 && q0 + si < cap) {
                 srow[q0 + si] = make_uint4(sp, other, (uint32_t)e, before + incl - w);
-                srow_y[q0 + si] = (ybase >> kSupShift) + si;
+                srow_y[q0 + si] = ((ybase >> kSupShift) + si) | (int)(t.seg << kRowSegShift);
             }
             before += __shfl(incl, kTallGW - 1, kTallGW);
         }
@@ -875,7 +837,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(8))) void k_
         if (sub == 0) {
             rp[2].w = __uint_as_float(before);
             ntiles[e] = tiles;
-            nsup[e] = before;
+            if (nsup) nsup[e] = before;
             if (!tiles && dkey) dkey[e] = 0u;  // (no per-entry keys when the eyes share the depth sort)
         }
     }
@@ -1280,13 +1242,14 @@ hipError_t tall_spans(const SegTable& tab, Raster& r, hipStream_t st) {
     RasterCounters* rc = r.cnt;
     // one scan gives each chunk's first footprint (low half) and first super
     // row (high half), and the totals
-    hipError_t e = scan_u64(r.pt_pack, r.pt_off, &rc->n_echunks, &rc->n_tall_e, &rc->n_srows, r.block_sums64, st);
+    hipError_t e = scan_u64(r.pt_pack, r.pt_off, &rc->n_echunks, r.max_entries / kEntryChunk + 1, &rc->n_tall_e,
+                            &rc->n_srows, r.block_sums64, st);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_tall_compact, dim3(kGridBlocks), dim3(NT), 0, st, r.pt_list, r.pt_pack, r.pt_off,
                        &rc->n_echunks, r.rec, r.trec, r.pt_sroff, r.tall_cap, rc);
     hipLaunchKernelGGL(k_tall_spans, grid_fit(k_tall_spans, r.tall_cap * kTallGW), dim3(NT), 0, st, tab, r.trec,
-                       r.pt_sroff, rc, r.tall_cap, r.rec, r.srow, r.srow_y, r.srow_cap, r.ntiles, r.nsup,
-                       r.shared_depth ? nullptr : r.dkey[0]);
+                       r.pt_sroff, rc, r.tall_cap, r.rec, r.srow, r.srow_y, r.srow_cap, r.ntiles,
+                       r.binned ? nullptr : r.nsup, r.binned || r.shared_depth ? nullptr : r.dkey[0]);
     return hipGetLastError();
 }
 
@@ -1297,10 +1260,12 @@ hipError_t raster_batch(const SegTable& tab_in, Raster& r, bool full_key_sort, b
     seg_supers(tab);
     RasterCounters* rc = r.cnt;
     mark(mk, 3, st);
+    r.binned = !full_key_sort && tab.total_sup <= kBinLists;
     PreArgs pa;
-    pa.tab = tab; pa.rc = rc; pa.rec = r.rec; pa.ntiles = r.ntiles; pa.nsup = r.nsup; pa.dkey = r.dkey[0];
-    pa.dval = r.dval[0];
-    pa.tall_list = r.pt_list; pa.tall_pack = r.pt_pack; pa.ranges = r.ranges; pa.n_ranges = 2 * (int64_t)tab.total_sup;
+    pa.tab = tab; pa.rc = rc; pa.rec = r.rec; pa.ntiles = r.ntiles; pa.brec = r.binned ? r.brec : nullptr;
+    pa.nsup = r.nsup; pa.dkey = r.dkey[0]; pa.dval = full_key_sort ? nullptr : r.dval[0];
+    pa.tall_list = r.pt_list; pa.tall_pack = r.pt_pack; pa.ranges = r.ranges;
+    pa.n_ranges = r.binned ? 0 : 2 * (int64_t)tab.total_sup;
     pa.max_entries = r.max_entries;
     r.shared_depth = !full_key_sort && eyes_share_rotation(tab);
     pa.shared_depth = r.shared_depth ? 1 : 0;
@@ -1315,7 +1280,10 @@ hipError_t raster_batch(const SegTable& tab_in, Raster& r, bool full_key_sort, b
     da.rc = rc; da.rec = r.rec; da.max_pairs = r.max_pairs; da.dkey = r.dkey[0];
     da.srow = r.srow; da.srow_y = r.srow_y; da.srow_cap = r.srow_cap; da.n_sort = r.n_sort;
     hipError_t e;
-    if (!full_key_sort) {
+    if (r.binned) {
+        e = bin_items(tab, r, st, mk);
+        if (e != hipSuccess) return e;
+    } else if (!full_key_sort) {
         // low 32 key bits (depth) first, per Gaussian
         int which = 0;
         // the last pass also lays the tile counts out in depth order (scnt);
@@ -1346,7 +1314,6 @@ hipError_t raster_batch(const SegTable& tab_in, Raster& r, bool full_key_sort, b
         if (e != hipSuccess) return e;
         mark(mk, 11, st);
         r.sorted_buf = pw;
-        r.key16 = k16;
         if (k16)
             hipLaunchKernelGGL(k_ranges<uint16_t>, grid_fit(k_ranges<uint16_t>, r.max_pairs / 8 + 1), dim3(NT), 0, st,
                                pk16[pw], r.n_sort, 0, r.ranges, (uint32_t)tab.total_sup);
@@ -1360,7 +1327,6 @@ hipError_t raster_batch(const SegTable& tab_in, Raster& r, bool full_key_sort, b
         mark(mk, 7, st);
         da.order = nullptr; da.offs = r.offs; da.items = r.nsup; da.key32 = nullptr; da.key16 = nullptr; da.key64 = r.pkey64[0];
         da.val = r.pval[0];
-        r.key16 = false;
         hipLaunchKernelGGL(k_dup_rows<true>, grid_fit(k_dup_rows<true>, r.max_entries), dim3(NT), 0, st, da);
         mark(mk, 8, st);
         mark(mk, 9, st);
@@ -1374,7 +1340,6 @@ hipError_t raster_batch(const SegTable& tab_in, Raster& r, bool full_key_sort, b
         hipLaunchKernelGGL(k_ranges<uint64_t>, grid_fit(k_ranges<uint64_t>, r.max_pairs / 8 + 1), dim3(NT), 0, st, r.pkey64[pw], r.n_sort,
                            32, r.ranges, (uint32_t)tab.total_sup);
     }
-    r.order = nullptr;
     hipStream_t bs = st;
     if (blend_st && blend_st != st) {
         e = hipEventRecord(front_done, st);

@@ -90,11 +90,6 @@ __global__ __launch_bounds__(NT) void k_scan_down64(const uint64_t* __restrict__
                                                     int32_t* total_lo, int32_t* total_hi) {
     __shared__ uint64_t wsum[NT / 64];
     uint64_t carry = block_carry<uint64_t>(block_sums, wsum);
-    if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) {
-        const uint64_t t = carry + block_sums[blockIdx.x];
-        *total_lo = (int32_t)(uint32_t)t;
-        *total_hi = (int32_t)(uint32_t)(t >> 32);
-    }
     int64_t b0, b1;
     chunk_of(count_of(n_dev, 0), SCAN_TILE, b0, b1);
     for (int64_t base = b0; base < b1; base += SCAN_TILE) {
@@ -113,6 +108,10 @@ __global__ __launch_bounds__(NT) void k_scan_down64(const uint64_t* __restrict__
             e += v[r];
         }
         carry += tot;
+    }
+    if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) {  // (past the last block's chunk)
+        *total_lo = (int32_t)(uint32_t)carry;
+        *total_hi = (int32_t)(uint32_t)(carry >> 32);
     }
 }
 
@@ -427,11 +426,13 @@ hipError_t scan_u32(const uint32_t* in, uint32_t* out, const int32_t* n_dev, int
     return hipGetLastError();
 }
 
-hipError_t scan_u64(const uint64_t* in, uint64_t* out, const int32_t* n_dev, int32_t* total_lo, int32_t* total_hi,
-                    uint64_t* block_sums, hipStream_t st) {
-    hipLaunchKernelGGL(k_scan_reduce64, dim3(kScanBlocks), dim3(NT), 0, st, in, n_dev, block_sums);
-    hipLaunchKernelGGL(k_scan_down64, dim3(kScanBlocks), dim3(NT), 0, st, in, out, n_dev, block_sums, total_lo,
-                       total_hi);
+hipError_t scan_u64(const uint64_t* in, uint64_t* out, const int32_t* n_dev, int64_t n_max, int32_t* total_lo,
+                    int32_t* total_hi, uint64_t* block_sums, hipStream_t st) {
+    // a block per tile, and no reduce pass for a single block
+    const int64_t tiles = (n_max + SCAN_TILE - 1) / SCAN_TILE;
+    const unsigned blocks = (unsigned)(tiles < 1 ? 1 : (tiles < kScanBlocks ? tiles : kScanBlocks));
+    if (blocks > 1) hipLaunchKernelGGL(k_scan_reduce64, dim3(blocks), dim3(NT), 0, st, in, n_dev, block_sums);
+    hipLaunchKernelGGL(k_scan_down64, dim3(blocks), dim3(NT), 0, st, in, out, n_dev, block_sums, total_lo, total_hi);
     return hipGetLastError();
 }
 

@@ -135,3 +135,69 @@ def test_halves_and_whole_tiles_match_oracle(gs, n, W, H):
     ok = ref["band"] == 0
     assert np.abs(T - ref["T"])[ok].max() <= 1e-4
     assert np.array_equal(nc[ok], ref["n_contrib"][ok])
+
+
+def depths(kind, n, rng):
+    if kind == "spread":
+        return rng.uniform(4.0, 12.0, n)
+    if kind == "equal":                       # one depth: the order is the entries'
+        return np.full(n, 8.0)
+    if kind == "planes":                      # two planes far apart: two buckets hold everything
+        return np.where(rng.uniform(size=n) < 0.5, 1.0, 4000.0)
+    z = rng.uniform(7.9999, 8.0001, n)        # a crowd at 8 among a few from 0.3 to 10,000
+    far = rng.uniform(size=n) < 0.01
+    z[far] = np.exp(rng.uniform(np.log(0.3), np.log(1e4), int(far.sum())))
+    return z
+
+
+@pytest.mark.parametrize("kind", ["spread", "equal", "planes", "crowd"])
+@pytest.mark.parametrize("n", [1, 2, 47, 512, 2048, 4096, 4097, 8192, 9000, 40000])
+def test_lists_of_every_length_and_depth_equal_full_key_sort(gs, n, kind):
+    """Every list in the order of the whole (super tile, depth) key with ties
+    by entry, against the radix sort of exactly that key: lists that fit one
+    block and ones that do not (2,048 items), divided by depth or, where the
+    depths crowd, merged; small and large footprints (tall ones among them)
+    over four super tiles."""
+    rng = np.random.default_rng(n + len(kind))
+    W, H = 64, 50
+    z = depths(kind, n, rng)
+    px, py = rng.uniform(-4, W + 4, n), rng.uniform(-4, H + 4, n)
+    cam = synth.look_camera((0, 0, 0), (0, 0, 1), (0, -1, 0), W, H, math.radians(60), math.radians(60))
+    fx, fy = W / (2 * math.tan(math.radians(30))), H / (2 * math.tan(math.radians(30)))
+    mu = np.stack([(px - W / 2) * z / fx, (py - H / 2) * z / fy, z], 1)
+    if not np.allclose(cam["R"], np.eye(3)):
+        mu = mu @ cam["R"]                    # camera axes to world
+    sig = np.exp(rng.uniform(np.log(0.5), np.log(30.0), n)) * z / fx
+    sig[rng.uniform(size=n) > 0.2] *= 0.05    # at most a fifth large
+    cov = np.zeros((n, 6)); cov[:, 0] = cov[:, 3] = cov[:, 5] = sig ** 2
+    rgb, al = rng.uniform(0, 1, (n, 3)), rng.uniform(0.01, 0.6, n)
+    a = run(gs, mu, cov, rgb, al, cam)
+    b = run(gs, mu, cov, rgb, al, cam, full_key=True)
+    assert np.array_equal(a[3], b[3])
+    for x, y in zip(a[:3], b[:3]):
+        assert np.array_equal(x, y)
+    assert np.array_equal(a[4].debug("raw_ranges"), b[4].debug("raw_ranges"))
+    assert np.array_equal(a[4].debug("sort_vals"), b[4].debug("sort_vals"))
+
+
+@pytest.mark.parametrize("W,H", [(4096, 2048), (4096, 2049), (16384, 31), (33, 16384)])
+def test_batches_around_the_most_lists_binned_equal_full_key_sort(gs, W, H):
+    """8,192 super tiles of 32x32 pixels are still binned, 8,320 radix-sorted:
+    the same lists and images as the sort of the whole key either way."""
+    n = 20000
+    rng = np.random.default_rng(W + H)
+    cam = synth.look_camera((0, 0, 0), (0, 0, 1), (0, -1, 0), W, H, math.radians(60), math.radians(60))
+    fx, fy = W / (2 * math.tan(math.radians(30))), H / (2 * math.tan(math.radians(30)))
+    z = rng.uniform(4.0, 12.0, n)
+    mu = np.stack([rng.uniform(-0.5, 0.5, n) * W * z / fx, rng.uniform(-0.5, 0.5, n) * H * z / fy, z], 1)
+    if not np.allclose(cam["R"], np.eye(3)):
+        mu = mu @ cam["R"]
+    sig = np.exp(rng.uniform(np.log(0.5), np.log(40.0), n)) * z / max(fx, fy)
+    cov = np.zeros((n, 6)); cov[:, 0] = cov[:, 3] = cov[:, 5] = sig ** 2
+    rgb, al = rng.uniform(0, 1, (n, 3)), rng.uniform(0.01, 0.6, n)
+    a = run(gs, mu, cov, rgb, al, cam)
+    b = run(gs, mu, cov, rgb, al, cam, full_key=True)
+    for x, y in zip(a[:4], b[:4]):
+        assert np.array_equal(x, y)
+    assert np.array_equal(a[4].debug("raw_ranges"), b[4].debug("raw_ranges"))
+    assert np.array_equal(a[4].debug("sort_vals"), b[4].debug("sort_vals"))
