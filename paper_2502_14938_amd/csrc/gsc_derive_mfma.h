@@ -7,11 +7,13 @@
 namespace gsc {
 
 // Weight fragments in MFMA lane order, built on the host at load time.
-// F32 (v_mfma_f32_16x16x4f32): layer 1 [6 hidden blocks][9 k-steps][64 lanes]
-// floats; layer 2 [out tiles][2 hidden blocks][4 steps][64] floats.
-// BF16 / FP8 (v_mfma_f32_16x16x16bf16_1k): layer 1 [6][3 k-blocks][64] x 4
-// bf16; layer 2 [out tiles][2][64] x 4 bf16 (FP8 stores the e4m3 codes'
-// exact bf16 values; the per-row scale multiplies the FP32 accumulator).
+// F32 (v_mfma_f32_16x16x4f32): layer 1 [14][64 lanes][4] floats, word i (of 54)
+// of a lane being k-step i / 6 of hidden block i % 6; layer 2 [out tiles][2
+// hidden blocks][64][4 steps].
+// BF16 / FP8 (v_mfma_f32_16x16x16bf16_1k): layer 1 [9][64][2 operands of 4
+// bf16], operand i (of 18) being k-block i / 6 of hidden block i % 6; layer 2
+// [out tiles][64][2 k-blocks of 4 bf16] (FP8 stores the e4m3 codes' exact bf16
+// values; the per-row scale multiplies the FP32 accumulator).
 struct MfmaFrags {
     const float* l1_f32;
     const float* l2_f32;

@@ -76,3 +76,32 @@ def test_images_vs_exact_oracle(gs, tiny, tiny_cams, prec):
             assert_image(img, ref[eye])
         else:
             assert p >= 40.0
+
+
+@pytest.mark.parametrize("prec,emu", [("f32", 0), ("bf16", 1), ("fp8", 2)])
+@pytest.mark.parametrize("n,k", [(1, 10), (17, 3), (500, 1), (700, 5), (333, 16), (9000, 2)])
+def test_derived_parameters_at_tile_edges(gs, n, k, prec, emu):
+    """Every k from one to the most (its outputs fill whole and partial matrix
+    tiles), counts of anchors that leave a tile ragged, and more tiles than
+    waves; the bounds of the test above."""
+    scene = synth.tiny_scene(n=n, k=k, seed=n + k)
+    L, R = synth.tiny_pair(64, 48)
+    _, _, der, G = frame(gs, scene, L, R, prec)
+    U = oracle.unified_camera(L, R)
+    ids, _ = oracle.select(scene, U)
+    ref = oracle.derive(scene, ids, U["pos"], emu)
+    keep = np.nonzero(ref["alpha"] > 0)[0]
+    common, gi, _ = np.intersect1d(G, keep, return_indices=True)
+    assert len(common) >= 0.99 * max(len(G), len(keep))
+    if not len(common):
+        return
+    d_alpha = np.abs(der[gi, 12] - ref["alpha"][common])
+    d_rgb = np.abs(der[gi, 9:12] - ref["rgb"][common]).max(1)
+    cov = ref["cov"][common]
+    d_cov = np.abs(der[gi, 3:9] - cov).max(1) / np.abs(cov).max(1)
+    d_mu = np.abs(der[gi, 0:3] - ref["mu"][common]).max(1)
+    assert d_mu.max() < 2e-6
+    if prec == "f32":
+        assert d_alpha.max() < 2e-6 and d_rgb.max() < 2e-6 and d_cov.max() < 2e-5
+    else:
+        assert d_alpha.max() < 3e-2 and d_rgb.max() < 3e-2 and np.median(d_cov) < 5e-3
