@@ -350,6 +350,7 @@ void gsc_destroy(gsc_ctx* c) {
     gsc::pred_free(c);
     gsc::free_explicit(c);
     gsc::free_all(c);
+    c->smem.release();
     for (int i = 0; i < 2; ++i) {
         if (c->front_done[i]) (void)hipEventDestroy(c->front_done[i]);
         if (c->blend_done[i]) (void)hipEventDestroy(c->blend_done[i]);
@@ -789,16 +790,19 @@ int gsc_ssim(gsc_ctx* c, const float* a, const float* b, int32_t channels, int32
         return fail(c, GSC_E_INVALID_ARG, "gsc_ssim: images of 1..65535 channels, at least 11 x 11 pixels");
     HIP_OR_FAIL(c, sync_all(c));  // the images may come from a frame still in flight
     const SsimWindow win = ssim_window();
-    const int64_t nb = ssim_blocks(channels, height, width);
-    double* buf = nullptr;  // [0]: total, [1..nb]: per-block sums
-    HIP_OR_FAIL(c, hipMalloc((void**)&buf, (size_t)(nb + 1) * sizeof(double)));
-    hipError_t e = ssim_launch(a, b, channels, height, width, win, buf + 1, buf, c->stream);
-    double tot = 0.0;
-    if (e == hipSuccess) e = hipMemcpyAsync(&tot, buf, sizeof(double), hipMemcpyDeviceToHost, c->stream);
+    const int64_t nb = ssim_slots(channels, height, width);
+    size_t acct = 0;
+    if (!c->ssim_total) {
+        if (!c->ssim_slots) HIP_OR_FAIL(c, dalloc(c->smem, acct, &c->ssim_slots, kSsimSlots));
+        HIP_OR_FAIL(c, halloc(c->smem, &c->ssim_total, 1));
+    }
+    double* own = nullptr;
+    if (nb > kSsimSlots) HIP_OR_FAIL(c, hipMalloc((void**)&own, (size_t)nb * sizeof(double)));
+    hipError_t e = ssim_launch(a, b, channels, height, width, win, own ? own : c->ssim_slots, c->ssim_total, c->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
-    (void)hipFree(buf);
+    if (own) (void)hipFree(own);
     if (e != hipSuccess) return hip_fail(c, e, "gsc_ssim");
-    *out = tot / ((double)channels * (double)(height - 10) * (double)(width - 10));
+    *out = *c->ssim_total / ((double)channels * (double)(height - 10) * (double)(width - 10));
     return GSC_OK;
 }
 

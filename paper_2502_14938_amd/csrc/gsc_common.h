@@ -305,7 +305,8 @@ struct SsimWindow {
     double w[11];
 };
 SsimWindow ssim_window();
-int64_t ssim_blocks(int C, int H, int W);
+constexpr int64_t kSsimSlots = 4096;  // kept with the context; larger maps allocate theirs for the call
+int64_t ssim_slots(int C, int H, int W);
 hipError_t ssim_launch(const float* a, const float* b, int C, int H, int W, const SsimWindow& win, double* partial,
                        double* total, hipStream_t st);
 

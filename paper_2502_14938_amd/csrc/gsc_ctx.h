@@ -150,6 +150,11 @@ struct gsc_ctx {
     int32_t* lab_iota = nullptr;
     uint8_t* lab_y = nullptr;
     int64_t lab_entries = 0;      // anchors * k the label scratch holds
+    // SSIM: slots of the strips' sums, and the total in pinned host memory
+    // (allocated on first use)
+    gsc::AllocSet smem;
+    double* ssim_slots = nullptr;
+    double* ssim_total = nullptr;
     bool count_work = false;       // blend counts visits / contributions (gsc_count_work)
     bool last_count_work = false;  // ... for the last rendered frame
     // stage timing (gsc_timing): one event set per frame since the last read

@@ -69,3 +69,18 @@ def test_ssim_size_limit(gs, r):
     x = torch.zeros(3, 10, 20, device="cuda")
     with pytest.raises(gs.GscError):
         r.ssim(x, x)
+
+
+@pytest.mark.parametrize("shape", [(1, 11, 74), (2, 12, 75), (1, 13, 76), (3, 24, 138), (1, 300, 11), (1, 400, 651),
+                                   (1100, 12, 14), (4200, 11, 12)])
+def test_ssim_at_strip_edges(r, shape):
+    """Maps of one row or column, columns on either side of a strip's 64 (and
+    of the pixels it may read past them), long and short strips, and more
+    planes than the slots that are kept; the bound of the test above."""
+    rng = np.random.default_rng(sum(shape))
+    x = rng.random(shape, dtype=np.float32)
+    y = np.clip(x + 0.1 * rng.standard_normal(shape).astype(np.float32), 0, 1).astype(np.float32)
+    X, Y = torch.from_numpy(x).cuda(), torch.from_numpy(y).cuda()
+    want = oracle.ssim(x, y)
+    for _ in range(2):
+        assert abs(r.ssim(X, Y) - want) < 1e-9
