@@ -24,6 +24,7 @@ constexpr uint32_t kEntryMask = (1u << kMaskShift) - 1u;
 constexpr int kBlendThreads = 64;     // one wave per 16x16 tile, half or quarter of one (blend)
 constexpr int kBlendRun = 128;        // consecutive parts of tiles one XCD takes in a row (blend)
 constexpr int kMaxSeg = 16;           // (viewer, eye) images per raster batch
+constexpr int kMaxViews = kMaxSeg / 2;  // viewers of one batch (two eyes each)
 constexpr int kGridBlocks = 2048;     // fixed grid of the grid-stride kernels
 constexpr int kScanBlocks = 1024;     // blocks of the device-wide scan
 constexpr int kSortBlocks = 1024;     // blocks of each radix pass
@@ -235,7 +236,8 @@ struct Raster {
 // ----------------------------------------------------------------- launchers
 // Every launcher enqueues on `st` and returns hipSuccess or the launch error.
 
-// Device-wide exclusive scan of n uint32 values (n from *n_dev if non-null),
+// Device-wide exclusive scan of n uint32 values (*n_dev, at most n_host, if
+// non-null, else n_host),
 // writing exclusive prefixes to out and the total to *total (device).
 hipError_t scan_u32(const uint32_t* in, uint32_t* out, const int32_t* n_dev, int64_t n_host, int32_t* total,
                     uint32_t* block_sums, hipStream_t st);
@@ -245,7 +247,7 @@ hipError_t scan_u32(const uint32_t* in, uint32_t* out, const int32_t* n_dev, int
 hipError_t scan_u64(const uint64_t* in, uint64_t* out, const int32_t* n_dev, int64_t n_max, int32_t* total_lo,
                     int32_t* total_hi, uint64_t* block_sums, hipStream_t st);
 // Stream compaction: ids[k] = the k-th i with flags[i] != 0 (flags 0 or 1,
-// n from *n_dev if non-null), the count to *total (device).
+// n as above), the count to *total (device).
 hipError_t compact_u32(const uint32_t* flags, const int32_t* n_dev, int64_t n_host, int32_t* total, int32_t* ids,
                        uint32_t* block_sums, hipStream_t st);
 
@@ -296,6 +298,8 @@ inline void mark(Marks* m, int i, hipStream_t st) {
 }
 
 hipError_t derive_frame(const DeriveArgs& a, hipStream_t st, Marks* mk = nullptr);
+// The same for n views of one scene and configuration (at most kMaxViews).
+hipError_t derive_batch(const DeriveArgs* a, int n, hipStream_t st);
 
 // Mean SSIM (gsc_metrics.hip): the normalised 11-tap Gaussian window, the
 // number of per-block partial sums for C channels of H x W (H, W >= 11),

@@ -1,5 +1,6 @@
-// Derive stage of one frame of one viewer (Section 4, Alg. 1):
-//   anchor indexing + filtering  -> k_select_flags + compaction (X_t, ascending)
+// Derive stage of one frame of one viewer, or of a batch of viewers at once
+// (Section 4, Alg. 1):
+//   anchor indexing + filtering  -> k_select, k_visible (X_t, ascending)
 //   cache scheduling             -> k_cache_* (invalidate at the reuse depth,
 //                                   hit/miss, learned staleness, slot
 //                                   allocation, eviction of outdated lines)
@@ -7,6 +8,13 @@
 //   configure the cache depth    -> depth_update (eq. 4, linear guide), in k_compose_reduce
 //   update the render buffer     -> k_compose_* (opacity mask, Section 6)
 // Every count stays on the device (Counters); the host only enqueues.
+//
+// Frames of a few thousand anchors and batches of viewers are bound by the
+// launches (4 to 5 us each, whatever they do), so the flags of a compaction
+// are made by the kernel that also adds them up, the compaction writes what
+// the next stage starts from, and the kernels take a grid row per view:
+// without a cache 5 launches in place of 7, with one line per anchor 6 in
+// place of 9, and for eight viewers 6 in place of 72.
 #include <cmath>
 
 #include "gsc_blockscan.h"
@@ -44,54 +52,139 @@ __device__ __forceinline__ void frame_begin(Counters* cnt, float* pu_hist, int32
 // the invalidation of Alg. 1 is done here too, anchor a's line dropped when
 // its age exceeds the current depth (the depth is the previous frame's
 // update; starting the frame leaves it alone).
-__global__ __launch_bounds__(NT) void k_select_flags(const float4* __restrict__ posr, const uint8_t* __restrict__ level,
-                                                     int64_t n, DeriveCam cam, uint32_t* __restrict__ flags,
-                                                     Counters* cnt, float* __restrict__ pu_hist, int32_t t,
-                                                     int32_t* __restrict__ line_anchor, const int32_t* __restrict__ line_tau,
-                                                     int32_t* __restrict__ slot_of) {
-    if (blockIdx.x == 0) frame_begin(cnt, pu_hist, t, cam);
-    const int32_t depth = cnt->depth;
-    for (int64_t a = gtid(); a < n; a += gstride()) {
-        if (line_anchor && line_anchor[a] >= 0 && t - line_tau[a] > depth) {
-            slot_of[a] = -1;
-            line_anchor[a] = -1;
-        }
-        float4 p = posr[a];
-        int l = level[a];
-        bool keep = true;
-        if (l != 0) {
-            float vx = p.x - cam.pos[0], vy = p.y - cam.pos[1], vz = p.z - cam.pos[2];
-            float lim = ldexpf(cam.d_ref, -l);
-            float d2 = vx * vx + vy * vy + vz * vz;
-            // with the fractional transition a level stays until its weight
-            // clamp(2 - dist / d_l, 0, 1) reaches 0 (the weight is applied
-            // by the rasteriser's preprocess)
-            keep = cam.fade ? d2 < 4.f * lim * lim : d2 <= lim * lim;
-        }
-#pragma unroll
-        for (int i = 0; i < 5; ++i) {
-            float s = cam.planes[i][0] * p.x + cam.planes[i][1] * p.y + cam.planes[i][2] * p.z + cam.planes[i][3];
-            keep = keep && (s >= -p.w);
-        }
-        flags[a] = keep ? 1u : 0u;
-    }
+
+// What the kernels of the stage need of one view.
+struct ViewStage {
+    DeriveCam cam;
+    Counters* cnt;
+    float* pu_hist;
+    int32_t *slot_of, *line_anchor, *line_tau, *line_last;
+    int32_t *visible, *vslot, *misses;
+    uint64_t* bits;   // a flag per anchor, then per visible position (64 to a word)
+    uint32_t* sums;   // the flags' sum per block
+    const uint16_t* line_mask;
+    int32_t* G;
+    int32_t t;
+};
+template <int V>
+struct Views {
+    ViewStage v[V];  // blockIdx.y: view
+};
+
+// Sum of the block's waves' counts, one value per wave (all its lanes alike).
+__device__ __forceinline__ uint32_t waves_sum(uint32_t count, uint32_t* wsum) {
+    if ((threadIdx.x & 63) == 0) wsum[threadIdx.x >> 6] = count;
+    __syncthreads();
+    uint32_t t = 0;
+    for (int i = 0; i < NT / 64; ++i) t += wsum[i];
+    return t;
 }
 
-// out[scan[i]] = i for flagged i (ascending).
-__global__ __launch_bounds__(NT) void k_compact_ids(const uint32_t* __restrict__ flags, const uint32_t* __restrict__ pos,
-                                                    int64_t n, const int32_t* n_dev, int32_t* __restrict__ out) {
-    int64_t m = n_dev ? *n_dev : n;
-    for (int64_t i = gtid(); i < m; i += gstride())
-        if (flags[i]) out[pos[i]] = (int32_t)i;
+// Signed distance of an anchor from a plane, n.x + w, its fused products
+// written out (from n_x x or from n_y y on): the set of visible anchors does
+// not depend on which ones the compiler would fuse.
+__device__ __forceinline__ float plane_side(const float (&q)[4], const float4& p, bool from_x) {
+#pragma clang fp contract(off)
+    const float s = from_x ? fmaf(q[1], p.y, q[0] * p.x) : fmaf(q[0], p.x, q[1] * p.y);
+    return fmaf(q[2], p.z, s) + q[3];
+}
+
+constexpr int kSelStep = 1024;  // anchors a block tests at a time, four per thread with their loads together
+
+template <int V>
+__global__ __launch_bounds__(NT) void k_select(Views<V> vs, const float4* __restrict__ posr,
+                                               const uint8_t* __restrict__ level, int64_t n, int direct) {
+    __shared__ uint32_t wsum[NT / 64];
+    const ViewStage& v = vs.v[V == 1 ? 0 : blockIdx.y];
+    if (blockIdx.x == 0) frame_begin(v.cnt, v.pu_hist, v.t, v.cam);
+    const DeriveCam& cam = v.cam;
+    const int32_t depth = v.cnt->depth, t = v.t;
+    int64_t b0, b1;
+    blockscan::chunk_of(n, kSelStep, b0, b1);
+    uint32_t count = 0;
+    for (int64_t base = b0; base < b1; base += kSelStep) {
+        float4 pos[4];
+        int lev[4], owner[4], tau[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int64_t a = base + u * NT + threadIdx.x, at = a < n ? a : n - 1;
+            pos[u] = posr[at];
+            lev[u] = level[at];
+            owner[u] = direct ? v.line_anchor[at] : -1;
+            tau[u] = direct ? v.line_tau[at] : 0;
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int64_t a = base + u * NT + threadIdx.x;
+            if (a < n && owner[u] >= 0 && t - tau[u] > depth) {
+                v.slot_of[a] = -1;
+                v.line_anchor[a] = -1;
+            }
+            const float4 p = pos[u];
+            const int l = lev[u];
+            bool keep = a < n;
+            if (l != 0) {
+                float vx = p.x - cam.pos[0], vy = p.y - cam.pos[1], vz = p.z - cam.pos[2];
+                float lim = ldexpf(cam.d_ref, -l);
+                float d2 = fmaf(vz, vz, fmaf(vx, vx, vy * vy));
+                // with the fractional transition a level stays until its weight
+                // clamp(2 - dist / d_l, 0, 1) reaches 0 (the weight is applied
+                // by the rasteriser's preprocess)
+                keep = keep && (cam.fade ? d2 < 4.f * lim * lim : d2 <= lim * lim);
+            }
+#pragma unroll
+            for (int i = 0; i < 5; ++i) {
+                keep = keep && (plane_side(cam.planes[i], p, i & 1) >= -p.w);
+            }
+            const uint64_t m = __ballot(keep);
+            if ((threadIdx.x & 63) == 0 && a < b1) v.bits[a >> 6] = m;
+            count += (uint32_t)__popcll(m);
+        }
+    }
+    const uint32_t total = waves_sum(count, wsum);
+    if (threadIdx.x == 0) v.sums[blockIdx.x] = total;
+}
+
+// X_t from the flags, ascending.  Without a cache every visible anchor is a
+// miss derived into line i, its visible position.
+template <int V, bool kNoCache>
+__global__ __launch_bounds__(NT) void k_visible(Views<V> vs, int64_t n) {
+    __shared__ uint32_t wsum[NT / 64];
+    const ViewStage& v = vs.v[V == 1 ? 0 : blockIdx.y];
+    uint32_t carry = blockscan::block_carry(v.sums, wsum, &v.cnt->n_visible);
+    if (kNoCache && blockIdx.x == gridDim.x - 1 && threadIdx.x == 0)
+        v.cnt->n_miss = (int32_t)(carry + v.sums[blockIdx.x]);
+    int64_t b0, b1;
+    blockscan::chunk_of(n, kSelStep, b0, b1);
+    for (int64_t base = b0; base < b1; base += kSelStep) {
+        const int64_t i0 = base + threadIdx.x * 4;
+        const uint32_t f = i0 < b1 ? (uint32_t)(v.bits[i0 >> 6] >> (i0 & 63)) & 15u : 0u;
+        uint32_t tot;
+        uint32_t e = carry + blockscan::block_excl_scan((uint32_t)__popc(f), wsum, tot);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            if (!(f >> u & 1u)) continue;
+            v.visible[e] = (int32_t)(i0 + u);
+            if (kNoCache) {
+                v.misses[e] = (int32_t)e;
+                v.vslot[e] = (int32_t)e;
+                v.line_anchor[e] = (int32_t)(i0 + u);
+            }
+            ++e;
+        }
+        carry += tot;
+    }
 }
 
 // ------------------------------------------------------------- cache
 
-// Alg. 1: invalidate every line whose age exceeds the current depth.
+// Alg. 1: invalidate every line whose age exceeds the current depth (and
+// clear the eviction's histogram).
 __global__ __launch_bounds__(NT) void k_cache_invalidate(int32_t* __restrict__ line_anchor, const int32_t* __restrict__ tau,
                                                          int32_t* __restrict__ slot_of, int64_t C, int32_t t,
-                                                         Counters* cnt) {
+                                                         Counters* cnt, uint32_t* __restrict__ evict_hist) {
     int32_t d = cnt->depth;
+    if (blockIdx.x == 0 && threadIdx.x < 64) evict_hist[threadIdx.x] = 0u;
     for (int64_t s = gtid(); s < C; s += gstride()) {
         int32_t a = line_anchor[s];
         if (a >= 0 && t - tau[s] > d) {
@@ -121,33 +214,19 @@ __device__ __forceinline__ void reuse_features(float4 p, int lvl, int lmax, cons
 
 
 struct LookupArgs {
-    const int32_t* visible;
-    const int32_t* slot_of;
-    int32_t* line_last;
-    const int32_t* line_tau;
-    uint32_t* miss_flag;   // [n_visible]
-    int32_t t;
-    int32_t reuse;
     int32_t predictor;
     float thr;
     const float4* posr;
     const uint8_t* level;
     const float* scale;
-    const float* pu_hist;
     int32_t lmax, dmax;
-    DeriveCam cam;
     const uint16_t* pred_wbf;
     const float* pred_w32;
-    float* cand_feat;      // optional: features of candidates (for label collection)
+    float* cand_feat;      // optional: features of candidates (for label collection; one view)
     int32_t* cand_id;
-    Counters* cnt;
     // direct-mapped cache: a miss takes line aid here, and every visible
     // anchor's render-buffer line is its own id
     int32_t direct;
-    int32_t* slot_of_w;
-    int32_t* line_anchor;
-    int32_t* line_tau_w;
-    int32_t* vslot;
 };
 
 // Direct-mapped lines, used when there is a line for every anchor: anchor a
@@ -162,27 +241,32 @@ struct LookupArgs {
 // Every visible owned line is stamped last_used = t.  The loop is uniform
 // per wave: the predictor runs on the whole wave (matrix cores) whenever one
 // of its lanes has a candidate.
-__global__ __launch_bounds__(NT) void k_cache_lookup(LookupArgs a) {
+template <int V>
+__global__ __launch_bounds__(NT) void k_cache_lookup(Views<V> vs, LookupArgs a) {
     __shared__ uint32_t s_h[NT / 64][kPredLdsWave];
-    const int32_t nv = a.cnt->n_visible;
-    const int lane = threadIdx.x & 63;
-    for (int64_t w0 = gtid() - lane; w0 < nv; w0 += gstride()) {
-        const int64_t i = w0 + lane;
+    __shared__ uint32_t wsum[NT / 64];
+    const ViewStage& v = vs.v[V == 1 ? 0 : blockIdx.y];
+    const int32_t nv = v.cnt->n_visible, t = v.t;
+    int64_t b0, b1;
+    blockscan::chunk_of(nv, NT, b0, b1);
+    uint32_t count = 0;
+    for (int64_t base = b0; base < b1; base += NT) {
+        const int64_t i = base + threadIdx.x;
         const bool valid = i < nv;
         bool hit = false;
         float f[kPredIn] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
         int32_t aid = 0, s = -1;
         if (valid) {
-            aid = a.visible[i];
-            s = a.slot_of[aid];
-            hit = s >= 0 && a.reuse;
-            if (s >= 0) a.line_last[s] = a.t;
+            aid = v.visible[i];
+            s = v.slot_of[aid];
+            hit = s >= 0;
+            if (s >= 0) v.line_last[s] = t;
             if (hit && (a.predictor || a.cand_feat)) {
-                const int32_t tau = a.line_tau[s];
-                reuse_features(a.posr[aid], a.level[aid], a.lmax, a.scale + 6 * (int64_t)aid, a.cam.pos,
-                               a.pu_hist + 4 * (tau & 63), a.t - tau, a.dmax, a.cam.fx, f);
+                const int32_t tau = v.line_tau[s];
+                reuse_features(a.posr[aid], a.level[aid], a.lmax, a.scale + 6 * (int64_t)aid, v.cam.pos,
+                               v.pu_hist + 4 * (tau & 63), t - tau, a.dmax, v.cam.fx, f);
                 if (a.cand_feat) {
-                    const int32_t c = atomicAdd(&a.cnt->n_cand, 1);
+                    const int32_t c = atomicAdd(&v.cnt->n_cand, 1);
                     for (int q = 0; q < kPredIn; ++q) a.cand_feat[(int64_t)c * kPredIn + q] = f[q];
                     a.cand_id[c] = aid;
                 }
@@ -192,20 +276,40 @@ __global__ __launch_bounds__(NT) void k_cache_lookup(LookupArgs a) {
             const float p = pred_prob_bf16_wave(a.pred_wbf, a.pred_w32, f, s_h[threadIdx.x >> 6]);
             if (hit && p > a.thr) hit = false;
         }
-        if (valid) {
-            a.miss_flag[i] = hit ? 0u : 1u;
-            if (a.direct) {
-                a.vslot[i] = aid;
-                if (!hit) {  // derived this frame into line aid
-                    if (s < 0) {
-                        a.slot_of_w[aid] = aid;
-                        a.line_anchor[aid] = aid;
-                        a.line_last[aid] = a.t;
-                    }
-                    a.line_tau_w[aid] = a.t;
+        const uint64_t m = __ballot(valid && !hit);
+        if ((threadIdx.x & 63) == 0 && valid) v.bits[i >> 6] = m;
+        count += (uint32_t)__popcll(m);
+        if (valid) v.vslot[i] = a.direct ? aid : s;  // (-1: k_assign finds it a line)
+        if (valid && a.direct) {
+            if (!hit) {  // derived this frame into line aid
+                if (s < 0) {
+                    v.slot_of[aid] = aid;
+                    v.line_anchor[aid] = aid;
+                    v.line_last[aid] = t;
                 }
+                v.line_tau[aid] = t;
             }
         }
+    }
+    const uint32_t total = waves_sum(count, wsum);
+    if (threadIdx.x == 0) v.sums[blockIdx.x] = total;
+}
+
+// Misses, ascending visible position (= ascending anchor id).
+template <int V>
+__global__ __launch_bounds__(NT) void k_misses(Views<V> vs) {
+    __shared__ uint32_t wsum[NT / 64];
+    const ViewStage& v = vs.v[V == 1 ? 0 : blockIdx.y];
+    uint32_t carry = blockscan::block_carry(v.sums, wsum, &v.cnt->n_miss);
+    int64_t b0, b1;
+    blockscan::chunk_of(v.cnt->n_visible, NT, b0, b1);
+    for (int64_t base = b0; base < b1; base += NT) {
+        const int64_t i = base + threadIdx.x;
+        const uint32_t f = i < b1 ? (uint32_t)(v.bits[i >> 6] >> (i & 63)) & 1u : 0u;
+        uint32_t tot;
+        const uint32_t e = carry + blockscan::block_excl_scan(f, wsum, tot);
+        if (f) v.misses[e] = (int32_t)i;
+        carry += tot;
     }
 }
 
@@ -244,46 +348,66 @@ __global__ __launch_bounds__(NT) void k_evict_hist(const int32_t* __restrict__ l
     if (threadIdx.x < dmax && h[threadIdx.x]) atomicAdd(&hist[threadIdx.x], h[threadIdx.x]);
 }
 
-__global__ void k_evict_plan(const uint32_t* __restrict__ hist, int32_t t, int32_t dmax, Counters* cnt,
-                             int32_t* scan_n, int64_t n_anchor) {
-    int32_t shortfall = cnt->n_need - cnt->n_free;
-    cnt->evict_short = shortfall > 0 ? shortfall : 0;
-    cnt->n_evict = 0;
-    *scan_n = 0;
-    if (shortfall <= 0) return;
+// The plan (run by every block of the flags' kernel; the first one stores it).
+struct EvictPlan {
+    int32_t thr, left, n_evict, scan_n, short_of;
+    bool over;
+};
+__device__ __forceinline__ EvictPlan evict_plan(const uint32_t* hist, int32_t t, int32_t dmax, int32_t shortfall,
+                                                int64_t n_anchor) {
+    EvictPlan p{t, 0, 0, 0, shortfall > 0 ? shortfall : 0, false};
+    if (shortfall <= 0) return p;
     int32_t acc = 0;
     for (int b = 0; b < dmax; ++b) {
         int32_t h = (int32_t)hist[b];
         if (acc + h >= shortfall) {
-            cnt->evict_thr = (t - dmax) + b;
-            cnt->evict_left = shortfall - acc;
-            cnt->n_evict = shortfall;
-            *scan_n = (int32_t)n_anchor;
-            return;
+            p.thr = (t - dmax) + b;
+            p.left = shortfall - acc;
+            p.n_evict = shortfall;
+            p.scan_n = (int32_t)n_anchor;
+            return p;
         }
         acc += h;
     }
-    cnt->overflow |= 2;  // fewer evictable lines than needed
-    cnt->evict_thr = t;  // evict every candidate; the frame is marked overflowed
-    cnt->evict_left = 0;
-    cnt->n_evict = acc;
+    p.over = true;  // fewer evictable lines than needed: evict every candidate
+    p.n_evict = acc;
+    return p;
 }
 
 // Anchors (ascending id) whose line sits in the threshold bin.
 __global__ __launch_bounds__(NT) void k_evict_thr_flags(const int32_t* __restrict__ slot_of,
-                                                        const int32_t* __restrict__ line_last, const int32_t* scan_n,
-                                                        Counters* cnt, uint32_t* __restrict__ flags) {
-    int64_t n = *scan_n;
-    int32_t thr = cnt->evict_thr;
-    for (int64_t a = gtid(); a < n; a += gstride()) {
+                                                        const int32_t* __restrict__ line_last,
+                                                        const uint32_t* __restrict__ hist, int32_t t, int32_t dmax,
+                                                        int64_t n_anchor, int32_t* scan_n, Counters* cnt,
+                                                        uint32_t* __restrict__ flags) {
+    __shared__ uint32_t h[64];
+    __shared__ EvictPlan s_plan;
+    if (threadIdx.x < 64) h[threadIdx.x] = hist[threadIdx.x];
+    __syncthreads();
+    if (threadIdx.x == 0) s_plan = evict_plan(h, t, dmax, cnt->n_need - cnt->n_free, n_anchor);
+    __syncthreads();
+    const EvictPlan p = s_plan;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        cnt->evict_short = p.short_of;
+        cnt->n_evict = p.n_evict;
+        *scan_n = p.scan_n;
+        if (p.short_of > 0) {
+            cnt->evict_thr = p.thr;
+            cnt->evict_left = p.left;
+        }
+        if (p.over) cnt->overflow |= 2;  // the frame is marked overflowed
+    }
+    for (int64_t a = gtid(); a < p.scan_n; a += gstride()) {
         int32_t s = slot_of[a];
-        flags[a] = (s >= 0 && line_last[s] == thr) ? 1u : 0u;
+        flags[a] = (s >= 0 && line_last[s] == p.thr) ? 1u : 0u;
     }
 }
 
 __global__ __launch_bounds__(NT) void k_evict_apply(int32_t* __restrict__ line_anchor, const int32_t* __restrict__ line_last,
                                                     int32_t* __restrict__ slot_of, const uint32_t* __restrict__ rank,
-                                                    int64_t C, int32_t t, Counters* cnt) {
+                                                    int64_t C, int32_t t, Counters* cnt, int32_t* scan_n) {
+    // the free list is made again if anything was evicted
+    if (gtid() == 0) *scan_n = cnt->evict_short > 0 ? (int32_t)C : 0;
     if (cnt->evict_short <= 0) return;
     int32_t thr = cnt->evict_thr, left = cnt->evict_left;
     for (int64_t s = gtid(); s < C; s += gstride()) {
@@ -304,7 +428,7 @@ __global__ __launch_bounds__(NT) void k_assign(const int32_t* __restrict__ misse
                                                int32_t* __restrict__ line_tau, int32_t* __restrict__ line_last,
                                                const uint32_t* __restrict__ need, const uint32_t* __restrict__ need_rank,
                                                const int32_t* __restrict__ free_list, int32_t t, int64_t C,
-                                               Counters* cnt) {
+                                               Counters* cnt, int32_t* __restrict__ vslot) {
     int32_t nm = cnt->n_miss;
     for (int64_t j = gtid(); j < nm; j += gstride()) {
         int32_t aid = visible[misses[j]];
@@ -319,6 +443,7 @@ __global__ __launch_bounds__(NT) void k_assign(const int32_t* __restrict__ misse
             slot_of[aid] = s;
             line_anchor[s] = aid;
             line_last[s] = t;
+            vslot[misses[j]] = s;
         } else {
             s = slot_of[aid];
         }
@@ -326,25 +451,6 @@ __global__ __launch_bounds__(NT) void k_assign(const int32_t* __restrict__ misse
     }
 }
 
-
-__global__ __launch_bounds__(NT) void k_vslot(const int32_t* __restrict__ visible, const int32_t* __restrict__ slot_of,
-                                              int32_t* __restrict__ vslot, Counters* cnt) {
-    int32_t nv = cnt->n_visible;
-    for (int64_t i = gtid(); i < nv; i += gstride()) vslot[i] = slot_of[visible[i]];
-}
-
-// No-cache schedule: every visible anchor is a miss derived into line i.
-__global__ __launch_bounds__(NT) void k_nocache(const int32_t* __restrict__ visible, int32_t* __restrict__ misses,
-                                                int32_t* __restrict__ vslot, int32_t* __restrict__ line_anchor,
-                                                Counters* cnt) {
-    int32_t nv = cnt->n_visible;
-    if (gtid() == 0) cnt->n_miss = nv;
-    for (int64_t i = gtid(); i < nv; i += gstride()) {
-        misses[i] = (int32_t)i;
-        vslot[i] = (int32_t)i;
-        line_anchor[i] = visible[i];
-    }
-}
 
 // Eq. 4 with the linear guiding function on the update (miss) rate.
 __device__ __forceinline__ void depth_update(Counters* cnt, int32_t dmax, int32_t guide) {
@@ -368,21 +474,11 @@ __device__ __forceinline__ void depth_update(Counters* cnt, int32_t dmax, int32_
 }
 
 
-__global__ void k_evict_freescan_n(const Counters* cnt, int32_t* scan_n, int64_t C) {
-    *scan_n = cnt->evict_short > 0 ? (int32_t)C : 0;
-}
-
 __global__ __launch_bounds__(NT) void k_free_flags_n(const int32_t* __restrict__ line_anchor, const int32_t* n_dev,
                                                      uint32_t* __restrict__ flags) {
     int64_t C = *n_dev;
     for (int64_t s = gtid(); s < C; s += gstride()) flags[s] = line_anchor[s] < 0 ? 1u : 0u;
 }
-
-__global__ void k_zero_u32(uint32_t* p, int n) {
-    for (int i = threadIdx.x; i < n; i += blockDim.x) p[i] = 0u;
-}
-
-
 
 // ------------------------------------------------------------- compose
 // G_t = [(i, j) : i visible ascending, j ascending, alpha_ij > 0]; each entry
@@ -402,51 +498,40 @@ __device__ __forceinline__ uint32_t compose_mask(const int32_t* __restrict__ vsl
     return slot < 0 ? 0u : (uint32_t)line_mask[slot];
 }
 
-__global__ __launch_bounds__(NT) void k_compose_reduce(const int32_t* __restrict__ vslot,
-                                                       const uint16_t* __restrict__ line_mask, Counters* cnt,
-                                                       int32_t dmax, int32_t guide, uint32_t* __restrict__ block_sums) {
+template <int V>
+__global__ __launch_bounds__(NT) void k_compose_reduce(Views<V> vs, int32_t dmax, int32_t guide) {
     __shared__ uint32_t wsum[NT / 64];
-    if (gtid() == 0) depth_update(cnt, dmax, guide);  // eq. 4, from this frame's counts
+    const ViewStage& v = vs.v[V == 1 ? 0 : blockIdx.y];
+    if (gtid() == 0) depth_update(v.cnt, dmax, guide);  // eq. 4, from this frame's counts
     int64_t b0, b1;
-    blockscan::chunk_of(cnt->n_visible, blockscan::kTile, b0, b1);
+    blockscan::chunk_of(v.cnt->n_visible, NT, b0, b1);
     uint32_t s = 0;
     for (int64_t i = b0 + threadIdx.x; i < b1; i += NT) {
         int32_t slot;
-        s += (uint32_t)__popc(compose_mask(vslot, line_mask, i, slot));
+        s += (uint32_t)__popc(compose_mask(v.vslot, v.line_mask, i, slot));
     }
     const uint32_t t = blockscan::block_sum(s, wsum);
-    if (threadIdx.x == 0) block_sums[blockIdx.x] = t;
+    if (threadIdx.x == 0) v.sums[blockIdx.x] = t;
 }
 
-__global__ __launch_bounds__(NT) void k_compose_scatter(const int32_t* __restrict__ vslot,
-                                                        const uint16_t* __restrict__ line_mask, int k, Counters* cnt,
-                                                        const uint32_t* __restrict__ block_sums, int32_t* __restrict__ G) {
+template <int V>
+__global__ __launch_bounds__(NT) void k_compose_scatter(Views<V> vs, int k) {
     __shared__ uint32_t wsum[NT / 64];
-    uint32_t carry = blockscan::block_carry(block_sums, wsum, &cnt->n_gauss);
+    const ViewStage& v = vs.v[V == 1 ? 0 : blockIdx.y];
+    uint32_t carry = blockscan::block_carry(v.sums, wsum, &v.cnt->n_gauss);
     int64_t b0, b1;
-    blockscan::chunk_of(cnt->n_visible, blockscan::kTile, b0, b1);
-    for (int64_t base = b0; base < b1; base += blockscan::kTile) {
-        uint32_t mk[4], s = 0;
-        int32_t slot[4];
-        const int64_t i0 = base + threadIdx.x * 4;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            mk[r] = 0u;
-            slot[r] = -1;
-            if (i0 + r < b1) mk[r] = compose_mask(vslot, line_mask, i0 + r, slot[r]);
-            s += (uint32_t)__popc(mk[r]);
-        }
+    blockscan::chunk_of(v.cnt->n_visible, NT, b0, b1);
+    for (int64_t base = b0; base < b1; base += NT) {
+        const int64_t i = base + threadIdx.x;
+        int32_t slot = -1;
+        uint32_t m = i < b1 ? compose_mask(v.vslot, v.line_mask, i, slot) : 0u;
         uint32_t tot;
-        uint32_t o = carry + blockscan::block_excl_scan(s, wsum, tot);
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int64_t gb = (int64_t)slot[r] * k;
-            uint32_t m = mk[r];
-            while (m) {
-                const int j = __ffs(m) - 1;
-                m &= m - 1u;
-                G[o++] = (int32_t)(gb + j);
-            }
+        uint32_t o = carry + blockscan::block_excl_scan((uint32_t)__popc(m), wsum, tot);
+        const int64_t gb = (int64_t)slot * k;
+        while (m) {
+            const int j = __ffs(m) - 1;
+            m &= m - 1u;
+            v.G[o++] = (int32_t)(gb + j);
         }
         carry += tot;
     }
@@ -460,71 +545,81 @@ __global__ __launch_bounds__(NT) void k_compose_scatter(const int32_t* __restric
         if (e_ != hipSuccess) return e_;        \
     } while (0)
 
-hipError_t derive_frame(const DeriveArgs& a, hipStream_t st, Marks* mk) {
+namespace {
+
+ViewStage view_stage(const DeriveArgs& a) {
+    View& v = *a.v;
+    ViewStage s;
+    s.cam = a.cam; s.cnt = v.cnt; s.pu_hist = v.pu_hist; s.slot_of = v.slot_of; s.line_anchor = v.line_anchor;
+    s.line_tau = v.line_tau; s.line_last = v.line_last; s.visible = v.visible; s.vslot = v.vslot; s.misses = v.misses;
+    s.bits = reinterpret_cast<uint64_t*>(v.tmp_a); s.sums = v.block_sums; s.line_mask = v.line_mask; s.G = v.G;
+    s.t = (int32_t)v.t;
+    return s;
+}
+
+// The derive stage of nv views (V = 1 or kMaxViews): all of them without a
+// cache, or with one line per anchor, or a single one.
+template <int V>
+hipError_t derive_stage(const DeriveArgs* views, int nv, hipStream_t st, Marks* mk) {
+    const DeriveArgs& a = views[0];
     const Scene& sc = *a.sc;
     View& v = *a.v;
     const int64_t n = sc.n;
     const int32_t t = (int32_t)v.t;
     Counters* cnt = v.cnt;
+    Views<V> vs;
+    for (int i = 0; i < V; ++i) vs.v[i] = view_stage(views[i < nv ? i : 0]);
     mark(mk, 0, st);
     // anchor indexing and filtering -> X_t ascending (the first block also
     // starts the frame's counters)
     const bool reuse = (a.flags & GSC_FLAG_REUSE) != 0;
     const bool direct = reuse && v.C >= n;  // line a holds anchor a or nothing
-    hipLaunchKernelGGL(k_select_flags, grid_fit(k_select_flags, n), dim3(NT), 0, st, sc.posr, sc.level, n, a.cam, v.tmp_a,
-                       cnt, v.pu_hist, t, direct ? v.line_anchor : nullptr, v.line_tau, v.slot_of);
-    GSC_TRY(compact_u32(v.tmp_a, nullptr, n, &cnt->n_visible, v.visible, v.block_sums, st));
-
+    // a block per step of anchors (of visible ones), up to the sums' number
+    auto blocks = [&](int step) {
+        const int64_t b = (n + step - 1) / step;
+        return dim3((unsigned)(b < kScanBlocks ? b : kScanBlocks), (unsigned)nv);
+    };
+    hipLaunchKernelGGL(k_select<V>, blocks(kSelStep), dim3(NT), 0, st, vs, sc.posr, sc.level, n, direct ? 1 : 0);
     if (!reuse) {
-        hipLaunchKernelGGL(k_nocache, grid_fit(k_nocache, n), dim3(NT), 0, st, v.visible, v.misses, v.vslot,
-                           v.line_anchor, cnt);
+        hipLaunchKernelGGL((k_visible<V, true>), blocks(kSelStep), dim3(NT), 0, st, vs, n);
     } else {
         const int64_t C = v.C;
-        if (!direct)  // (direct: done in k_select_flags)
+        hipLaunchKernelGGL((k_visible<V, false>), blocks(kSelStep), dim3(NT), 0, st, vs, n);
+        if (!direct)  // (direct: done in k_select)
             hipLaunchKernelGGL(k_cache_invalidate, grid_fit(k_cache_invalidate, C), dim3(NT), 0, st, v.line_anchor, v.line_tau,
-                               v.slot_of, C, t, cnt);
+                               v.slot_of, C, t, cnt, v.evict_hist);
         LookupArgs la;
-        la.visible = v.visible; la.slot_of = v.slot_of; la.line_last = v.line_last; la.line_tau = v.line_tau;
-        la.miss_flag = v.tmp_a; la.t = t; la.reuse = 1;
         la.predictor = (a.flags & GSC_FLAG_PREDICTOR) ? 1 : 0;
-        la.thr = a.pred_thr; la.posr = sc.posr; la.level = sc.level; la.scale = sc.scale; la.pu_hist = v.pu_hist;
-        la.lmax = sc.l_max; la.dmax = a.d_max; la.cam = a.cam; la.pred_wbf = a.pred_wbf; la.pred_w32 = a.pred_w;
-        la.cand_feat = a.collect ? v.cand_feat : nullptr; la.cand_id = v.cand_id; la.cnt = cnt;
-        la.direct = direct ? 1 : 0; la.slot_of_w = v.slot_of; la.line_anchor = v.line_anchor; la.line_tau_w = v.line_tau;
-        la.vslot = v.vslot;
-        hipLaunchKernelGGL(k_cache_lookup, grid_fit(k_cache_lookup, n), dim3(NT), 0, st, la);
-        // misses, ascending visible position (= ascending anchor id)
-        GSC_TRY(compact_u32(v.tmp_a, &cnt->n_visible, 0, &cnt->n_miss, v.misses, v.block_sums, st));
+        la.thr = a.pred_thr; la.posr = sc.posr; la.level = sc.level; la.scale = sc.scale;
+        la.lmax = sc.l_max; la.dmax = a.d_max; la.pred_wbf = a.pred_wbf; la.pred_w32 = a.pred_w;
+        la.cand_feat = a.collect ? v.cand_feat : nullptr; la.cand_id = v.cand_id;
+        la.direct = direct ? 1 : 0;
+        hipLaunchKernelGGL(k_cache_lookup<V>, blocks(NT), dim3(NT), 0, st, vs, la);
+        hipLaunchKernelGGL(k_misses<V>, blocks(NT), dim3(NT), 0, st, vs);
         if (!direct) {
             // misses that need a line, and their ranks
             uint32_t* need = v.tmp_a;
             uint32_t* need_rank = v.tmp_b;
             hipLaunchKernelGGL(k_need_flags, grid_fit(k_need_flags, n), dim3(NT), 0, st, v.misses, v.visible, v.slot_of, cnt, need);
-            GSC_TRY(scan_u32(need, need_rank, &cnt->n_miss, 0, &cnt->n_need, v.block_sums, st));
+            GSC_TRY(scan_u32(need, need_rank, &cnt->n_miss, n, &cnt->n_need, v.block_sums, st));
             // free lines, ascending
             uint32_t* fflag = reinterpret_cast<uint32_t*>(v.tmp_c);
             uint32_t* fpos = reinterpret_cast<uint32_t*>(v.tmp_d);
             hipLaunchKernelGGL(k_free_flags, grid_fit(k_free_flags, C), dim3(NT), 0, st, v.line_anchor, C, fflag);
-            GSC_TRY(scan_u32(fflag, fpos, nullptr, C, &cnt->n_free, v.block_sums, st));
-            hipLaunchKernelGGL(k_compact_ids, grid_fit(k_compact_ids, C), dim3(NT), 0, st, fflag, fpos, C, nullptr, v.free_list);
+            GSC_TRY(compact_u32(fflag, nullptr, C, &cnt->n_free, v.free_list, v.block_sums, st));
             // eviction of outdated lines when free lines are short
-            hipLaunchKernelGGL(k_zero_u32, dim3(1), dim3(64), 0, st, v.evict_hist, 64);
             hipLaunchKernelGGL(k_evict_hist, grid_fit(k_evict_hist, C), dim3(NT), 0, st, v.line_anchor, v.line_last, C, t, a.d_max,
                                cnt, v.evict_hist);
-            hipLaunchKernelGGL(k_evict_plan, dim3(1), dim3(1), 0, st, v.evict_hist, t, a.d_max, cnt, v.evict_scan_n, n);
-            hipLaunchKernelGGL(k_evict_thr_flags, grid_fit(k_evict_thr_flags, n), dim3(NT), 0, st, v.slot_of, v.line_last, v.evict_scan_n,
-                               cnt, fflag);
-            GSC_TRY(scan_u32(fflag, fpos, v.evict_scan_n, 0, nullptr, v.block_sums, st));
+            hipLaunchKernelGGL(k_evict_thr_flags, grid_fit(k_evict_thr_flags, n), dim3(NT), 0, st, v.slot_of, v.line_last,
+                               v.evict_hist, t, a.d_max, n, v.evict_scan_n, cnt, fflag);
+            GSC_TRY(scan_u32(fflag, fpos, v.evict_scan_n, n, nullptr, v.block_sums, st));
             hipLaunchKernelGGL(k_evict_apply, grid_fit(k_evict_apply, C), dim3(NT), 0, st, v.line_anchor, v.line_last, v.slot_of, fpos,
-                               C, t, cnt);
+                               C, t, cnt, v.evict_scan_n);
             // free list again if anything was evicted (count 0 otherwise)
-            hipLaunchKernelGGL(k_evict_freescan_n, dim3(1), dim3(1), 0, st, cnt, v.evict_scan_n, C);
             hipLaunchKernelGGL(k_free_flags_n, grid_fit(k_free_flags_n, C), dim3(NT), 0, st, v.line_anchor, v.evict_scan_n, fflag);
-            GSC_TRY(scan_u32(fflag, fpos, v.evict_scan_n, 0, nullptr, v.block_sums, st));
-            hipLaunchKernelGGL(k_compact_ids, grid_fit(k_compact_ids, C), dim3(NT), 0, st, fflag, fpos, 0, v.evict_scan_n, v.free_list);
+            GSC_TRY(compact_u32(fflag, v.evict_scan_n, C, nullptr, v.free_list, v.block_sums, st));
             hipLaunchKernelGGL(k_assign, grid_fit(k_assign, n), dim3(NT), 0, st, v.misses, v.visible, v.slot_of, v.line_anchor,
-                               v.line_tau, v.line_last, need, need_rank, v.free_list, t, C, cnt);
-            hipLaunchKernelGGL(k_vslot, grid_fit(k_vslot, n), dim3(NT), 0, st, v.visible, v.slot_of, v.vslot, cnt);
+                               v.line_tau, v.line_last, need, need_rank, v.free_list, t, C, cnt, v.vslot);
         }
     }
     // decode the misses on the matrix cores
@@ -532,24 +627,35 @@ hipError_t derive_frame(const DeriveArgs& a, hipStream_t st, Marks* mk) {
     {
         MfmaDeriveArgs m;
         m.posr = sc.posr; m.feat = sc.feat; m.scale = sc.scale; m.offsets = sc.offsets; m.k = sc.k;
-        m.visible = v.visible; m.misses = v.misses; m.vslot = v.vslot; m.L0 = v.L0; m.L1 = v.L1; m.L2 = v.L2;
-        m.L3 = v.L3; m.line_mask = v.line_mask; m.cam_pos[0] = a.cam.pos[0]; m.cam_pos[1] = a.cam.pos[1]; m.cam_pos[2] = a.cam.pos[2];
+        for (int i = 0; i < nv; ++i) m.v[i] = derive_view(*views[i].v, views[i].cam.pos);
         m.inv_dist_unit = sc.dist_unit > 0.f ? 1.0f / sc.dist_unit : 0.f;
-        m.n_miss = &cnt->n_miss; m.mode = a.precision;
+        m.mode = a.precision;
         m.fr.l1_f32 = sc.fr_l1_f32; m.fr.l2_f32 = sc.fr_l2_f32; m.fr.l1_bf16 = sc.fr_l1_bf16;
         m.fr.l2_bf16 = sc.fr_l2_bf16; m.fr.l1_fp8 = sc.fr_l1_fp8; m.fr.l2_fp8 = sc.fr_l2_fp8;
         m.fr.b1 = sc.fr_b1; m.fr.b2 = sc.fr_b2; m.fr.s1 = sc.fr_s1; m.fr.s2 = sc.fr_s2;
         m.fr.n_at = sc.n_at; m.fr.n_ct = sc.n_ct; m.fr.n_vt = sc.n_vt;
-        GSC_TRY(derive_mfma(m, n, st));
+        GSC_TRY(derive_mfma(m, nv, n, st));
     }
     mark(mk, 2, st);
     // compose the render buffer
-    hipLaunchKernelGGL(k_compose_reduce, dim3(kScanBlocks), dim3(NT), 0, st, v.vslot, v.line_mask, cnt, a.d_max, a.guide,
-                       v.block_sums);
-    hipLaunchKernelGGL(k_compose_scatter, dim3(kScanBlocks), dim3(NT), 0, st, v.vslot, v.line_mask, sc.k, cnt,
-                       v.block_sums, v.G);
+    hipLaunchKernelGGL(k_compose_reduce<V>, blocks(NT), dim3(NT), 0, st, vs, a.d_max, a.guide);
+    hipLaunchKernelGGL(k_compose_scatter<V>, blocks(NT), dim3(NT), 0, st, vs, sc.k);
     mark(mk, 3, st);
     return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t derive_frame(const DeriveArgs& a, hipStream_t st, Marks* mk) { return derive_stage<1>(&a, 1, st, mk); }
+
+hipError_t derive_batch(const DeriveArgs* a, int n, hipStream_t st) {
+    // views with fewer lines than anchors go one by one (their eviction plan
+    // has a kernel per step and view)
+    bool together = n > 1 && n <= kMaxViews;
+    for (int i = 0; i < n; ++i) together = together && (!(a[i].flags & GSC_FLAG_REUSE) || a[i].v->C >= a[i].sc->n);
+    if (together) return derive_stage<kMaxViews>(a, n, st, nullptr);
+    for (int i = 0; i < n; ++i) GSC_TRY(derive_stage<1>(a + i, 1, st, nullptr));
+    return hipSuccess;
 }
 
 }  // namespace gsc

@@ -39,12 +39,8 @@ struct HostFrags {
 };
 HostFrags pack_frags(const gsc_mlp& mlp, int k, int n_in);
 
-struct MfmaDeriveArgs {
-    const float4* posr;
-    const float* feat;
-    const float* scale;
-    const float* offsets;
-    int k;
+// The misses of one view and the lines they are decoded into.
+struct MfmaView {
     const int32_t* visible;
     const int32_t* misses;
     const int32_t* vslot;
@@ -54,13 +50,32 @@ struct MfmaDeriveArgs {
     float* L3;
     uint16_t* line_mask;  // [lines] bit j: Gaussian j has alpha > 0 (may be null)
     float cam_pos[3];
-    float inv_dist_unit;  // > 0: layer 1 takes |x - p_u| * inv_dist_unit as input 35
     const int32_t* n_miss;
+};
+
+struct MfmaDeriveArgs {
+    const float4* posr;
+    const float* feat;
+    const float* scale;
+    const float* offsets;
+    int k;
+    float inv_dist_unit;  // > 0: layer 1 takes |x - p_u| * inv_dist_unit as input 35
+    MfmaView v[kMaxViews];
     int mode;  // GSC_PREC_*
     MfmaFrags fr;
 };
 
-// Enqueue the MFMA derivation for up to n_max misses (count on the device).
-hipError_t derive_mfma(const MfmaDeriveArgs& a, int64_t n_max, hipStream_t st);
+// A view's part of the arguments from its buffers.
+inline MfmaView derive_view(const View& v, const float* cam_pos) {
+    MfmaView m;
+    m.visible = v.visible; m.misses = v.misses; m.vslot = v.vslot; m.L0 = v.L0; m.L1 = v.L1; m.L2 = v.L2; m.L3 = v.L3;
+    m.line_mask = v.line_mask; m.n_miss = &v.cnt->n_miss;
+    for (int i = 0; i < 3; ++i) m.cam_pos[i] = cam_pos[i];
+    return m;
+}
+
+// Enqueue the MFMA derivation of nv views for up to n_max misses each (counts
+// on the device).
+hipError_t derive_mfma(const MfmaDeriveArgs& a, int nv, int64_t n_max, hipStream_t st);
 
 }  // namespace gsc

@@ -272,10 +272,11 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int q = lane >> 4, col = lane & 15;
     const MfmaFrags& fr = a.fr;
+    const MfmaView& v = a.v[blockIdx.y];
     const int nt = fr.n_at + fr.n_ct + fr.n_vt;
     const int k = a.k, pitch = (11 * k) | 1;
     float* O = s_mem + kW1 * 64 * 4 + w * 16 * pitch;
-    const int32_t n = *a.n_miss;
+    const int32_t n = *v.n_miss;
     const int ntiles = (n + 15) / 16;
     if ((int)blockIdx.x >= ntiles) return;  // (block-uniform)
     // (consecutive tiles go to different blocks: few tiles spread over the chip)
@@ -284,9 +285,9 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_
     auto anchor_of = [&](int t, int32_t& aid, int32_t& line) {
         const int m = t * 16 + col;
         const bool ok = t < ntiles && m < n;
-        const int32_t pos = ok ? a.misses[m] : 0;
-        aid = ok ? a.visible[pos] : 0;
-        line = ok ? a.vslot[pos] : -1;
+        const int32_t pos = ok ? v.misses[m] : 0;
+        aid = ok ? v.visible[pos] : 0;
+        line = ok ? v.vslot[pos] : -1;
     };
     int32_t aid, line;
     anchor_of(tile, aid, line);
@@ -307,7 +308,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_
             sLine[w][col] = line;
             sMask[w][col] = 0;
         }
-        float vx = in.x.x - a.cam_pos[0], vy = in.x.y - a.cam_pos[1], vz = in.x.z - a.cam_pos[2];
+        float vx = in.x.x - v.cam_pos[0], vy = in.x.y - v.cam_pos[1], vz = in.x.z - v.cam_pos[2];
         const float nv = sqrtf(fmaf(vz, vz, fmaf(vx, vx, vy * vy)));
         const float inv = 1.0f / nv;
         const float dv[3] = {vx * inv, vy * inv, vz * inv};
@@ -435,18 +436,18 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_
             const int64_t e = (int64_t)gl * k + j0;
             // position relative to the anchor (small, so FP32 keeps it to
             // ~1e-7 m); the rasteriser adds anchor - camera in FP64
-            a.L0[e] = make_float4(sh.sc[0] * sh.off[0], sh.sc[1] * sh.off[1], sh.sc[2] * sh.off[2], alpha);
-            a.L1[e] = make_float4(S[0], S[1], S[2], S[3]);
-            a.L2[e] = make_float4(S[4], S[5], r, gg);
-            a.L3[e] = bb;
+            v.L0[e] = make_float4(sh.sc[0] * sh.off[0], sh.sc[1] * sh.off[1], sh.sc[2] * sh.off[2], alpha);
+            v.L1[e] = make_float4(S[0], S[1], S[2], S[3]);
+            v.L2[e] = make_float4(S[4], S[5], r, gg);
+            v.L3[e] = bb;
             if (alpha > 0.f) atomicOr(&sMask[w][al0], 1u << j0);
         }
         __builtin_amdgcn_wave_barrier();
         // the line's mask of kept Gaussians (alpha > 0, the render buffer's
         // test), from the same alphas
-        if (a.line_mask && lane < 16) {
+        if (v.line_mask && lane < 16) {
             const int m = tile * 16 + lane, gl = sLine[w][lane];
-            if (m < n && gl >= 0) a.line_mask[gl] = (uint16_t)sMask[w][lane];
+            if (m < n && gl >= 0) v.line_mask[gl] = (uint16_t)sMask[w][lane];
         }
         __builtin_amdgcn_wave_barrier();
     }
@@ -454,20 +455,22 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_
 
 }  // namespace
 
-hipError_t derive_mfma(const MfmaDeriveArgs& a, int64_t n_max, hipStream_t st) {
+hipError_t derive_mfma(const MfmaDeriveArgs& a, int nv, int64_t n_max, hipStream_t st) {
     const int64_t tiles = (n_max + 15) / 16;
     const size_t lds = ((a.mode == GSC_PREC_F32 ? 14 : 9) * 64 * 4 + NT / 64 * 16 * (size_t)((11 * a.k) | 1)) * sizeof(float);
-    // a wave per tile, up to what the chip holds at once (4 waves per SIMD)
-    const unsigned blocks = (unsigned)(tiles < 1 ? 1 : (tiles < kMaxBlocks ? tiles : kMaxBlocks));
+    // a wave per tile, up to what the chip holds at once (4 waves per SIMD),
+    // shared by the views
+    const int64_t most = kMaxBlocks / nv;
+    const dim3 blocks((unsigned)(tiles < 1 ? 1 : (tiles < most ? tiles : most)), (unsigned)nv);
     switch (a.mode) {
         case GSC_PREC_F32:
-            hipLaunchKernelGGL(k_derive_mfma<GSC_PREC_F32>, dim3(blocks), dim3(NT), lds, st, a);
+            hipLaunchKernelGGL(k_derive_mfma<GSC_PREC_F32>, blocks, dim3(NT), lds, st, a);
             break;
         case GSC_PREC_BF16:
-            hipLaunchKernelGGL(k_derive_mfma<GSC_PREC_BF16>, dim3(blocks), dim3(NT), lds, st, a);
+            hipLaunchKernelGGL(k_derive_mfma<GSC_PREC_BF16>, blocks, dim3(NT), lds, st, a);
             break;
         default:
-            hipLaunchKernelGGL(k_derive_mfma<GSC_PREC_FP8>, dim3(blocks), dim3(NT), lds, st, a);
+            hipLaunchKernelGGL(k_derive_mfma<GSC_PREC_FP8>, blocks, dim3(NT), lds, st, a);
             break;
     }
     return hipGetLastError();

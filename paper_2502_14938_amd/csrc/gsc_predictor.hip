@@ -538,16 +538,17 @@ int gsc_predictor_labels(gsc_ctx* c, float* X_out, uint8_t* y_out, int32_t* ids_
     // derive every candidate again with this frame's unified camera, FP32
     MfmaDeriveArgs m;
     m.posr = sc.posr; m.feat = sc.feat; m.scale = sc.scale; m.offsets = sc.offsets; m.k = sc.k;
-    m.visible = v.cand_id; m.misses = c->lab_iota; m.vslot = c->lab_iota;
-    m.L0 = c->lab_L0; m.L1 = c->lab_L1; m.L2 = c->lab_L2; m.L3 = c->lab_L3; m.line_mask = nullptr;
-    for (int i = 0; i < 3; ++i) m.cam_pos[i] = (float)c->unified.pos[i];
+    MfmaView& mv = m.v[0];
+    mv.visible = v.cand_id; mv.misses = c->lab_iota; mv.vslot = c->lab_iota;
+    mv.L0 = c->lab_L0; mv.L1 = c->lab_L1; mv.L2 = c->lab_L2; mv.L3 = c->lab_L3; mv.line_mask = nullptr;
+    for (int i = 0; i < 3; ++i) mv.cam_pos[i] = (float)c->unified.pos[i];
     m.inv_dist_unit = sc.dist_unit > 0.f ? 1.0f / sc.dist_unit : 0.f;
-    m.n_miss = &v.cnt->n_cand; m.mode = GSC_PREC_F32;
+    mv.n_miss = &v.cnt->n_cand; m.mode = GSC_PREC_F32;
     m.fr.l1_f32 = sc.fr_l1_f32; m.fr.l2_f32 = sc.fr_l2_f32; m.fr.l1_bf16 = sc.fr_l1_bf16;
     m.fr.l2_bf16 = sc.fr_l2_bf16; m.fr.l1_fp8 = sc.fr_l1_fp8; m.fr.l2_fp8 = sc.fr_l2_fp8;
     m.fr.b1 = sc.fr_b1; m.fr.b2 = sc.fr_b2; m.fr.s1 = sc.fr_s1; m.fr.s2 = sc.fr_s2;
     m.fr.n_at = sc.n_at; m.fr.n_ct = sc.n_ct; m.fr.n_vt = sc.n_vt;
-    if (derive_mfma(m, sc.n, st) != hipSuccess) return fail(c, GSC_E_HIP, "gsc_predictor_labels: derive failed");
+    if (derive_mfma(m, 1, sc.n, st) != hipSuccess) return fail(c, GSC_E_HIP, "gsc_predictor_labels: derive failed");
     hipLaunchKernelGGL(k_pred_labels, dim3(blocks_for(sc.n)), dim3(NT), 0, st, v.cand_id, v.slot_of, v.cnt, sc.k,
                        v.cand_feat, c->lab_L0, c->lab_L1, c->lab_L2, c->lab_L3, v.L0, v.L1, v.L2, v.L3, c->lab_y);
     if (hipStreamSynchronize(st) != hipSuccess) return fail(c, GSC_E_HIP, "gsc_predictor_labels: kernels failed");

@@ -1293,7 +1293,7 @@ hipError_t raster_batch(const SegTable& tab_in, Raster& r, bool full_key_sort, b
                            r.block_sums, &which, st, r.nsup, r.scnt, r.shared_depth);
         if (e != hipSuccess) return e;
         mark(mk, 6, st);
-        e = scan_u32(r.scnt, r.offs, &rc->n_entries, 0, &rc->n_pairs, r.block_sums, st);
+        e = scan_u32(r.scnt, r.offs, &rc->n_entries, r.max_entries, &rc->n_pairs, r.block_sums, st);
         if (e != hipSuccess) return e;
         mark(mk, 7, st);
         // keys in 16 bits when the batch's global super-tile ids fit
@@ -1322,7 +1322,7 @@ hipError_t raster_batch(const SegTable& tab_in, Raster& r, bool full_key_sort, b
                                r.pkey[pw], r.n_sort, 0, r.ranges, (uint32_t)tab.total_sup);
     } else {
         mark(mk, 6, st);  // no per-Gaussian depth pass in this mode
-        e = scan_u32(r.nsup, r.offs, &rc->n_entries, 0, &rc->n_pairs, r.block_sums, st);
+        e = scan_u32(r.nsup, r.offs, &rc->n_entries, r.max_entries, &rc->n_pairs, r.block_sums, st);
         if (e != hipSuccess) return e;
         mark(mk, 7, st);
         da.order = nullptr; da.offs = r.offs; da.items = r.nsup; da.key32 = nullptr; da.key16 = nullptr; da.key64 = r.pkey64[0];

@@ -1,9 +1,10 @@
 // Device-wide primitives: exclusive scan and stable LSD radix sort.
 //
-// Both use a fixed grid whose blocks own contiguous chunks of the input and
-// read the element count from device memory, so a frame never needs a host
-// round trip to size a launch.  Wave64 throughout: wave scans use
-// __shfl_up over 64 lanes, digit ranking uses 64-bit ballots.
+// Both use a grid whose blocks own contiguous chunks of the input (fixed, or
+// sized by the most elements there may be) and read the element count from
+// device memory, so a frame never needs a host round trip to size a launch.
+// Wave64 throughout: wave scans use __shfl_up over 64 lanes, digit ranking
+// uses 64-bit ballots.
 #include "gsc_blockscan.h"
 #include "gsc_common.h"
 
@@ -417,20 +418,25 @@ hipError_t radix_sort_impl(K* keys[2], uint32_t* vals[2], const int32_t* n_dev, 
     return hipGetLastError();
 }
 
+// A block per tile of the most values a scan may have.
+unsigned scan_blocks(int64_t n_max) {
+    const int64_t tiles = (n_max + SCAN_TILE - 1) / SCAN_TILE;
+    return (unsigned)(tiles < 1 ? 1 : (tiles < kScanBlocks ? tiles : kScanBlocks));
+}
+
 }  // namespace
 
 hipError_t scan_u32(const uint32_t* in, uint32_t* out, const int32_t* n_dev, int64_t n_host, int32_t* total,
                     uint32_t* block_sums, hipStream_t st) {
-    hipLaunchKernelGGL(k_scan_reduce, dim3(kScanBlocks), dim3(NT), 0, st, in, n_dev, n_host, block_sums);
-    hipLaunchKernelGGL(k_scan_down, dim3(kScanBlocks), dim3(NT), 0, st, in, out, n_dev, n_host, block_sums, total);
+    const dim3 blocks(scan_blocks(n_host));
+    hipLaunchKernelGGL(k_scan_reduce, blocks, dim3(NT), 0, st, in, n_dev, n_host, block_sums);
+    hipLaunchKernelGGL(k_scan_down, blocks, dim3(NT), 0, st, in, out, n_dev, n_host, block_sums, total);
     return hipGetLastError();
 }
 
 hipError_t scan_u64(const uint64_t* in, uint64_t* out, const int32_t* n_dev, int64_t n_max, int32_t* total_lo,
                     int32_t* total_hi, uint64_t* block_sums, hipStream_t st) {
-    // a block per tile, and no reduce pass for a single block
-    const int64_t tiles = (n_max + SCAN_TILE - 1) / SCAN_TILE;
-    const unsigned blocks = (unsigned)(tiles < 1 ? 1 : (tiles < kScanBlocks ? tiles : kScanBlocks));
+    const unsigned blocks = scan_blocks(n_max);  // (no reduce pass for a single block)
     if (blocks > 1) hipLaunchKernelGGL(k_scan_reduce64, dim3(blocks), dim3(NT), 0, st, in, n_dev, block_sums);
     hipLaunchKernelGGL(k_scan_down64, dim3(blocks), dim3(NT), 0, st, in, out, n_dev, block_sums, total_lo, total_hi);
     return hipGetLastError();
@@ -438,8 +444,9 @@ hipError_t scan_u64(const uint64_t* in, uint64_t* out, const int32_t* n_dev, int
 
 hipError_t compact_u32(const uint32_t* flags, const int32_t* n_dev, int64_t n_host, int32_t* total, int32_t* ids,
                        uint32_t* block_sums, hipStream_t st) {
-    hipLaunchKernelGGL(k_scan_reduce, dim3(kScanBlocks), dim3(NT), 0, st, flags, n_dev, n_host, block_sums);
-    hipLaunchKernelGGL(k_scan_compact, dim3(kScanBlocks), dim3(NT), 0, st, flags, ids, n_dev, n_host, block_sums, total);
+    const dim3 blocks(scan_blocks(n_host));
+    hipLaunchKernelGGL(k_scan_reduce, blocks, dim3(NT), 0, st, flags, n_dev, n_host, block_sums);
+    hipLaunchKernelGGL(k_scan_compact, blocks, dim3(NT), 0, st, flags, ids, n_dev, n_host, block_sums, total);
     return hipGetLastError();
 }
 

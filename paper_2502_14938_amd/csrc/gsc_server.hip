@@ -124,6 +124,26 @@ struct Batch {
     std::vector<double> t_arrival;
 };
 
+// A batch's counters into its report, one launch for all of them (a copy per
+// viewer took 3 us of the stream each).
+struct ReportArgs {
+    const RasterCounters* rc;
+    const Counters* vc[kMaxBatchViewers];
+    int n;
+};
+static_assert(sizeof(RasterCounters) % 4 == 0 && sizeof(Counters) % 4 == 0, "counters are copied in words");
+__global__ __launch_bounds__(256) void k_report(ReportArgs a, BatchReport* rep) {
+    constexpr int kR = sizeof(RasterCounters) / 4, kV = sizeof(Counters) / 4;
+    for (int i = threadIdx.x; i < kR + a.n * kV; i += 256) {
+        if (i < kR) {
+            reinterpret_cast<uint32_t*>(&rep->rc)[i] = reinterpret_cast<const uint32_t*>(a.rc)[i];
+        } else {
+            const int v = (i - kR) / kV, w = (i - kR) % kV;
+            reinterpret_cast<uint32_t*>(&rep->vc[v])[w] = reinterpret_cast<const uint32_t*>(a.vc[v])[w];
+        }
+    }
+}
+
 int sfail(gsc_server* s, int code, const std::string& msg) {
     if (s) s->err = msg;
     return code;
@@ -448,11 +468,13 @@ int gsc_server_step(gsc_server* s) {
     std::memset(&tab, 0, sizeof(tab));
     tab.paired = 1;  // each viewer's two eyes read its one view
     int tiles = 0;
+    DeriveArgs args[kMaxBatchViewers];
+    ReportArgs ra;
     for (int i = 0; i < (int)pick.size(); ++i) {
         Viewer& v = *s->viewers[pick[i]];
         Request r = v.queue.front();
         v.queue.pop_front();
-        DeriveArgs a;
+        DeriveArgs& a = args[i];
         a.sc = &c->scene;
         a.v = &v.v;
         a.cam = derive_cam(r.unified, c->scene.d_ref, (c->cfg.flags & GSC_FLAG_LOD_FADE) != 0);
@@ -468,10 +490,6 @@ int gsc_server_step(gsc_server* s) {
         b->viewer_of.push_back(i);
         b->viewer_id.push_back(pick[i]);
         b->t_arrival.push_back(r.t_arrival);
-        hipError_t e = derive_frame(a, s->st);
-        if (e != hipSuccess)
-            return abort_batch(s, b, std::string("gsc_server_step: derive: ") + hipGetErrorString(e));
-        v.v.t += 1;
         for (int eye = 0; eye < 2; ++eye) {
             Seg& sg = tab.s[tab.n++];
             sg.L0 = v.v.L0; sg.L1 = v.v.L1; sg.L2 = v.v.L2; sg.L3 = v.v.L3;
@@ -486,9 +504,14 @@ int gsc_server_step(gsc_server* s) {
             sg.out_T = nullptr;
             sg.out_nc = nullptr;
         }
-        if (hipMemcpyAsync(&rep->vc[i], v.v.cnt, sizeof(Counters), hipMemcpyDeviceToHost, s->st) != hipSuccess)
-            return abort_batch(s, b, "gsc_server_step: counter copy");
+        ra.vc[i] = v.v.cnt;
     }
+    {
+        const hipError_t e = derive_batch(args, (int)pick.size(), s->st);
+        if (e != hipSuccess)
+            return abort_batch(s, b, std::string("gsc_server_step: derive: ") + hipGetErrorString(e));
+    }
+    for (int32_t i : pick) s->viewers[i]->v.t += 1;
     tab.total_tiles = tiles;
     // two batches in flight: this batch's raster set was last read by the
     // blend two batches back, which must finish before the preprocess
@@ -500,8 +523,12 @@ int gsc_server_step(gsc_server* s) {
     if (e == hipSuccess)
         e = raster_batch(tab, R, (c->cfg.flags & GSC_FLAG_FULL_KEY_SORT) != 0, false, s->st, nullptr,
                          s->overlap ? s->blend_st : nullptr, s->overlap ? s->front_done[set] : nullptr);
-    if (e == hipSuccess)
-        e = hipMemcpyAsync(&rep->rc, R.cnt, sizeof(RasterCounters), hipMemcpyDeviceToHost, s->st);
+    if (e == hipSuccess) {
+        ra.rc = R.cnt;
+        ra.n = (int)pick.size();
+        hipLaunchKernelGGL(k_report, dim3(1), dim3(256), 0, s->st, ra, rep);
+        e = hipGetLastError();
+    }
     hipStream_t done_st = s->st;
     if (e == hipSuccess && s->overlap) {
         // completion after the blend and after the counter copies on the

@@ -206,3 +206,32 @@ def test_mixed_city_batch_matches_oracle(gs):
             for eye, key in ((0, "left"), (1, "right")):
                 rep = assert_image(outs[i][t][eye].cpu().numpy(), ref[key])
                 print("\nviewer %d (%dx%d) frame %d %s: %s" % (i, W, H, t, key, rep))
+
+
+@pytest.mark.parametrize("n,kw", [(1, {}), (63, {"reuse": False}), (65, {"precision": "fp8"}), (1025, {"predictor": True}),
+                                  (3000, {"reuse": False, "precision": "bf16"})])
+def test_batched_derive_equals_frames(gs, n, kw):
+    """Eight viewers derived together (without a cache, with a line per anchor,
+    with the predictor): the images of each are those of its own frames, bit
+    for bit.  Anchor counts that leave words of 64 flags and steps of 1,024
+    anchors ragged."""
+    scene = synth.tiny_scene(n=n, seed=n)
+    kw = {"reuse": True, **kw}
+
+    def renderer():
+        r = gs.Renderer(k=scene.k, max_width=256, max_height=256, **kw)
+        if kw.get("predictor"):
+            r.predictor_load(gs.pack_params(synth.predictor_init(seed=3)))
+        r.load(scene)
+        return r
+
+    viewers = [(SIZES[i % 4][0], SIZES[i % 4][1], walk(4, *SIZES[i % 4], seed=70 + i)) for i in range(8)]
+    mixed, done, _, _ = serve(gs, renderer(), viewers)
+    assert all(s == 0 for _, _, s in done)
+    for i, (W, H, frames) in enumerate(viewers):
+        ref = renderer()
+        for t, (L, R) in enumerate(frames):
+            a = torch.zeros(3, H, W, device="cuda"); b = torch.zeros(3, H, W, device="cuda")
+            ref.frame(L, R, a, b)
+            torch.cuda.synchronize()
+            assert torch.equal(mixed[i][t][0], a) and torch.equal(mixed[i][t][1], b), (i, t)
