@@ -27,6 +27,7 @@ constexpr int kMaxSeg = 16;           // (viewer, eye) images per raster batch
 constexpr int kMaxViews = kMaxSeg / 2;  // viewers of one batch (two eyes each)
 constexpr int kGridBlocks = 2048;     // fixed grid of the grid-stride kernels
 constexpr int kScanBlocks = 1024;     // blocks of the device-wide scan
+constexpr int kMaxPreBlocks = 2048;   // blocks of the preprocess
 constexpr int kSortBlocks = 1024;     // blocks of each radix pass
 constexpr int kSortCap = 2048;        // items a block sorts in LDS (binning)
 constexpr int kBinLists = 8192;       // super tiles of the largest batch that is binned
@@ -193,8 +194,8 @@ struct Raster {
     float4* rec = nullptr;      // [4 * entries]: (mean2d, conic a b), (conic c, alpha, r g), (b, rows, seg, count),
                                 // spans (tall footprints: first stored span, output offset)
     int32_t* pt_list = nullptr;   // [max_entries] tall entries (entry ids) in their chunk's slots
-    uint64_t* pt_pack = nullptr;  // [max_entries / 256 + 1] per chunk of entries: tall ones | their super rows << 32
-    uint64_t* pt_off = nullptr;   // [max_entries / 256 + 1] exclusive prefix of pt_pack
+    uint64_t* pt_pack = nullptr;  // tall entries | their super rows << 32: [kMaxPreBlocks] of the preprocess's blocks,
+                                  // [max_entries / 256 + 1][2] of a chunk of entries and of its block's earlier chunks
     TallRec* trec = nullptr;  // [tall_cap] the tall footprints (ellipse, entry, rows, segment), dense
     uint32_t* pt_sroff = nullptr;  // [tall_cap] first stored super row of each
     int64_t tall_cap = 0;
@@ -224,7 +225,6 @@ struct Raster {
     int32_t* ranges = nullptr;  // [max_tiles][2]
     uint32_t* hist = nullptr;   // [256 * kSortBlocks] radix digit counts per block
     uint32_t* block_sums = nullptr;
-    uint64_t* block_sums64 = nullptr;  // [kScanBlocks] scan scratch of the tall path's 64-bit scan
     RasterCounters* cnt = nullptr;
     RasterCounters* cnt_host = nullptr;
     int sorted_buf = 0;         // which pval (pkey, pkey64) buffer holds the sorted items
@@ -241,11 +241,6 @@ struct Raster {
 // writing exclusive prefixes to out and the total to *total (device).
 hipError_t scan_u32(const uint32_t* in, uint32_t* out, const int32_t* n_dev, int64_t n_host, int32_t* total,
                     uint32_t* block_sums, hipStream_t st);
-// Exclusive scan of n (from *n_dev, at most n_max) uint64 values, each two
-// 32-bit counts (low, high) that scan independently; the totals of the two go
-// to *total_lo and *total_hi (device).  block_sums: kScanBlocks values.
-hipError_t scan_u64(const uint64_t* in, uint64_t* out, const int32_t* n_dev, int64_t n_max, int32_t* total_lo,
-                    int32_t* total_hi, uint64_t* block_sums, hipStream_t st);
 // Stream compaction: ids[k] = the k-th i with flags[i] != 0 (flags 0 or 1,
 // n as above), the count to *total (device).
 hipError_t compact_u32(const uint32_t* flags, const int32_t* n_dev, int64_t n_host, int32_t* total, int32_t* ids,

@@ -46,7 +46,7 @@ hipError_t raster_layout(Raster& r, int64_t max_entries, int64_t max_pairs, int6
     hipError_t e;
 #define A_(p, cnt) if ((e = A(p, cnt)) != hipSuccess) return e
     A_(r.rec, 4 * max_entries); A_(r.ntiles, max_entries);
-    A_(r.pt_list, max_entries); A_(r.pt_pack, max_entries / 256 + 1); A_(r.pt_off, max_entries / 256 + 1);
+    A_(r.pt_list, max_entries); A_(r.pt_pack, kMaxPreBlocks + 2 * (max_entries / 256 + 1));
     // tall footprints: at most a quarter of the entries (more are flagged as overflow)
     A_(r.trec, max_entries / 4 + 256); A_(r.pt_sroff, max_entries / 4 + 256);
     A_(r.srow, max_entries); A_(r.srow_y, max_entries);
@@ -65,7 +65,7 @@ hipError_t raster_layout(Raster& r, int64_t max_entries, int64_t max_pairs, int6
     A_(r.chunks, max_pairs / (kSortCap / 2) + 1); A_(r.long_lists, max_pairs / kSortCap + 1);
     A_(r.pieces, max_pairs / 512 + 1); A_(r.sup_total, kBinLists);
     A_(r.ranges, 2 * max_tiles); A_(r.tile_eval, 2 * max_tiles); A_(r.hist, 256 * kSortBlocks);
-    A_(r.block_sums, kScanBlocks); A_(r.block_sums64, kScanBlocks);
+    A_(r.block_sums, kScanBlocks);
     A_(r.n_sort, 1); A_(r.cnt, 1);
 #undef A_
     return hipSuccess;

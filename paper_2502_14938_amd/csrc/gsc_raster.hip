@@ -319,7 +319,8 @@ struct PreArgs {
     uint32_t* dkey;
     uint32_t* dval;       // and the depth sort's values (nullptr with full keys)
     int32_t* tall_list;   // tall entries of each chunk of 256 entries, in the chunk's slots
-    uint64_t* tall_pack;  // per chunk: its tall entries | their super rows << 32
+    uint64_t* tall_pack;  // tall entries | their super rows << 32: per block [kMaxPreBlocks], then per chunk its own
+                          // and those of the block's earlier chunks
     int32_t* ranges;     // [2 * super tiles] cleared here, unless the binning (n_ranges = 0) writes them all
     int64_t n_ranges;
     int64_t max_entries;
@@ -331,6 +332,7 @@ struct PreArgs {
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(7))) void k_preprocess(PreArgs p) {
     __shared__ uint32_t s_wtall[NT / 64];
     __shared__ uint32_t s_srows;  // super rows of the step's tall footprints
+    __shared__ uint64_t s_sum;    // tall_pack of the block's earlier steps (thread 0's)
     // the block's records, copied out together once complete (whole lines,
     // coalesced: a record written in two halves far apart in time would
     // leave half-written lines for the L2 to evict)
@@ -350,7 +352,10 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(7))) void k_
             p.rc->n_echunks = (s_ne + NT - 1) / NT;
         }
     }
-    if (threadIdx.x == 0) s_srows = 0u;
+    if (threadIdx.x == 0) {
+        s_srows = 0u;
+        s_sum = 0ull;
+    }
     for (int64_t i = gtid(); i < p.n_ranges; i += gstride()) p.ranges[i] = 0;
     __syncthreads();
     const int64_t ne = s_ne;
@@ -463,28 +468,6 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(7))) void k_
                 if (p.dval) p.dval[e] = (uint32_t)e;
             }
         }
-        const uint64_t m = __ballot(tall);
-        if (lane == 0) s_wtall[threadIdx.x >> 6] = (uint32_t)__popcll(m);
-        if (tall) atomicAdd(&s_srows, (uint32_t)((y1 >> kSupShift) - (y0 >> kSupShift) + 1));
-        __syncthreads();
-        const int64_t chunk = base / NT;
-        if (tall) {
-            uint32_t at = (uint32_t)__popcll(m & ((1ull << lane) - 1ull));
-            for (int q = 0; q < (int)(threadIdx.x >> 6); ++q) at += s_wtall[q];
-            p.tall_list[chunk * NT + at] = (int32_t)e;
-        }
-        if (threadIdx.x == 0) {
-            uint32_t n = 0;
-            for (int q = 0; q < NT / 64; ++q) n += s_wtall[q];
-            p.tall_pack[chunk] = (uint64_t)n | ((uint64_t)s_srows << 32);
-            s_srows = 0u;  // (read above; the next step's adds come after the barrier below)
-        }
-        {
-            const int nv = (int)(ne - base < NT ? ne - base : NT);
-            float4* dst = p.rec + kRec * base;
-            for (int i = threadIdx.x; i < kRec * nv; i += NT) dst[i] = s_rec[i];
-        }
-        __syncthreads();  // s_wtall and s_rec are rewritten by the next step
         // The eyes' entries 2j, 2j+1 sit in neighbouring lanes.  With one
         // rotation for both eyes their view depths differ by a constant, so
         // one key orders both: the left eye's depth when that eye draws the
@@ -502,7 +485,32 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(7))) void k_
             p.dkey[e >> 1] = key;
             p.dval[e >> 1] = (uint32_t)(e >> 1);
         }
+        const uint64_t m = __ballot(tall);
+        if (lane == 0) s_wtall[threadIdx.x >> 6] = (uint32_t)__popcll(m);
+        if (tall) atomicAdd(&s_srows, (uint32_t)((y1 >> kSupShift) - (y0 >> kSupShift) + 1));
+        __syncthreads();
+        const int64_t chunk = base / NT;
+        if (tall) {
+            uint32_t at = (uint32_t)__popcll(m & ((1ull << lane) - 1ull));
+            for (int q = 0; q < (int)(threadIdx.x >> 6); ++q) at += s_wtall[q];
+            p.tall_list[chunk * NT + at] = (int32_t)e;
+        }
+        if (threadIdx.x == 0) {
+            uint32_t n = 0;
+            for (int q = 0; q < NT / 64; ++q) n += s_wtall[q];
+            const uint64_t pack = (uint64_t)n | ((uint64_t)s_srows << 32);
+            reinterpret_cast<ulonglong2*>(p.tall_pack + kMaxPreBlocks)[chunk] = make_ulonglong2(pack, s_sum);
+            s_sum += pack;
+            s_srows = 0u;  // (read above; the next step's adds come after the barrier below)
+        }
+        {
+            const int nv = (int)(ne - base < NT ? ne - base : NT);
+            float4* dst = p.rec + kRec * base;
+            for (int i = threadIdx.x; i < kRec * nv; i += NT) dst[i] = s_rec[i];
+        }
+        __syncthreads();  // s_wtall and s_rec are rewritten by the next step
     }
+    if (threadIdx.x == 0) p.tall_pack[blockIdx.x] = s_sum;
 }
 
 struct DupArgs {
@@ -659,25 +667,62 @@ __global__ __launch_bounds__(NT) void k_dup_rows(DupArgs d) {
 
 
 // Dense records of the tall entries the preprocess listed per chunk of 256
-// entries: chunk c's footprints at f = its offset + i (the scan's low half),
-// their super rows (pairs of tile rows 2 Y, 2 Y + 1) from the chunk's
-// super-row offset (the high half) on, in list order.
+// entries: chunk c's footprints at f = its offset + i (the low half), their
+// super rows (pairs of tile rows 2 Y, 2 Y + 1) from the chunk's super-row
+// offset (the high half) on, in list order.  A chunk's offset is that of the
+// preprocess block that projected it, block c mod `blocks`, plus that within
+// the block; the blocks' offsets are prefixes of their sums, which every block
+// here makes for itself (at most kMaxPreBlocks values, in place of a scan over
+// the chunks: two launches of 4.7 us in a frame).
 __global__ __launch_bounds__(NT) void k_tall_compact(const int32_t* __restrict__ list, const uint64_t* __restrict__ pack,
-                                                     const uint64_t* __restrict__ off, const int32_t* n_chunks,
-                                                     const float4* __restrict__ rec, TallRec* __restrict__ trec,
-                                                     uint32_t* __restrict__ sroff, int64_t tall_cap,
-                                                     RasterCounters* rc) {
+                                                     int blocks, const float4* __restrict__ rec,
+                                                     TallRec* __restrict__ trec, uint32_t* __restrict__ sroff,
+                                                     int64_t tall_cap, RasterCounters* rc) {
+    constexpr int PER = kMaxPreBlocks / NT;
     __shared__ uint32_t wsum[NT / 64];
-    const int64_t nc = *n_chunks;
+    __shared__ uint64_t wsum64[NT / 64];
+    __shared__ uint64_t s_off[kMaxPreBlocks];
+    const int64_t nc = rc->n_echunks;
+    if ((int64_t)blockIdx.x >= nc && blockIdx.x != 0) return;  // (block-uniform)
+    // (the first chunk's words are on their way while the prefixes are made)
+    const ulonglong2* chunks = reinterpret_cast<const ulonglong2*>(pack + kMaxPreBlocks);
+    ulonglong2 po = make_ulonglong2(0ull, 0ull);
+    int32_t x = 0;
+    if ((int64_t)blockIdx.x < nc) {
+        po = chunks[blockIdx.x];
+        if (threadIdx.x < (uint32_t)po.x) x = list[(int64_t)blockIdx.x * NT + threadIdx.x];
+    }
+    {
+        uint64_t v[PER], mine = 0, total;
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+            const int q = threadIdx.x * PER + i;
+            v[i] = q < blocks ? pack[q] : 0ull;
+            mine += v[i];
+        }
+        uint64_t at = blockscan::block_excl_scan<uint64_t>(mine, wsum64, total);
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+            s_off[threadIdx.x * PER + i] = at;
+            at += v[i];
+        }
+        if (blockIdx.x == 0 && threadIdx.x == 0) {
+            rc->n_tall_e = (int32_t)(uint32_t)total;
+            rc->n_srows = (int32_t)(uint32_t)(total >> 32);
+        }
+        __syncthreads();
+    }
     for (int64_t c = blockIdx.x; c < nc; c += gridDim.x) {  // block-uniform
-        const uint32_t n = (uint32_t)pack[c];
-        const uint64_t o = off[c];
+        if (c != blockIdx.x) {
+            po = chunks[c];
+            if (threadIdx.x < (uint32_t)po.x) x = list[c * NT + threadIdx.x];
+        }
+        const uint32_t n = (uint32_t)po.x;
+        const uint64_t o = s_off[c % blocks] + po.y;
         const bool mine = threadIdx.x < n;
-        int32_t x = 0;
         float4 A = make_float4(0.f, 0.f, 0.f, 0.f), B = A, C = A;
         uint32_t nsr = 0;
         if (mine) {
-            x = list[c * NT + threadIdx.x];
             const float4* rp = rec + kRec * (int64_t)x;
             A = rp[0]; B = rp[1]; C = rp[2];
             const uint32_t rows = __float_as_uint(C.y);
@@ -1236,17 +1281,13 @@ static bool eyes_share_rotation(const SegTable& tab) {
 }
 
 // Tall footprints (more than kSmallRows tile rows): dense list of the
-// entries k_preprocess listed per chunk, offsets of their super rows, then
-// each footprint's super rows, spans and counts.
-hipError_t tall_spans(const SegTable& tab, Raster& r, hipStream_t st) {
+// entries k_preprocess (of `blocks` blocks) listed per chunk, offsets of their
+// super rows, then each footprint's super rows, spans and counts.
+hipError_t tall_spans(const SegTable& tab, Raster& r, int blocks, hipStream_t st) {
     RasterCounters* rc = r.cnt;
-    // one scan gives each chunk's first footprint (low half) and first super
-    // row (high half), and the totals
-    hipError_t e = scan_u64(r.pt_pack, r.pt_off, &rc->n_echunks, r.max_entries / kEntryChunk + 1, &rc->n_tall_e,
-                            &rc->n_srows, r.block_sums64, st);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_tall_compact, dim3(kGridBlocks), dim3(NT), 0, st, r.pt_list, r.pt_pack, r.pt_off,
-                       &rc->n_echunks, r.rec, r.trec, r.pt_sroff, r.tall_cap, rc);
+    const int64_t chunks = r.max_entries / kEntryChunk + 1;
+    hipLaunchKernelGGL(k_tall_compact, dim3((unsigned)(chunks < kGridBlocks ? chunks : kGridBlocks)), dim3(NT), 0, st,
+                       r.pt_list, r.pt_pack, blocks, r.rec, r.trec, r.pt_sroff, r.tall_cap, rc);
     hipLaunchKernelGGL(k_tall_spans, grid_fit(k_tall_spans, r.tall_cap * kTallGW), dim3(NT), 0, st, tab, r.trec,
                        r.pt_sroff, rc, r.tall_cap, r.rec, r.srow, r.srow_y, r.srow_cap, r.ntiles,
                        r.binned ? nullptr : r.nsup, r.binned || r.shared_depth ? nullptr : r.dkey[0]);
@@ -1269,9 +1310,11 @@ hipError_t raster_batch(const SegTable& tab_in, Raster& r, bool full_key_sort, b
     pa.max_entries = r.max_entries;
     r.shared_depth = !full_key_sort && eyes_share_rotation(tab);
     pa.shared_depth = r.shared_depth ? 1 : 0;
-    hipLaunchKernelGGL(k_preprocess, grid_fit(k_preprocess, r.max_entries), dim3(NT), 0, st, pa);
+    dim3 pre = grid_fit(k_preprocess, r.max_entries);
+    if (pre.x > (unsigned)kMaxPreBlocks) pre.x = kMaxPreBlocks;
+    hipLaunchKernelGGL(k_preprocess, pre, dim3(NT), 0, st, pa);
     mark(mk, 4, st);
-    hipError_t e0 = tall_spans(tab, r, st);
+    hipError_t e0 = tall_spans(tab, r, (int)pre.x, st);
     if (e0 != hipSuccess) return e0;
     mark(mk, 5, st);
     const int tile_bits = bits_for(tab.total_sup);  // the sort's key: the global super-tile id
