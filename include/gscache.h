@@ -219,8 +219,8 @@ int gsc_render_gaussians(gsc_ctx* ctx, const gsc_gaussians* g, const gsc_camera*
 /* Allocation-free variant of gsc_render_gaussians, for callers that cannot
  * allocate device memory: code under HIP graph capture, tight serving loops,
  * harnesses that forbid hipMalloc.  No context: the intermediate buffers
- * (the Gaussians' staged copy, per-Gaussian records, sort keys, tile pairs,
- * ranges, counters) live in one static device array of the library (48 MiB,
+ * (per-Gaussian records, sort keys, tile pairs, ranges, counters) live in one
+ * static device array of the library (48 MiB,
  * held by each device that loads the library until the process ends), and
  * the call allocates nothing.  Same kernels and results as
  * gsc_render_gaussians (depth pre-sorted pairs, no work counting).

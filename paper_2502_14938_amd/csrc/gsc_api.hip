@@ -119,9 +119,7 @@ void free_explicit(gsc_ctx* c) {
     (void)sync_all(c);
     c->xmem.release();
     c->xraster = Raster();
-    c->xg = {};
     c->xg_cap = 0;
-    c->xg_bytes = 0;
 }
 
 void free_labels(gsc_ctx* c) {
@@ -237,29 +235,9 @@ hipError_t reset_view(View& v, int64_t n, int dmax, hipStream_t st) {
     return hipGetLastError();
 }
 
-__global__ void k_pack_explicit(const float* __restrict__ mu, const float* __restrict__ cov,
-                                const float* __restrict__ rgb, const float* __restrict__ alpha, int64_t n, float4* L0,
-                                float4* L1, float4* L2, float* L3) {
-    int64_t st = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += st) {
-        L0[i] = make_float4(mu[3 * i], mu[3 * i + 1], mu[3 * i + 2], alpha[i]);
-        L1[i] = make_float4(cov[6 * i], cov[6 * i + 1], cov[6 * i + 2], cov[6 * i + 3]);
-        L2[i] = make_float4(cov[6 * i + 4], cov[6 * i + 5], rgb[3 * i], rgb[3 * i + 1]);
-        L3[i] = rgb[3 * i + 2];
-    }
-}
-
-hipError_t pack_explicit(const gsc_gaussians& g, float4* L0, float4* L1, float4* L2, float* L3, hipStream_t st) {
-    if (g.n <= 0) return hipSuccess;
-    int64_t blocks = (g.n + 255) / 256;
-    if (blocks > kGridBlocks) blocks = kGridBlocks;
-    hipLaunchKernelGGL(k_pack_explicit, dim3((unsigned)blocks), dim3(256), 0, st, g.mu, g.cov, g.rgb, g.alpha, g.n,
-                       L0, L1, L2, L3);
-    return hipGetLastError();
-}
-
-hipError_t explicit_gaussians(gsc_ctx* c, const gsc_gaussians& g, int64_t ntiles) {
-    int64_t need = g.n > 1 ? g.n : 1;
+// xraster for n explicit Gaussians and ntiles tiles.
+hipError_t explicit_raster(gsc_ctx* c, int64_t n, int64_t ntiles) {
+    int64_t need = n > 1 ? n : 1;
     if (c->xg_cap < need || c->xraster.max_tiles < ntiles) {
         free_explicit(c);
         int64_t cap = 1024;
@@ -267,19 +245,15 @@ hipError_t explicit_gaussians(gsc_ctx* c, const gsc_gaussians& g, int64_t ntiles
         int64_t pairs = c->cfg.max_pairs > 0 ? c->cfg.max_pairs : 64 * cap;
         if (pairs > (1ll << 31) - 1) pairs = (1ll << 31) - 1;
         int64_t tiles = ntiles > 1 ? ntiles : 1;
-        hipError_t e = hipSuccess;
-        if ((e = dalloc(c->xmem, c->xg_bytes, &c->xg.L0, cap)) == hipSuccess &&
-            (e = dalloc(c->xmem, c->xg_bytes, &c->xg.L1, cap)) == hipSuccess &&
-            (e = dalloc(c->xmem, c->xg_bytes, &c->xg.L2, cap)) == hipSuccess &&
-            (e = dalloc(c->xmem, c->xg_bytes, &c->xg.L3, cap)) == hipSuccess)
-            e = alloc_raster(c->xmem, c->xraster, cap, pairs, tiles, (c->cfg.flags & GSC_FLAG_FULL_KEY_SORT) != 0);
+        const hipError_t e =
+            alloc_raster(c->xmem, c->xraster, cap, pairs, tiles, (c->cfg.flags & GSC_FLAG_FULL_KEY_SORT) != 0);
         if (e != hipSuccess) {
             free_explicit(c);
             return e;
         }
         c->xg_cap = cap;
     }
-    return pack_explicit(g, c->xg.L0, c->xg.L1, c->xg.L2, c->xg.L3, c->stream);
+    return hipSuccess;
 }
 
 // Event set of the frame being issued (nullptr when timing is off).
@@ -588,21 +562,19 @@ int gsc_render_gaussians(gsc_ctx* c, const gsc_gaussians* g, const gsc_camera* c
         return fail(c, GSC_E_INVALID_ARG, "gsc_render_gaussians: invalid camera or image too large");
     if (g->n > (1ll << 30)) return fail(c, GSC_E_INVALID_ARG, "gsc_render_gaussians: too many Gaussians");
     int64_t ntiles = (int64_t)((cam->width + kTile - 1) / kTile) * ((cam->height + kTile - 1) / kTile);
-    hipError_t e = explicit_gaussians(c, *g, ntiles);
+    hipError_t e = explicit_raster(c, g->n, ntiles);
     if (e != hipSuccess) return hip_fail(c, e, "gsc_render_gaussians");
     SegTable tab;
     std::memset(&tab, 0, sizeof(tab));
     tab.n = 1;
     Seg& s = tab.s[0];
-    s.L0 = c->xg.L0; s.L1 = c->xg.L1; s.L2 = c->xg.L2; s.L3 = c->xg.L3; s.G = nullptr; s.nG = nullptr;
-    s.anchor_pos = nullptr; s.line_anchor = nullptr; s.k = 1;
-    s.nG_host = (int32_t)g->n;
+    raw_segment(s, *g);
     seg_camera(s, *cam);
     s.tile_base = 0;
     s.out_rgb = out_chw; s.out_T = out_T; s.out_nc = out_nc;
     tab.total_tiles = s.ntx * s.nty;
     e = raster_batch(tab, c->xraster, (c->cfg.flags & GSC_FLAG_FULL_KEY_SORT) != 0, c->count_work || out_nc,
-                     c->stream);
+                     c->stream, nullptr, nullptr, nullptr, true);
     if (e != hipSuccess) return hip_fail(c, e, "gsc_render_gaussians");
     c->last_tab = tab;
     c->rendered = true;
@@ -731,7 +703,7 @@ int gsc_get_stats(gsc_ctx* c, gsc_frame_stats* st) {
     st->depth_next = k.depth;
     st->overflow = ((r.overflow & 7) ? 1 : 0) | (k.overflow & 2);
     st->n_tall = r.n_tall_e;
-    size_t bytes = c->scene.bytes + c->view[0].bytes + c->view[1].bytes + c->raster.bytes + c->raster2.bytes + c->xg_bytes;
+    size_t bytes = c->scene.bytes + c->view[0].bytes + c->view[1].bytes + c->raster.bytes + c->raster2.bytes;
     st->device_bytes = (int64_t)bytes;
     if (c->rendered && !c->explicit_render && c->last_count_work && c->last_tab.total_tiles > 0) {
         std::vector<int32_t> te(2 * (size_t)c->last_tab.total_tiles);

@@ -577,7 +577,9 @@ constexpr uint32_t kCrowd = 64;
 __global__ __launch_bounds__(NS) __attribute__((amdgpu_waves_per_eu(6))) void k_bin_sort(uint64_t* __restrict__ items, const int32_t* __restrict__ ranges,
                                                  int total_sup, const RasterCounters* rc,
                                                  const SortPiece* __restrict__ pieces,
-                                                 const uint2* __restrict__ chunks, uint32_t* __restrict__ words) {
+                                                 const uint2* __restrict__ chunks, uint32_t* __restrict__ words,
+                 int32_t* status) {
+    if (status && blockIdx.x == 0 && threadIdx.x == 0) *status = rc->overflow;  // (final since k_bin<true>)
     __shared__ uint64_t lds[kSortCap];
     __shared__ uint32_t s_cnt[kBuckets + 1];
     __shared__ uint16_t s_cdf[kBuckets + 2];
@@ -768,7 +770,7 @@ __global__ __launch_bounds__(NM) void k_bin_merge(const uint64_t* __restrict__ i
 
 }  // namespace
 
-hipError_t bin_items(const SegTable& tab, Raster& r, hipStream_t st, Marks* mk) {
+hipError_t bin_items(const SegTable& tab, Raster& r, int32_t* status, hipStream_t st, Marks* mk) {
     BinArgs a;
     for (int q = 0; q < kMaxSeg; ++q)
         a.sg[q] = SupGeo{q < tab.n ? tab.s[q].sup_base : 0, q < tab.n ? tab.s[q].nsx : 0};
@@ -814,7 +816,7 @@ hipError_t bin_items(const SegTable& tab, Raster& r, hipStream_t st, Marks* mk) 
         hipLaunchKernelGGL(k_bin_split, grid_fit(k_bin_split, (int64_t)tab.total_sup * NP, NP), dim3(NP), 0, st, r.items,
                            r.ranges, r.long_lists, r.cnt, pieces, r.chunks, r.pval[0]);
     hipLaunchKernelGGL(k_bin_sort, dim3((unsigned)(tab.total_sup + (longer ? 1024 : 0))), dim3(NS), 0, st, r.items,
-                       r.ranges, tab.total_sup, r.cnt, pieces, r.chunks, r.pval[0]);
+                       r.ranges, tab.total_sup, r.cnt, pieces, r.chunks, r.pval[0], status);
     if (longer)
         hipLaunchKernelGGL(k_bin_merge, grid_fit(k_bin_merge, r.max_pairs / 4, NM), dim3(NM), 0, st, r.items, r.ranges,
                            r.cnt, r.chunks, r.pval[0]);

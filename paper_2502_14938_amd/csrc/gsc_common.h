@@ -316,12 +316,17 @@ hipError_t ssim_launch(const float* a, const float* b, int C, int H, int W, cons
 // blend_st (optional): the stream the blend runs on, after front_done is
 // recorded on st once the tile ranges are written (the stage marks of the
 // blend go to blend_st as well).
+// raw: the one segment's Gaussians are explicit ones (raw_segment), read from
+// the caller's arrays in place; a copy into packed arrays first cost 9 us for
+// 500,000 of them.
+// status (optional, device; binned batches): receives the overflow flags.
 hipError_t raster_batch(const SegTable& tab, Raster& r, bool full_key_sort, bool count_work, hipStream_t st,
-                        Marks* mk = nullptr, hipStream_t blend_st = nullptr, hipEvent_t front_done = nullptr);
+                        Marks* mk = nullptr, hipStream_t blend_st = nullptr, hipEvent_t front_done = nullptr,
+                        bool raw = false, int32_t* status = nullptr);
 
 // Every super tile's depth-ordered list of a batch (pval[0], ranges) from the
 // entries' spans, after the preprocess and the tall footprints' spans.
-hipError_t bin_items(const SegTable& tab, Raster& r, hipStream_t st, Marks* mk);
+hipError_t bin_items(const SegTable& tab, Raster& r, int32_t* status, hipStream_t st, Marks* mk);
 
 // Blocks of `threads` threads of `kernel` the whole device holds at once
 // (occupancy x compute units; cached per kernel and device).  Grid-stride

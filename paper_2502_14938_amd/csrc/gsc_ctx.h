@@ -71,8 +71,16 @@ hipError_t raster_layout(Raster& r, int64_t max_entries, int64_t max_pairs, int6
     return hipSuccess;
 }
 
-// Explicit Gaussians (public arrays) into the four line arrays, on st.
-hipError_t pack_explicit(const gsc_gaussians& g, float4* L0, float4* L1, float4* L2, float* L3, hipStream_t st);
+// Explicit Gaussians (public arrays) as a segment that k_preprocess reads raw.
+inline void raw_segment(Seg& s, const gsc_gaussians& g) {
+    s.L0 = reinterpret_cast<const float4*>(g.mu);
+    s.L1 = reinterpret_cast<const float4*>(g.cov);
+    s.L2 = reinterpret_cast<const float4*>(g.rgb);
+    s.L3 = g.alpha;
+    s.G = nullptr; s.nG = nullptr;
+    s.anchor_pos = nullptr; s.line_anchor = nullptr; s.k = 1;
+    s.nG_host = (int32_t)g.n;
+}
 // Set the thread's context-free error message (gsc_last_error(NULL)).
 int global_fail(int code, const std::string& msg);
 
@@ -123,15 +131,8 @@ struct gsc_ctx {
     double t_arrival = 0.0;
     int64_t frame = -1;
     gsc::SegTable last_tab{};
-    // explicit Gaussians of the raster-only entry (allocated on first use)
+    // most explicit Gaussians xraster is sized for (allocated on first use)
     int64_t xg_cap = 0;
-    size_t xg_bytes = 0;
-    struct {
-        float4* L0;
-        float4* L1;
-        float4* L2;
-        float* L3;
-    } xg{};
     // reuse predictor
     float* pred_w = nullptr;      // fp32 parameters
     uint16_t* pred_wbf = nullptr; // bf16 copy for inference
@@ -168,7 +169,7 @@ namespace gsc {
 // Waits for the context's stream and, with two frames in flight, for the
 // blend stream.
 hipError_t sync_all(gsc_ctx* c);
-hipError_t explicit_gaussians(gsc_ctx* c, const gsc_gaussians& g, int64_t ntiles);
+hipError_t explicit_raster(gsc_ctx* c, int64_t n, int64_t ntiles);
 void free_explicit(gsc_ctx* c);
 void free_labels(gsc_ctx* c);
 void pred_free(gsc_ctx* c);

@@ -27,16 +27,13 @@ constexpr int64_t kNaTiles = (int64_t)(GSC_NOALLOC_MAX_SIDE / kTile) * (GSC_NOAL
 constexpr size_t kNaBytes = (size_t)48 << 20;  // holds the layout below (checked at set-up)
 constexpr size_t kNaAlign = 256;
 constexpr int kNaDevices = 64;
+static_assert(kNaTiles <= 4 * kBinLists, "every image is binned (the sort then reports the status)");
 
 __device__ __align__(256) uint8_t scratch[kNaBytes];
 
 // Per device: the array's device address and the buffers carved from it.
 struct NaDevice {
     bool ready = false;
-    float4* L0 = nullptr;
-    float4* L1 = nullptr;
-    float4* L2 = nullptr;
-    float* L3 = nullptr;
     Raster r;
 };
 
@@ -62,7 +59,7 @@ struct Carve {
 // Once per device, with that device current: the array's address, then the
 // layout (the raster buffers for GSC_NOALLOC_MAX_GAUSSIANS entries,
 // GSC_NOALLOC_MAX_PAIRS pairs and the tiles of a GSC_NOALLOC_MAX_SIDE square
-// image, after the Gaussians' four line arrays).
+// image).
 int na_setup(int dev, NaDevice*& out) {
     std::lock_guard<std::mutex> lk(g_na_mu);
     NaDevice& d = g_na[dev];
@@ -75,9 +72,7 @@ int na_setup(int dev, NaDevice*& out) {
         Carve cv{static_cast<uint8_t*>(ptr), 0, kNaBytes};
         const int64_t n = GSC_NOALLOC_MAX_GAUSSIANS;
         NaDevice t;
-        if (cv(t.L0, n) != hipSuccess || cv(t.L1, n) != hipSuccess || cv(t.L2, n) != hipSuccess ||
-            cv(t.L3, n) != hipSuccess ||
-            raster_layout(t.r, n, GSC_NOALLOC_MAX_PAIRS, kNaTiles, false, cv) != hipSuccess)
+        if (raster_layout(t.r, n, GSC_NOALLOC_MAX_PAIRS, kNaTiles, false, cv) != hipSuccess)
             return global_fail(GSC_E_HIP, "gsc_render_gaussians_noalloc: the static buffer is too small for its layout");
         t.r.max_entries = n;
         t.r.max_pairs = GSC_NOALLOC_MAX_PAIRS;
@@ -90,10 +85,6 @@ int na_setup(int dev, NaDevice*& out) {
     }
     out = &d;
     return GSC_OK;
-}
-
-__global__ void k_na_status(const RasterCounters* rc, int32_t* status) {
-    if (threadIdx.x == 0 && blockIdx.x == 0) *status = rc->overflow;
 }
 
 bool na_camera_ok(const gsc_camera& c) {
@@ -132,19 +123,12 @@ int gsc_render_gaussians_noalloc(const gsc_gaussians* g, const gsc_camera* cam, 
     std::memset(&tab, 0, sizeof(tab));
     tab.n = 1;
     Seg& s = tab.s[0];
-    s.L0 = d->L0; s.L1 = d->L1; s.L2 = d->L2; s.L3 = d->L3; s.G = nullptr; s.nG = nullptr;
-    s.anchor_pos = nullptr; s.line_anchor = nullptr; s.k = 1;
-    s.nG_host = (int32_t)g->n;
+    raw_segment(s, *g);
     seg_camera(s, *cam);
     s.tile_base = 0;
     s.out_rgb = out_chw; s.out_T = out_T; s.out_nc = nullptr;
     tab.total_tiles = s.ntx * s.nty;
-    e = pack_explicit(*g, d->L0, d->L1, d->L2, d->L3, st);
-    if (e == hipSuccess) e = raster_batch(tab, r, false, false, st);
-    if (e == hipSuccess && status) {
-        hipLaunchKernelGGL(k_na_status, dim3(1), dim3(64), 0, st, r.cnt, status);
-        e = hipGetLastError();
-    }
+    e = raster_batch(tab, r, false, false, st, nullptr, nullptr, nullptr, true, status);
     if (e != hipSuccess) return global_fail(GSC_E_HIP, std::string("gsc_render_gaussians_noalloc: ") + hipGetErrorString(e));
     return GSC_OK;
 }

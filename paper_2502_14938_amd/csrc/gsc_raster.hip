@@ -329,6 +329,9 @@ struct PreArgs {
 
 // (at most 72 VGPRs, no spill: seven waves per SIMD to cover the chain of
 // dependent loads of an entry)
+// kRaw: the segment's Gaussians are explicit ones, read from the caller's
+// arrays (mu, cov, rgb and alpha in the places of L0 to L3).
+template <bool kRaw>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(7))) void k_preprocess(PreArgs p) {
     __shared__ uint32_t s_wtall[NT / 64];
     __shared__ uint32_t s_srows;  // super rows of the step's tall footprints
@@ -378,13 +381,24 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(7))) void k_
             locate_entry(p.tab, s_base, e, si, g);
             const Seg& s = p.tab.s[si];
             int64_t src = s.G ? (int64_t)s.G[g] : g;
-            float4 l0 = s.L0[src], l1 = s.L1[src], l2 = s.L2[src];
-            lb = s.L3[src];
+            float4 l0, l1, l2;
+            if (kRaw) {
+                const float* mu = reinterpret_cast<const float*>(s.L0) + 3 * src;
+                const float* cov = reinterpret_cast<const float*>(s.L1) + 6 * src;
+                const float* rgb = reinterpret_cast<const float*>(s.L2) + 3 * src;
+                l0 = make_float4(mu[0], mu[1], mu[2], s.L3[src]);
+                l1 = make_float4(cov[0], cov[1], cov[2], cov[3]);
+                l2 = make_float4(cov[4], cov[5], rgb[0], rgb[1]);
+                lb = rgb[2];
+            } else {
+                l0 = s.L0[src]; l1 = s.L1[src]; l2 = s.L2[src];
+                lb = s.L3[src];
+            }
             // mu - eye = (anchor - eye) + (mu - anchor): the first term in FP64
             // from the exact FP32 anchor, the second as stored
             double ax = 0.0, ay = 0.0, az = 0.0;
             float lod_w = 1.f;
-            if (s.anchor_pos) {
+            if (!kRaw && s.anchor_pos) {
                 const int32_t an = s.line_anchor ? s.line_anchor[src / s.k] : (int32_t)(src / s.k);  // valid for every line in the buffer
                 const int32_t ai = an >= 0 ? an : 0;
                 const float4 ap = s.anchor_pos[ai];
@@ -1295,12 +1309,13 @@ hipError_t tall_spans(const SegTable& tab, Raster& r, int blocks, hipStream_t st
 }
 
 hipError_t raster_batch(const SegTable& tab_in, Raster& r, bool full_key_sort, bool count_work, hipStream_t st,
-                        Marks* mk, hipStream_t blend_st, hipEvent_t front_done) {
+                        Marks* mk, hipStream_t blend_st, hipEvent_t front_done, bool raw, int32_t* status) {
     if (r.max_entries > (int64_t)kEntryMask + 1) return hipErrorInvalidValue;  // entry ids share the value with the masks
     SegTable tab = tab_in;
     seg_supers(tab);
     RasterCounters* rc = r.cnt;
     mark(mk, 3, st);
+    if (status && (full_key_sort || tab.total_sup > kBinLists)) return hipErrorInvalidValue;
     r.binned = !full_key_sort && tab.total_sup <= kBinLists;
     PreArgs pa;
     pa.tab = tab; pa.rc = rc; pa.rec = r.rec; pa.ntiles = r.ntiles; pa.brec = r.binned ? r.brec : nullptr;
@@ -1310,9 +1325,12 @@ hipError_t raster_batch(const SegTable& tab_in, Raster& r, bool full_key_sort, b
     pa.max_entries = r.max_entries;
     r.shared_depth = !full_key_sort && eyes_share_rotation(tab);
     pa.shared_depth = r.shared_depth ? 1 : 0;
-    dim3 pre = grid_fit(k_preprocess, r.max_entries);
+    dim3 pre = raw ? grid_fit(k_preprocess<true>, r.max_entries) : grid_fit(k_preprocess<false>, r.max_entries);
     if (pre.x > (unsigned)kMaxPreBlocks) pre.x = kMaxPreBlocks;
-    hipLaunchKernelGGL(k_preprocess, pre, dim3(NT), 0, st, pa);
+    if (raw)
+        hipLaunchKernelGGL(k_preprocess<true>, pre, dim3(NT), 0, st, pa);
+    else
+        hipLaunchKernelGGL(k_preprocess<false>, pre, dim3(NT), 0, st, pa);
     mark(mk, 4, st);
     hipError_t e0 = tall_spans(tab, r, (int)pre.x, st);
     if (e0 != hipSuccess) return e0;
@@ -1324,7 +1342,7 @@ hipError_t raster_batch(const SegTable& tab_in, Raster& r, bool full_key_sort, b
     da.srow = r.srow; da.srow_y = r.srow_y; da.srow_cap = r.srow_cap; da.n_sort = r.n_sort;
     hipError_t e;
     if (r.binned) {
-        e = bin_items(tab, r, st, mk);
+        e = bin_items(tab, r, status, st, mk);
         if (e != hipSuccess) return e;
     } else if (!full_key_sort) {
         // low 32 key bits (depth) first, per Gaussian
