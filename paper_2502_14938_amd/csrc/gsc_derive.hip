@@ -241,8 +241,10 @@ struct LookupArgs {
 // Every visible owned line is stamped last_used = t.  The loop is uniform
 // per wave: the predictor runs on the whole wave (matrix cores) whenever one
 // of its lanes has a candidate.
+// (at most 128 VGPRs: four waves per SIMD; three took 25 us of the city's
+// lookup with the predictor, four 21)
 template <int V>
-__global__ __launch_bounds__(NT) void k_cache_lookup(Views<V> vs, LookupArgs a) {
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_cache_lookup(Views<V> vs, LookupArgs a) {
     __shared__ uint32_t s_h[NT / 64][kPredLdsWave];
     __shared__ uint32_t wsum[NT / 64];
     const ViewStage& v = vs.v[V == 1 ? 0 : blockIdx.y];

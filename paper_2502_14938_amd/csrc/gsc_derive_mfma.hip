@@ -74,10 +74,10 @@ double h_e4m3(double x) {
     return x < 0 ? -r : r;
 }
 
-__device__ __forceinline__ short d_bf16(float x) {
-    uint32_t u = __float_as_uint(x);
-    u += 0x7fffu + ((u >> 16) & 1u);
-    return (short)(u >> 16);
+// Four floats as bfloat16 (nearest even).
+__device__ __forceinline__ shortx4 d_bf16x4(float a, float b, float c, float d) {
+    const uint2 v = make_uint2(bf16_pair(a, b), bf16_pair(c, d));
+    return __builtin_bit_cast(shortx4, v);
 }
 
 __device__ __forceinline__ float sigm(float x) { return 1.0f / (1.0f + expf(-x)); }
@@ -335,9 +335,9 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_
             }
         } else {
             shortx4 b[3];
-            b[0] = shortx4{d_bf16(in.z[0]), d_bf16(in.z[1]), d_bf16(in.z[2]), d_bf16(in.z[3])};
-            b[1] = shortx4{d_bf16(in.z[4]), d_bf16(in.z[5]), d_bf16(in.z[6]), d_bf16(in.z[7])};
-            b[2] = q == 0 ? shortx4{d_bf16(dv[0]), d_bf16(dv[1]), d_bf16(dv[2]), d_bf16(dn)} : shortx4{0, 0, 0, 0};
+            b[0] = d_bf16x4(in.z[0], in.z[1], in.z[2], in.z[3]);
+            b[1] = d_bf16x4(in.z[4], in.z[5], in.z[6], in.z[7]);
+            b[2] = q == 0 ? d_bf16x4(dv[0], dv[1], dv[2], dn) : shortx4{0, 0, 0, 0};
 #pragma unroll
             for (int i2 = 0; i2 < 9; ++i2) {
                 const uint4 v = s_w1[i2 * 64 + lane];
@@ -372,7 +372,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_
                 h[hb][i] = fmaxf(v + comp(b1, i), 0.f);
             }
             if (MODE != GSC_PREC_F32)
-                hh[hb] = shortx4{d_bf16(h[hb][0]), d_bf16(h[hb][1]), d_bf16(h[hb][2]), d_bf16(h[hb][3])};
+                hh[hb] = d_bf16x4(h[hb][0], h[hb][1], h[hb][2], h[hb][3]);
         }
         // ---- layer 2: O^T = W2 H^T per 16-output tile, head by head
         int ot = 0;

@@ -357,12 +357,17 @@ __global__ __launch_bounds__(NT) void k_pred_to_bf16(const float* __restrict__ w
 
 
 // One candidate per lane; the loop is uniform per wave (the predictor runs
-// on the whole wave).
-__global__ __launch_bounds__(NT) void k_pred_infer(const uint16_t* __restrict__ wb, const float* __restrict__ w32,
+// on the whole wave).  Bound by latency (inputs, scalar weights, LDS, matrix
+// fragments, one after the other), so four waves a SIMD: 234,567 rows then
+// are one round of waves.  15.4 -> 13.2 us.
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_pred_infer(const uint16_t* __restrict__ wb, const float* __restrict__ w32,
                                                    const float* __restrict__ X, int64_t n, float* __restrict__ out) {
     __shared__ uint32_t s_h[NT / 64][kPredLdsWave];
     const int lane = threadIdx.x & 63;
     for (int64_t w0 = gtid() - lane; w0 < n; w0 += gstride()) {
+        // (the weights are loaded each time around: hoisted out of the loop,
+        // they would take 260 scalar registers and spill)
+        asm volatile("" : "+s"(wb), "+s"(w32));
         const int64_t r = w0 + lane;
         float x[kPredIn] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
         if (r < n) {
