@@ -24,10 +24,10 @@
 // Measured, a whole pass with the radix sorts and with this: 2,000 Gaussians
 // at 256x256 141 and 57 us, 60,000 at 1000x560 194 and 103 us, 500,000 at
 // 1920x1081 325 and 225 us, a stereo frame of 2 x 2048x1080 (6 M items) 729
-// and 699 us.  Of that last one's 230 us the writes take 75: they go to 4,352
+// and 699 us.  Of that last one's 205 us the writes take 75: they go to 4,352
 // lists at once, more than an XCD's L2 holds the ends of, so four of five
 // 8-byte items leave it as a partial line of their own (195 MB for 48); the
-// sort takes 74 (LDS), the division of the long lists 48, the counts 28.
+// sort takes 57, the division of the long lists 41, the counts 28.
 // With more lists the writes gather less and less, and the radix sorts, whose
 // launches are spread over more items, win: batches of stereo images with 6,192
 // super tiles take 588 us binned and 611 radix-sorted, with 13,392 1,031 and
@@ -495,11 +495,16 @@ static_assert(sizeof(SortPiece) == sizeof(int4), "one 16-byte word");
 // buckets out as pieces of kPieceRun items or more, up to kSortCap.  The
 // items themselves stay where they are.  A list that this does not divide
 // (one bucket holds too much, or it has more pieces than the block counts)
-// is sorted in chunks and merged instead.
-constexpr int NP = 1024;
+// is sorted in chunks and merged instead.  Bound by the latency of its three
+// passes over the list, so the keys are read once (the first 4,096 of a list,
+// which is all of most) and half as many threads as a block may have let the
+// lists of a frame be in flight together: the city's 48 -> 41 us.
+constexpr int NP = 512;
+constexpr int kHeld = 8;  // keys of a list a thread keeps in registers
+constexpr int kPieceBlocks = 3072;
 constexpr int kSplitBuckets = 8192;
 constexpr int kPieceRun = kSortCap / 2;
-constexpr int kMaxPieces = 2048;
+constexpr int kMaxPieces = 1024;
 __global__ __launch_bounds__(NP) void k_bin_split(const uint64_t* __restrict__ items, const int32_t* __restrict__ ranges,
                                                   const int32_t* __restrict__ long_lists, RasterCounters* rc,
                                                   SortPiece* __restrict__ pieces, uint2* __restrict__ chunks,
@@ -512,9 +517,22 @@ __global__ __launch_bounds__(NP) void k_bin_split(const uint64_t* __restrict__ i
         const int S = long_lists[li];
         const int start = ranges[2 * S], n = ranges[2 * S + 1] - start;
         const uint64_t* src = items + start;
-        uint32_t lo = 0xffffffffu, hi = 0u;
+        // the first kHeld keys of a thread stay in registers for the three
+        // passes over the list (most long lists have no more)
+        uint32_t held[kHeld], lo = 0xffffffffu, hi = 0u;
+#pragma unroll
+        for (int j = 0; j < kHeld; ++j) {
+            const int i = j * NP + (int)threadIdx.x;
+            held[j] = i < n ? reinterpret_cast<const uint32_t*>(src)[2 * i + 1] : 0u;
+        }
+#pragma unroll
+        for (int j = 0; j < kHeld; ++j) {
+            if (j * NP + (int)threadIdx.x >= n) continue;
+            lo = min(lo, held[j]);
+            hi = max(hi, held[j]);
+        }
 #pragma unroll 4
-        for (int i = threadIdx.x; i < n; i += NP) {
+        for (int i = kHeld * NP + threadIdx.x; i < n; i += NP) {
             const uint32_t k = (uint32_t)(src[i] >> 32);
             lo = min(lo, k);
             hi = max(hi, k);
@@ -522,8 +540,11 @@ __global__ __launch_bounds__(NP) void k_bin_split(const uint64_t* __restrict__ i
         for (int i = threadIdx.x; i < kSplitBuckets; i += NP) s_cnt[i] = 0u;
         block_min_max<NP>(lo, hi, s_red);
         const float scale = bucket_scale(lo, hi, kSplitBuckets);
+#pragma unroll
+        for (int j = 0; j < kHeld; ++j)
+            if (j * NP + (int)threadIdx.x < n) atomicAdd(&s_cnt[bucket_of(held[j], lo, scale, kSplitBuckets)], 1u);
 #pragma unroll 4
-        for (int i = threadIdx.x; i < n; i += NP)
+        for (int i = kHeld * NP + threadIdx.x; i < n; i += NP)
             atomicAdd(&s_cnt[bucket_of((uint32_t)(src[i] >> 32), lo, scale, kSplitBuckets)], 1u);
         __syncthreads();
         const uint32_t big = block_scan_counts<NP, kSplitBuckets / NP>(s_cnt, s_red);
@@ -551,8 +572,13 @@ __global__ __launch_bounds__(NP) void k_bin_split(const uint64_t* __restrict__ i
             pieces[atomicAdd(&rc->n_pieces, 1)] = SortPiece{start + (int)first, (int)(end - first), start, 1};
         }
         __syncthreads();  // (the prefixes become cursors)
+#pragma unroll
+        for (int j = 0; j < kHeld; ++j) {
+            const int i = j * NP + (int)threadIdx.x;
+            if (i < n) words[start + (int)atomicAdd(&s_cnt[bucket_of(held[j], lo, scale, kSplitBuckets)], 1u)] = (uint32_t)i;
+        }
 #pragma unroll 4
-        for (int i = threadIdx.x; i < n; i += NP) {
+        for (int i = kHeld * NP + threadIdx.x; i < n; i += NP) {
             const uint32_t at = atomicAdd(&s_cnt[bucket_of((uint32_t)(src[i] >> 32), lo, scale, kSplitBuckets)], 1u);
             words[start + at] = (uint32_t)i;
         }
@@ -572,13 +598,16 @@ __global__ __launch_bounds__(NP) void k_bin_split(const uint64_t* __restrict__ i
 // themselves say how: read as a piecewise linear distribution function they
 // spread the same keys over buckets of equal share.  What still crowds after
 // that (ties, mostly) takes the merge sort.
+// Latency again (barriers, LDS round trips): seven blocks a CU, and a block
+// per piece up to 3,072 of them (1,024, three pieces one after another, left a
+// third of the chip idle at the end): the city's 75 -> 57 us.
 constexpr int kBuckets = 1024;
 constexpr uint32_t kCrowd = 64;
-__global__ __launch_bounds__(NS) __attribute__((amdgpu_waves_per_eu(6))) void k_bin_sort(uint64_t* __restrict__ items, const int32_t* __restrict__ ranges,
+__global__ __launch_bounds__(NS) __attribute__((amdgpu_waves_per_eu(7))) void k_bin_sort(uint64_t* __restrict__ items, const int32_t* __restrict__ ranges,
                                                  int total_sup, const RasterCounters* rc,
                                                  const SortPiece* __restrict__ pieces,
                                                  const uint2* __restrict__ chunks, uint32_t* __restrict__ words,
-                 int32_t* status) {
+                                                 int32_t* status) {
     if (status && blockIdx.x == 0 && threadIdx.x == 0) *status = rc->overflow;  // (final since k_bin<true>)
     __shared__ uint64_t lds[kSortCap];
     __shared__ uint32_t s_cnt[kBuckets + 1];
@@ -811,14 +840,17 @@ hipError_t bin_items(const SegTable& tab, Raster& r, int32_t* status, hipStream_
     mark(mk, 10, st);
     // a list longer than kSortCap needs as many entries
     const bool longer = entries > kSortCap;
+    // (blocks for the pieces, a few entries' worth each: without work they cost
+    // a small batch more than they take from a large one)
+    const int64_t piece_blocks = !longer ? 0 : (entries < 256 * kPieceBlocks ? (entries + 255) / 256 : kPieceBlocks);
     SortPiece* pieces = reinterpret_cast<SortPiece*>(r.pieces);
     if (longer)
         hipLaunchKernelGGL(k_bin_split, grid_fit(k_bin_split, (int64_t)tab.total_sup * NP, NP), dim3(NP), 0, st, r.items,
                            r.ranges, r.long_lists, r.cnt, pieces, r.chunks, r.pval[0]);
-    hipLaunchKernelGGL(k_bin_sort, dim3((unsigned)(tab.total_sup + (longer ? 1024 : 0))), dim3(NS), 0, st, r.items,
+    hipLaunchKernelGGL(k_bin_sort, dim3((unsigned)(tab.total_sup + (unsigned)piece_blocks)), dim3(NS), 0, st, r.items,
                        r.ranges, tab.total_sup, r.cnt, pieces, r.chunks, r.pval[0], status);
     if (longer)
-        hipLaunchKernelGGL(k_bin_merge, grid_fit(k_bin_merge, r.max_pairs / 4, NM), dim3(NM), 0, st, r.items, r.ranges,
+        hipLaunchKernelGGL(k_bin_merge, dim3(512), dim3(NM), 0, st, r.items, r.ranges,
                            r.cnt, r.chunks, r.pval[0]);
     mark(mk, 11, st);
     r.sorted_buf = 0;
