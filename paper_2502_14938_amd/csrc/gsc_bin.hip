@@ -211,12 +211,20 @@ __global__ __launch_bounds__(NB) void k_bin(BinArgs a) {
     // (block-uniform loop: whole waves take part in the wide footprints' items)
     const int ne = a.rc->n_entries, near = a.run >> 8;
     const int place = (lane & 15) * (a.run >> 4) + wv * near + (lane >> 4);
+    const bool here = (lane >> 4) < near;
+    auto load = [&](int64_t e) {
+        if (!here || e >= ne) return make_uint4(1u, 0u, 0u, 0u);  // (not binned)
+        return a.brec[e];
+    };
+    uint4 next = load((int64_t)b * a.run + place);
     for (int64_t eb = (int64_t)b * a.run; eb < ne; eb += (int64_t)nblk * a.run) {
         const int64_t e = eb + place;
         Row r0{0, 0, 0, 0u, 0u}, r1 = r0, r2 = r0;
         uint32_t depth = 0;
-        if (e < ne && (lane >> 4) < near) {
-            const uint4 w = a.brec[e];
+        {
+            // (the next run's record is on its way while this one's items are written)
+            const uint4 w = next;
+            next = load(e + (int64_t)nblk * a.run);
             const BinRec r = unpack_bin(w);
             if (r.binned) {
                 const SupGeo sg = s_sg[r.seg];
