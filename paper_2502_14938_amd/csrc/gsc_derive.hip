@@ -89,6 +89,23 @@ __device__ __forceinline__ float plane_side(const float (&q)[4], const float4& p
     return fmaf(q[2], p.z, s) + q[3];
 }
 
+// Does anchor position p (bounding radius in w) at level l stay?
+__device__ __forceinline__ bool keep_anchor(const DeriveCam& cam, const float4& p, int l) {
+    bool keep = true;
+    if (l != 0) {
+        float vx = p.x - cam.pos[0], vy = p.y - cam.pos[1], vz = p.z - cam.pos[2];
+        float lim = ldexpf(cam.d_ref, -l);
+        float d2 = fmaf(vz, vz, fmaf(vx, vx, vy * vy));
+        // with the fractional transition a level stays until its weight
+        // clamp(2 - dist / d_l, 0, 1) reaches 0 (the weight is applied
+        // by the rasteriser's preprocess)
+        keep = cam.fade ? d2 < 4.f * lim * lim : d2 <= lim * lim;
+    }
+#pragma unroll
+    for (int i = 0; i < 5; ++i) keep = keep && (plane_side(cam.planes[i], p, i & 1) >= -p.w);
+    return keep;
+}
+
 constexpr int kSelStep = 1024;  // anchors a block tests at a time, four per thread with their loads together
 
 template <int V>
@@ -120,22 +137,7 @@ __global__ __launch_bounds__(NT) void k_select(Views<V> vs, const float4* __rest
                 v.slot_of[a] = -1;
                 v.line_anchor[a] = -1;
             }
-            const float4 p = pos[u];
-            const int l = lev[u];
-            bool keep = a < n;
-            if (l != 0) {
-                float vx = p.x - cam.pos[0], vy = p.y - cam.pos[1], vz = p.z - cam.pos[2];
-                float lim = ldexpf(cam.d_ref, -l);
-                float d2 = fmaf(vz, vz, fmaf(vx, vx, vy * vy));
-                // with the fractional transition a level stays until its weight
-                // clamp(2 - dist / d_l, 0, 1) reaches 0 (the weight is applied
-                // by the rasteriser's preprocess)
-                keep = keep && (cam.fade ? d2 < 4.f * lim * lim : d2 <= lim * lim);
-            }
-#pragma unroll
-            for (int i = 0; i < 5; ++i) {
-                keep = keep && (plane_side(cam.planes[i], p, i & 1) >= -p.w);
-            }
+            const bool keep = a < n && keep_anchor(cam, pos[u], lev[u]);
             const uint64_t m = __ballot(keep);
             if ((threadIdx.x & 63) == 0 && a < b1) v.bits[a >> 6] = m;
             count += (uint32_t)__popcll(m);
@@ -143,6 +145,69 @@ __global__ __launch_bounds__(NT) void k_select(Views<V> vs, const float4* __rest
     }
     const uint32_t total = waves_sum(count, wsum);
     if (threadIdx.x == 0) v.sums[blockIdx.x] = total;
+}
+
+// A scene of at most kOneBlock anchors takes one block for the selection and
+// one for the composition, each with its scan inside: two launches of 3.5 us
+// less of the small stereo frame's 90.
+constexpr int kOneBlock = 4096;
+constexpr int NO = 1024;
+
+// Exclusive prefix of v over the block of NO threads from carry on, which
+// becomes the carry after them.
+__device__ __forceinline__ uint32_t one_block_scan(uint32_t v, uint32_t& carry, uint32_t* wsum) {
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    uint32_t x = v;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t y = __shfl_up(x, o, 64);
+        if (lane >= o) x += y;
+    }
+    if (lane == 63) wsum[w] = x;
+    __syncthreads();
+    uint32_t before = carry, all = carry;
+    for (int i = 0; i < NO / 64; ++i) {
+        before += i < w ? wsum[i] : 0u;
+        all += wsum[i];
+    }
+    __syncthreads();
+    carry = all;
+    return before + x - v;
+}
+
+// k_select and k_visible of a small scene.
+template <int V, bool kNoCache>
+__global__ __launch_bounds__(NO) void k_select_small(Views<V> vs, const float4* __restrict__ posr,
+                                                     const uint8_t* __restrict__ level, int n, int direct) {
+    __shared__ uint32_t wsum[NO / 64];
+    const ViewStage& v = vs.v[V == 1 ? 0 : blockIdx.y];
+    frame_begin(v.cnt, v.pu_hist, v.t, v.cam);
+    const int32_t depth = v.cnt->depth;
+    uint32_t carry = 0;
+    for (int base = 0; base < n; base += NO) {
+        const int a = base + threadIdx.x;
+        bool keep = false;
+        if (a < n) {
+            if (direct && v.line_anchor[a] >= 0 && v.t - v.line_tau[a] > depth) {
+                v.slot_of[a] = -1;
+                v.line_anchor[a] = -1;
+            }
+            keep = keep_anchor(v.cam, posr[a], level[a]);
+        }
+        const uint32_t e = one_block_scan(keep ? 1u : 0u, carry, wsum);
+        if (keep) {
+            v.visible[e] = a;
+            if (kNoCache) {
+                v.misses[e] = (int32_t)e;
+                v.vslot[e] = (int32_t)e;
+                v.line_anchor[e] = a;
+            }
+        }
+    }
+    if (threadIdx.x == 0) {
+        v.cnt->n_visible = (int32_t)carry;
+        if (kNoCache) v.cnt->n_miss = (int32_t)carry;
+    }
 }
 
 // X_t from the flags, ascending.  Without a cache every visible anchor is a
@@ -539,6 +604,29 @@ __global__ __launch_bounds__(NT) void k_compose_scatter(Views<V> vs, int k) {
     }
 }
 
+// k_compose_reduce and k_compose_scatter of a small scene.
+template <int V>
+__global__ __launch_bounds__(NO) void k_compose_small(Views<V> vs, int k, int32_t dmax, int32_t guide) {
+    __shared__ uint32_t wsum[NO / 64];
+    const ViewStage& v = vs.v[V == 1 ? 0 : blockIdx.y];
+    if (threadIdx.x == 0) depth_update(v.cnt, dmax, guide);  // eq. 4, from this frame's counts
+    const int nv = v.cnt->n_visible;
+    uint32_t carry = 0;
+    for (int base = 0; base < nv; base += NO) {
+        const int i = base + threadIdx.x;
+        int32_t slot = -1;
+        uint32_t m = i < nv ? compose_mask(v.vslot, v.line_mask, i, slot) : 0u;
+        uint32_t o = one_block_scan((uint32_t)__popc(m), carry, wsum);
+        const int64_t gb = (int64_t)slot * k;
+        while (m) {
+            const int j = __ffs(m) - 1;
+            m &= m - 1u;
+            v.G[o++] = (int32_t)(gb + j);
+        }
+    }
+    if (threadIdx.x == 0) v.cnt->n_gauss = (int32_t)carry;
+}
+
 }  // namespace
 
 #define GSC_TRY(x)                              \
@@ -581,12 +669,19 @@ hipError_t derive_stage(const DeriveArgs* views, int nv, hipStream_t st, Marks* 
         const int64_t b = (n + step - 1) / step;
         return dim3((unsigned)(b < kScanBlocks ? b : kScanBlocks), (unsigned)nv);
     };
-    hipLaunchKernelGGL(k_select<V>, blocks(kSelStep), dim3(NT), 0, st, vs, sc.posr, sc.level, n, direct ? 1 : 0);
-    if (!reuse) {
-        hipLaunchKernelGGL((k_visible<V, true>), blocks(kSelStep), dim3(NT), 0, st, vs, n);
+    const bool small = n <= kOneBlock;
+    const dim3 one(1, (unsigned)nv);
+    if (small && !reuse) {
+        hipLaunchKernelGGL((k_select_small<V, true>), one, dim3(NO), 0, st, vs, sc.posr, sc.level, (int)n, 0);
+    } else if (small) {
+        hipLaunchKernelGGL((k_select_small<V, false>), one, dim3(NO), 0, st, vs, sc.posr, sc.level, (int)n, direct ? 1 : 0);
     } else {
+        hipLaunchKernelGGL(k_select<V>, blocks(kSelStep), dim3(NT), 0, st, vs, sc.posr, sc.level, n, direct ? 1 : 0);
+        if (reuse) hipLaunchKernelGGL((k_visible<V, false>), blocks(kSelStep), dim3(NT), 0, st, vs, n);
+        else hipLaunchKernelGGL((k_visible<V, true>), blocks(kSelStep), dim3(NT), 0, st, vs, n);
+    }
+    if (reuse) {
         const int64_t C = v.C;
-        hipLaunchKernelGGL((k_visible<V, false>), blocks(kSelStep), dim3(NT), 0, st, vs, n);
         if (!direct)  // (direct: done in k_select)
             hipLaunchKernelGGL(k_cache_invalidate, grid_fit(k_cache_invalidate, C), dim3(NT), 0, st, v.line_anchor, v.line_tau,
                                v.slot_of, C, t, cnt, v.evict_hist);
@@ -640,8 +735,12 @@ hipError_t derive_stage(const DeriveArgs* views, int nv, hipStream_t st, Marks* 
     }
     mark(mk, 2, st);
     // compose the render buffer
-    hipLaunchKernelGGL(k_compose_reduce<V>, blocks(NT), dim3(NT), 0, st, vs, a.d_max, a.guide);
-    hipLaunchKernelGGL(k_compose_scatter<V>, blocks(NT), dim3(NT), 0, st, vs, sc.k);
+    if (small) {
+        hipLaunchKernelGGL(k_compose_small<V>, one, dim3(NO), 0, st, vs, sc.k, a.d_max, a.guide);
+    } else {
+        hipLaunchKernelGGL(k_compose_reduce<V>, blocks(NT), dim3(NT), 0, st, vs, a.d_max, a.guide);
+        hipLaunchKernelGGL(k_compose_scatter<V>, blocks(NT), dim3(NT), 0, st, vs, sc.k);
+    }
     mark(mk, 3, st);
     return hipGetLastError();
 }

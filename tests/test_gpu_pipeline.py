@@ -199,3 +199,25 @@ def test_wide_stereo_frame_with_32bit_tile_keys(gs, tiny):
         assert_pairs_large(pairs[eye], codes_g, ref[key], codes_o, ex, ref[key]["pre"]["depth"])
     assert_image(iL, ref["left"])
     assert_image(iR, ref["right"])
+
+
+@pytest.mark.parametrize("n", [1, 64, 1023, 1025, 4096, 4097, 5200])
+def test_selection_and_render_buffer_of_small_and_larger_scenes(gs, n):
+    """Scenes on either side of the most anchors that one block selects and
+    composes (4,096): visible anchors and render buffer are the oracle's, and
+    the same with a cache, in order."""
+    scene = synth.tiny_lod_scene(n=n, seed=n)
+    W, H = 96, 64
+    plain, cached = (gs.Renderer(k=scene.k, reuse=reuse, max_width=W, max_height=H) for reuse in (False, True))
+    plain.load(scene)
+    cached.load(scene)
+    for head in ((0.0, 0.0, -15.0), (0.5, 0.2, -13.0)):
+        L, R = synth.stereo_pair(head, (0, 0, 1), (0, -1, 0), W, H, math.radians(50), math.radians(35))
+        gpu_frame(plain, L, R)
+        gpu_frame(cached, L, R)
+        ref = oracle.render_frame(scene, L, R, debug=True)
+        vis, G = plain.debug("visible"), plain.debug("gauss")
+        assert_visible_and_buffer(vis, G, ref, scene.k)
+        st = plain.stats()
+        assert st["n_visible"] == len(vis) and st["n_gauss"] == len(G)
+        assert np.array_equal(cached.debug("visible"), vis)
