@@ -173,11 +173,10 @@ struct View {
     uint32_t* tmp_c = nullptr;  // [max(n, C)] scratch
     uint32_t* tmp_d = nullptr;  // [max(n, C)] scratch
     uint32_t* evict_hist = nullptr;  // [64]
-    int32_t* evict_scan_n = nullptr; // [1] count for the eviction scans
     int32_t* misses = nullptr;  // [n] visible positions of misses
     int32_t* free_list = nullptr; // [C]
     int32_t* G = nullptr;       // [max_gauss]
-    uint32_t* block_sums = nullptr;  // scan scratch
+    uint32_t* block_sums = nullptr;  // [4 kScanBlocks] sums per block of the stage's scans
     float* cand_feat = nullptr; // [n, 6] predictor features
     int32_t* cand_id = nullptr; // [n]
     Counters* cnt = nullptr;
@@ -248,11 +247,6 @@ struct Raster {
 // writing exclusive prefixes to out and the total to *total (device).
 hipError_t scan_u32(const uint32_t* in, uint32_t* out, const int32_t* n_dev, int64_t n_host, int32_t* total,
                     uint32_t* block_sums, hipStream_t st);
-// Stream compaction: ids[k] = the k-th i with flags[i] != 0 (flags 0 or 1,
-// n as above), the count to *total (device).
-hipError_t compact_u32(const uint32_t* flags, const int32_t* n_dev, int64_t n_host, int32_t* total, int32_t* ids,
-                       uint32_t* block_sums, hipStream_t st);
-
 // Stable LSD radix sort of (key, value) pairs over bits [bit0, bit1),
 // 8-bit digits, reduce-then-scan per pass (digit counts per block, a scan of
 // the counts in digit-major order, a scatter through LDS).  Count from

@@ -66,6 +66,9 @@ struct ViewStage {
     int32_t* G;
     int32_t t;
 };
+// the sums of the misses without a line, of the free lines, and of the lines at
+// the eviction's threshold lie behind them
+constexpr int kNeedSums = kScanBlocks, kFreeSums = 2 * kScanBlocks, kThrSums = 3 * kScanBlocks;
 template <int V>
 struct Views {
     ViewStage v[V];  // blockIdx.y: view
@@ -243,20 +246,40 @@ __global__ __launch_bounds__(NT) void k_visible(Views<V> vs, int64_t n) {
 
 // ------------------------------------------------------------- cache
 
-// Alg. 1: invalidate every line whose age exceeds the current depth (and
-// clear the eviction's histogram).
+// The free lines as flags (64 to a word) and their sum per block, from what
+// each line's `free_line` says; all threads of the block take part.
+template <class Fn>
+__device__ __forceinline__ void free_flags(int64_t C, uint64_t* bits, uint32_t* sums, uint32_t* wsum, Fn&& free_line) {
+    int64_t b0, b1;
+    blockscan::chunk_of(C, kSelStep, b0, b1);
+    uint32_t count = 0;
+    for (int64_t base = b0; base < b1; base += NT) {
+        const int64_t s = base + threadIdx.x;
+        const uint64_t m = __ballot(s < b1 && free_line(s));
+        if ((threadIdx.x & 63) == 0 && s < b1) bits[s >> 6] = m;
+        count += (uint32_t)__popcll(m);
+    }
+    const uint32_t total = waves_sum(count, wsum);
+    if (threadIdx.x == 0) sums[blockIdx.x] = total;
+}
+
+// Alg. 1: invalidate every line whose age exceeds the current depth; flags the
+// free lines and clears the eviction's histogram.
 __global__ __launch_bounds__(NT) void k_cache_invalidate(int32_t* __restrict__ line_anchor, const int32_t* __restrict__ tau,
                                                          int32_t* __restrict__ slot_of, int64_t C, int32_t t,
-                                                         Counters* cnt, uint32_t* __restrict__ evict_hist) {
-    int32_t d = cnt->depth;
+                                                         Counters* cnt, uint32_t* __restrict__ evict_hist,
+                                                         uint64_t* __restrict__ bits, uint32_t* __restrict__ sums) {
+    __shared__ uint32_t wsum[NT / 64];
+    const int32_t d = cnt->depth;
     if (blockIdx.x == 0 && threadIdx.x < 64) evict_hist[threadIdx.x] = 0u;
-    for (int64_t s = gtid(); s < C; s += gstride()) {
-        int32_t a = line_anchor[s];
-        if (a >= 0 && t - tau[s] > d) {
-            slot_of[a] = -1;
-            line_anchor[s] = -1;
-        }
-    }
+    free_flags(C, bits, sums, wsum, [&](int64_t s) {
+        const int32_t a = line_anchor[s];
+        if (a < 0) return true;
+        if (t - tau[s] <= d) return false;
+        slot_of[a] = -1;
+        line_anchor[s] = -1;
+        return true;
+    });
 }
 
 // Learned staleness (reuse predictor): features of one candidate.
@@ -316,7 +339,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_
     const int32_t nv = v.cnt->n_visible, t = v.t;
     int64_t b0, b1;
     blockscan::chunk_of(nv, NT, b0, b1);
-    uint32_t count = 0;
+    uint32_t count = 0, need = 0;  // misses, and those without a line
     for (int64_t base = b0; base < b1; base += NT) {
         const int64_t i = base + threadIdx.x;
         const bool valid = i < nv;
@@ -346,6 +369,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_
         const uint64_t m = __ballot(valid && !hit);
         if ((threadIdx.x & 63) == 0 && valid) v.bits[i >> 6] = m;
         count += (uint32_t)__popcll(m);
+        need += (uint32_t)__popcll(__ballot(valid && !hit && s < 0));
         if (valid) v.vslot[i] = a.direct ? aid : s;  // (-1: k_assign finds it a line)
         if (valid && a.direct) {
             if (!hit) {  // derived this frame into line aid
@@ -360,14 +384,30 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_
     }
     const uint32_t total = waves_sum(count, wsum);
     if (threadIdx.x == 0) v.sums[blockIdx.x] = total;
+    if (a.direct) return;
+    __syncthreads();
+    const uint32_t need_total = waves_sum(need, wsum);
+    if (threadIdx.x == 0) v.sums[kNeedSums + blockIdx.x] = need_total;
 }
 
-// Misses, ascending visible position (= ascending anchor id).
+// Misses, ascending visible position (= ascending anchor id).  With fewer
+// lines than anchors (need_rank) also the rank of each miss that owns no line
+// among those (kOwnsLine: it does), and the number of free lines.
+constexpr uint32_t kOwnsLine = 0xffffffffu;
 template <int V>
-__global__ __launch_bounds__(NT) void k_misses(Views<V> vs) {
+__global__ __launch_bounds__(NT) void k_misses(Views<V> vs, uint32_t* __restrict__ need_rank, int free_blocks) {
     __shared__ uint32_t wsum[NT / 64];
     const ViewStage& v = vs.v[V == 1 ? 0 : blockIdx.y];
-    uint32_t carry = blockscan::block_carry(v.sums, wsum, &v.cnt->n_miss);
+    uint32_t carry = blockscan::block_carry(v.sums, wsum, &v.cnt->n_miss), carry2 = 0;
+    if (need_rank) {
+        carry2 = blockscan::block_carry(v.sums + kNeedSums, wsum, &v.cnt->n_need);
+        if (blockIdx.x == 0) {
+            uint32_t n = 0;
+            for (int i = threadIdx.x; i < free_blocks; i += NT) n += v.sums[kFreeSums + i];
+            n = blockscan::block_sum(n, wsum);
+            if (threadIdx.x == 0) v.cnt->n_free = (int32_t)n;
+        }
+    }
     int64_t b0, b1;
     blockscan::chunk_of(v.cnt->n_visible, NT, b0, b1);
     for (int64_t base = b0; base < b1; base += NT) {
@@ -377,20 +417,12 @@ __global__ __launch_bounds__(NT) void k_misses(Views<V> vs) {
         const uint32_t e = carry + blockscan::block_excl_scan(f, wsum, tot);
         if (f) v.misses[e] = (int32_t)i;
         carry += tot;
+        if (!need_rank) continue;  // (block-uniform)
+        const uint32_t need = f && v.vslot[i] < 0 ? 1u : 0u;
+        const uint32_t rank = carry2 + blockscan::block_excl_scan(need, wsum, tot);
+        if (f) need_rank[e] = need ? rank : kOwnsLine;
+        carry2 += tot;
     }
-}
-
-// need[j] = 1 iff miss j (visible position misses[j]) owns no line.
-__global__ __launch_bounds__(NT) void k_need_flags(const int32_t* __restrict__ misses, const int32_t* __restrict__ visible,
-                                                   const int32_t* __restrict__ slot_of, Counters* cnt,
-                                                   uint32_t* __restrict__ need) {
-    int32_t nm = cnt->n_miss;
-    for (int64_t j = gtid(); j < nm; j += gstride()) need[j] = slot_of[visible[misses[j]]] < 0 ? 1u : 0u;
-}
-
-__global__ __launch_bounds__(NT) void k_free_flags(const int32_t* __restrict__ line_anchor, int64_t C,
-                                                   uint32_t* __restrict__ flags) {
-    for (int64_t s = gtid(); s < C; s += gstride()) flags[s] = line_anchor[s] < 0 ? 1u : 0u;
 }
 
 // Eviction plan: lines not visible now (last_used < t) are candidates; take
@@ -417,12 +449,11 @@ __global__ __launch_bounds__(NT) void k_evict_hist(const int32_t* __restrict__ l
 
 // The plan (run by every block of the flags' kernel; the first one stores it).
 struct EvictPlan {
-    int32_t thr, left, n_evict, scan_n, short_of;
+    int32_t thr, left, n_evict, short_of;
     bool over;
 };
-__device__ __forceinline__ EvictPlan evict_plan(const uint32_t* hist, int32_t t, int32_t dmax, int32_t shortfall,
-                                                int64_t n_anchor) {
-    EvictPlan p{t, 0, 0, 0, shortfall > 0 ? shortfall : 0, false};
+__device__ __forceinline__ EvictPlan evict_plan(const uint32_t* hist, int32_t t, int32_t dmax, int32_t shortfall) {
+    EvictPlan p{t, 0, 0, shortfall > 0 ? shortfall : 0, false};
     if (shortfall <= 0) return p;
     int32_t acc = 0;
     for (int b = 0; b < dmax; ++b) {
@@ -431,7 +462,6 @@ __device__ __forceinline__ EvictPlan evict_plan(const uint32_t* hist, int32_t t,
             p.thr = (t - dmax) + b;
             p.left = shortfall - acc;
             p.n_evict = shortfall;
-            p.scan_n = (int32_t)n_anchor;
             return p;
         }
         acc += h;
@@ -441,50 +471,87 @@ __device__ __forceinline__ EvictPlan evict_plan(const uint32_t* hist, int32_t t,
     return p;
 }
 
-// Anchors (ascending id) whose line sits in the threshold bin.
+// Anchors (ascending id) whose line sits in the threshold bin: flags and sums.
 __global__ __launch_bounds__(NT) void k_evict_thr_flags(const int32_t* __restrict__ slot_of,
                                                         const int32_t* __restrict__ line_last,
                                                         const uint32_t* __restrict__ hist, int32_t t, int32_t dmax,
-                                                        int64_t n_anchor, int32_t* scan_n, Counters* cnt,
-                                                        uint32_t* __restrict__ flags) {
+                                                        int64_t n, Counters* cnt, uint64_t* __restrict__ bits,
+                                                        uint32_t* __restrict__ sums) {
     __shared__ uint32_t h[64];
+    __shared__ uint32_t wsum[NT / 64];
     __shared__ EvictPlan s_plan;
     if (threadIdx.x < 64) h[threadIdx.x] = hist[threadIdx.x];
     __syncthreads();
-    if (threadIdx.x == 0) s_plan = evict_plan(h, t, dmax, cnt->n_need - cnt->n_free, n_anchor);
+    if (threadIdx.x == 0) s_plan = evict_plan(h, t, dmax, cnt->n_need - cnt->n_free);
     __syncthreads();
     const EvictPlan p = s_plan;
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         cnt->evict_short = p.short_of;
         cnt->n_evict = p.n_evict;
-        *scan_n = p.scan_n;
         if (p.short_of > 0) {
             cnt->evict_thr = p.thr;
             cnt->evict_left = p.left;
         }
         if (p.over) cnt->overflow |= 2;  // the frame is marked overflowed
     }
-    for (int64_t a = gtid(); a < p.scan_n; a += gstride()) {
-        int32_t s = slot_of[a];
-        flags[a] = (s >= 0 && line_last[s] == p.thr) ? 1u : 0u;
-    }
+    if (p.left <= 0) return;  // nothing evicted, or every candidate
+    free_flags(n, bits, sums, wsum, [&](int64_t a) {
+        const int32_t s = slot_of[a];
+        return s >= 0 && line_last[s] == p.thr;
+    });
 }
 
+// Evicts the lines of the anchors (ascending id) that the plan takes: those
+// last used before the threshold, and the first `left` at it.
 __global__ __launch_bounds__(NT) void k_evict_apply(int32_t* __restrict__ line_anchor, const int32_t* __restrict__ line_last,
-                                                    int32_t* __restrict__ slot_of, const uint32_t* __restrict__ rank,
-                                                    int64_t C, int32_t t, Counters* cnt, int32_t* scan_n) {
-    // the free list is made again if anything was evicted
-    if (gtid() == 0) *scan_n = cnt->evict_short > 0 ? (int32_t)C : 0;
+                                                    int32_t* __restrict__ slot_of, const uint64_t* __restrict__ bits,
+                                                    const uint32_t* __restrict__ sums, int64_t n, int32_t t, Counters* cnt) {
+    __shared__ uint32_t wsum[NT / 64];
     if (cnt->evict_short <= 0) return;
-    int32_t thr = cnt->evict_thr, left = cnt->evict_left;
-    for (int64_t s = gtid(); s < C; s += gstride()) {
-        int32_t a = line_anchor[s];
-        int32_t lu = line_last[s];
-        if (a < 0 || lu >= t) continue;
-        if (lu < thr || (lu == thr && (int32_t)rank[a] < left)) {
+    const int32_t thr = cnt->evict_thr, left = cnt->evict_left;
+    uint32_t carry = left > 0 ? blockscan::block_carry<uint32_t>(sums, wsum) : 0u;
+    int64_t b0, b1;
+    blockscan::chunk_of(n, kSelStep, b0, b1);
+    for (int64_t base = b0; base < b1; base += NT) {
+        const int64_t a = base + threadIdx.x;
+        const uint32_t at = left > 0 && a < b1 ? (uint32_t)(bits[a >> 6] >> (a & 63)) & 1u : 0u;
+        uint32_t tot;
+        const uint32_t rank = carry + blockscan::block_excl_scan(at, wsum, tot);
+        carry += tot;
+        const int32_t s = a < b1 ? slot_of[a] : -1;
+        if (s < 0) continue;
+        const int32_t lu = line_last[s];
+        if (lu < t && (lu < thr || (at && (int32_t)rank < left))) {
             slot_of[a] = -1;
             line_anchor[s] = -1;
         }
+    }
+}
+
+// The free lines again, if anything was evicted.
+__global__ __launch_bounds__(NT) void k_free_flags(const int32_t* __restrict__ line_anchor, int64_t C, const Counters* cnt,
+                                                   uint64_t* __restrict__ bits, uint32_t* __restrict__ sums) {
+    __shared__ uint32_t wsum[NT / 64];
+    if (cnt->evict_short <= 0) return;
+    free_flags(C, bits, sums, wsum, [&](int64_t s) { return line_anchor[s] < 0; });
+}
+
+// And listed, ascending.
+__global__ __launch_bounds__(NT) void k_free_list(const uint64_t* __restrict__ bits, const uint32_t* __restrict__ sums,
+                                                  int64_t C, int32_t* __restrict__ free_list) {
+    __shared__ uint32_t wsum[NT / 64];
+    uint32_t carry = blockscan::block_carry<uint32_t>(sums, wsum);
+    int64_t b0, b1;
+    blockscan::chunk_of(C, kSelStep, b0, b1);
+    for (int64_t base = b0; base < b1; base += kSelStep) {
+        const int64_t i0 = base + threadIdx.x * 4;
+        const uint32_t f = i0 < b1 ? (uint32_t)(bits[i0 >> 6] >> (i0 & 63)) & 15u : 0u;
+        uint32_t tot;
+        uint32_t e = carry + blockscan::block_excl_scan((uint32_t)__popc(f), wsum, tot);
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (f >> u & 1u) free_list[e++] = (int32_t)(i0 + u);
+        carry += tot;
     }
 }
 
@@ -493,15 +560,15 @@ __global__ __launch_bounds__(NT) void k_evict_apply(int32_t* __restrict__ line_a
 __global__ __launch_bounds__(NT) void k_assign(const int32_t* __restrict__ misses, const int32_t* __restrict__ visible,
                                                int32_t* __restrict__ slot_of, int32_t* __restrict__ line_anchor,
                                                int32_t* __restrict__ line_tau, int32_t* __restrict__ line_last,
-                                               const uint32_t* __restrict__ need, const uint32_t* __restrict__ need_rank,
+                                               const uint32_t* __restrict__ need_rank,
                                                const int32_t* __restrict__ free_list, int32_t t, int64_t C,
                                                Counters* cnt, int32_t* __restrict__ vslot) {
     int32_t nm = cnt->n_miss;
     for (int64_t j = gtid(); j < nm; j += gstride()) {
         int32_t aid = visible[misses[j]];
         int32_t s;
-        if (need[j]) {
-            uint32_t r = need_rank[j];
+        const uint32_t r = need_rank[j];
+        if (r != kOwnsLine) {
             if ((int64_t)r >= C || r >= (uint32_t)max(cnt->n_free + cnt->n_evict, 0)) {
                 atomicOr(&cnt->overflow, 2);
                 continue;
@@ -541,11 +608,7 @@ __device__ __forceinline__ void depth_update(Counters* cnt, int32_t dmax, int32_
 }
 
 
-__global__ __launch_bounds__(NT) void k_free_flags_n(const int32_t* __restrict__ line_anchor, const int32_t* n_dev,
-                                                     uint32_t* __restrict__ flags) {
-    int64_t C = *n_dev;
-    for (int64_t s = gtid(); s < C; s += gstride()) flags[s] = line_anchor[s] < 0 ? 1u : 0u;
-}
+
 
 // ------------------------------------------------------------- compose
 // G_t = [(i, j) : i visible ascending, j ascending, alpha_ij > 0]; each entry
@@ -682,9 +745,14 @@ hipError_t derive_stage(const DeriveArgs* views, int nv, hipStream_t st, Marks* 
     }
     if (reuse) {
         const int64_t C = v.C;
+        // free lines and eviction flags of a cache with fewer lines than anchors
+        uint64_t* fbits = reinterpret_cast<uint64_t*>(v.tmp_c);
+        uint64_t* tbits = reinterpret_cast<uint64_t*>(v.tmp_d);
+        const int64_t cb = (C + kSelStep - 1) / kSelStep;
+        const dim3 cblocks((unsigned)(cb < kScanBlocks ? cb : kScanBlocks));
         if (!direct)  // (direct: done in k_select)
-            hipLaunchKernelGGL(k_cache_invalidate, grid_fit(k_cache_invalidate, C), dim3(NT), 0, st, v.line_anchor, v.line_tau,
-                               v.slot_of, C, t, cnt, v.evict_hist);
+            hipLaunchKernelGGL(k_cache_invalidate, cblocks, dim3(NT), 0, st, v.line_anchor, v.line_tau, v.slot_of, C, t, cnt,
+                               v.evict_hist, fbits, v.block_sums + kFreeSums);
         LookupArgs la;
         la.predictor = (a.flags & GSC_FLAG_PREDICTOR) ? 1 : 0;
         la.thr = a.pred_thr; la.posr = sc.posr; la.level = sc.level; la.scale = sc.scale;
@@ -692,31 +760,20 @@ hipError_t derive_stage(const DeriveArgs* views, int nv, hipStream_t st, Marks* 
         la.cand_feat = a.collect ? v.cand_feat : nullptr; la.cand_id = v.cand_id;
         la.direct = direct ? 1 : 0;
         hipLaunchKernelGGL(k_cache_lookup<V>, blocks(NT), dim3(NT), 0, st, vs, la);
-        hipLaunchKernelGGL(k_misses<V>, blocks(NT), dim3(NT), 0, st, vs);
+        hipLaunchKernelGGL(k_misses<V>, blocks(NT), dim3(NT), 0, st, vs, direct ? nullptr : v.tmp_b, (int)cblocks.x);
         if (!direct) {
-            // misses that need a line, and their ranks
-            uint32_t* need = v.tmp_a;
-            uint32_t* need_rank = v.tmp_b;
-            hipLaunchKernelGGL(k_need_flags, grid_fit(k_need_flags, n), dim3(NT), 0, st, v.misses, v.visible, v.slot_of, cnt, need);
-            GSC_TRY(scan_u32(need, need_rank, &cnt->n_miss, n, &cnt->n_need, v.block_sums, st));
-            // free lines, ascending
-            uint32_t* fflag = reinterpret_cast<uint32_t*>(v.tmp_c);
-            uint32_t* fpos = reinterpret_cast<uint32_t*>(v.tmp_d);
-            hipLaunchKernelGGL(k_free_flags, grid_fit(k_free_flags, C), dim3(NT), 0, st, v.line_anchor, C, fflag);
-            GSC_TRY(compact_u32(fflag, nullptr, C, &cnt->n_free, v.free_list, v.block_sums, st));
             // eviction of outdated lines when free lines are short
+            const dim3 nblocks(blocks(kSelStep).x);
             hipLaunchKernelGGL(k_evict_hist, grid_fit(k_evict_hist, C), dim3(NT), 0, st, v.line_anchor, v.line_last, C, t, a.d_max,
                                cnt, v.evict_hist);
-            hipLaunchKernelGGL(k_evict_thr_flags, grid_fit(k_evict_thr_flags, n), dim3(NT), 0, st, v.slot_of, v.line_last,
-                               v.evict_hist, t, a.d_max, n, v.evict_scan_n, cnt, fflag);
-            GSC_TRY(scan_u32(fflag, fpos, v.evict_scan_n, n, nullptr, v.block_sums, st));
-            hipLaunchKernelGGL(k_evict_apply, grid_fit(k_evict_apply, C), dim3(NT), 0, st, v.line_anchor, v.line_last, v.slot_of, fpos,
-                               C, t, cnt, v.evict_scan_n);
-            // free list again if anything was evicted (count 0 otherwise)
-            hipLaunchKernelGGL(k_free_flags_n, grid_fit(k_free_flags_n, C), dim3(NT), 0, st, v.line_anchor, v.evict_scan_n, fflag);
-            GSC_TRY(compact_u32(fflag, v.evict_scan_n, C, nullptr, v.free_list, v.block_sums, st));
+            hipLaunchKernelGGL(k_evict_thr_flags, nblocks, dim3(NT), 0, st, v.slot_of, v.line_last, v.evict_hist, t, a.d_max, n,
+                               cnt, tbits, v.block_sums + kThrSums);
+            hipLaunchKernelGGL(k_evict_apply, nblocks, dim3(NT), 0, st, v.line_anchor, v.line_last, v.slot_of, tbits,
+                               v.block_sums + kThrSums, n, t, cnt);
+            hipLaunchKernelGGL(k_free_flags, cblocks, dim3(NT), 0, st, v.line_anchor, C, cnt, fbits, v.block_sums + kFreeSums);
+            hipLaunchKernelGGL(k_free_list, cblocks, dim3(NT), 0, st, fbits, v.block_sums + kFreeSums, C, v.free_list);
             hipLaunchKernelGGL(k_assign, grid_fit(k_assign, n), dim3(NT), 0, st, v.misses, v.visible, v.slot_of, v.line_anchor,
-                               v.line_tau, v.line_last, need, need_rank, v.free_list, t, C, cnt, v.vslot);
+                               v.line_tau, v.line_last, v.tmp_b, v.free_list, t, C, cnt, v.vslot);
         }
     }
     // decode the misses on the matrix cores

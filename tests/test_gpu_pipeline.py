@@ -221,3 +221,26 @@ def test_selection_and_render_buffer_of_small_and_larger_scenes(gs, n):
         st = plain.stats()
         assert st["n_visible"] == len(vis) and st["n_gauss"] == len(G)
         assert np.array_equal(cached.debug("visible"), vis)
+
+
+@pytest.mark.parametrize("n", [65, 1025, 4099, 9001])
+def test_one_line_fewer_than_anchors_equals_a_line_each(gs, n):
+    """A cache of n - 1 lines keeps free lists and plans evictions, one of n
+    does not: while nothing has to be evicted the frames, hits and misses are
+    the same, at sizes that leave words of 64 flags and steps of 1,024 ragged."""
+    scene = synth.tiny_lod_scene(n=n, seed=n)
+    W, H = 96, 64
+    rs = [gs.Renderer(k=scene.k, reuse=True, max_width=W, max_height=H, cache_capacity=c) for c in (n, n - 1)]
+    for r in rs:
+        r.load(scene)
+    for i in range(6):
+        L, R = synth.stereo_pair((0.3 * i, 0.1 * i, -15.0 + 0.5 * i), (0.02 * i, 0, 1), (0, -1, 0), W, H,
+                                 math.radians(50), math.radians(35))
+        imgs = [gpu_frame(r, L, R) for r in rs]
+        st = [r.stats() for r in rs]
+        if st[1]["n_evicted"]:
+            break  # (as many anchors seen as there are lines)
+        assert np.array_equal(imgs[0][0], imgs[1][0]) and np.array_equal(imgs[0][1], imgs[1][1])
+        for key in ("n_visible", "n_miss", "n_gauss", "depth_used"):
+            assert st[0][key] == st[1][key]
+        assert np.array_equal(rs[0].debug("misses"), rs[1].debug("misses"))
