@@ -985,8 +985,10 @@ __global__ __launch_bounds__(NT) void k_ranges(const K* __restrict__ keys, const
 // equal to min(0.99, o exp(-q/2)) of the conic quadratic q (the hardware
 // exp2 flushes results below 2^-126 to zero, far below the 1/255 cut-off).
 // Per pixel: skip alpha < 1/255; stop before a Gaussian that would take
-// T(1 - alpha) below 1e-4; otherwise composite.  The composite step is
-// predicated (no branches); the wave stops once all its pixels are done.
+// T(1 - alpha) below 1e-4; otherwise composite.  The wave stops once all its
+// pixels are done.  Bound by vector issue: 13 instructions and an exponential
+// (worth four) a pixel and Gaussian, 115 M a wave in the city's two images,
+// 187 us at one every four cycles.
 static_assert(kBlendThreads == 64, "k_blend maps one wave onto a part of a 16x16 tile");
 
 // Can a staged Gaussian reach alpha >= 1/255 anywhere on the pixel centres
@@ -1154,9 +1156,19 @@ __global__ __launch_bounds__(kBlendThreads) __attribute__((amdgpu_waves_per_eu(k
                     const bool uu = live[i] && al >= kMinAlpha;
                     const bool ac = uu && tn >= kTStop;  // composite
                     const bool st = uu && !ac;           // stop here
-                    const float w = ac ? wf : 0.f;
-                    cr[i] = fmaf(gb.z, w, cr[i]); cg[i] = fmaf(gb.w, w, cg[i]); cbl[i] = fmaf(gc, w, cbl[i]);
-                    T[i] = ac ? tn : T[i];
+                    // a branch for whole tiles, whose waves are many enough to
+                    // cover it (eight viewers 782 -> 759 us); halves and
+                    // quarters go on without (178 against 189 us, 62 against 72)
+                    if (kPx == 4) {
+                        if (ac) {
+                            cr[i] = fmaf(gb.z, wf, cr[i]); cg[i] = fmaf(gb.w, wf, cg[i]); cbl[i] = fmaf(gc, wf, cbl[i]);
+                            T[i] = tn;
+                        }
+                    } else {
+                        const float w = ac ? wf : 0.f;
+                        cr[i] = fmaf(gb.z, w, cr[i]); cg[i] = fmaf(gb.w, w, cg[i]); cbl[i] = fmaf(gc, w, cbl[i]);
+                        T[i] = ac ? tn : T[i];
+                    }
                     if (kCount) nc[i] += ac ? 1 : 0;
                     if (kCount == 2) stp[i] = st ? own + k : stp[i];
                     live[i] = live[i] && !st;
