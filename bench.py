@@ -401,8 +401,8 @@ def run_frames(args):
     cand = {k: per_frame[k] for k in DOM_CANDIDATES}
     top = max(cand, key=cand.get)
     if max(per_frame["dup_rows"], per_frame["dup_big"]) > cand[top]:
-        dom, dom_stages, kname, drow = "duplicate", ["dup_rows", "tall_list", "dup_big"], \
-            "k_dup_rows + k_tall_compact + k_dup_big", "duplicate"
+        # a 2048x1080 stereo pair is binned: its items are written by k_bin<true>
+        dom, dom_stages, kname, drow = "duplicate", ["dup_rows", "tall_list", "dup_big"], "k_bin", "duplicate"
     else:
         dom, dom_stages = top, [top]
         kname, drow = DOM_CANDIDATES[top]

@@ -11,7 +11,7 @@
  *                         compose of the render buffer (Section 4, Alg. 1,
  *                         eq. 4; Section 3.1 eq. 3; Section 6 AnchorDecoder)
  *   gsc_render_stereo     per-eye EWA projection, opacity-aware exact tile
- *                         binning, (tile | depth) radix sort, front-to-back
+ *                         binning, (tile | depth) order, front-to-back
  *                         compositing (Section 3.1; Section 6
  *                         RasterizeGaussians)
  *
@@ -223,7 +223,7 @@ int gsc_render_gaussians(gsc_ctx* ctx, const gsc_gaussians* g, const gsc_camera*
  * static device array of the library (48 MiB,
  * held by each device that loads the library until the process ends), and
  * the call allocates nothing.  Same kernels and results as
- * gsc_render_gaussians (depth pre-sorted pairs, no work counting).
+ * gsc_render_gaussians (same list order, no work counting).
  * g: device arrays as for gsc_render_gaussians, n <= GSC_NOALLOC_MAX_GAUSSIANS;
  * cam: host, width and height <= GSC_NOALLOC_MAX_SIDE; out_chw [3,H,W] and
  * out_T [H,W] (may be NULL): caller-owned device float32; status (device,
@@ -258,9 +258,10 @@ int gsc_reset_cache(gsc_ctx* ctx);
 #define GSC_DBG_PREPROC 6   /* float32 [n_gauss, 8]: mean2d.x, .y, conic a b c, alpha, depth,
                                tile count (as float) for eye */
 #define GSC_DBG_DEPTH 7     /* int32 [1]: current reuse depth */
-#define GSC_DBG_SORT_KEYS 8 /* uint32 [sorted items of the last raster batch]: the sorted keys, global
-                               super-tile ids (a super tile is 2x2 tiles; images in order), as the
-                               ranges read them */
+#define GSC_DBG_SORT_KEYS 8 /* uint32 [sorted items of the last raster batch]: each item's global
+                               super-tile id (a super tile is 2x2 tiles; images in order): the sorted
+                               keys as the ranges read them, or, of a binned batch, the same ids
+                               written out from its ranges */
 #define GSC_DBG_RAW_RANGES 9 /* int32 [global super tiles, 2]: [start, end) of every super tile in the
                                sorted keys ([0, 0) for one without pairs) */
 #define GSC_DBG_SORT_VALS 10 /* uint32 [sorted items]: entry | mask << 28, the mask's bit
@@ -299,8 +300,9 @@ int gsc_pipeline(gsc_ctx* ctx, int enable);
  * 1.5, normalised), C1 = 0.01^2, C2 = 0.03^2, the map averaged over every
  * window position inside the image and over channels.  Waits for the
  * context's streams first (the images may come from a frame in flight) and
- * at the end; allocates a small scratch buffer per call.  height and width
- * at least 11, channels 1..65535 (GSC_E_INVALID_ARG otherwise). */
+ * at the end; a small scratch buffer is kept with the context (images that
+ * need a larger one allocate it for the call).  height and width at least
+ * 11, channels 1..65535 (GSC_E_INVALID_ARG otherwise). */
 int gsc_ssim(gsc_ctx* ctx, const float* a, const float* b, int32_t channels, int32_t height, int32_t width,
              double* out);
 
@@ -308,19 +310,25 @@ int gsc_ssim(gsc_ctx* ctx, const float* a, const float* b, int32_t channels, int
  * With timing on, every frame (gsc_derive + gsc_render_stereo) records HIP
  * events on the context's stream at its stage boundaries; gsc_timing_read
  * synchronises and returns the summed device milliseconds per stage over the
- * frames issued since timing was switched on or last read.  Stages: */
+ * frames issued since timing was switched on or last read.  A batch of at
+ * most 8,192 super tiles (2x2 tiles) is binned: stages 6, 7 and 10 do its
+ * work and stages 5, 8, 9 and 11 read next to nothing.  A larger batch, and
+ * one under GSC_FLAG_FULL_KEY_SORT, is sorted by radix passes.  Stages: */
 #define GSC_STAGE_SCHEDULE 0    /* unified-camera selection, cache schedule */
 #define GSC_STAGE_DERIVE 1      /* MLP derivation of the misses (MFMA) */
 #define GSC_STAGE_COMPOSE 2     /* depth update, render buffer */
 #define GSC_STAGE_PREPROCESS 3  /* projection, conic, extent, spans of footprints up to 4 tile rows */
 #define GSC_STAGE_TALL_SPANS 4  /* row spans and tile counts of taller footprints */
-#define GSC_STAGE_DEPTH_SORT 5  /* per-Gaussian depth radix passes */
-#define GSC_STAGE_PAIR_SCAN 6   /* pair offsets in depth order */
-#define GSC_STAGE_DUP_ROWS 7    /* pair emission, footprints of up to 4 tile rows */
-#define GSC_STAGE_TALL_LIST 8   /* dense list of the taller footprints */
-#define GSC_STAGE_DUP_BIG 9     /* pair emission, taller footprints */
-#define GSC_STAGE_TILE_SORT 10  /* tile-id radix passes over the pairs */
-#define GSC_STAGE_RANGES 11     /* per-tile ranges */
+#define GSC_STAGE_DEPTH_SORT 5  /* per-Gaussian depth radix passes (sorted batches) */
+#define GSC_STAGE_PAIR_SCAN 6   /* binned: items per super tile and their columns' sums;
+                                   sorted: pair offsets in depth order */
+#define GSC_STAGE_DUP_ROWS 7    /* binned: items written to their super tiles' lists;
+                                   sorted: emission, footprints of up to 4 tile rows */
+#define GSC_STAGE_TALL_LIST 8   /* sorted: dense list of the taller footprints */
+#define GSC_STAGE_DUP_BIG 9     /* sorted: emission, taller footprints */
+#define GSC_STAGE_TILE_SORT 10  /* binned: every list split and put in depth order;
+                                   sorted: tile-id radix passes over the items */
+#define GSC_STAGE_RANGES 11     /* sorted: ranges of the super tiles */
 #define GSC_STAGE_BLEND 12      /* blend */
 #define GSC_NUM_STAGES 13
 /* Switch timing on (enable != 0) or off; clears what was recorded.  Waits
