@@ -504,9 +504,12 @@ static_assert(sizeof(SortPiece) == sizeof(int4), "one 16-byte word");
 // items themselves stay where they are.  A list that this does not divide
 // (one bucket holds too much, or it has more pieces than the block counts)
 // is sorted in chunks and merged instead.  Bound by the latency of its three
-// passes over the list, so the keys are read once (the first 4,096 of a list,
-// which is all of most) and half as many threads as a block may have let the
-// lists of a frame be in flight together: the city's 48 -> 41 us.
+// passes over the list, so the first 4,096 keys, all of most lists, are read
+// once, the others' next step is loaded while a step is counted or placed, and
+// half as many threads as a block may have let the lists of a frame be in
+// flight together: the city's 48 -> 41 us high above it, and 107 -> 88 near
+// the ground, where lists have up to 46,000 items (before the loads ahead).
+// Steps twice as long, by keys or by threads, take as long or longer (93, 89).
 constexpr int NP = 512;
 constexpr int kHeld = 8;  // keys of a list a thread keeps in registers
 constexpr int kPieceBlocks = 3072;
@@ -525,35 +528,46 @@ __global__ __launch_bounds__(NP) void k_bin_split(const uint64_t* __restrict__ i
         const int S = long_lists[li];
         const int start = ranges[2 * S], n = ranges[2 * S + 1] - start;
         const uint64_t* src = items + start;
-        // the first kHeld keys of a thread stay in registers for the three
-        // passes over the list (most long lists have no more)
+        // A step is kHeld keys of every thread.  The first step's stay in
+        // registers for the three passes (many long lists have no more); the
+        // others' are loaded a step ahead.
+        const uint32_t* keys = reinterpret_cast<const uint32_t*>(src) + 1;
         uint32_t held[kHeld], lo = 0xffffffffu, hi = 0u;
+        auto load = [&](int base, uint32_t (&k)[kHeld]) {
 #pragma unroll
-        for (int j = 0; j < kHeld; ++j) {
-            const int i = j * NP + (int)threadIdx.x;
-            held[j] = i < n ? reinterpret_cast<const uint32_t*>(src)[2 * i + 1] : 0u;
-        }
+            for (int j = 0; j < kHeld; ++j) {
+                const int i = base + j * NP + (int)threadIdx.x;
+                k[j] = i < n ? keys[2 * (int64_t)i] : 0u;
+            }
+        };
+        load(0, held);
+        auto steps = [&](auto&& f) {
+            uint32_t cur[kHeld], next[kHeld] = {};
 #pragma unroll
-        for (int j = 0; j < kHeld; ++j) {
-            if (j * NP + (int)threadIdx.x >= n) continue;
-            lo = min(lo, held[j]);
-            hi = max(hi, held[j]);
-        }
-#pragma unroll 4
-        for (int i = kHeld * NP + threadIdx.x; i < n; i += NP) {
-            const uint32_t k = (uint32_t)(src[i] >> 32);
-            lo = min(lo, k);
-            hi = max(hi, k);
-        }
+            for (int j = 0; j < kHeld; ++j) cur[j] = held[j];
+            for (int base = 0; base < n; base += kHeld * NP) {  // block-uniform
+                if (base + kHeld * NP < n) load(base + kHeld * NP, next);
+                f(base + (int)threadIdx.x, cur, base + kHeld * NP <= n);
+#pragma unroll
+                for (int j = 0; j < kHeld; ++j) cur[j] = next[j];
+            }
+        };
+        steps([&](int i, const uint32_t (&k)[kHeld], bool) {
+#pragma unroll
+            for (int j = 0; j < kHeld; ++j)
+                if (i + j * NP < n) {
+                    lo = min(lo, k[j]);
+                    hi = max(hi, k[j]);
+                }
+        });
         for (int i = threadIdx.x; i < kSplitBuckets; i += NP) s_cnt[i] = 0u;
         block_min_max<NP>(lo, hi, s_red);
         const float scale = bucket_scale(lo, hi, kSplitBuckets);
+        steps([&](int i, const uint32_t (&k)[kHeld], bool) {
 #pragma unroll
-        for (int j = 0; j < kHeld; ++j)
-            if (j * NP + (int)threadIdx.x < n) atomicAdd(&s_cnt[bucket_of(held[j], lo, scale, kSplitBuckets)], 1u);
-#pragma unroll 4
-        for (int i = kHeld * NP + threadIdx.x; i < n; i += NP)
-            atomicAdd(&s_cnt[bucket_of((uint32_t)(src[i] >> 32), lo, scale, kSplitBuckets)], 1u);
+            for (int j = 0; j < kHeld; ++j)
+                if (i + j * NP < n) atomicAdd(&s_cnt[bucket_of(k[j], lo, scale, kSplitBuckets)], 1u);
+        });
         __syncthreads();
         const uint32_t big = block_scan_counts<NP, kSplitBuckets / NP>(s_cnt, s_red);
         const int np = (n + kPieceRun - 1) / kPieceRun;
@@ -580,16 +594,21 @@ __global__ __launch_bounds__(NP) void k_bin_split(const uint64_t* __restrict__ i
             pieces[atomicAdd(&rc->n_pieces, 1)] = SortPiece{start + (int)first, (int)(end - first), start, 1};
         }
         __syncthreads();  // (the prefixes become cursors)
+        steps([&](int i, const uint32_t (&k)[kHeld], bool full) {
+            if (full) {  // (the step's places asked for together)
+                uint32_t at[kHeld];
 #pragma unroll
-        for (int j = 0; j < kHeld; ++j) {
-            const int i = j * NP + (int)threadIdx.x;
-            if (i < n) words[start + (int)atomicAdd(&s_cnt[bucket_of(held[j], lo, scale, kSplitBuckets)], 1u)] = (uint32_t)i;
-        }
-#pragma unroll 4
-        for (int i = kHeld * NP + threadIdx.x; i < n; i += NP) {
-            const uint32_t at = atomicAdd(&s_cnt[bucket_of((uint32_t)(src[i] >> 32), lo, scale, kSplitBuckets)], 1u);
-            words[start + at] = (uint32_t)i;
-        }
+                for (int j = 0; j < kHeld; ++j) at[j] = atomicAdd(&s_cnt[bucket_of(k[j], lo, scale, kSplitBuckets)], 1u);
+#pragma unroll
+                for (int j = 0; j < kHeld; ++j) words[start + (int)at[j]] = (uint32_t)(i + j * NP);
+            } else {
+#pragma unroll
+                for (int j = 0; j < kHeld; ++j)
+                    if (i + j * NP < n)
+                        words[start + (int)atomicAdd(&s_cnt[bucket_of(k[j], lo, scale, kSplitBuckets)], 1u)] =
+                            (uint32_t)(i + j * NP);
+            }
+        });
         __syncthreads();  // before the next list
     }
 }
