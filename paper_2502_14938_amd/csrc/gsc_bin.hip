@@ -643,7 +643,13 @@ __global__ __launch_bounds__(NS) __attribute__((amdgpu_waves_per_eu(7))) void k_
     const bool own = (int)blockIdx.x < total_sup;
     const int np = own ? 1 : rc->n_pieces, total = own ? 1 : np + rc->n_chunks;
     const int step = own ? 1 : (int)gridDim.x - total_sup;
-    for (int i = own ? 0 : (int)blockIdx.x - total_sup; i < total; i += step) {  // block-uniform
+    // Blocks go to the 8 XCDs in turn: an eighth of the pieces in a row to
+    // each, so that a list's pieces, which gather its items from all over it,
+    // read one L2 (frames near the ground, 8 M items in pieces: 81 -> 62 us).
+    const int per = (total + 7) / 8, rounds = own ? 1 : 8 * per;
+    for (int b = own ? 0 : (int)blockIdx.x - total_sup; b < rounds; b += step) {  // block-uniform
+        const int i = own ? 0 : (b & 7) * per + (b >> 3);
+        if (i >= total) continue;
         SortPiece p;
         if (own) {
             p = SortPiece{ranges[2 * blockIdx.x], 0, 0, 0};
