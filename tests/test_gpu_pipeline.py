@@ -244,3 +244,30 @@ def test_one_line_fewer_than_anchors_equals_a_line_each(gs, n):
         for key in ("n_visible", "n_miss", "n_gauss", "depth_used"):
             assert st[0][key] == st[1][key]
         assert np.array_equal(rs[0].debug("misses"), rs[1].debug("misses"))
+
+
+@pytest.mark.parametrize("n,fov,C", [(9001, 20.0, 4158), (20011, 8.0, 4482)])
+def test_eviction_over_many_blocks_matches_model(gs, n, fov, C):
+    """Evictions in a cache whose free lines and threshold flags span several
+    blocks (1,024 lines or anchors each) and whose scene is too large for the
+    one-block selection: misses, evictions, depths and images of every frame
+    of a pan are the model's.  The capacities were chosen with the model: every
+    visible anchor fits, and four frames evict, up to 2,212 lines at once."""
+    scene = synth.tiny_scene(n=n, seed=n)
+    r = gs.Renderer(k=scene.k, reuse=True, d_max=10, max_width=128, max_height=96, cache_capacity=C)
+    r.load(scene)
+    sim = oracle.CacheSim(n, C, 10)
+    lines = {}
+    evicting = 0
+    for i, (L, R) in enumerate(pan(10, fov, 0.2)):
+        iL, iR = gpu_frame(r, L, R)
+        ref = oracle.render_frame(scene, L, R, cache=sim, cache_lines=lines)
+        st = r.stats()
+        assert st["overflow"] == 0
+        assert st["n_miss"] == ref["cache"]["n_miss"] and st["n_evicted"] == len(ref["cache"]["evicted"]), i
+        assert st["depth_next"] == ref["cache"]["d_next"], i
+        assert np.array_equal(r.debug("misses"), ref["cache"]["misses"]), i
+        evicting += st["n_evicted"] > 0
+        assert_image(iL, ref["left"])
+        assert_image(iR, ref["right"])
+    assert evicting == 4
