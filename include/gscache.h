@@ -90,7 +90,9 @@ typedef struct gsc_config {
     int64_t cache_capacity;     /* cache lines (anchors); 0 = number of anchors */
     int32_t max_width;          /* largest eye image the context renders */
     int32_t max_height;
-    int64_t max_pairs;          /* tile-pair capacity per eye; 0 = 24 x max Gaussians */
+    int64_t max_pairs;          /* tile-pair capacity per eye; 0 = 24 x max Gaussians.  A batch that needs more
+                                   (GSC_E_CAPACITY) keeps the pairs of its nearest Gaussians, the same ones
+                                   every time (with GSC_FLAG_FULL_KEY_SORT: of the first in the buffer) */
 } gsc_config;
 
 /* Pinhole camera: world -> camera rotation R (row-major 3x3, rows = right,
@@ -228,8 +230,8 @@ int gsc_render_gaussians(gsc_ctx* ctx, const gsc_gaussians* g, const gsc_camera*
  * cam: host, width and height <= GSC_NOALLOC_MAX_SIDE; out_chw [3,H,W] and
  * out_T [H,W] (may be NULL): caller-owned device float32; status (device,
  * may be NULL) receives the overflow bits after the kernels run (0, or bit0
- * when more than GSC_NOALLOC_MAX_PAIRS tile pairs were needed and the excess
- * dropped).  stream: hipStream_t (NULL = default stream); asynchronous.
+ * when more than GSC_NOALLOC_MAX_PAIRS tile pairs were needed and those of
+ * the farthest Gaussians dropped).  stream: hipStream_t (NULL = default stream); asynchronous.
  * Sizes beyond the maxima return GSC_E_INVALID_ARG before any device work.
  * Every call on one device shares that device's array: calls that overlap
  * on one device (other streams, other host threads) race. */

@@ -5,7 +5,8 @@
 //                  (counters in LDS)
 //   k_bin_columns  per super tile, the blocks' first positions and the total
 //   k_bin<true>    every block writes its items (depth key, entry, tile mask)
-//                  at its positions of each super tile's range
+//                  at its positions of each super tile's range; where the items
+//                  are more than the buffers hold, the nearest ones (write_cut)
 //   k_bin_split    the lists of more than kSortCap items, divided by depth
 //                  into pieces that fit
 //   k_bin_sort     every list and piece in the order (depth key, entry), one
@@ -52,8 +53,10 @@ struct BinArgs {
     const uint4* srow;        // super rows of the tall footprints (see k_tall_spans)
     const int32_t* srow_y;
     int64_t srow_cap;
+    const float4* rec;        // the entries' records (a tall footprint's item count)
     uint32_t* hist;           // [blocks][stride] counts, then first positions, of each super tile
     uint32_t* total;          // [stride]
+    uint32_t* kept;           // [2 stride] items that stay of each super tile and those placed, where some are left out
     uint64_t* items;          // depth key << 32 | entry << 4 | mask
     int32_t* ranges;
     int32_t* n_sort;
@@ -144,71 +147,49 @@ __device__ __forceinline__ Row make_row(const SupGeo& sg, int Y, uint32_t sa, ui
     return r;
 }
 
+// Where the items are more than the buffers hold, those of the nearest
+// entries stay, in the order (depth key, entry), and of the entry at the cut
+// the first `keep` (row by row): what sorting the entries by depth and
+// emitting them up to the capacity leaves.
+struct Cut {
+    uint32_t depth, entry;
+    int32_t keep;
+};
+constexpr int kKeepAll = 1 << 30;
+__device__ __forceinline__ int items_left(const Cut& c, uint32_t depth, uint32_t e) {
+    if (depth == c.depth && e == c.entry) return c.keep;
+    return depth < c.depth || (depth == c.depth && e < c.entry) ? kKeepAll : 0;
+}
+__device__ __forceinline__ void trim_row(Row& r, int& left) {
+    const int n = r.n;
+    r.n = max(min(n, left), 0);
+    left -= n;
+}
+
+// The super rows of a short footprint from its binning record.
+__device__ __forceinline__ void footprint_rows(const BinRec& r, const SupGeo& sg, Row& r0, Row& r1, Row& r2) {
+    // super row i is Y = y0 / 2 + i: tile rows (0, 1), (2, 3)
+    // from an even y0; (-, 0), (1, 2), (3, -) from an odd one
+    const bool odd = r.y0 & 1;
+    const int Y = r.y0 >> kSupShift;
+    r0 = make_row(sg, Y, odd ? kEmptySpan : r.sp[0], odd ? r.sp[0] : r.sp[1]);
+    r1 = make_row(sg, Y + 1, odd ? r.sp[1] : r.sp[2], odd ? r.sp[2] : r.sp[3]);
+    r2 = make_row(sg, Y + 2, odd ? r.sp[3] : kEmptySpan, kEmptySpan);
+}
+
 // Block b takes every nblk-th run of the entries, for their short footprints
 // (from their binning records), and every nblk-th run of the stored super
 // rows of the tall ones: entries come in anchor order, coarse levels first, so
 // a contiguous share would give a few blocks all the wide footprints (264 us
-// instead of 20 on the city).  The same runs when counting and when writing.  Blocks go to the XCDs round-robin, so blocks
-// whose items land side by side in every list are given to one XCD: its L2
-// then completes most of the lines that they write parts of.
-template <bool kWrite>
-__global__ __launch_bounds__(NB) void k_bin(BinArgs a) {
-    __shared__ __align__(16) uint32_t s_cnt[kBinLists];
-    __shared__ uint32_t s_part[NB / 64];
-    __shared__ SupGeo s_sg[kMaxSeg];
-    constexpr int PER = kBinLists / NB;
-    const int nblk = gridDim.x, lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const int b = nblk % 8 == 0 ? (int)(blockIdx.x % 8) * (nblk / 8) + (int)(blockIdx.x / 8) : (int)blockIdx.x;
-    uint32_t* row = a.hist + (int64_t)b * a.stride;
-    if (threadIdx.x < kMaxSeg) s_sg[threadIdx.x] = a.sg[threadIdx.x];
-    if (kWrite) {
-        // the super tiles' first positions, 8 a thread
-        uint32_t t[PER], sum = 0;
-#pragma unroll
-        for (int i = 0; i < PER; ++i) {
-            const int c = threadIdx.x * PER + i;
-            t[i] = c < a.stride ? a.total[c] : 0u;
-            sum += t[i];
-        }
-        uint32_t x = sum;
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const uint32_t v = __shfl_up(x, o, 64);
-            if (lane >= o) x += v;
-        }
-        if (lane == 63) s_part[wv] = x;
-        __syncthreads();
-        uint32_t first = x - sum;
-        for (int i = 0; i < wv; ++i) first += s_part[i];
-#pragma unroll
-        for (int i = 0; i < PER; ++i) {
-            const int c = threadIdx.x * PER + i;
-            if (c < a.stride) s_cnt[c] = first + row[c];
-            if (b == 0 && c < a.total_sup) {
-                const int64_t lo = first, hi = min((int64_t)first + t[i], a.max_pairs);
-                const int n = (int)max(hi - lo, (int64_t)0);
-                a.ranges[2 * c] = n ? (int32_t)lo : 0;
-                a.ranges[2 * c + 1] = n ? (int32_t)hi : 0;
-                if (n > kSortCap) a.long_lists[atomicAdd(&a.rc->n_long, 1)] = c;
-            }
-            first += t[i];
-        }
-        if (b == 0 && threadIdx.x == NB - 1) {
-            // (`first` is now the total)
-            const int64_t all = first;
-            a.rc->n_pairs = (int32_t)first;
-            if (all > a.max_pairs) atomicOr(&a.rc->overflow, 1);
-            *a.n_sort = (int32_t)min(all, a.max_pairs);
-        }
-        __syncthreads();
-    } else {
-        for (int c = threadIdx.x; c < a.stride; c += NB) s_cnt[c] = 0u;
-        __syncthreads();
-    }
+// instead of 20 on the city).  The same runs when counting and when writing.
+// kCut: only the items that `cut` leaves.
+template <bool kWrite, bool kCut>
+__device__ __forceinline__ void walk(const BinArgs& a, uint32_t* s_cnt, const SupGeo* s_sg, int b, int nblk, const Cut& cut) {
     // Sixteen lanes run / 16 entries apart (and up to four neighbours at each):
     // a Gaussian's eyes and an anchor's Gaussians, which fall on the same super
     // tiles, come together, and LDS adds to one address wait for each other.
     // (block-uniform loop: whole waves take part in the wide footprints' items)
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const int ne = a.rc->n_entries, near = a.run >> 8;
     const int place = (lane & 15) * (a.run >> 4) + wv * near + (lane >> 4);
     const bool here = (lane >> 4) < near;
@@ -227,15 +208,14 @@ __global__ __launch_bounds__(NB) void k_bin(BinArgs a) {
             next = load(e + (int64_t)nblk * a.run);
             const BinRec r = unpack_bin(w);
             if (r.binned) {
-                const SupGeo sg = s_sg[r.seg];
                 depth = w.w;
-                // super row i is Y = y0 / 2 + i: tile rows (0, 1), (2, 3)
-                // from an even y0; (-, 0), (1, 2), (3, -) from an odd one
-                const bool odd = r.y0 & 1;
-                const int Y = r.y0 >> kSupShift;
-                r0 = make_row(sg, Y, odd ? kEmptySpan : r.sp[0], odd ? r.sp[0] : r.sp[1]);
-                r1 = make_row(sg, Y + 1, odd ? r.sp[1] : r.sp[2], odd ? r.sp[2] : r.sp[3]);
-                r2 = make_row(sg, Y + 2, odd ? r.sp[3] : kEmptySpan, kEmptySpan);
+                footprint_rows(r, s_sg[r.seg], r0, r1, r2);
+                if (kCut) {
+                    int left = items_left(cut, depth, (uint32_t)e);
+                    trim_row(r0, left);
+                    trim_row(r1, left);
+                    trim_row(r2, left);
+                }
             }
         }
         if (kWrite) {
@@ -258,44 +238,328 @@ __global__ __launch_bounds__(NB) void k_bin(BinArgs a) {
         const uint4 sr = a.srow[q];
         const uint32_t e = sr.z, ys = (uint32_t)a.srow_y[q];
         int x0;
-        const int n = (int)sup_cols(sr.x, sr.y, x0);
+        int n = (int)sup_cols(sr.x, sr.y, x0);
         if (sub >= n) continue;
         const SupGeo sg = s_sg[(ys >> kRowSegShift) % kMaxSeg];
         const int64_t sup = sg.base + (int64_t)(ys & kRowMask) * sg.nsx + x0;
         // (a row that a capacity overflow left unwritten may hold anything)
         if (e >= (uint32_t)ne || sup < 0 || sup + n > a.total_sup) continue;
+        uint32_t depth = 0;
+        if (kWrite || kCut) depth = a.brec[e].w;
+        if (kCut) n = (int)max(min((int64_t)n, (int64_t)items_left(cut, depth, e) - sr.w), (int64_t)0);
         if (!kWrite) {
-            count_row(s_cnt, (int)sup, n, a.total_sup);
+            if (n) count_row(s_cnt, (int)sup, n, a.total_sup);
             continue;
         }
-        const uint32_t depth = a.brec[e].w;
         for (int k = sub; k < n; k += kRowLanes)
             write_item(a, s_cnt, (int)sup + k, (e << 4) | sup_mask(sr.x, sr.y, x0 + k), depth);
     }
-    if (!kWrite) {
-        // the running sum over the super tiles, 8 a thread
+}
+
+constexpr int kListsThread = kBinLists / NB;  // super tiles of a thread, in a row
+
+// The counts of the thread's super tiles (c0 on) from what counting left in
+// s_cnt (a running sum); all threads of the block take part.
+__device__ __forceinline__ void list_counts(const uint32_t* s_cnt, uint32_t* s_part, int total_sup, int stride, int c0,
+                                            uint32_t (&n)[kListsThread]) {
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    __syncthreads();
+    uint32_t sum = 0;
+#pragma unroll
+    for (int i = 0; i < kListsThread; ++i) {
+        const int c = c0 + i;
+        sum += c < stride ? s_cnt[c] : 0u;
+        n[i] = sum;
+    }
+    uint32_t x = sum;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t v = __shfl_up(x, o, 64);
+        if (lane >= o) x += v;
+    }
+    if (lane == 63) s_part[wv] = x;
+    __syncthreads();
+    uint32_t before = x - sum;
+    for (int i = 0; i < wv; ++i) before += s_part[i];
+#pragma unroll
+    for (int i = 0; i < kListsThread; ++i) {
+        const int c = c0 + i;
+        n[i] = c < total_sup ? before + n[i] : 0u;
+    }
+}
+
+// Exclusive prefix of v over the block; s: 16 words, free again after the next
+// barrier.  32-bit sums saturate: all that lies past 2^32 - 1 is past every capacity.
+__device__ __forceinline__ uint32_t add_sat(uint32_t x, uint32_t y) { return __builtin_elementwise_add_sat(x, y); }
+__device__ __forceinline__ uint64_t add_sat(uint64_t x, uint64_t y) { return x + y; }  // (2^28 entries of 2^13 items at most)
+template <typename T>
+__device__ __forceinline__ T block_prefix(T v, T* s) {
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    T x = v;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const T y = __shfl_up(x, o, 64);
+        if (lane >= o) x = add_sat(x, y);
+    }
+    if (lane == 63) s[wv] = x;
+    T before = __shfl_up(x, 1, 64);
+    if (lane == 0) before = 0;
+    __syncthreads();
+    for (int i = 0; i < wv; ++i) before = add_sat(before, s[i]);
+    return before;
+}
+
+// The ranges of the thread's super tiles (c0 on) from their counts t and first
+// positions, and the longer ones' list.
+__device__ __forceinline__ void put_ranges(const BinArgs& a, int c0, const uint32_t (&t)[kListsThread], uint32_t first) {
+#pragma unroll
+    for (int i = 0; i < kListsThread; ++i) {
+        const int c = c0 + i;
+        if (c < a.total_sup) {
+            const int64_t lo = first, hi = min((int64_t)first + t[i], a.max_pairs);
+            const int n = (int)max(hi - lo, (int64_t)0);
+            a.ranges[2 * c] = n ? (int32_t)lo : 0;
+            a.ranges[2 * c + 1] = n ? (int32_t)hi : 0;
+            if (n > kSortCap) a.long_lists[atomicAdd(&a.rc->n_long, 1)] = c;
+        }
+        first += t[i];
+    }
+    if (threadIdx.x == NB - 1) *a.n_sort = (int32_t)min((int64_t)first, a.max_pairs);  // (`first` is now the total)
+}
+
+// ------------------------------------------- items over the capacity
+// Blocks of one launch that work together with barriers between them: those
+// that have started when the first one closes the team (it waits a while for
+// the rest, up to kTeamMost; whoever comes later leaves).  Every member is
+// running, so every wait for the others ends, whatever else is on the device.
+// What the members share within the launch they read and write by device-scope
+// atomics alone, so a barrier waits for those and needs no cache write-back.
+struct Team {
+    RasterCounters* rc;
+    int part, size;  // size 0: not a member
+    uint32_t met;    // barriers passed
+};
+constexpr uint32_t kTeamMost = 128, kTeamClosed = 1u << 31;
+template <typename T>
+__device__ __forceinline__ T agent_load(const T* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+template <typename T>
+__device__ __forceinline__ void agent_store(T* p, T v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+template <typename T>
+__device__ __forceinline__ T agent_add(T* p, T v) { return __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+// (all threads of the block; s: two words)
+__device__ __forceinline__ Team join_team(RasterCounters* rc, uint32_t blocks, uint32_t* s) {
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        const uint32_t at = agent_add(&rc->team, 1u), most = min(blocks, kTeamMost);
+        if (at == 0) {
+            for (int i = 0; i < 1024 && agent_load(&rc->team) < most; ++i) __builtin_amdgcn_s_sleep(8);
+            const uint32_t n = __hip_atomic_fetch_or(&rc->team, kTeamClosed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            agent_store(&rc->team_size, min(n, most));
+        }
+        uint32_t size = 0;
+        if (at < most)  // (not closed yet)
+            while ((size = agent_load(&rc->team_size)) == 0) __builtin_amdgcn_s_sleep(8);
+        s[0] = at;
+        s[1] = at < size ? size : 0u;
+    }
+    __syncthreads();
+    const Team t{rc, __builtin_amdgcn_readfirstlane((int)s[0]), __builtin_amdgcn_readfirstlane((int)s[1]), 0u};
+    __syncthreads();
+    return t;
+}
+__device__ __forceinline__ void team_barrier(Team& t) {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wave's atomics are done
+    __syncthreads();
+    ++t.met;
+    if (threadIdx.x == 0) {
+        agent_add(&t.rc->team_met, 1u);
+        while (agent_load(&t.rc->team_met) < t.met * (uint32_t)t.size) __builtin_amdgcn_s_sleep(8);
+    }
+    __syncthreads();
+}
+
+// The writing when there are more items than the buffers hold: finds the
+// entry at the cut by its 60-bit (depth key, entry), twelve bits a pass (how
+// many items the entries of each value have), counts the items that stay, and
+// writes those.  A frame of 940,000 entries cut to 100,000 and to 500,000 items
+// takes 340 and 389 us, with the radix sorts, which emit in depth order, 376
+// and 389 (the cut found by one block: 3,517; by all blocks, with cache
+// write-backs at every barrier: 799 and 1,962).
+constexpr int kCutBits = 12, kCutPasses = 5, kCutValues = 1 << kCutBits;
+__device__ __forceinline__ void write_cut(const BinArgs& a, uint32_t all, uint32_t* s_cnt, const SupGeo* s_sg,
+                                          uint32_t* s_part) {
+    constexpr int PER = kCutValues / NB, kAhead = 2;
+    static_assert(kCutValues * 2 <= kBinLists && kCutBits * kCutPasses >= 32 + kMaskShift, "the counts fit, and the key");
+    static_assert(kCutPasses * kCutValues * 2 <= 256 * kSortBlocks, "the passes' counts fit the blocks' counts");
+    __shared__ int s_value;
+    __shared__ uint64_t s_left;
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));  // (addresses made here, not kept from the kernel's start on)
+    Team team = join_team(a.rc, gridDim.x, s_part);
+    if (!team.size) return;
+    typedef unsigned long long u64;
+    u64* s_w = reinterpret_cast<u64*>(s_cnt);
+    u64* count = reinterpret_cast<u64*>(a.hist);  // [pass][value], in the place of the blocks' counts
+    const int64_t step = (int64_t)team.size * NB, me = (int64_t)team.part * NB + tid;
+    for (int64_t i = me; i < kCutPasses * kCutValues; i += step)
+        agent_store(&count[i], (u64)0);
+    for (int64_t i = me; i < 2 * a.stride; i += step)
+        agent_store(&a.kept[i], 0u);
+    team_barrier(team);
+    const int64_t ne = a.rc->n_entries;
+    uint64_t high = 0, left = (uint64_t)a.max_pairs;
+    bool found = true;
+    for (int pass = 0; pass < kCutPasses && found; ++pass, count += kCutValues) {  // (the same in every member)
+        const int shift = kCutBits * (kCutPasses - 1 - pass);
+        for (int i = tid; i < kCutValues; i += NB) s_w[i] = 0;
+        if (tid == 0) s_value = -1;
         __syncthreads();
+        for (int64_t e0 = me; e0 < ne; e0 += kAhead * step) {
+            uint4 w[kAhead];
+#pragma unroll
+            for (int u = 0; u < kAhead; ++u) {
+                const int64_t e = e0 + u * step;
+                w[u] = e < ne ? a.brec[e] : make_uint4(1u, 0u, 0u, 0u);  // (no items)
+            }
+#pragma unroll
+            for (int u = 0; u < kAhead; ++u) {
+                const int64_t e = e0 + u * step;
+                const uint64_t key = ((uint64_t)w[u].w << kMaskShift) | (uint64_t)e;
+                if (pass && key >> (shift + kCutBits) != high) continue;
+                const BinRec r = unpack_bin(w[u]);
+                uint32_t n;
+                if (r.binned) {
+                    Row r0, r1, r2;
+                    footprint_rows(r, s_sg[r.seg], r0, r1, r2);
+                    n = (uint32_t)(r0.n + r1.n + r2.n);
+                } else {
+                    n = w[u].w ? __float_as_uint(a.rec[kRec * e + 2].w) : 0u;  // (a tall one, or without items)
+                }
+                if (n) atomicAdd(&s_w[(key >> shift) & (kCutValues - 1)], (u64)n);
+            }
+        }
+        __syncthreads();
+        for (int i = tid; i < kCutValues; i += NB)
+            if (s_w[i]) agent_add(&count[i], s_w[i]);
+        team_barrier(team);
+        uint64_t v[PER], sum = 0;
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+            v[i] = agent_load(&count[tid * PER + i]);
+            sum += v[i];
+        }
+        uint64_t before = block_prefix(sum, reinterpret_cast<uint64_t*>(s_part));
+        if (before <= left && left < before + sum) {  // (at most one thread)
+            int i = 0;
+            while (left >= before + v[i]) before += v[i++];
+            s_value = tid * PER + i;
+            s_left = left - before;
+        }
+        __syncthreads();
+        found = s_value >= 0;
+        if (found) {
+            high = (high << kCutBits) | (uint64_t)s_value;
+            left = s_left;
+        }
+        __syncthreads();
+    }
+    // (not found: super rows that an overflow of theirs left unwritten were counted)
+    Cut cut = found ? Cut{(uint32_t)(high >> kMaskShift), (uint32_t)high & kEntryMask, (int32_t)left}
+                    : Cut{0xffffffffu, 0xffffffffu, 0};
+    cut.depth = (uint32_t)__builtin_amdgcn_readfirstlane((int)cut.depth);  // (the same in every lane)
+    cut.entry = (uint32_t)__builtin_amdgcn_readfirstlane((int)cut.entry);
+    cut.keep = __builtin_amdgcn_readfirstlane(cut.keep);
+    for (int c = tid; c < a.stride; c += NB) s_cnt[c] = 0u;
+    __syncthreads();
+    walk<false, true>(a, s_cnt, s_sg, team.part, team.size, cut);
+    const int c0 = tid * kListsThread;
+    uint32_t t[kListsThread], sum = 0;
+    list_counts(s_cnt, s_part, a.total_sup, a.stride, c0, t);
+#pragma unroll
+    for (int i = 0; i < kListsThread; ++i) {
+        const int c = c0 + i;
+        s_cnt[c] = t[i];
+        if (t[i]) agent_add(&a.kept[c], t[i]);
+    }
+    team_barrier(team);
+#pragma unroll
+    for (int i = 0; i < kListsThread; ++i) {
+        const int c = c0 + i;
+        t[i] = c < a.stride ? agent_load(&a.kept[c]) : 0u;
+        sum += t[i];
+    }
+    uint32_t first = block_prefix(sum, s_part);
+    if (team.part == 0) {
+        put_ranges(a, c0, t, first);
+        if (tid == 0) {
+            a.rc->n_pairs = (int32_t)min(all, 0x7fffffffu);
+            atomicOr(&a.rc->overflow, 1);
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < kListsThread; ++i) {
+        const int c = c0 + i;
+        const uint32_t mine = s_cnt[c];
+        if (mine)
+            s_cnt[c] = first + agent_add(&a.kept[a.stride + c], mine);
+        first += t[i];
+    }
+    __syncthreads();
+    walk<true, true>(a, s_cnt, s_sg, team.part, team.size, cut);
+}
+
+// Blocks go to the XCDs round-robin, so blocks whose items land side by side
+// in every list are given to one XCD: its L2 then completes most of the lines
+// that they write parts of.
+template <bool kWrite>
+__global__ __launch_bounds__(NB) __attribute__((amdgpu_waves_per_eu(8))) void k_bin(BinArgs a) {
+    __shared__ __align__(16) uint32_t s_cnt[kBinLists];
+    __shared__ __align__(16) uint32_t s_part[2 * NB / 64];
+    __shared__ uint32_t s_all;
+    __shared__ SupGeo s_sg[kMaxSeg];
+    constexpr int PER = kListsThread;
+    const int nblk = gridDim.x;
+    const int b = nblk % 8 == 0 ? (int)(blockIdx.x % 8) * (nblk / 8) + (int)(blockIdx.x / 8) : (int)blockIdx.x;
+    uint32_t* row = a.hist + (int64_t)b * a.stride;
+    if (threadIdx.x < kMaxSeg) s_sg[threadIdx.x] = a.sg[threadIdx.x];
+    if (kWrite) {
+        // the super tiles' first positions, 8 a thread
         uint32_t t[PER], sum = 0;
 #pragma unroll
         for (int i = 0; i < PER; ++i) {
             const int c = threadIdx.x * PER + i;
-            sum += c < a.stride ? s_cnt[c] : 0u;
-            t[i] = sum;
+            t[i] = c < a.stride ? a.total[c] : 0u;
+            sum += t[i];
         }
-        uint32_t x = sum;
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const uint32_t v = __shfl_up(x, o, 64);
-            if (lane >= o) x += v;
-        }
-        if (lane == 63) s_part[wv] = x;
-        __syncthreads();
-        uint32_t before = x - sum;
-        for (int i = 0; i < wv; ++i) before += s_part[i];
+        uint32_t first = block_prefix(sum, s_part);
+        if (threadIdx.x == NB - 1) s_all = add_sat(first, sum);
+        uint32_t at = first;
 #pragma unroll
         for (int i = 0; i < PER; ++i) {
             const int c = threadIdx.x * PER + i;
-            if (c < a.stride) row[c] = c < a.total_sup ? before + t[i] : 0u;
+            if (c < a.stride) s_cnt[c] = at + row[c];
+            at += t[i];
+        }
+        __syncthreads();
+        if ((int64_t)s_all > a.max_pairs) {  // (the same in every block)
+            write_cut(a, s_all, s_cnt, s_sg, s_part);
+            return;
+        }
+        if (b == 0) {
+            put_ranges(a, threadIdx.x * PER, t, first);
+            if (threadIdx.x == 0) a.rc->n_pairs = (int32_t)s_all;
+        }
+        walk<true, false>(a, s_cnt, s_sg, b, nblk, Cut{});
+    } else {
+        for (int c = threadIdx.x; c < a.stride; c += NB) s_cnt[c] = 0u;
+        __syncthreads();
+        walk<false, false>(a, s_cnt, s_sg, b, nblk, Cut{});
+        uint32_t n[PER];
+        list_counts(s_cnt, s_part, a.total_sup, a.stride, threadIdx.x * PER, n);
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+            const int c = threadIdx.x * PER + i;
+            if (c < a.stride) row[c] = n[i];
         }
     }
 }
@@ -836,7 +1100,7 @@ hipError_t bin_items(const SegTable& tab, Raster& r, int32_t* status, hipStream_
     BinArgs a;
     for (int q = 0; q < kMaxSeg; ++q)
         a.sg[q] = SupGeo{q < tab.n ? tab.s[q].sup_base : 0, q < tab.n ? tab.s[q].nsx : 0};
-    a.rc = r.cnt; a.brec = r.brec; a.srow = r.srow; a.srow_y = r.srow_y; a.srow_cap = r.srow_cap;
+    a.rc = r.cnt; a.rec = r.rec; a.brec = r.brec; a.srow = r.srow; a.srow_y = r.srow_y; a.srow_cap = r.srow_cap;
     a.items = r.items; a.ranges = r.ranges; a.n_sort = r.n_sort; a.long_lists = r.long_lists;
     a.max_pairs = r.max_pairs; a.total_sup = tab.total_sup;
     a.stride = (tab.total_sup + kColTile - 1) / kColTile * kColTile;
@@ -862,6 +1126,7 @@ hipError_t bin_items(const SegTable& tab, Raster& r, int32_t* status, hipStream_
     if (nblk >= 8) nblk &= ~(int64_t)7;
     a.hist = r.max_pairs > digits ? r.pval[1] : r.hist;
     a.total = r.sup_total;
+    a.kept = r.block_sums;
     mark(mk, 6, st);
     hipLaunchKernelGGL(k_bin<false>, dim3((unsigned)nblk), dim3(NB), 0, st, a);
     hipLaunchKernelGGL(k_bin_columns, dim3((unsigned)(a.stride / kColTile)), dim3(NB), 0, st, a.hist, r.sup_total,

@@ -77,6 +77,7 @@ struct RasterCounters {
     int32_t n_long;               // super tiles whose lists are longer than kSortCap
     int32_t n_pieces;             // the pieces they are sorted in
     int32_t n_chunks;             // chunks of those that are merged instead
+    uint32_t team, team_size, team_met;  // blocks that choose the items together where they exceed the capacity
 };
 
 // One (viewer, eye) image of a raster batch; passed by value in kernel args.
@@ -230,7 +231,7 @@ struct Raster {
     uint64_t* pkey64[2] = {nullptr, nullptr};// full-key mode
     int32_t* ranges = nullptr;  // [max_tiles][2]
     uint32_t* hist = nullptr;   // [256 * kSortBlocks] radix digit counts per block
-    uint32_t* block_sums = nullptr;
+    uint32_t* block_sums = nullptr;  // [2 kBinLists] scan scratch; binning: where items are left out, those of each super tile that stay
     RasterCounters* cnt = nullptr;
     RasterCounters* cnt_host = nullptr;
     int sorted_buf = 0;         // which pval (pkey, pkey64) buffer holds the sorted items

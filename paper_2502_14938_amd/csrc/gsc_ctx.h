@@ -65,7 +65,7 @@ hipError_t raster_layout(Raster& r, int64_t max_entries, int64_t max_pairs, int6
     A_(r.chunks, max_pairs / (kSortCap / 2) + 1); A_(r.long_lists, max_pairs / kSortCap + 1);
     A_(r.pieces, max_pairs / 512 + 1); A_(r.sup_total, kBinLists);
     A_(r.ranges, 2 * max_tiles); A_(r.tile_eval, 2 * max_tiles); A_(r.hist, 256 * kSortBlocks);
-    A_(r.block_sums, kScanBlocks);
+    A_(r.block_sums, 2 * kBinLists);
     A_(r.n_sort, 1); A_(r.cnt, 1);
 #undef A_
     return hipSuccess;

@@ -352,6 +352,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(7))) void k_
             p.rc->n_entries = s_ne;
             p.rc->n_gpairs = s_ne >> 1;
             p.rc->n_long = p.rc->n_pieces = p.rc->n_chunks = 0;
+            p.rc->team = p.rc->team_size = p.rc->team_met = 0u;
             p.rc->n_echunks = (s_ne + NT - 1) / NT;
         }
     }

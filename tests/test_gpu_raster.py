@@ -201,3 +201,95 @@ def test_batches_around_the_most_lists_binned_equal_full_key_sort(gs, W, H):
         assert np.array_equal(x, y)
     assert np.array_equal(a[4].debug("raw_ranges"), b[4].debug("raw_ranges"))
     assert np.array_equal(a[4].debug("sort_vals"), b[4].debug("sort_vals"))
+
+
+def render_capped(gs, g, cam, max_pairs):
+    """Image, transmittance, ranges and sorted items of two renders with a
+    pair capacity (0: the default one), and whether it was exceeded."""
+    W, H = cam["width"], cam["height"]
+    r = gs.Renderer(max_width=W, max_height=H, max_pairs=max_pairs)
+    out = []
+    for _ in range(2):
+        img, T = torch.zeros(3, H, W, device="cuda"), torch.zeros(H, W, device="cuda")
+        r.render_gaussians(*g, cam, img, T)
+        torch.cuda.synchronize()
+        over = False
+        try:
+            r.sync()
+        except gs.GscError as e:
+            assert e.code == gs.GSC_E_CAPACITY
+            over = True
+        out.append((img.cpu().numpy(), T.cpu().numpy(), r.debug("raw_ranges").reshape(-1, 2), r.debug("sort_vals")))
+    r.close()
+    for a, b in zip(*out):
+        assert np.array_equal(a, b)
+    return out[0] + (over,)
+
+
+def capped_lists(ranges, vals, z, cap):
+    """The lists that remain of the whole ones where only the first `cap`
+    items fit, entries in the order (float32 depth, entry), each entry's items
+    by super tile: ranges and items."""
+    sup = np.repeat(np.arange(len(ranges)), ranges[:, 1] - ranges[:, 0])
+    entry = (vals & 0x0fffffff).astype(np.int64)
+    order = np.lexsort((sup, entry, z.astype(np.float32)[entry]))
+    keep = np.zeros(len(vals), bool)
+    keep[order[:cap]] = True
+    count = np.bincount(sup[keep], minlength=len(ranges))
+    end = np.cumsum(count)
+    rg = np.stack([end - count, end], 1)
+    rg[count == 0] = 0
+    return rg, vals[keep]
+
+
+# 3,000 short and tall footprints on 35 super tiles; more entries than one
+# run of them; all at one depth; as many super tiles as are binned, and more
+# (radix sorts)
+@pytest.mark.parametrize("n,W,H,kind,caps", [(3000, 200, 150, "spread", (1, 77, 0.3, -1, 0)), (70000, 250, 190, "crowd", (4099, 0.7)),
+                                             (2500, 130, 97, "equal", (500, 0.5)), (30000, 4096, 2048, "planes", (1000, 0.5)),
+                                             (3000, 4096, 2049, "spread", (1000, 0.5))])
+def test_pair_capacity_keeps_the_nearest(gs, n, W, H, kind, caps):
+    """An image that needs more (super tile, entry) pairs than the capacity
+    keeps those of the nearest entries, whichever way its lists are made, the
+    same ones every time, and reports GSC_E_CAPACITY."""
+    rng = np.random.default_rng(n + W)
+    z = depths(kind, n, rng).astype(np.float32).astype(np.float64)
+    fx, fy = W / (2 * math.tan(math.radians(30))), H / (2 * math.tan(math.radians(30)))
+    cam = {"R": np.eye(3), "pos": np.zeros(3), "fovx": math.radians(60), "fovy": math.radians(60), "width": W,
+           "height": H, "znear": 0.01}   # (depth = z, bit for bit)
+    mu = np.stack([rng.uniform(-0.5, 0.5, n) * W * z / fx, rng.uniform(-0.5, 0.5, n) * H * z / fy, z], 1)
+    sig = np.exp(rng.uniform(np.log(0.5), np.log(30.0), n)) * z / max(fx, fy)
+    sig[rng.uniform(size=n) > 0.2] *= 0.1
+    cov = np.zeros((n, 6)); cov[:, 0] = cov[:, 3] = cov[:, 5] = sig ** 2
+    rgb, al = rng.uniform(0, 1, (n, 3)), rng.uniform(0.01, 0.6, n)
+    g = [torch.from_numpy(np.ascontiguousarray(a, np.float32)).cuda() for a in (mu, cov, rgb, al)]
+    _, _, ranges, vals, over = render_capped(gs, g, cam, 0)
+    assert not over
+    total = len(vals)
+    for c in caps:
+        cap = total + c if c <= 0 else int(c * total) if c < 1 else c
+        img, T, rg, v, over = render_capped(gs, g, cam, cap)
+        assert over == (cap < total) and len(v) == min(cap, total)
+        want_rg, want_v = capped_lists(ranges, vals, z, cap)
+        assert np.array_equal(rg, want_rg), cap
+        assert np.array_equal(v, want_v), cap
+
+
+def test_pair_capacity_of_the_allocation_free_entry(gs):
+    """The allocation-free entry's 2,097,152 pairs, exceeded: status bit 0, and
+    the image of a context with that capacity."""
+    n, W, H = 60000, 1024, 96
+    mu, _, rgb, al = synth.random_gaussians(n, seed=4, box=0.4, zc=8.0)
+    cov = np.zeros((n, 6))
+    cov[:, 0], cov[:, 3], cov[:, 5] = 4.0, 1e-4, 1e-4      # needles across the whole image
+    cam = synth.look_camera((0, 0, 0), (0, 0, 1), (0, -1, 0), W, H, math.radians(50), math.radians(6))
+    g = [torch.from_numpy(np.ascontiguousarray(a, np.float32)).cuda() for a in (mu, cov, rgb, al)]
+    img, T, _, v, over = render_capped(gs, g, cam, gs.NOALLOC_MAX_PAIRS)
+    assert over and len(v) == gs.NOALLOC_MAX_PAIRS
+    out, T2 = torch.zeros(3, H, W, device="cuda"), torch.zeros(H, W, device="cuda")
+    status = torch.zeros(1, dtype=torch.int32, device="cuda")
+    for _ in range(2):
+        gs.render_gaussians_noalloc(*g, cam, out, T2, status)
+        torch.cuda.synchronize()
+        assert int(status) & 1
+        assert np.array_equal(out.cpu().numpy(), img) and np.array_equal(T2.cpu().numpy(), T)
