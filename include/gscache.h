@@ -314,8 +314,9 @@ int gsc_ssim(gsc_ctx* ctx, const float* a, const float* b, int32_t channels, int
  * synchronises and returns the summed device milliseconds per stage over the
  * frames issued since timing was switched on or last read.  A batch of at
  * most 8,192 super tiles (2x2 tiles) is binned: stages 6, 7 and 10 do its
- * work and stages 5, 8, 9 and 11 read next to nothing.  A larger batch, and
- * one under GSC_FLAG_FULL_KEY_SORT, is sorted by radix passes.  Stages: */
+ * work and stages 5, 8, 9 and 11 read next to nothing.  A larger batch, one of
+ * more than 65,536 explicit Gaussians for every super tile, and one under
+ * GSC_FLAG_FULL_KEY_SORT is sorted by radix passes.  Stages: */
 #define GSC_STAGE_SCHEDULE 0    /* unified-camera selection, cache schedule */
 #define GSC_STAGE_DERIVE 1      /* MLP derivation of the misses (MFMA) */
 #define GSC_STAGE_COMPOSE 2     /* depth update, render buffer */

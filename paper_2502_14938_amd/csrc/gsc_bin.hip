@@ -13,6 +13,9 @@
 //                  block each, in LDS
 //   k_bin_merge    long lists whose depths no division separates: their
 //                  chunks, which k_bin_sort sorted one by one
+// Lists of more than kHugeList items, too many for one block to divide, are
+// sorted by chunks in the same three launches: the chunks (k_bin_split), groups
+// of chunks merged (k_bin_sort), the groups merged (k_bin_merge).
 //
 // One counting pass over the super tiles puts every item in its list, and
 // what is left to sort are lists that fit a block's LDS: two passes over the
@@ -60,7 +63,8 @@ struct BinArgs {
     uint64_t* items;          // depth key << 32 | entry << 4 | mask
     int32_t* ranges;
     int32_t* n_sort;
-    int32_t* long_lists;      // super tiles with more than kSortCap items
+    int32_t* long_lists;      // super tiles with more than kSortCap items,
+    int32_t* huge_lists;      // or more than kHugeList
     int64_t max_pairs;
     int32_t total_sup, stride;
     int32_t run;              // entries a block takes at a time: 16 waves of 16, 32 or 64
@@ -320,7 +324,11 @@ __device__ __forceinline__ void put_ranges(const BinArgs& a, int c0, const uint3
             const int n = (int)max(hi - lo, (int64_t)0);
             a.ranges[2 * c] = n ? (int32_t)lo : 0;
             a.ranges[2 * c + 1] = n ? (int32_t)hi : 0;
-            if (n > kSortCap) a.long_lists[atomicAdd(&a.rc->n_long, 1)] = c;
+            // (two ifs, so that each counter's adds stay one for the wave: a
+            // counter chosen per lane took 30 us more for 2,000 long lists)
+            if (n > kSortCap && n <= kHugeList) a.long_lists[atomicAdd(&a.rc->n_long, 1)] = c;
+            if (__ballot(n > kHugeList))
+                if (n > kHugeList) a.huge_lists[atomicAdd(&a.rc->n_huge, 1)] = c;
         }
         first += t[i];
     }
@@ -761,13 +769,146 @@ struct SortPiece {
 };
 static_assert(sizeof(SortPiece) == sizeof(int4), "one 16-byte word");
 
+// Huge lists: chunks of kHugeRun items are sorted one by one, then as many
+// chunks as there will be groups are merged to one group each, then the groups:
+// an item is placed among 2 sqrt(chunks) others' windows, in place of every
+// chunk's.  The chunks lie in the list words' two buffers (low and high words;
+// the second is free once the items are written), the groups in the items'
+// place.  Whole passes of one 32x32 image, with the radix sorts, with one block
+// a list and with this: 500,000 Gaussians 646, 858 and 372 us, at one depth
+// 702, 2,490 and 312; 2,000,000 735, 20,695 and 575, at one depth 749, 17,404
+// and 470; 5,000,000 1,200, not measured and 1,330.  The line lies at 65,536
+// items: 130,000 at one depth take 724 us undivided, 282 so, spread ones 284
+// and 276.
+constexpr int kHugeRun = 4096;
+// (Even: blocks eight apart, which share an L2, then have the same part of
+// their groups, and the other groups' windows with it.)
+__device__ __forceinline__ int huge_group(int n) {
+    const int chunks = (n + kHugeRun - 1) / kHugeRun;
+    int g = 2;
+    while (g * g < chunks) g += 2;
+    return g;
+}
+
+// The huge lists' units (count(items) each) dealt to `blocks` blocks in turn:
+// f(first item of the list, its items, unit).
+template <class Count, class Fn>
+__device__ __forceinline__ void huge_units(const int32_t* __restrict__ huge_lists, int lists,
+                                           const int32_t* __restrict__ ranges, int block, int blocks, Count&& count, Fn&& f) {
+    int next = block;
+    for (int h = 0; h < lists; ++h) {
+        const int S = huge_lists[h], start = ranges[2 * S], n = ranges[2 * S + 1] - start, units = count(n);
+        for (; next < units; next += blocks) f(start, n, next);
+        next -= units;
+    }
+}
+
+// Merge of sorted runs: a block takes the (at most) kMergeRun items from `off`
+// on of a list of n items in runs of R, `group` runs to a group; an item's
+// place in its group is its index in its run plus the items before it in every
+// other run of the group, which are found in that run's window between the
+// block's first and last item, through LDS (a window much longer than the
+// block's items, where the depths are uneven: item by item).
+// s_win: kWindow (twice the block's items: most windows are one step), s_at:
+// NM words.
+constexpr int kMergeRun = 1024, kWindow = 2 * kMergeRun, NM = 256, kLongWindow = 4 * kWindow;
+template <class Load, class Put>
+__device__ __forceinline__ void merge_runs(Load&& load, Put&& put, int n, int R, int group, int off, uint64_t* s_win,
+                                           int* s_at) {
+    constexpr int PER = kMergeRun / NM;
+    const int own = off / R, runs = (n + R - 1) / R;
+    const int g0 = group < runs ? own / group * group : 0, g1 = group < runs ? min(g0 + group, runs) : runs;
+    const int r0 = off - own * R;                       // the block's first item within its run
+    const int cnt = min(min(n - own * R, R) - r0, kMergeRun);
+    uint64_t v[PER];
+    int rank[PER];
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+        const int i = (int)threadIdx.x * PER + j;
+        v[j] = i < cnt ? load(off + i) : ~0ull;
+        rank[j] = r0 + i;
+    }
+    const uint64_t first = load(off), last = load(off + cnt - 1);
+    auto before = [&](int base, int lo, int hi, uint64_t key) {  // items of [base + lo, base + hi) below key, from base
+        while (lo < hi) {
+            const int mid = (lo + hi) >> 1;
+            if (load(base + mid) < key) lo = mid + 1;
+            else hi = mid;
+        }
+        return lo;
+    };
+    for (int c0 = g0; c0 < g1; c0 += NM / 2) {  // the other runs, NM / 2 windows at a time
+        const int gn = min(g1 - c0, NM / 2);
+        __syncthreads();
+        if ((int)threadIdx.x < 2 * gn) {
+            const int q = threadIdx.x >> 1, base = (c0 + q) * R;
+            s_at[threadIdx.x] = before(base, 0, min(n - base, R), threadIdx.x & 1 ? last : first);
+        }
+        __syncthreads();
+        for (int q = 0; q < gn; ++q) {
+            if (c0 + q == own) continue;
+            const int wl = s_at[2 * q], wh = s_at[2 * q + 1], base = (c0 + q) * R;  // (block-uniform)
+            if (wh - wl > kLongWindow) {
+#pragma unroll
+                for (int j = 0; j < PER; ++j) rank[j] += before(base, wl, wh, v[j]);
+                continue;
+            }
+#pragma unroll
+            for (int j = 0; j < PER; ++j) rank[j] += wl;
+            for (int t0 = wl; t0 < wh; t0 += kWindow) {
+                const int tn = min(wh - t0, kWindow);
+                uint64_t w[kWindow / NM];  // (all on their way together)
+#pragma unroll
+                for (int u = 0; u < kWindow / NM; ++u) {
+                    const int i = u * NM + (int)threadIdx.x;
+                    w[u] = i < tn ? load(base + t0 + i) : 0;
+                }
+                __syncthreads();
+#pragma unroll
+                for (int u = 0; u < kWindow / NM; ++u) {
+                    const int i = u * NM + (int)threadIdx.x;
+                    if (i < tn) s_win[i] = w[u];
+                }
+                __syncthreads();
+                // (a thread's items are neighbours: the first one's place by
+                // bisection, the others' from there on in growing steps)
+                int lo = 0, hi = tn;
+#pragma unroll
+                for (int j = 0; j < PER; ++j) {
+                    if (j) {
+                        int step = 1;
+                        hi = lo;
+                        while (hi < tn && s_win[hi] < v[j]) {
+                            lo = hi + 1;
+                            hi += step;
+                            step <<= 1;
+                        }
+                        hi = min(hi, tn);
+                    }
+                    while (lo < hi) {
+                        const int mid = (lo + hi) >> 1;
+                        if (s_win[mid] < v[j]) lo = mid + 1;
+                        else hi = mid;
+                    }
+                    rank[j] += lo;
+                }
+            }
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+        const int i = (int)threadIdx.x * PER + j;
+        if (i < cnt) put(g0 * R + rank[j], v[j]);
+    }
+    __syncthreads();
+}
+
 // Divides the long lists by depth: a block per list counts its items into
 // kSplitBuckets buckets between its nearest and farthest, writes the items'
 // indices in bucket order to the list's (not yet used) words, and hands the
-// buckets out as pieces of kPieceRun items or more, up to kSortCap.  The
+// buckets out as pieces of up to kSortCap items, kPieceRun on average.  The
 // items themselves stay where they are.  A list that this does not divide
-// (one bucket holds too much, or it has more pieces than the block counts)
-// is sorted in chunks and merged instead.  Bound by the latency of its three
+// (one bucket holds too much) is sorted in chunks and merged instead.  Bound by the latency of its three
 // passes over the list, so the first 4,096 keys, all of most lists, are read
 // once, the others' next step is loaded while a step is counted or placed, and
 // half as many threads as a block may have let the lists of a frame be in
@@ -779,15 +920,34 @@ constexpr int kHeld = 8;  // keys of a list a thread keeps in registers
 constexpr int kPieceBlocks = 3072;
 constexpr int kSplitBuckets = 8192;
 constexpr int kPieceRun = kSortCap / 2;
-constexpr int kMaxPieces = 1024;
+constexpr int kMaxPieces = kHugeList / kPieceRun;
 __global__ __launch_bounds__(NP) void k_bin_split(const uint64_t* __restrict__ items, const int32_t* __restrict__ ranges,
-                                                  const int32_t* __restrict__ long_lists, RasterCounters* rc,
+                                                  const int32_t* __restrict__ long_lists,
+                                                  const int32_t* __restrict__ huge_lists, RasterCounters* rc,
                                                   SortPiece* __restrict__ pieces, uint2* __restrict__ chunks,
-                                                  uint32_t* __restrict__ words) {
-    __shared__ uint32_t s_cnt[kSplitBuckets + 1];
+                                                  uint32_t* __restrict__ words, uint32_t* __restrict__ high_words) {
+    __shared__ __align__(16) uint32_t s_cnt[kSplitBuckets + 1];
     __shared__ uint32_t s_piece[kMaxPieces + 1];
     __shared__ uint32_t s_red[2 * NP / 64];
-    const int nl = rc->n_long;
+    static_assert(kHugeRun == NP * 8 && kHugeRun * 2 <= kSplitBuckets, "a chunk is 8 items a thread and fits the counts' place");
+    const int nl = rc->n_long, nh = rc->n_huge;  // (one load)
+    if (nh)
+        huge_units(huge_lists, nh, ranges, blockIdx.x, gridDim.x, [](int n) { return (n + kHugeRun - 1) / kHugeRun; },
+                   [&](int start, int n, int unit) {
+            const int off = unit * kHugeRun, m = min(n - off, kHugeRun), o = threadIdx.x * 8;
+            const uint64_t* src = items + start + off;
+            uint64_t v[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) v[j] = o + j < m ? src[o + j] : ~0ull;
+            merge_sort(m, reinterpret_cast<uint64_t*>(s_cnt), v);
+#pragma unroll
+            for (int j = 0; j < 8; ++j)
+                if (o + j < m) {
+                    words[start + off + o + j] = (uint32_t)v[j];
+                    high_words[start + off + o + j] = (uint32_t)(v[j] >> 32);
+                }
+            __syncthreads();
+        });
     for (int li = blockIdx.x; li < nl; li += gridDim.x) {
         const int S = long_lists[li];
         const int start = ranges[2 * S], n = ranges[2 * S + 1] - start;
@@ -835,7 +995,7 @@ __global__ __launch_bounds__(NP) void k_bin_split(const uint64_t* __restrict__ i
         __syncthreads();
         const uint32_t big = block_scan_counts<NP, kSplitBuckets / NP>(s_cnt, s_red);
         const int np = (n + kPieceRun - 1) / kPieceRun;
-        if (big > (uint32_t)kPieceRun || np > kMaxPieces) {  // block-uniform
+        if (big > (uint32_t)kPieceRun) {  // block-uniform
             if (threadIdx.x == 0) {
                 const int m = (n + kSortCap - 1) / kSortCap, at = atomicAdd(&rc->n_chunks, m);
                 for (int q = 0; q < m; ++q) chunks[at + q] = make_uint2((uint32_t)S, (uint32_t)q);
@@ -898,7 +1058,8 @@ __global__ __launch_bounds__(NS) __attribute__((amdgpu_waves_per_eu(7))) void k_
                                                  int total_sup, const RasterCounters* rc,
                                                  const SortPiece* __restrict__ pieces,
                                                  const uint2* __restrict__ chunks, uint32_t* __restrict__ words,
-                                                 int32_t* status) {
+                                                 const int32_t* __restrict__ huge_lists,
+                                                 const uint32_t* __restrict__ high_words, int32_t* status) {
     if (status && blockIdx.x == 0 && threadIdx.x == 0) *status = rc->overflow;  // (final since k_bin<true>)
     __shared__ uint64_t lds[kSortCap];
     __shared__ uint32_t s_cnt[kBuckets + 1];
@@ -1006,92 +1167,51 @@ __global__ __launch_bounds__(NS) __attribute__((amdgpu_waves_per_eu(7))) void k_
         }
         __syncthreads();
     }
+    if (!own && rc->n_huge)
+        huge_units(huge_lists, rc->n_huge, ranges, (int)blockIdx.x - total_sup, step,
+                   [](int n) { return (n + kMergeRun - 1) / kMergeRun; }, [&](int start, int n, int unit) {
+            const uint32_t* low = words + start;
+            const uint32_t* high = high_words + start;
+            uint64_t* out = items + start;
+            merge_runs([&](int i) { return ((uint64_t)high[i] << 32) | low[i]; }, [&](int i, uint64_t v) { out[i] = v; }, n,
+                       kHugeRun, huge_group(n), unit * kMergeRun, lds, reinterpret_cast<int*>(s_cnt));
+        });
 }
 
-// Sorted chunks of a list: a block takes kMergeRun consecutive items of one;
-// an item's place is its index plus the items before it in every other
-// chunk, which are found in that chunk's window between the run's first and
-// last item, through LDS.
-constexpr int kMergeRun = 1024, NM = 256;
+// The chunks of the crowded lists, and the groups of the huge ones, merged to
+// the lists' words.
 __global__ __launch_bounds__(NM) void k_bin_merge(const uint64_t* __restrict__ items,
                                                   const int32_t* __restrict__ ranges, const RasterCounters* rc,
-                                                  const uint2* __restrict__ chunks, uint32_t* __restrict__ words) {
-    constexpr int PER = kMergeRun / NM, kUnits = kSortCap / kMergeRun;
-    __shared__ uint64_t s_win[kMergeRun];
-    __shared__ int s_lo[NM], s_hi[NM];
+                                                  const uint2* __restrict__ chunks,
+                                                  const int32_t* __restrict__ huge_lists, uint32_t* __restrict__ words) {
+    constexpr int kUnits = kSortCap / kMergeRun;
+    __shared__ uint64_t s_win[kWindow];
+    __shared__ int s_at[NM];
+    auto merge = [&](int start, int n, int R, int off) {
+        const uint64_t* list = items + start;
+        uint32_t* out = words + start;
+        merge_runs([&](int i) { return list[i]; }, [&](int i, uint64_t v) { out[i] = list_word(v); }, n, R, 1 << 30, off, s_win,
+                   s_at);
+    };
     const int nu = rc->n_chunks * kUnits;
     for (int u = blockIdx.x; u < nu; u += gridDim.x) {
         const uint2 ch = chunks[u / kUnits];
         const int start = ranges[2 * ch.x], n = ranges[2 * ch.x + 1] - start;
-        const int m = (n + kSortCap - 1) / kSortCap;
-        const int mine = (int)ch.y * kSortCap;                  // the chunk's first item within the list
-        const int mlen = min(n - mine, kSortCap), r0 = (u % kUnits) * kMergeRun;
-        const int cnt = min(mlen - r0, kMergeRun);
-        if (cnt <= 0) continue;  // block-uniform
-        const uint64_t* list = items + start;
-        uint64_t v[PER];
-        int rank[PER];
-#pragma unroll
-        for (int j = 0; j < PER; ++j) {
-            const int i = j * NM + (int)threadIdx.x;
-            v[j] = i < cnt ? list[mine + r0 + i] : ~0ull;
-            rank[j] = r0 + i;
-        }
-        const uint64_t first = list[mine + r0], last = list[mine + r0 + cnt - 1];
-        for (int g0 = 0; g0 < m; g0 += NM) {  // the other chunks, NM windows at a time
-            const int gn = min(m - g0, NM);
-            __syncthreads();
-            if ((int)threadIdx.x < gn) {
-                const int c = g0 + threadIdx.x;
-                const uint64_t* p = list + (int64_t)c * kSortCap;
-                const int len = min(n - c * kSortCap, kSortCap);
-                int w[2];
-#pragma unroll
-                for (int q = 0; q < 2; ++q) {
-                    const uint64_t key = q ? last : first;
-                    int lo = 0, hi = len;
-                    while (lo < hi) {
-                        const int mid = (lo + hi) >> 1;
-                        if (p[mid] < key) lo = mid + 1;
-                        else hi = mid;
-                    }
-                    w[q] = lo;
-                }
-                s_lo[threadIdx.x] = w[0];
-                s_hi[threadIdx.x] = w[1];
-            }
-            __syncthreads();
-            for (int q = 0; q < gn; ++q) {
-                const int c = g0 + q;
-                if (c == (int)ch.y) continue;
-                const int wl = s_lo[q], wh = s_hi[q];
-#pragma unroll
-                for (int j = 0; j < PER; ++j) rank[j] += wl;
-                const uint64_t* p = list + (int64_t)c * kSortCap;
-                for (int t0 = wl; t0 < wh; t0 += kMergeRun) {  // block-uniform bounds
-                    const int tn = min(wh - t0, kMergeRun);
-                    __syncthreads();
-                    for (int i = threadIdx.x; i < tn; i += NM) s_win[i] = p[t0 + i];
-                    __syncthreads();
-#pragma unroll
-                    for (int j = 0; j < PER; ++j) {
-                        int lo = 0, hi = tn;
-                        while (lo < hi) {
-                            const int mid = (lo + hi) >> 1;
-                            if (s_win[mid] < v[j]) lo = mid + 1;
-                            else hi = mid;
-                        }
-                        rank[j] += lo;
-                    }
-                }
-            }
-        }
-#pragma unroll
-        for (int j = 0; j < PER; ++j) {
-            const int i = j * NM + (int)threadIdx.x;
-            if (i < cnt) words[start + rank[j]] = list_word(v[j]);
-        }
+        const int off = (int)ch.y * kSortCap + (u % kUnits) * kMergeRun;
+        if (off < n) merge(start, n, kSortCap, off);  // block-uniform
     }
+    if (rc->n_huge)
+        // (the same part of every group one after another, eight parts side by side, for the L2s)
+        huge_units(huge_lists, rc->n_huge, ranges, blockIdx.x, gridDim.x,
+                   [](int n) {
+                       const int R = kHugeRun * huge_group(n);
+                       return (n + R - 1) / R * (R / kMergeRun);
+                   },
+                   [&](int start, int n, int unit) {
+                       const int R = kHugeRun * huge_group(n), runs = (n + R - 1) / R, w = unit >> 3;
+                       const int off = w % runs * R + (w / runs * 8 + (unit & 7)) * kMergeRun;
+                       if (off < n) merge(start, n, R, off);
+                   });
 }
 
 }  // namespace
@@ -1101,15 +1221,11 @@ hipError_t bin_items(const SegTable& tab, Raster& r, int32_t* status, hipStream_
     for (int q = 0; q < kMaxSeg; ++q)
         a.sg[q] = SupGeo{q < tab.n ? tab.s[q].sup_base : 0, q < tab.n ? tab.s[q].nsx : 0};
     a.rc = r.cnt; a.rec = r.rec; a.brec = r.brec; a.srow = r.srow; a.srow_y = r.srow_y; a.srow_cap = r.srow_cap;
-    a.items = r.items; a.ranges = r.ranges; a.n_sort = r.n_sort; a.long_lists = r.long_lists;
+    a.items = r.items; a.ranges = r.ranges; a.n_sort = r.n_sort; a.long_lists = r.long_lists; a.huge_lists = r.huge_lists;
     a.max_pairs = r.max_pairs; a.total_sup = tab.total_sup;
     a.stride = (tab.total_sup + kColTile - 1) / kColTile * kColTile;
     if (a.stride > kBinLists) return hipErrorInvalidValue;
-    const int per = tab.paired ? 2 : 1;
-    int64_t entries = 0;  // where the host knows them
-    for (int q = 0; q < tab.n; q += per)
-        entries = entries < 0 || tab.s[q].nG ? -1 : entries + per * (int64_t)tab.s[q].nG_host;
-    if (entries < 0 || entries > r.max_entries) entries = r.max_entries;
+    const int64_t known = known_entries(tab, r.max_entries), entries = known < 0 ? r.max_entries : known;
     // Blocks: one per run of entries, up to what two blocks on every CU hold
     // (more only lengthen k_bin_columns), within the counts' buffer.  A batch
     // that runs of 1,024 would leave on a few CUs takes shorter ones, with
@@ -1142,14 +1258,20 @@ hipError_t bin_items(const SegTable& tab, Raster& r, int32_t* status, hipStream_
     // a small batch more than they take from a large one)
     const int64_t piece_blocks = !longer ? 0 : (entries < 256 * kPieceBlocks ? (entries + 255) / 256 : kPieceBlocks);
     SortPiece* pieces = reinterpret_cast<SortPiece*>(r.pieces);
+    // (a block per long list, of which there are no more than super tiles, or per huge list's chunk)
+    const int64_t chunks = entries > kHugeList ? (entries + kHugeRun - 1) / kHugeRun : 0;
+    const int64_t split_blocks = chunks > tab.total_sup ? chunks : tab.total_sup;
     if (longer)
-        hipLaunchKernelGGL(k_bin_split, grid_fit(k_bin_split, (int64_t)tab.total_sup * NP, NP), dim3(NP), 0, st, r.items,
-                           r.ranges, r.long_lists, r.cnt, pieces, r.chunks, r.pval[0]);
+        hipLaunchKernelGGL(k_bin_split, grid_fit(k_bin_split, split_blocks * NP, NP), dim3(NP), 0, st, r.items,
+                           r.ranges, r.long_lists, r.huge_lists, r.cnt, pieces, r.chunks, r.pval[0], r.pval[1]);
     hipLaunchKernelGGL(k_bin_sort, dim3((unsigned)(tab.total_sup + (unsigned)piece_blocks)), dim3(NS), 0, st, r.items,
-                       r.ranges, tab.total_sup, r.cnt, pieces, r.chunks, r.pval[0], status);
+                       r.ranges, tab.total_sup, r.cnt, pieces, r.chunks, r.pval[0], r.huge_lists, r.pval[1], status);
+    // (two blocks a CU for the crowded lists; as many as fit for huge ones, 2 M
+    // items 692 -> 439 us)
+    const int64_t merge_units = chunks * (kHugeRun / kMergeRun);
     if (longer)
-        hipLaunchKernelGGL(k_bin_merge, dim3(512), dim3(NM), 0, st, r.items, r.ranges,
-                           r.cnt, r.chunks, r.pval[0]);
+        hipLaunchKernelGGL(k_bin_merge, grid_fit(k_bin_merge, (merge_units > 512 ? merge_units : 512) * NM, NM), dim3(NM), 0, st,
+                           r.items, r.ranges, r.cnt, r.chunks, r.huge_lists, r.pval[0]);
     mark(mk, 11, st);
     r.sorted_buf = 0;
     return hipGetLastError();

@@ -30,6 +30,7 @@ constexpr int kScanBlocks = 1024;     // blocks of the device-wide scan
 constexpr int kMaxPreBlocks = 2048;   // blocks of the preprocess
 constexpr int kSortBlocks = 1024;     // blocks of each radix pass
 constexpr int kSortCap = 2048;        // items a block sorts in LDS (binning)
+constexpr int kHugeList = 65536;      // items of the longest list that one block divides (binning)
 constexpr int kBinLists = 8192;       // super tiles of the largest batch that is binned
 constexpr int kF = 32;                // feature length the kernels are built for
 constexpr int kH = 32;                // MLP hidden width the kernels are built for
@@ -74,7 +75,8 @@ struct RasterCounters {
     int32_t n_srows;              // their super rows (pairs of tile rows), stored
     int32_t overflow;             // bit0: pair capacity, bit1: entries, bit2: tall footprints' super rows
     int32_t n_gpairs;             // entries / 2: the depth sort's length when the eyes share it
-    int32_t n_long;               // super tiles whose lists are longer than kSortCap
+    int32_t n_long;               // super tiles whose lists are longer than kSortCap, up to kHugeList
+    int32_t n_huge;               // and longer
     int32_t n_pieces;             // the pieces they are sorted in
     int32_t n_chunks;             // chunks of those that are merged instead
     uint32_t team, team_size, team_met;  // blocks that choose the items together where they exceed the capacity
@@ -215,6 +217,7 @@ struct Raster {
     int32_t* n_sort = nullptr;  // [1] (super tile, entry) items (clamped to capacity)
     uint64_t* items = nullptr;  // [max_pairs] depth key << 32 | entry << 4 | mask, by super tile
     int32_t* long_lists = nullptr;  // [max_pairs / kSortCap + 1] super tiles with more than kSortCap items
+    int32_t* huge_lists = nullptr;  // [max_pairs / kHugeList + 1] super tiles with more than kHugeList items
     int4* pieces = nullptr;     // [max_pairs / 512 + 1] their pieces (see k_bin_split)
     uint2* chunks = nullptr;    // [max_pairs / (kSortCap / 2) + 1] chunks of those merged (super tile, chunk)
     uint32_t* sup_total = nullptr;  // [kBinLists] items per super tile
@@ -326,6 +329,8 @@ hipError_t raster_batch(const SegTable& tab, Raster& r, bool full_key_sort, bool
                         Marks* mk = nullptr, hipStream_t blend_st = nullptr, hipEvent_t front_done = nullptr,
                         bool raw = false, int32_t* status = nullptr);
 
+// Entries of a batch where the host knows their number, at most max_entries; else -1.
+int64_t known_entries(const SegTable& tab, int64_t max_entries);
 // Every super tile's depth-ordered list of a batch (pval[0], ranges) from the
 // entries' spans, after the preprocess and the tall footprints' spans.
 hipError_t bin_items(const SegTable& tab, Raster& r, int32_t* status, hipStream_t st, Marks* mk);

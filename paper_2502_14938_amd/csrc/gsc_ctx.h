@@ -63,6 +63,7 @@ hipError_t raster_layout(Raster& r, int64_t max_entries, int64_t max_pairs, int6
     }
     if (full_key) { A_(r.pkey64[0], max_pairs); A_(r.pkey64[1], max_pairs); }
     A_(r.chunks, max_pairs / (kSortCap / 2) + 1); A_(r.long_lists, max_pairs / kSortCap + 1);
+    A_(r.huge_lists, max_pairs / kHugeList + 1);
     A_(r.pieces, max_pairs / 512 + 1); A_(r.sup_total, kBinLists);
     A_(r.ranges, 2 * max_tiles); A_(r.tile_eval, 2 * max_tiles); A_(r.hist, 256 * kSortBlocks);
     A_(r.block_sums, 2 * kBinLists);

@@ -14,7 +14,8 @@
 //                      tile, half or quarter of one (interleaved runs per
 //                      XCD); a tile stages the entries of its super tile's
 //                      list that carry its mask bit, wave-wide early exit
-// Batches of more than kBinLists super tiles are radix-sorted instead:
+// Batches of more than kBinLists super tiles, and ones with more than kHugeList
+// explicit Gaussians for every super tile, are radix-sorted instead:
 //   depth radix pass   stable sort of entries by float32 depth (the low 32
 //                      bits of the (tile | depth) key, applied per Gaussian
 //                      before duplication); the last pass also lays the tile
@@ -351,7 +352,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(7))) void k_
             p.rc->overflow = over ? 2 : 0;
             p.rc->n_entries = s_ne;
             p.rc->n_gpairs = s_ne >> 1;
-            p.rc->n_long = p.rc->n_pieces = p.rc->n_chunks = 0;
+            p.rc->n_long = p.rc->n_huge = p.rc->n_pieces = p.rc->n_chunks = 0;
             p.rc->team = p.rc->team_size = p.rc->team_met = 0u;
             p.rc->n_echunks = (s_ne + NT - 1) / NT;
         }
@@ -1307,6 +1308,17 @@ static bool eyes_share_rotation(const SegTable& tab) {
     return true;
 }
 
+// Entries of a batch where the host knows their number (explicit Gaussians), else -1.
+int64_t known_entries(const SegTable& tab, int64_t max_entries) {
+    const int per = tab.paired ? 2 : 1;
+    int64_t entries = 0;
+    for (int q = 0; q < tab.n; q += per) {
+        if (tab.s[q].nG) return -1;
+        entries += per * (int64_t)tab.s[q].nG_host;
+    }
+    return entries < max_entries ? entries : max_entries;
+}
+
 // Tall footprints (more than kSmallRows tile rows): dense list of the
 // entries k_preprocess (of `blocks` blocks) listed per chunk, offsets of their
 // super rows, then each footprint's super rows, spans and counts.
@@ -1328,8 +1340,15 @@ hipError_t raster_batch(const SegTable& tab_in, Raster& r, bool full_key_sort, b
     seg_supers(tab);
     RasterCounters* rc = r.cnt;
     mark(mk, 3, st);
-    if (status && (full_key_sort || tab.total_sup > kBinLists)) return hipErrorInvalidValue;
-    r.binned = !full_key_sort && tab.total_sup <= kBinLists;
+    // Binned up to kBinLists lists (gsc_bin.hip), unless the host knows of more
+    // than kHugeList entries for every list: the radix sorts spread such a batch
+    // over the chip better.  One 32x32 image of 50,000 Gaussians 193 us binned
+    // and 207 sorted, 100,000 236 and 227, 2,000,000 581 and 370; 64x64,
+    // 200,000 356 and 363, 500,000 737 and 730; 128x128, 500,000 276 and 303,
+    // 2,000,000 864 and 809; 256x256, 2,000,000 339 and 381.
+    const int64_t known = known_entries(tab, r.max_entries);
+    r.binned = !full_key_sort && tab.total_sup <= kBinLists && known <= (int64_t)kHugeList * tab.total_sup;
+    if (status && !r.binned) return hipErrorInvalidValue;
     PreArgs pa;
     pa.tab = tab; pa.rc = rc; pa.rec = r.rec; pa.ntiles = r.ntiles; pa.brec = r.binned ? r.brec : nullptr;
     pa.nsup = r.nsup; pa.dkey = r.dkey[0]; pa.dval = full_key_sort ? nullptr : r.dval[0];
