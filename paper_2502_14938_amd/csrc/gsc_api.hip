@@ -995,16 +995,23 @@ int gsc_debug_copy(gsc_ctx* c, int what, int eye, void* dst, int64_t cap, int64_
                 HIP_OR_FAIL(c, hipMemcpy(k64.data(), R.pkey64[R.sorted_buf], m * 8, hipMemcpyDeviceToHost));
                 for (int64_t i = 0; i < m; ++i) ((uint32_t*)dst)[i] = (uint32_t)(k64[i] >> 32);
             } else {
-                // the lists are in super-tile order: each item's key is the
-                // super tile whose range holds it
                 SegTable tab = c->last_tab;
                 seg_supers(tab);
-                std::vector<int32_t> rg(2 * (size_t)tab.total_sup);
-                HIP_OR_FAIL(c, hipMemcpy(rg.data(), R.ranges, rg.size() * 4, hipMemcpyDeviceToHost));
-                std::fill((uint32_t*)dst, (uint32_t*)dst + m, 0xffffffffu);
-                for (int32_t q = 0; q < tab.total_sup; ++q)
-                    for (int64_t i = rg[2 * (size_t)q]; i < rg[2 * (size_t)q + 1] && i < m; ++i)
-                        ((uint32_t*)dst)[i] = (uint32_t)q;
+                if (R.binned) {
+                    // no keys were made: each item's is the super tile whose range holds it
+                    std::vector<int32_t> rg(2 * (size_t)tab.total_sup);
+                    HIP_OR_FAIL(c, hipMemcpy(rg.data(), R.ranges, rg.size() * 4, hipMemcpyDeviceToHost));
+                    std::fill((uint32_t*)dst, (uint32_t*)dst + m, 0xffffffffu);
+                    for (int32_t q = 0; q < tab.total_sup; ++q)
+                        for (int64_t i = rg[2 * (size_t)q]; i < rg[2 * (size_t)q + 1] && i < m; ++i)
+                            ((uint32_t*)dst)[i] = (uint32_t)q;
+                } else if (keys16(tab)) {
+                    std::vector<uint16_t> k16(m);
+                    HIP_OR_FAIL(c, hipMemcpy(k16.data(), R.pkey[R.sorted_buf], m * 2, hipMemcpyDeviceToHost));
+                    for (int64_t i = 0; i < m; ++i) ((uint32_t*)dst)[i] = k16[i];
+                } else {
+                    HIP_OR_FAIL(c, hipMemcpy(dst, R.pkey[R.sorted_buf], m * 4, hipMemcpyDeviceToHost));
+                }
             }
             break;
         }

@@ -355,5 +355,7 @@ void seg_camera(Seg& s, const gsc_camera& c);
 // Super-tile geometry of every segment (sup_base, nsx, nsy) and the total,
 // from the segments' tile grids, in segment order.
 void seg_supers(SegTable& tab);
+// The radix sorts' keys are 16-bit when the batch's super-tile ids fit.
+inline bool keys16(const SegTable& tab) { return tab.total_sup <= 65536; }
 
 }  // namespace gsc

@@ -1389,8 +1389,7 @@ hipError_t raster_batch(const SegTable& tab_in, Raster& r, bool full_key_sort, b
         e = scan_u32(r.scnt, r.offs, &rc->n_entries, r.max_entries, &rc->n_pairs, r.block_sums, st);
         if (e != hipSuccess) return e;
         mark(mk, 7, st);
-        // keys in 16 bits when the batch's global super-tile ids fit
-        const bool k16 = tab.total_sup <= 65536;
+        const bool k16 = keys16(tab);
         uint16_t* pk16[2] = {reinterpret_cast<uint16_t*>(r.pkey[0]), reinterpret_cast<uint16_t*>(r.pkey[1])};
         da.order = r.dval[which]; da.offs = r.offs; da.items = r.scnt; da.key64 = nullptr; da.val = r.pval[0];
         da.key32 = k16 ? nullptr : r.pkey[0];

@@ -354,3 +354,25 @@ def test_many_items_in_few_lists_are_not_slower_than_sorted(gs, kind):
         best.append(min(times))
     print("binned %.3f ms, sorted by the whole key %.3f ms" % tuple(best))
     assert best[0] <= 1.5 * best[1]
+
+
+@pytest.mark.parametrize("n,W,H", [(300_000, 64, 64), (20000, 4096, 2049), (20000, 16384, 4128)])
+def test_radix_sorted_keys_and_ranges(gs, n, W, H):
+    """Batches that are radix-sorted: more than 65,536 entries to every super
+    tile, 8,320 super tiles (16-bit keys, two passes) and 66,048 (32-bit keys,
+    three).  The sorted keys as the device holds them against the runs that
+    k_ranges found in them, and key for key against the sort of the whole key."""
+    mu, cov, rgb, al, cam = thumbnail(n, W, H, "spread")
+    g = [torch.from_numpy(np.ascontiguousarray(a, np.float32)).cuda() for a in (mu, cov, rgb, al)]
+    out = torch.zeros(3, H, W, device="cuda")
+    keys, vals = [], []
+    for full_key in (False, True):
+        r = gs.Renderer(max_width=W, max_height=H, full_key_sort=full_key)
+        r.render_gaussians(*g, cam, out)
+        torch.cuda.synchronize()
+        r.sync()
+        keys.append(r.debug("sort_keys"))
+        vals.append(r.debug("sort_vals"))
+        assert assert_ranges_from_keys(keys[-1], r.debug("raw_ranges")) > 1
+        r.close()
+    assert np.array_equal(keys[0], keys[1]) and np.array_equal(vals[0], vals[1])
