@@ -11,7 +11,7 @@ The timed form (default: cache + BF16 derivation + learned reuse) is gated
 on PSNR >= 40 dB against the plain FP32 form, frame by frame (untimed
 pass); the plain FP32 form is timed beside it.  Per-stage device times
 come from the library's own HIP events on its stream over the timed
-region; the roofline object is for the stage kernel with the largest
+region; the roofline object is for the stage with the largest
 total time.  The CPU leg times the FP64 oracle on a bounded sample.
 
 --mode serving runs the multi-viewer workload instead (8 viewers, Poisson
@@ -20,6 +20,7 @@ arrivals, uneven resolutions) and reports p50/p99 latency and throughput.
 Prints ONE JSON line.
 """
 import argparse
+import ctypes
 import hashlib
 import json
 import math
@@ -207,7 +208,7 @@ def timed_pass(torch, r, traj, steps, warmup, W, H, tag="timed", stages=None, in
     return t1 - t0, lat, stages, frames
 
 
-def quality_pass(torch, r, plain, traj, W, H):
+def quality_pass(gs, torch, r, plain, traj, W, H):
     """Every frame of the trajectory with the form (fresh cache) and the
     plain FP32 form: per-eye PSNR and the per-frame counters."""
     r.reset_cache()
@@ -218,6 +219,7 @@ def quality_pass(torch, r, plain, traj, W, H):
     for L, R in traj:
         r.frame(L, R, a[0], a[1])
         st = r.stats()
+        st["n_items"] = item_count(gs, r)
         if plain is not r:
             plain.frame(L, R, a[2], a[3])
             ps += [psnr_dev(torch, a[0], a[2]), psnr_dev(torch, a[1], a[3])]
@@ -239,6 +241,7 @@ STAGE_ROWS = {
     "preprocess": ("preprocess",), "tall_spans": ("preprocess",), "pair_scan": ("scan",),
     "dup_rows": ("duplicate",), "tall_list": ("duplicate",), "dup_big": ("duplicate",),
     "depth_sort": ("sort",), "tile_sort": ("sort",), "ranges": ("ranges",), "blend": ("blend",)}
+STAGE_ROW_NAMES = ("select", "schedule", "derive", "compose", "preprocess", "scan", "duplicate", "sort", "ranges", "blend")
 RASTER_ROWS = ("preprocess", "scan", "duplicate", "sort", "ranges", "blend")
 
 
@@ -253,8 +256,7 @@ def algorithmic_work(counts, frames, W, H, n_anchors, k):
     """{row: [bytes, flops]} summed over `frames` frames (frame i uses the
     counters of trajectory frame i % len(counts))."""
     P, n_tiles = radix_passes(W, H)
-    rows = {r: [0.0, 0.0] for r in ("select", "schedule", "derive", "compose", "preprocess", "scan", "duplicate",
-                                    "sort", "ranges", "blend")}
+    rows = {r: [0.0, 0.0] for r in STAGE_ROW_NAMES}
     n = len(counts)
     for i in range(frames):
         c = counts[i % n]
@@ -272,6 +274,29 @@ def algorithmic_work(counts, frames, W, H, n_anchors, k):
         rows["ranges"][0] += K2 * 8 + 2 * n_tiles * 8
         rows["blend"][0] += K2 * 40 + 2 * W * H * 12
         rows["blend"][1] += BLEND_OPS_PER_VISIT * float(sum(c["n_eval"]))
+    return rows
+
+
+def implemented_work(counts, frames, W, H, n_anchors, k):
+    """The same for what a binned pair's kernels cannot do without, in their
+    own formats: 52-B cached Gaussians and ids in, 64-B records, 16-B binning
+    records and tile counts out; the binning records read to count and to
+    write the 8-byte items; the items read and 4-byte list words written in
+    order; the words read and the images written by the blend (the records
+    that it shares through L2 are left out, so its bytes stay a lower bound).
+    counts: with "n_items", the (super tile, entry) items of both eyes."""
+    rows = algorithmic_work(counts, frames, W, H, n_anchors, k)
+    for r in RASTER_ROWS:
+        rows[r][0] = 0.0
+    n = len(counts)
+    for i in range(frames):
+        G, items = float(counts[i % n]["n_gauss"]), float(counts[i % n]["n_items"])
+        rows["preprocess"][0] += G * (4 + 52) + 2 * G * (64 + 16 + 4)
+        rows["scan"][0] += 2 * G * 16
+        rows["duplicate"][0] += 2 * G * 16 + items * 8
+        rows["sort"][0] += items * (8 + 4)
+        rows["ranges"][0] += 2 * (-(-W // 32) * -(-H // 32)) * 8
+        rows["blend"][0] += items * 4 + 2 * W * H * 12
     return rows
 
 
@@ -375,9 +400,17 @@ def host_cores():
 
 # --------------------------------------------------------------------------- frames mode
 
-DOM_CANDIDATES = {  # single-kernel stages: kernel name, method row whose bytes it carries
+DOM_CANDIDATES = {  # stages of a 2048x1080 pair (binned): kernels, method row whose bytes they carry
     "derive": ("k_derive_mfma", "derive"), "preprocess": ("k_preprocess", "preprocess"),
-    "ranges": ("k_ranges", "ranges"), "blend": ("k_blend", "blend")}
+    "dup_rows": ("k_bin<true>", "duplicate"), "tile_sort": ("k_bin_split + k_bin_sort + k_bin_merge", "sort"),
+    "blend": ("k_blend", "blend")}
+
+
+def item_count(gs, r):
+    """(super tile, entry) items of the last frame (the count of a debug copy of none)."""
+    n = ctypes.c_int64(0)
+    gs.lib().gsc_debug_copy(r.h, gs.DBG["sort_vals"], 0, None, 0, ctypes.byref(n))
+    return n.value
 
 
 def run_frames(args):
@@ -398,14 +431,8 @@ def run_frames(args):
     # stage boundary; it picks the kernel whose roofline is reported
     _, _, all_stages, all_frames = timed_pass(torch, r, traj, args.steps, args.warmup, W, H, "stages:" + form)
     per_frame = {k: v / max(1, all_frames) for k, v in all_stages.items()}
-    cand = {k: per_frame[k] for k in DOM_CANDIDATES}
-    top = max(cand, key=cand.get)
-    if max(per_frame["dup_rows"], per_frame["dup_big"]) > cand[top]:
-        # a 2048x1080 stereo pair is binned: its items are written by k_bin<true>
-        dom, dom_stages, kname, drow = "duplicate", ["dup_rows", "tall_list", "dup_big"], "k_bin", "duplicate"
-    else:
-        dom, dom_stages = top, [top]
-        kname, drow = DOM_CANDIDATES[top]
+    dom = max(DOM_CANDIDATES, key=per_frame.get)
+    dom_stages, (kname, drow) = [dom], DOM_CANDIDATES[dom]
     # the timed pass: events at the frame's ends (latency) and around the
     # dominant kernel only (its live launch time, on the library's stream)
     total_s, lat, stages, frames = timed_pass(torch, r, traj, args.steps, args.warmup, W, H, "timed:" + form,
@@ -437,7 +464,7 @@ def run_frames(args):
     quality = None
     if not args.no_quality:
         ref = plain if plain is not None else (make_renderer(gs, scene, "plain", W, H, args) if form != "plain" else r)
-        ps, ss, counts = quality_pass(torch, r, ref, traj, W, H)
+        ps, ss, counts = quality_pass(gs, torch, r, ref, traj, W, H)
         if form != "plain":
             tf = np.arange(min(args.steps, n_traj))
             pt = ps.reshape(-1, 2)[tf].reshape(-1)
@@ -453,7 +480,7 @@ def run_frames(args):
         oL = torch.zeros(3, H, W, device="cuda"); oR = torch.zeros(3, H, W, device="cuda")
         for L, R_ in traj[:max(1, min(n_traj, args.steps))]:
             r.frame(L, R_, oL, oR)
-            counts.append(r.stats())
+            counts.append(dict(r.stats(), n_items=item_count(gs, r)))
         r.count_work(False)
     if args.copy_calibration:
         src = torch.empty(1 << 28, dtype=torch.float32, device="cuda")  # 1 GiB
@@ -462,32 +489,40 @@ def run_frames(args):
         torch.cuda.synchronize()
         del src, dst
 
-    # ---- roofline: algorithmic work of each method row over the timed frames
-    work = algorithmic_work(counts, frames, W, H, scene.n, scene.k)
-    row_ms = {row: 0.0 for row in work}
+    # ---- roofline: work of each method row over the timed frames, by the
+    # method's byte model and by what the kernels of a binned pair need
+    row_ms = {row: 0.0 for row in STAGE_ROW_NAMES}
     for st, rows in STAGE_ROWS.items():
         for row in rows:
             row_ms[row] += per_frame[st] / len(rows)
-    rows_out = {}
-    for row, (b, f) in work.items():
-        bound_ms = 1e3 * row_bound_s(row, b, f) / frames
-        rows_out[row] = {"ms": round(row_ms[row], 4), "mb": round(b / frames / 1e6, 2),
-                         "bound_ms": round(bound_ms, 4),
-                         "frac": round(bound_ms / row_ms[row], 3) if row_ms[row] > 0 else None}
-    bound_frame = sum(1e3 * row_bound_s(rw, *work[rw]) for rw in work) / frames
-    bound_raster = sum(1e3 * row_bound_s(rw, *work[rw]) for rw in RASTER_ROWS) / frames
     raster_ms = sum(per_frame[st] for st, rows in STAGE_ROWS.items() if rows[0] in RASTER_ROWS)
     ms_step = 1000 * total_s / args.steps
-    roofline_path = {
-        "frame": {"bound_ms": round(bound_frame, 4), "measured_ms": round(ms_step, 4),
-                  "frac": round(bound_frame / ms_step, 4),
-                  "bytes_per_frame_mb": round(sum(b for b, _ in work.values()) / frames / 1e6, 1)},
-        "rasterizer": {"rows": list(RASTER_ROWS), "bound_ms": round(bound_raster, 4),
-                       "measured_ms": round(raster_ms, 4), "frac": round(bound_raster / raster_ms, 4),
-                       "target_frac": 0.5},
-        "rows": rows_out,
-        "note": "bound = max(HBM bytes / 8 TB/s, flops / peak) per row from algorithmic counts; frame measured = "
-                "timed ms per step; rasterizer measured = its stages' times in the stage pass"}
+
+    def path(work, note):
+        rows_out = {}
+        for row, (b, f) in work.items():
+            bound_ms = 1e3 * row_bound_s(row, b, f) / frames
+            rows_out[row] = {"ms": round(row_ms[row], 4), "mb": round(b / frames / 1e6, 2),
+                             "bound_ms": round(bound_ms, 4),
+                             "frac": round(bound_ms / row_ms[row], 3) if row_ms[row] > 0 else None}
+        bound_frame = sum(1e3 * row_bound_s(rw, *work[rw]) for rw in work) / frames
+        bound_raster = sum(1e3 * row_bound_s(rw, *work[rw]) for rw in RASTER_ROWS) / frames
+        return {"frame": {"bound_ms": round(bound_frame, 4), "measured_ms": round(ms_step, 4),
+                          "frac": round(bound_frame / ms_step, 4),
+                          "bytes_per_frame_mb": round(sum(b for b, _ in work.values()) / frames / 1e6, 1)},
+                "rasterizer": {"rows": list(RASTER_ROWS), "bound_ms": round(bound_raster, 4),
+                               "measured_ms": round(raster_ms, 4), "frac": round(bound_raster / raster_ms, 4)},
+                "rows": rows_out, "note": note}
+
+    work = implemented_work(counts, frames, W, H, scene.n, scene.k)
+    roofline_path = path(work, "bound = max(HBM bytes / 8 TB/s, flops / peak) per row, bytes in the formats of the "
+                               "kernels that ran; frame measured = timed ms per step; rasterizer measured = its "
+                               "stages' times in the stage pass")
+    method_path = path(algorithmic_work(counts, frames, W, H, scene.n, scene.k),
+                       "the same by the method's own byte model: 24 B a tile pair in each of six radix passes and a "
+                       "pass for the ranges, which a binned pair does not run, and a 40-B record read for every "
+                       "tile pair; a row above 1 is no bound of what ran")
+    method_path["rasterizer"]["target_frac"] = 0.5
 
     # ---- the dominant kernel, timed live in the timed pass
     launches = frames
@@ -508,24 +543,14 @@ def run_frames(args):
                     "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": traffic}
     roofline.update({"avg_launch_us": round(1e6 * sec / launches, 2),
                      "algorithmic_bytes_per_launch": round(b / launches),
-                     "per_unit": {"preprocess": "168 B per Gaussian (84 per eye)",
-                                  "blend": "40 B per tile pair + 12 B per pixel per eye; 20 ops per visit",
-                                  "derive": "804 B per missed anchor", "ranges": "8 B per pair + 8 B per tile",
-                                  "duplicate": "44 B per Gaussian per eye + 12 B per pair"}[drow],
+                     "per_unit": {"preprocess": "56 B in, 84 B per eye out per Gaussian",
+                                  "blend": "4 B per (super tile, entry) item + 12 B per pixel per eye; 20 ops per visit",
+                                  "derive": "804 B per missed anchor", "sort": "12 B per (super tile, entry) item",
+                                  "duplicate": "16 B per Gaussian per eye + 8 B per (super tile, entry) item"}[drow],
                      "launches": launches, "frames": timed_frames})
     if drow == "blend":
         roofline["alu_flop_per_launch"] = round(f / launches)
-        if roofline["bound"] == "hbm":
-            # the byte model counts every tile pair's record as read from HBM;
-            # the tiles of a super tile share those records through L2 and LDS
-            alu = f / sec / 1e12 if sec > 0 else 0.0
-            roofline.update({"alu_achieved_tflops": round(alu, 2), "alu_frac": round(alu / ALU_FP32_PUBLISHED_TFS, 4),
-                             "alu_frac_vs_nonpacked_fp32": round(alu / VALU_FP32_NONPACKED_TFS, 4),
-                             "note": "achieved counts every tile pair's 40-B record as an HBM read (the rasterizer "
-                                     "rows' byte model), so frac can reach 1; the records are shared through L2 "
-                                     "and LDS (measured HBM bytes: traffic) and the kernel is bound by its "
-                                     "vector ALU (alu_frac)"})
-    dstat = rows_out["derive"]
+    dstat = roofline_path["rows"]["derive"]
     derive_mfma = None
     if per_frame["derive"] > 0:
         tf = work["derive"][1] / frames / (per_frame["derive"] * 1e-3) / 1e12
@@ -554,9 +579,11 @@ def run_frames(args):
                            "blend_visits": round(float(np.mean([sum(c["n_eval"]) for c in counts])) if counts else 0),
                            "blend_contrib": round(float(np.mean([sum(c["n_contrib"]) for c in counts])) if counts else 0),
                            "tall_footprints": round(float(np.mean([c["n_tall"] for c in counts])) if counts else 0),
+                           "items": round(mean("n_items")),
                            "pairs_per_eye": round(float(np.mean([sum(c["n_pairs"]) / 2 for c in counts])) if counts else 0),
                            "frames": "all %d frames" % len(counts)},
-           "roofline": roofline, "roofline_path": roofline_path, "derive_mfma": derive_mfma}
+           "roofline": roofline, "roofline_path": roofline_path, "roofline_path_method_model": method_path,
+           "derive_mfma": derive_mfma}
     out.update(log)
     if not args.no_cpu_baseline:
         out["cpu_baseline"] = cpu_baseline(synth, scene, traj, host_cores())

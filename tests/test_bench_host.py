@@ -36,3 +36,20 @@ def test_blend_alu_bound_when_visits_dominate():
     b, f = w["blend"]
     assert f == 20 * 10 ** 10
     assert bench.row_bound_s("blend", b, f) == pytest.approx(f / 157.3e12)
+
+
+def test_implemented_work_of_a_binned_pair():
+    """Bytes of the kernels' own formats: below the method's model wherever
+    that one counts radix passes, nothing for a row without units."""
+    c = {"n_visible": 220000, "n_miss": 220000, "n_gauss": 1100000, "n_pairs": [6600000, 6600000],
+         "n_items": 6000000, "n_eval": [0, 0]}
+    m, w = (f([c], 1, 2048, 1080, 1000000, 10) for f in (bench.algorithmic_work, bench.implemented_work))
+    assert w["sort"][0] == 6000000 * 12 and w["duplicate"][0] == 2 * 1100000 * 16 + 6000000 * 8
+    assert w["preprocess"][0] == 1100000 * 56 + 2 * 1100000 * 84
+    assert w["blend"][0] == 6000000 * 4 + 2 * 2048 * 1080 * 12
+    assert w["ranges"][0] == 2 * 64 * 34 * 8
+    for row in ("select", "schedule", "derive", "compose"):
+        assert w[row] == m[row]
+    for row in ("sort", "ranges", "blend"):
+        assert w[row][0] < m[row][0]
+    assert set(r for _, r in bench.DOM_CANDIDATES.values()) <= set(w)
