@@ -315,7 +315,8 @@ int gsc_ssim(gsc_ctx* ctx, const float* a, const float* b, int32_t channels, int
  * frames issued since timing was switched on or last read.  A batch of at
  * most 8,192 super tiles (2x2 tiles) is binned: stages 6, 7 and 10 do its
  * work and stages 5, 8, 9 and 11 read next to nothing.  A larger batch, one of
- * more than 65,536 explicit Gaussians for every super tile, and one under
+ * more than 65,536 explicit Gaussians for every super tile (of a render buffer:
+ * if it may hold more than 32,768 for each), and one under
  * GSC_FLAG_FULL_KEY_SORT is sorted by radix passes.  Stages: */
 #define GSC_STAGE_SCHEDULE 0    /* unified-camera selection, cache schedule */
 #define GSC_STAGE_DERIVE 1      /* MLP derivation of the misses (MFMA) */

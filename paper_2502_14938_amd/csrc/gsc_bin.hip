@@ -1238,7 +1238,7 @@ hipError_t bin_items(const SegTable& tab, Raster& r, int32_t* status, hipStream_
     a.max_pairs = r.max_pairs; a.total_sup = tab.total_sup;
     a.stride = (tab.total_sup + kColTile - 1) / kColTile * kColTile;
     if (a.stride > kBinLists) return hipErrorInvalidValue;
-    const int64_t known = known_entries(tab, r.max_entries), entries = known < 0 ? r.max_entries : known;
+    const int64_t entries = entry_bound(tab, r.max_entries);
     // Blocks: one per run of entries, up to what two blocks on every CU hold
     // (more only lengthen k_bin_columns), within the counts' buffer.  A batch
     // that runs of 1,024 would leave on a few CUs takes shorter ones, with

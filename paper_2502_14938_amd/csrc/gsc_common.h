@@ -90,7 +90,7 @@ struct Seg {
     const float* L3;    // b
     const int32_t* G;   // render buffer: cache entry per Gaussian (nullptr = identity)
     const int32_t* nG;  // device count of G (nullptr = nG_host)
-    int32_t nG_host;
+    int32_t nG_host;    // the count, or with nG the most there may be
     const float4* anchor_pos;    // anchors (x, y, z, radius); nullptr: L0 holds absolute positions
     const int32_t* line_anchor;  // anchor of each cache line (nullptr: line i belongs to anchor i)
     int32_t k;                   // entries per cache line
@@ -329,8 +329,8 @@ hipError_t raster_batch(const SegTable& tab, Raster& r, bool full_key_sort, bool
                         Marks* mk = nullptr, hipStream_t blend_st = nullptr, hipEvent_t front_done = nullptr,
                         bool raw = false, int32_t* status = nullptr);
 
-// Entries of a batch where the host knows their number, at most max_entries; else -1.
-int64_t known_entries(const SegTable& tab, int64_t max_entries);
+// Most entries a batch may have, at most max_entries.
+int64_t entry_bound(const SegTable& tab, int64_t max_entries);
 // Every super tile's depth-ordered list of a batch (pval[0], ranges) from the
 // entries' spans, after the preprocess and the tall footprints' spans.
 hipError_t bin_items(const SegTable& tab, Raster& r, int32_t* status, hipStream_t st, Marks* mk);

@@ -82,6 +82,13 @@ inline void raw_segment(Seg& s, const gsc_gaussians& g) {
     s.anchor_pos = nullptr; s.line_anchor = nullptr; s.k = 1;
     s.nG_host = (int32_t)g.n;
 }
+// A view's render buffer as a segment's Gaussians.
+inline void view_gaussians(Seg& s, const View& v, const Scene& sc) {
+    s.G = v.G;
+    s.nG = &v.cnt->n_gauss;
+    const int64_t most = (v.C < sc.n ? v.C : sc.n) * sc.k;
+    s.nG_host = (int32_t)(most < 0x7fffffff ? most : 0x7fffffff);
+}
 // Set the thread's context-free error message (gsc_last_error(NULL)).
 int global_fail(int code, const std::string& msg);
 

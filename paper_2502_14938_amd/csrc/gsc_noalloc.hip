@@ -27,7 +27,7 @@ constexpr int64_t kNaTiles = (int64_t)(GSC_NOALLOC_MAX_SIDE / kTile) * (GSC_NOAL
 constexpr size_t kNaBytes = (size_t)48 << 20;  // holds the layout below (checked at set-up)
 constexpr size_t kNaAlign = 256;
 constexpr int kNaDevices = 64;
-static_assert(kNaTiles <= 4 * kBinLists && GSC_NOALLOC_MAX_GAUSSIANS <= kHugeList,
+static_assert(kNaTiles <= 4 * kBinLists && GSC_NOALLOC_MAX_GAUSSIANS <= 65536,
               "every image is binned (the sort then reports the status)");
 
 __device__ __align__(256) uint8_t scratch[kNaBytes];

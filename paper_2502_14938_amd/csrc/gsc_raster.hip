@@ -14,8 +14,8 @@
 //                      tile, half or quarter of one (interleaved runs per
 //                      XCD); a tile stages the entries of its super tile's
 //                      list that carry its mask bit, wave-wide early exit
-// Batches of more than kBinLists super tiles, and ones with more than kHugeList
-// explicit Gaussians for every super tile, are radix-sorted instead:
+// Batches of more than kBinLists super tiles, and ones with very many entries
+// to every super tile (bin_batch), are radix-sorted instead:
 //   depth radix pass   stable sort of entries by float32 depth (the low 32
 //                      bits of the (tile | depth) key, applied per Gaussian
 //                      before duplication); the last pass also lays the tile
@@ -1308,15 +1308,30 @@ static bool eyes_share_rotation(const SegTable& tab) {
     return true;
 }
 
-// Entries of a batch where the host knows their number (explicit Gaussians), else -1.
-int64_t known_entries(const SegTable& tab, int64_t max_entries) {
+int64_t entry_bound(const SegTable& tab, int64_t max_entries) {
     const int per = tab.paired ? 2 : 1;
     int64_t entries = 0;
-    for (int q = 0; q < tab.n; q += per) {
-        if (tab.s[q].nG) return -1;
-        entries += per * (int64_t)tab.s[q].nG_host;
-    }
+    for (int q = 0; q < tab.n; q += per) entries += per * (int64_t)tab.s[q].nG_host;
     return entries < max_entries ? entries : max_entries;
+}
+
+// Binned up to kBinLists lists (gsc_bin.hip), unless there are too many
+// entries for every list: the radix sorts spread such a batch over the chip
+// better.  Explicit Gaussians, whose number the host knows (us a call, binned
+// and sorted): one 32x32 image of 50,000 193 and 207, 100,000 236 and 227,
+// 2,000,000 581 and 370; 64x64, 200,000 356 and 363, 500,000 737 and 730;
+// 128x128, 500,000 276 and 303, 2,000,000 864 and 809; 256x256, 2,000,000 339
+// and 381: the line lies at 65,536 a list.  A render buffer's number is the
+// device's, and the host knows the most there may be; a seventh of it is usual
+// and unevenly spread over the image, so the line lies at 32,768 of those.
+// Stereo frames of the city, low and high above it: 1 M anchors at 256x256
+// (156,250 a list) 644 and 471, 2,256 and 1,956; 640x360 (41,667) 609 and
+// 508, 668 and 701; 960x540 (19,608) 594 and 563, 492 and 558; 1280x720
+// (10,870) 535 and 617, 470 and 553; 300,000 anchors at 256x256 (46,875) 314
+// and 236, 637 and 648; 640x360 (12,500) 220 and 275, 228 and 291.
+bool bin_batch(const SegTable& tab, int64_t max_entries) {
+    const int64_t most = tab.s[0].nG ? 32768 : 65536;
+    return tab.total_sup <= kBinLists && entry_bound(tab, max_entries) <= most * tab.total_sup;
 }
 
 // Tall footprints (more than kSmallRows tile rows): dense list of the
@@ -1340,14 +1355,7 @@ hipError_t raster_batch(const SegTable& tab_in, Raster& r, bool full_key_sort, b
     seg_supers(tab);
     RasterCounters* rc = r.cnt;
     mark(mk, 3, st);
-    // Binned up to kBinLists lists (gsc_bin.hip), unless the host knows of more
-    // than kHugeList entries for every list: the radix sorts spread such a batch
-    // over the chip better.  One 32x32 image of 50,000 Gaussians 193 us binned
-    // and 207 sorted, 100,000 236 and 227, 2,000,000 581 and 370; 64x64,
-    // 200,000 356 and 363, 500,000 737 and 730; 128x128, 500,000 276 and 303,
-    // 2,000,000 864 and 809; 256x256, 2,000,000 339 and 381.
-    const int64_t known = known_entries(tab, r.max_entries);
-    r.binned = !full_key_sort && tab.total_sup <= kBinLists && known <= (int64_t)kHugeList * tab.total_sup;
+    r.binned = !full_key_sort && bin_batch(tab, r.max_entries);
     if (status && !r.binned) return hipErrorInvalidValue;
     PreArgs pa;
     pa.tab = tab; pa.rc = rc; pa.rec = r.rec; pa.ntiles = r.ntiles; pa.brec = r.binned ? r.brec : nullptr;

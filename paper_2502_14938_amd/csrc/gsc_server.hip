@@ -495,7 +495,7 @@ int gsc_server_step(gsc_server* s) {
             sg.L0 = v.v.L0; sg.L1 = v.v.L1; sg.L2 = v.v.L2; sg.L3 = v.v.L3;
             const bool direct = (c->cfg.flags & GSC_FLAG_REUSE) && v.v.C >= c->scene.n;  // line a = anchor a
             sg.anchor_pos = c->scene.posr; sg.line_anchor = direct ? nullptr : v.v.line_anchor; sg.k = c->scene.k;
-            sg.G = v.v.G; sg.nG = &v.v.cnt->n_gauss; sg.nG_host = 0;
+            view_gaussians(sg, v.v, c->scene);
             seg_camera(sg, r.eye[eye]);
             if (c->cfg.flags & GSC_FLAG_LOD_FADE) seg_lod_fade(sg, c->scene, r.unified);
             sg.tile_base = tiles;
