@@ -6,8 +6,9 @@
 // C2 = 0.03^2 (dynamic range 1), the SSIM map over every window position
 // inside the image, averaged over positions and channels.
 //
-//   k_ssim        a wave per strip of 64 window columns and some rows, no
-//                 wave waiting for another.  Four image rows at a time: a
+//   k_ssim        a wave per strip of 64 window columns (of two or four planes
+//                 whose maps are narrow) and some rows, no wave waiting for
+//                 another.  Four image rows at a time: a
 //                 lane makes the five horizontal window sums (mean a, mean b,
 //                 a^2, b^2, a b) of four neighbouring positions of one row
 //                 from 14 pixels of its own, and they change to a lane per
@@ -78,31 +79,36 @@ __device__ __forceinline__ void load_pixels(Pixels& p, const float* __restrict__
 struct Strips {
     int cols, rows;  // strips across and down the map
     int height;      // window rows of a strip
+    int planes;      // groups of planes that share their strips
 };
 
+// kWide: a strip's columns of one plane (64 / kWide planes side by side).
+template <int kWide>
 __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(2))) void k_ssim(
-    const float* __restrict__ a, const float* __restrict__ b, int H, int W, SsimWindow win, Strips sp,
+    const float* __restrict__ a, const float* __restrict__ b, int C, int H, int W, SsimWindow win, Strips sp,
     double* __restrict__ partial) {
+    constexpr int kPlanes = kCols / kWide;
     __shared__ __align__(16) double s_h[kWaves][5][kRows][kCols];  // horizontal sums of the wave's rows
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int strip = blockIdx.x * kWaves + w, strips = sp.cols * sp.rows;
     if (strip >= strips) return;  // (waves share nothing)
-    const int64_t plane = (int64_t)H * W;
-    const float* A = a + blockIdx.y * plane;
-    const float* B = b + blockIdx.y * plane;
     const int x0 = strip % sp.cols * kCols, y0 = strip / sp.cols * sp.height;
     const int y1 = min(y0 + sp.height, H - kWin + 1);  // the strip's window rows [y0, y1)
     const int tr = lane >> 4, tc = (lane & 15) * 4;    // horizontal sums: row, first column
-    const bool column = x0 + lane <= W - kWin;         // this lane's window column is in the map
+    // this lane's window column is in the map of a plane
+    const bool column = x0 + lane % kWide <= W - kWin && (int)blockIdx.y * kPlanes + lane / kWide < C;
+    const int64_t plane = (int64_t)min((int)blockIdx.y * kPlanes + tc / kWide, C - 1) * H * W;
+    const float *A = a + plane, *B = b + plane;
+    const int xh = x0 + tc % kWide;
     double acc[kWin][5];  // acc[t]: rows 0 .. t of the window that has come to its row t
 #pragma unroll
     for (int t = 0; t < kWin; ++t)
 #pragma unroll
         for (int q = 0; q < 5; ++q) acc[t][q] = 0.0;
-    const bool inside = x0 + kCols + kWin - 1 <= W;    // (wave-uniform)
+    const bool inside = kPlanes == 1 && x0 + kCols + kWin - 1 <= W;  // (wave-uniform)
     double sum = 0.0;
     Pixels px;
-    load_pixels(px, A, B, y0 + tr, x0 + tc, H, W, inside);
+    load_pixels(px, A, B, y0 + tr, xh, H, W, inside);
     for (int yb = y0; yb < y1 + kWin - 1; yb += kRows) {
         {
             double h[4][5];
@@ -127,7 +133,7 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(2))
                 for (int j = 0; j < 4; ++j) s_h[w][q][tr][tc + j] = h[j][q];
         }
         // the next rows' pixels are on their way during the vertical sums
-        load_pixels(px, A, B, yb + kRows + tr, x0 + tc, H, W, inside);
+        load_pixels(px, A, B, yb + kRows + tr, xh, H, W, inside);
         __builtin_amdgcn_wave_barrier();  // a wave's LDS accesses complete in order
         // (every row gives a value: a strip's first ten complete no window of
         // its own and count for nothing)
@@ -157,12 +163,19 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(2))
 // Strips of a map of C planes: one wave on every SIMD (its 55 chains of sums
 // are enough to fill it, and each strip reads ten rows more than it has: twice
 // as many strips took 67 us in place of 63), of at least two rows, a whole
-// number of steps of kRows image rows each.
+// number of steps of kRows image rows each.  Many planes of at most 32 or 16
+// window columns share their strips by two or four (4,000 of 12x12 54 -> 31 us
+// a call, 65,535 of 11x11 554 -> 179, 1,000 of 40x40 51 -> 44); few of them
+// are better off with a strip each (1 of 20,000x20 38 -> 34).
+int planes_of(int C, int W) {
+    return C < 512 || W - kWin + 1 > 32 ? 1 : (W - kWin + 1 > 16 ? 2 : 4);
+}
 Strips strips_of(int C, int H, int W) {
-    const int64_t h = H - kWin + 1, waves = 1024;
+    const int64_t h = H - kWin + 1, waves = 1024, np = planes_of(C, W);
     Strips sp;
     sp.cols = (W - kWin + 1 + kCols - 1) / kCols;
-    int64_t down = waves / ((int64_t)C * sp.cols);
+    sp.planes = (int)((C + np - 1) / np);
+    int64_t down = waves / ((int64_t)sp.planes * sp.cols);
     if (down < 1) down = 1;
     const int64_t rows = (h + down - 1) / down + kWin - 1;
     sp.height = (int)((rows + kRows - 1) / kRows * kRows - (kWin - 1));
@@ -199,14 +212,19 @@ SsimWindow ssim_window() {
 
 int64_t ssim_slots(int C, int H, int W) {
     const Strips sp = strips_of(C, H, W);
-    return (int64_t)sp.cols * sp.rows * C;
+    return (int64_t)sp.cols * sp.rows * sp.planes;
 }
 
 hipError_t ssim_launch(const float* a, const float* b, int C, int H, int W, const SsimWindow& win, double* partial,
                        double* total, hipStream_t st) {
     const Strips sp = strips_of(C, H, W);
     const unsigned blocks = (unsigned)((sp.cols * sp.rows + kWaves - 1) / kWaves);
-    hipLaunchKernelGGL(k_ssim, dim3(blocks, (unsigned)C), dim3(64 * kWaves), 0, st, a, b, H, W, win, sp, partial);
+    const dim3 grid(blocks, (unsigned)sp.planes);
+    switch (planes_of(C, W)) {
+        case 4: hipLaunchKernelGGL(k_ssim<16>, grid, dim3(64 * kWaves), 0, st, a, b, C, H, W, win, sp, partial); break;
+        case 2: hipLaunchKernelGGL(k_ssim<32>, grid, dim3(64 * kWaves), 0, st, a, b, C, H, W, win, sp, partial); break;
+        default: hipLaunchKernelGGL(k_ssim<64>, grid, dim3(64 * kWaves), 0, st, a, b, C, H, W, win, sp, partial);
+    }
     hipLaunchKernelGGL(k_ssim_total, dim3(1), dim3(256), 0, st, partial, ssim_slots(C, H, W), total);
     return hipGetLastError();
 }

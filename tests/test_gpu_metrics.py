@@ -84,3 +84,36 @@ def test_ssim_at_strip_edges(r, shape):
     want = oracle.ssim(x, y)
     for _ in range(2):
         assert abs(r.ssim(X, Y) - want) < 1e-9
+
+
+@pytest.mark.parametrize("shape", [(511, 13, 12), (512, 13, 12), (514, 14, 26), (513, 12, 27), (600, 30, 42), (601, 12, 43),
+                                   (2051, 21, 11)])
+def test_ssim_of_many_narrow_planes(r, shape):
+    """Planes that share a strip by four (up to 16 window columns) and by two
+    (up to 32), the last group of them not full, and ones that do not; the
+    bound of the first test."""
+    rng = np.random.default_rng(sum(shape))
+    x = rng.random(shape, dtype=np.float32)
+    y = np.clip(x + 0.1 * rng.standard_normal(shape).astype(np.float32), 0, 1).astype(np.float32)
+    want = oracle.ssim(x, y)
+    assert abs(r.ssim(torch.from_numpy(x).cuda(), torch.from_numpy(y).cuda()) - want) < 1e-9
+
+
+def test_many_narrow_planes_take_less_than_wide_ones(r):
+    """65,535 planes of one window each share a strip of 64 columns by four;
+    33 columns wide, each has a strip of its own.  A quarter of the strips, so
+    at most 0.6 of the time (0.18 ms a call; 0.55 when they had a strip each)."""
+    def best(shape):
+        x, y = torch.rand(shape, device="cuda"), torch.rand(shape, device="cuda")
+        times = []
+        for _ in range(12):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            r.ssim(x, y)
+            b.record()
+            b.synchronize()
+            times.append(a.elapsed_time(b))
+        return min(times)
+    narrow, wide = best((65535, 11, 11)), best((65535, 11, 43))
+    print("%.3f ms, %.3f" % (narrow, wide))
+    assert narrow <= 0.6 * wide
