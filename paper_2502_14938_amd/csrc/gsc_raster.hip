@@ -1017,9 +1017,12 @@ __device__ __forceinline__ bool part_hit(const float4& a, const float2& b, float
 }
 
 // kCount 0: no counts; 1: contributors per pixel (out_nc); 2: also the visits
-// and contributions of each tile (whole tiles only, nothing left out).
+// and contributions of each tile (whole tiles only, nothing left out; with
+// registers for five waves per SIMD: for six they spill, which every wave
+// pays for, however short its list: a counted 8192x8192 image of 100,000
+// Gaussians 541 us against 576).
 template <int kPx, int kCount>
-__global__ __launch_bounds__(kBlendThreads) __attribute__((amdgpu_waves_per_eu(kPx == 4 ? 6 : 7))) void k_blend(SegTable tab, const int32_t* __restrict__ ranges,
+__global__ __launch_bounds__(kBlendThreads) __attribute__((amdgpu_waves_per_eu(kCount == 2 ? 5 : (kPx == 4 ? 6 : 7)))) void k_blend(SegTable tab, const int32_t* __restrict__ ranges,
                                               const uint32_t* __restrict__ vals, const float4* __restrict__ rec,
                                               uint32_t max_entries, int32_t* __restrict__ tile_eval) {
     static_assert(kCount < 2 || kPx == 4, "work is counted per tile");
@@ -1160,8 +1163,10 @@ __global__ __launch_bounds__(kBlendThreads) __attribute__((amdgpu_waves_per_eu(k
                     const bool st = uu && !ac;           // stop here
                     // a branch for whole tiles, whose waves are many enough to
                     // cover it (eight viewers 782 -> 759 us); halves and
-                    // quarters go on without (178 against 189 us, 62 against 72)
-                    if (kPx == 4) {
+                    // quarters go on without (178 against 189 us, 62 against
+                    // 72), and so does the kernel that counts work (a counted
+                    // 4096x2160 image of 400,000 Gaussians 455 us against 498)
+                    if (kPx == 4 && kCount < 2) {
                         if (ac) {
                             cr[i] = fmaf(gb.z, wf, cr[i]); cg[i] = fmaf(gb.w, wf, cg[i]); cbl[i] = fmaf(gc, wf, cbl[i]);
                             T[i] = tn;

@@ -376,3 +376,34 @@ def test_radix_sorted_keys_and_ranges(gs, n, W, H):
         assert assert_ranges_from_keys(keys[-1], r.debug("raw_ranges")) > 1
         r.close()
     assert np.array_equal(keys[0], keys[1]) and np.array_equal(vals[0], vals[1])
+
+
+@pytest.mark.parametrize("W,H,n,s_lo,s_hi,bound", [
+    # counted over uncounted 1.13; 1.24 when the kernel took a branch around every composite step
+    (4096, 2160, 400000, 0.004, 0.02, 1.19),
+    # 1.16; 1.225 when its registers spilled
+    (8192, 8192, 100000, 0.004, 0.01, 1.195),
+])
+def test_counting_work_costs_a_few_instructions(gs, W, H, n, s_lo, s_hi, bound):
+    """Counting the blend's work costs a big image a fraction of its time, at
+    most halfway between what it does and what it once did, and the image is
+    the same."""
+    g = [torch.from_numpy(x).cuda() for x in synth.random_gaussians(n, seed=1, box=3.0, zc=8.0, s_lo=s_lo, s_hi=s_hi)]
+    cam = synth.look_camera((0.1, -0.2, 0), (0.05, 0.02, 1), (0, -1, 0), W, H, math.radians(60), math.radians(60))
+    r = gs.Renderer(max_width=W, max_height=H)
+    out = [torch.zeros(3, H, W, device="cuda") for _ in range(2)]
+    best = [1e9, 1e9]
+    for _ in range(25):
+        for count in (0, 1):
+            r.count_work(bool(count))
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            r.render_gaussians(*g, cam, out[count])
+            b.record()
+            r.sync()  # raises if a capacity was exceeded
+            b.synchronize()
+            best[count] = min(best[count], a.elapsed_time(b))
+    r.close()
+    assert torch.equal(out[0], out[1])
+    print("%.3f ms, counted %.3f" % tuple(best))
+    assert best[1] <= bound * best[0]
