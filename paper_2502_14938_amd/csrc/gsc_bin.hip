@@ -26,12 +26,13 @@
 // the blocks' lanes take positions.
 //
 // Measured, a whole pass with the radix sorts and with this: 2,000 Gaussians
-// at 256x256 141 and 57 us, 60,000 at 1000x560 194 and 103 us, 500,000 at
-// 1920x1081 325 and 225 us, a stereo frame of 2 x 2048x1080 (6 M items) 729
-// and 699 us.  Of that last one's 205 us the writes take 75: they go to 4,352
-// lists at once, more than an XCD's L2 holds the ends of, so four of five
-// 8-byte items leave it as a partial line of their own (195 MB for 48); the
-// sort takes 57, the division of the long lists 41, the counts 28.
+// at 256x256 134 and 54 us, 60,000 at 1000x560 185 and 102 us, 500,000 at
+// 1920x1081 301 and 205 us, a stereo frame of 2 x 2048x1080 high above the
+// city (6 M items) 659 and 595 us.  Of that last one's 203 us the writes take
+// 75: they go to 4,352 lists at once, more than an XCD's L2 holds the ends of,
+// so four of five 8-byte items leave it as a partial line of their own (195 MB
+// for 48); the sort takes 56, the division of the long lists 40, the counts 20,
+// their columns 7, the merge 5.
 // With more lists the writes gather less and less, and the radix sorts, whose
 // launches are spread over more items, win: batches of stereo images with 6,192
 // super tiles take 588 us binned and 611 radix-sorted, with 13,392 1,031 and

@@ -57,14 +57,15 @@ struct Counters {
     int32_t pad[3];
 };
 
-// Device counters of one raster batch.
-// Two floats as a pair of bfloat16, nearest even (one instruction on gfx950).
+// Two floats rounded to BF16 (nearest even), packed lo | hi << 16: one
+// hardware conversion of the pair.
 __device__ __forceinline__ uint32_t bf16_pair(float lo, float hi) {
     typedef float f2 __attribute__((ext_vector_type(2)));
     typedef __bf16 b2 __attribute__((ext_vector_type(2)));
     return __builtin_bit_cast(uint32_t, __builtin_convertvector((f2{lo, hi}), b2));
 }
 
+// Device counters of one raster batch.
 struct RasterCounters {
     int32_t n_entries;            // total (segment, Gaussian) entries
     int32_t entry_base[kMaxSeg + 1];  // entry of Gaussian 0 of each segment (total last)

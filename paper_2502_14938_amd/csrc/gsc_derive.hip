@@ -329,8 +329,8 @@ struct LookupArgs {
 // Every visible owned line is stamped last_used = t.  The loop is uniform
 // per wave: the predictor runs on the whole wave (matrix cores) whenever one
 // of its lanes has a candidate.
-// (at most 128 VGPRs: four waves per SIMD; three took 25 us of the city's
-// lookup with the predictor, four 21)
+// (at most 128 VGPRs: four waves per SIMD.  The lookup with the predictor in
+// views high above the city took 25 us with three, 21 with four)
 template <int V>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_cache_lookup(Views<V> vs, LookupArgs a) {
     __shared__ uint32_t s_h[NT / 64][kPredLdsWave];

@@ -25,7 +25,7 @@
 // here, not 4).  Sums kept in registers down a strip of rows and products made
 // once per pixel take the place of 26 x 26 patches per 16 x 16 positions with
 // every product made eleven times and every horizontal sum 1.6 times: 123 ->
-// 63 us, and the sum of one slot per strip in place of one per tile 28 -> 6 us.
+// 63 us, and the sum of one slot per strip in place of one per tile 28 -> 4 us.
 #include <cmath>
 
 #include "gsc_common.h"

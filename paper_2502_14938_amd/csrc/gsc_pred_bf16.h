@@ -10,13 +10,6 @@ namespace gsc {
 
 typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
 
-// Two floats rounded to BF16 (nearest-even) and packed low | high << 16
-// (one hardware conversion of the pair).
-__device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
-    const bf16x2_t v = {(__bf16)lo, (__bf16)hi};
-    return __builtin_bit_cast(uint32_t, v);
-}
-
 // acc + w.lo * h.lo + w.hi * h.hi (BF16 pairs, FP32 accumulation).
 __device__ __forceinline__ float dot2_bf16(uint32_t w, uint32_t h, float acc) {
     return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, w), __builtin_bit_cast(bf16x2_t, h), acc,
@@ -60,7 +53,7 @@ __device__ __forceinline__ float pred_prob_bf16_wave(const uint16_t* __restrict_
     const int lane = threadIdx.x & 63, col = lane & 15, q = lane >> 4;
     uint32_t x2[kPredIn / 2];
 #pragma unroll
-    for (int i = 0; i < kPredIn / 2; ++i) x2[i] = pack_bf16x2(f[2 * i], f[2 * i + 1]);
+    for (int i = 0; i < kPredIn / 2; ++i) x2[i] = bf16_pair(f[2 * i], f[2 * i + 1]);
     uint32_t* row = lds + lane * kPredLdsStride;
 #pragma unroll
     for (int r = 0; r < kPredW; r += 2) {
@@ -70,7 +63,7 @@ __device__ __forceinline__ float pred_prob_bf16_wave(const uint16_t* __restrict_
             a0 = dot2_bf16(wp[(oW1 + r * kPredIn) / 2 + c], x2[c], a0);
             a1 = dot2_bf16(wp[(oW1 + (r + 1) * kPredIn) / 2 + c], x2[c], a1);
         }
-        row[r / 2] = pack_bf16x2(fmaxf(a0, 0.f), fmaxf(a1, 0.f));
+        row[r / 2] = bf16_pair(fmaxf(a0, 0.f), fmaxf(a1, 0.f));
     }
     __builtin_amdgcn_wave_barrier();  // a wave's LDS accesses complete in issue order
     // B fragments: candidate 16 nt + col, hidden units 16 ks + 4 q .. + 3

@@ -359,7 +359,7 @@ __global__ __launch_bounds__(NT) void k_pred_to_bf16(const float* __restrict__ w
 // One candidate per lane; the loop is uniform per wave (the predictor runs
 // on the whole wave).  Bound by latency (inputs, scalar weights, LDS, matrix
 // fragments, one after the other), so four waves a SIMD: 234,567 rows then
-// are one round of waves.  15.4 -> 13.2 us.
+// are one round of waves.  15.9 -> 12.7 us.
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_pred_infer(const uint16_t* __restrict__ wb, const float* __restrict__ w32,
                                                    const float* __restrict__ X, int64_t n, float* __restrict__ out) {
     __shared__ uint32_t s_h[NT / 64][kPredLdsWave];
