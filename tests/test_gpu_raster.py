@@ -392,8 +392,8 @@ def test_counting_work_costs_a_few_instructions(gs, W, H, n, s_lo, s_hi, bound):
     cam = synth.look_camera((0.1, -0.2, 0), (0.05, 0.02, 1), (0, -1, 0), W, H, math.radians(60), math.radians(60))
     r = gs.Renderer(max_width=W, max_height=H)
     out = [torch.zeros(3, H, W, device="cuda") for _ in range(2)]
-    best = [1e9, 1e9]
-    for _ in range(25):
+    ms = [[], []]
+    for _ in range(40):
         for count in (0, 1):
             r.count_work(bool(count))
             a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
@@ -402,8 +402,9 @@ def test_counting_work_costs_a_few_instructions(gs, W, H, n, s_lo, s_hi, bound):
             b.record()
             r.sync()  # raises if a capacity was exceeded
             b.synchronize()
-            best[count] = min(best[count], a.elapsed_time(b))
+            ms[count].append(a.elapsed_time(b))
     r.close()
     assert torch.equal(out[0], out[1])
-    print("%.3f ms, counted %.3f" % tuple(best))
-    assert best[1] <= bound * best[0]
+    plain, counted = (float(np.median(x)) for x in ms)
+    print("%.3f ms, counted %.3f" % (plain, counted))
+    assert counted <= bound * plain
